@@ -310,7 +310,7 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
         first_blk[i + 1] = first_blk[i] + (fused[i] == 2 || chain[i] == 2 ? 0
                                            : (size_t)G * (chain[i] == 1 ? 3 : chain[i] == 3 || chain[i] == 4 || fused[i] == 1 ? 2 : (m.ops[i].sub > 1 ? m.ops[i].sub : 1)));
     const size_t n_blk = first_blk[m.ops.size()];
-    std::vector<char> host((n_blk + (size_t)G) * slot, 0);
+    std::vector<char> host(n_blk * slot, 0);
     if (!may_alloc && (!g.d_args || g.d_args_bytes < host.size())) return ENS_E_INVALID;
     if (g.d_args && g.d_args_bytes < host.size()) { (void)hipFree(g.d_args); g.d_args = nullptr; }
     if (!g.d_args) { HIP_TRY(hipMalloc((void**)&g.d_args, host.size())); g.d_args_bytes = host.size(); }
@@ -539,24 +539,39 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
         const size_t nb_i = first_blk[i + 1] - first_blk[i];
         for (size_t k = 1; k < nb_i; k++) memmove(base + k * sz, base + k * slot, sz);
     }
-    g.stage.src = nullptr;                                       // bound per request
+    g.stage.src = nullptr;                                       // named per request
+    g.stage.slot = nullptr;
     g.stage.dst = leader.arena + leader.layout.offset[0];
     g.stage.nb = leader.batch; g.stage.sh = h->base_h; g.stage.sw = h->base_w;
     g.stage.dh = m.in_h; g.stage.dw = m.in_w; g.stage.dc = m.tensors[0].cs; g.stage.s2d = m.stem_s2d ? 1 : 0;
-    g.d_stage = (const StageArgs*)(g.d_args + n_blk * slot);
     HIP_TRY(hipMemcpy(g.d_args, host.data(), host.size(), hipMemcpyHostToDevice));
     return ENS_OK;
 }
 
 static int ensure_buffers(ens_handle* h, int64_t n);
 
-static void destroy_workers(ens_handle* h) {
-    for (Gang& g : h->gangs) {
-        if (g.stream) (void)hipStreamSynchronize(g.stream);
-        if (g.d_args) (void)hipFree(g.d_args);
-        if (g.done) (void)hipEventDestroy(g.done);
-        if (g.stream) (void)hipStreamDestroy(g.stream);
+// Recorded requests hold launch geometry, argument block addresses and the batches' sizes.
+static void drop_graphs(ens_handle* h) {
+    for (RequestGraph& r : h->graphs)
+        for (hipGraphExec_t& e : r.exec)
+            if (e) (void)hipGraphExecDestroy(e);
+    h->graphs.clear();
+    h->sizes_seen.clear();
+}
+
+static hipError_t wait_lanes(ens_handle* h) {
+    for (int l = 0; l < LANES && h->have_lanes; l++) {
+        const hipError_t e = hipStreamSynchronize(h->lanes[l]);
+        if (e != hipSuccess) return e;
     }
+    return hipSuccess;
+}
+
+static void destroy_workers(ens_handle* h) {
+    (void)wait_lanes(h);
+    drop_graphs(h);
+    for (Gang& g : h->gangs)
+        if (g.d_args) (void)hipFree(g.d_args);
     h->gangs.clear();
     for (Worker& w : h->workers)
         if (w.arena) (void)hipFree(w.arena);
@@ -649,18 +664,10 @@ static int install_alloc(ens_handle* h, const ens_alloc& a, int segment_size) {
     }
     cu_budget() = stream_share(h);
     for (Gang& g : h->gangs) {
-        hipError_t e = hipStreamCreateWithFlags(&g.stream, hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&g.done, hipEventDisableTiming);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            destroy_workers(h);
-            return ENS_E_HIP;
-        }
         const int rc = build_launches(h, g);
         if (rc != ENS_OK) { destroy_workers(h); return rc; }
     }
     h->args_stale = false;
-    h->bound_images = nullptr;
     h->alloc = a;
     h->alloc.bytes = need;
     h->segment_size = segment_size;
@@ -698,8 +705,8 @@ static hipError_t issue(const Launch& L, bool bf16, int G, int nb, long long fir
 
 // One batch of one gang: stage the images into the leader's arena, run every member, write the
 // logits rows of the batch.
-static int forward_batch(ens_handle* h, Gang& g, int64_t first, int nb) {
-    const hipStream_t st = h->one_stream ? h->main_stream : g.stream;
+// The images are at `src`, or where `slot` says when the launches are being recorded.
+static int forward_batch(ens_handle* h, Gang& g, int64_t first, int nb, const float* src, const RequestSlot* slot, hipStream_t st) {
     const Worker& leader = h->workers[g.workers[0]];
     const Member& m = h->members[leader.member];
     const int G = (int)g.workers.size();
@@ -723,7 +730,10 @@ static int forward_batch(ens_handle* h, Gang& g, int64_t first, int nb) {
         return ENS_OK;
     }
     const double stage_bytes = (double)leader.batch * (h->base_h * h->base_w * 12.0 + (double)m.tensors[0].h * m.tensors[0].w * g.stage.dc * (m.bf16 ? 2 : 4));
-    HIP_TRY(timed(h->stage_klass, 0.0, stage_bytes, [&] { return launch_stage(g.stage, g.d_stage, 1, nb, first, m.bf16, st); }));
+    g.stage.src = src;
+    g.stage.slot = slot;
+    g.stage.sh = h->base_h; g.stage.sw = h->base_w;
+    HIP_TRY(timed(h->stage_klass, 0.0, stage_bytes, [&] { return launch_stage(g.stage, nb, first, m.bf16, st); }));
     for (const Launch& L : g.launches) {
         if (L.kind == L_SKIP) continue;
         HIP_TRY(timed(L.klass, L.flop * G, L.bytes * G, [&] { return issue(L, m.bf16, G, nb, first, st); }));
@@ -745,22 +755,19 @@ static int ensure_buffers(ens_handle* h, int64_t n) {
         for (size_t m = 0; m < h->members.size(); m++)
             HIP_TRY(hipMalloc((void**)&h->d_logits_heap[m], rows * h->members[m].classes * sizeof(float)));
         h->d_logits_heap_rows = rows;
-        if (!h->d_logit_ptrs) HIP_TRY(hipMalloc((void**)&h->d_logit_ptrs, ENS_MAX_MEMBERS * sizeof(float*)));
         moved = true;
     }
-    if (moved || h->logits_static || h->d_logit_table != h->d_logit_ptrs) {   // (back) to the library's own buffers
+    if (moved || h->logits_static) {                           // (back) to the library's own buffers
         h->d_logits = h->d_logits_heap;
         h->d_logits_rows = h->d_logits_heap_rows;
-        h->d_logit_table = h->d_logit_ptrs;
         h->logits_static = false;
         h->args_stale = true;                                  // the FC argument blocks name these buffers
-        HIP_TRY(hipMemcpy((void*)h->d_logit_ptrs, h->d_logits.data(), h->members.size() * sizeof(float*), hipMemcpyHostToDevice));
     }
     return ENS_OK;
 }
 
-// Points the per-member logits at slices of the fixed device array: a table of the members' pointers
-// in its first bytes, then one block of `rows` x classes floats per member.  Allocates nothing.
+// Points the per-member logits at slices of the fixed device array: behind its reserved head one block of
+// `rows` x classes floats per member.  Allocates nothing.
 static int use_static_logits(ens_handle* h, int64_t n) {
     void* base = nullptr;
     size_t bytes = 0;
@@ -774,17 +781,14 @@ static int use_static_logits(ens_handle* h, int64_t n) {
         return ENS_E_TOOBIG;
     }
     float* first = (float*)((char*)base + STATIC_SCRATCH_TABLE_BYTES);
-    const bool there = h->logits_static && h->d_logit_table == (const float**)base && !h->d_logits.empty() && h->d_logits[0] == first;
+    const bool there = h->logits_static && !h->d_logits.empty() && h->d_logits[0] == first;
     if (!there) {
         h->d_logits.assign(M, nullptr);
         for (size_t m = 0; m < M; m++) h->d_logits[m] = first + m * rows_cap * (size_t)h->classes;
         h->d_logits_rows = rows_cap;
-        h->d_logit_table = (const float**)base;
         h->logits_static = true;
         h->args_stale = true;                                  // the FC argument blocks name these buffers
     }
-    // the table is written on every call: another handle's call may have left its own there
-    HIP_TRY(hipMemcpy(base, h->d_logits.data(), M * sizeof(float*), hipMemcpyHostToDevice));
     return ENS_OK;
 }
 
@@ -798,56 +802,11 @@ static int grow(float** p, size_t* cap, size_t want_floats) {
     return ENS_OK;
 }
 
-// f(X, A) -> Y with X and Y on the device.  `mask` selects the members that take part (all
-// members for a real request; a single member when the BBS baseline times it alone).
-// may_alloc false (the allocation-free entry point): the logits buffers are already in place and
-// nothing on the way may allocate or free device memory.
-static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_probs, uint64_t mask, bool may_alloc = true) {
-    if (n == 0) return ENS_OK;
-    cu_budget() = stream_share(h);
-    int rc = may_alloc ? ensure_buffers(h, n) : ENS_OK;
-    if (rc != ENS_OK) return rc;
-    if ((size_t)n > h->d_logits_rows) return ENS_E_INVALID;
-    const int M = (int)h->members.size();
+// Calls fn(gang, first image, images, segment) for every batch of a request of n images, in the order of issue.
+template <typename F>
+static int each_batch(ens_handle* h, int64_t n, uint64_t mask, const std::vector<std::vector<int32_t>>& owner, F&& fn) {
     const int seg = h->segment_size;
     const int64_t n_seg = (n + seg - 1) / seg;
-    if (h->args_stale || h->bound_images != d_images) {          // (re)bind request buffers in the argument blocks
-        for (Gang& g : h->gangs) {
-            if (h->args_stale) {
-                rc = build_launches(h, g, may_alloc);
-                if (rc != ENS_OK) return rc;
-            }
-            g.stage.src = d_images;
-            g.stage.sh = h->base_h; g.stage.sw = h->base_w;
-            HIP_TRY(hipMemcpyAsync((void*)g.d_stage, &g.stage, sizeof(StageArgs), hipMemcpyHostToDevice, h->main_stream));
-        }
-        h->args_stale = false;
-        h->bound_images = d_images;
-    }
-    // the workers start once the request images are in place on the main stream
-    HIP_TRY(hipEventRecord(h->input_ready, h->main_stream));
-    for (Gang& g : h->gangs) HIP_TRY(hipStreamWaitEvent(g.stream, h->input_ready, 0));
-    // every segment id goes once to every member; a member's workers share its segments as they
-    // would by taking them from one queue, the faster worker more of them (planner.cpp, hand_out)
-    std::vector<std::vector<int32_t>> owner(M);
-    for (int c = 0; c < M; c++) {
-        std::vector<int32_t> batches;
-        const Gang* first = nullptr;
-        for (const Worker& w : h->workers)                       // in slot order = rank order
-            if (w.member == c) {
-                batches.push_back(w.batch);
-                if (w.rank == 0) first = &h->gangs[w.gang];
-            }
-        if (batches.size() <= 1 || !first) continue;
-        double flop = 0;
-        int launches = 1;
-        for (const Launch& L : first->launches)
-            if (L.kind != L_SKIP) { flop += L.flop; launches++; }
-        const double launch_cost = launches * 8e-6;              // a kernel of a small batch lasts about this long whatever it does
-        const double image_cost = flop / batches[0] / (h->members[c].bf16 ? 4e14 : 2e13);
-        rc = hand_out(n, seg, batches.data(), (int)batches.size(), launch_cost, image_cost, &owner[c]);
-        if (rc != ENS_OK) return rc;
-    }
     for (int64_t s = 0; s < n_seg; s++) {
         const int64_t start = s * seg, end = std::min<int64_t>((s + 1) * seg, n);
         for (Gang& g : h->gangs) {
@@ -858,29 +817,248 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
             if (!wanted) continue;
             const int b = h->workers[g.workers[0]].batch;
             for (int64_t a = start; a < end; a += b) {
-                rc = forward_batch(h, g, a, (int)std::min<int64_t>(b, end - a));
+                const int rc = fn(g, a, (int)std::min<int64_t>(b, end - a), s);
                 if (rc != ENS_OK) return rc;
             }
         }
     }
-    for (Gang& g : h->gangs) {
-        HIP_TRY(hipEventRecord(g.done, g.stream));
-        HIP_TRY(hipStreamWaitEvent(h->main_stream, g.done, 0));
-    }
-    if (mask == ~0ull || M == 1) {
-        ProfRec r{prof_class(h, "combine_kernel"), nullptr, nullptr, 0.0, (double)n * h->classes * 4.0 * (M + 1)};
-        if (h->profiling) {
-            r.start = take_event(h); r.stop = take_event(h);
-            if (!r.start || !r.stop) return ENS_E_HIP;
-            next_launch_events() = LaunchEvents{r.start, r.stop};
+    return ENS_OK;
+}
+
+// Deals the gangs to the lanes for a request of n images: the longest first, each to the lane with the least so far.
+// The times are estimates that only have to rank: 4 us for a launch, or its work at a tenth of the chip's rates.
+// Returns the number of lanes in use, and in *launches how many launches the request takes.
+static int deal_lanes(ens_handle* h, int64_t n, uint64_t mask, const std::vector<std::vector<int32_t>>& owner, int64_t* launches) {
+    std::vector<double> est(h->gangs.size(), 0.0);
+    *launches = 0;
+    (void)each_batch(h, n, mask, owner, [&](Gang& g, int64_t, int nb, int64_t) {
+        const Worker& leader = h->workers[g.workers[0]];
+        const double share = (double)nb / leader.batch * (double)g.workers.size();
+        double t = 4e-6;
+        for (const Launch& L : g.launches) {
+            if (L.kind == L_SKIP) continue;
+            t += std::max(4e-6, share * std::max(L.flop / 4e14, L.bytes / 3e12));
+            ++*launches;
         }
-        HIP_TRY(launch_combine(h->d_logit_table, h->d_weights, h->combine_rule, M, n, h->classes, d_probs, h->main_stream));
-        if (h->profiling) {
-            next_launch_events() = LaunchEvents{};
-            h->prof_recs.push_back(r);
+        ++*launches;
+        est[&g - h->gangs.data()] += t;
+        return ENS_OK;
+    });
+    std::vector<int> order(h->gangs.size());
+    for (size_t i = 0; i < order.size(); i++) order[i] = (int)i;
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return est[x] > est[y]; });
+    double load[LANES] = {0};
+    int used = 0;
+    for (int i : order) {
+        if (est[i] == 0.0) continue;
+        int best = 0;
+        for (int l = 1; l < LANES; l++)
+            if (load[l] < load[best]) best = l;
+        if (h->one_stream) best = 0;
+        h->gangs[i].lane = best;
+        load[best] += est[i];
+        used = std::max(used, best + 1);                        // lanes fill from the first on
+    }
+    return used;
+}
+
+static CombineArgs combine_args(ens_handle* h, int64_t n, int lanes) {
+    CombineArgs a;
+    memset(&a, 0, sizeof(a));
+    for (size_t m = 0; m < h->members.size(); m++) a.logits[m] = h->d_logits[m];
+    a.weights = h->d_weights;
+    a.arrivals = h->d_arrivals;
+    a.lanes = lanes;
+    a.n_members = (int)h->members.size();
+    a.classes = h->classes;
+    a.rule = h->combine_rule;
+    a.n = n;
+    return a;
+}
+
+// ---- requests recorded as graphs ------------------------------------------------------------------
+// Issuing a launch costs the host 2.7 us, so a small request through many layers waits for the host: one image through
+// twelve members is 940 launches.  A request of a size that comes again is recorded, one graph of plain kernel launches in a row
+// per lane, and from then on costs 0.2 to 0.5 us per launch.  (One graph over all the lanes with its forks and joins was
+// measured too: 2.2 us per launch.)  Recording takes 3 us per launch and is done the second time a size is seen; the recorded
+// launches find the request's buffers through a slot per lane.  Requests with more launches than this keep the GPU
+// busy for longer than the host needs to issue them.
+constexpr int64_t GRAPH_MAX_LAUNCHES = 2048;
+constexpr size_t GRAPHS_KEPT = 8, SIZES_KEPT = 32;
+
+static RequestGraph* find_graph(ens_handle* h, int64_t n) {
+    for (RequestGraph& r : h->graphs)
+        if (r.n == n) return &r;
+    return nullptr;
+}
+
+// Has a request of this size come before?  Notes that it has.
+static bool seen_before(ens_handle* h, int64_t n) {
+    for (auto& s : h->sizes_seen)
+        if (s.first == n) {
+            s.second = h->requests;
+            return true;
+        }
+    if (h->sizes_seen.size() >= SIZES_KEPT)
+        h->sizes_seen.erase(std::min_element(h->sizes_seen.begin(), h->sizes_seen.end(), [](auto& x, auto& y) { return x.second < y.second; }));
+    h->sizes_seen.emplace_back(n, h->requests);
+    return false;
+}
+
+// Records the request on the handle's own stream; nothing runs.  Failure leaves no graph: the request is then issued launch by launch.
+static RequestGraph* record_request(ens_handle* h, int64_t n, int lanes, const std::vector<std::vector<int32_t>>& owner) {
+    RequestGraph r;
+    r.n = n;
+    r.lanes = lanes;
+    bool ok = true;
+    for (int l = 0; l < lanes && ok; l++) {
+        ok = hipStreamBeginCapture(h->main_stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
+        if (!ok) break;
+        const RequestSlot* slot = h->d_slots + l;
+        int rc = each_batch(h, n, ~0ull, owner, [&](Gang& g, int64_t first, int nb, int64_t) {
+            return g.lane == l ? forward_batch(h, g, first, nb, nullptr, slot, h->main_stream) : ENS_OK;
+        });
+        CombineArgs c = combine_args(h, n, lanes);
+        c.slot = slot;
+        if (rc == ENS_OK && launch_combine(c, h->main_stream) != hipSuccess) rc = ENS_E_HIP;
+        hipGraph_t graph = nullptr;
+        ok = hipStreamEndCapture(h->main_stream, &graph) == hipSuccess && rc == ENS_OK && graph;
+        ok = ok && hipGraphInstantiate(&r.exec[l], graph, nullptr, nullptr, 0) == hipSuccess;
+        if (graph) (void)hipGraphDestroy(graph);
+    }
+    if (!ok) {
+        (void)hipGetLastError();
+        for (hipGraphExec_t& e : r.exec)
+            if (e) (void)hipGraphExecDestroy(e);
+        return nullptr;
+    }
+    if (h->graphs.size() >= GRAPHS_KEPT) {
+        auto old = std::min_element(h->graphs.begin(), h->graphs.end(), [](const RequestGraph& x, const RequestGraph& y) { return x.used < y.used; });
+        for (hipGraphExec_t& e : old->exec)
+            if (e) (void)hipGraphExecDestroy(e);
+        h->graphs.erase(old);
+    }
+    for (const Worker& w : h->workers) r.last_nb.push_back(w.last_nb);
+    h->graphs.push_back(r);
+    return &h->graphs.back();
+}
+
+// f(X, A) -> Y with Y on the device (or in pinned host memory).  The images are at d_images; when host_images is
+// given they are still to be copied there from host memory, segment by segment beside the kernels of the segments before.
+// `mask` selects the members that take part (all members for a real request; a single member when the BBS baseline
+// times it alone).  may_alloc false (the allocation-free entry point): the logits buffers are already in place and
+// nothing on the way may allocate or free device memory.  Returns with the work on the lanes: wait_lanes.
+static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_probs, uint64_t mask, bool may_alloc = true,
+                      const float* host_images = nullptr) {
+    if (n == 0) return ENS_OK;
+    cu_budget() = stream_share(h);
+    int rc = may_alloc ? ensure_buffers(h, n) : ENS_OK;
+    if (rc != ENS_OK) return rc;
+    if ((size_t)n > h->d_logits_rows) return ENS_E_INVALID;
+    const int M = (int)h->members.size();
+    const int seg = h->segment_size;
+    const int64_t n_seg = (n + seg - 1) / seg;
+    if (h->args_stale) {                                         // the logits moved
+        drop_graphs(h);
+        for (Gang& g : h->gangs) {
+            rc = build_launches(h, g, may_alloc);
+            if (rc != ENS_OK) return rc;
+        }
+        h->args_stale = false;
+    }
+    h->requests++;
+    const bool plain_only = !may_alloc || h->profiling || h->fake_predictor || h->one_stream || mask != ~0ull;
+    RequestGraph* graph = plain_only || (host_images && n_seg > 1) ? nullptr : find_graph(h, n);
+    // every segment id goes once to every member; a member's workers share its segments as they
+    // would by taking them from one queue, the faster worker more of them (planner.cpp, hand_out)
+    std::vector<std::vector<int32_t>> owner(M);
+    int lanes = graph ? graph->lanes : 0;
+    if (!graph) {
+        for (int c = 0; c < M; c++) {
+            std::vector<int32_t> batches;
+            const Gang* first = nullptr;
+            for (const Worker& w : h->workers)                   // in slot order = rank order
+                if (w.member == c) {
+                    batches.push_back(w.batch);
+                    if (w.rank == 0) first = &h->gangs[w.gang];
+                }
+            if (batches.size() <= 1 || !first) continue;
+            double flop = 0;
+            int launches = 1;
+            for (const Launch& L : first->launches)
+                if (L.kind != L_SKIP) { flop += L.flop; launches++; }
+            const double launch_cost = launches * 8e-6;          // a kernel of a small batch lasts about this long whatever it does
+            const double image_cost = flop / batches[0] / (h->members[c].bf16 ? 4e14 : 2e13);
+            rc = hand_out(n, seg, batches.data(), (int)batches.size(), launch_cost, image_cost, &owner[c]);
+            if (rc != ENS_OK) return rc;
+        }
+        int64_t launches = 0;
+        lanes = deal_lanes(h, n, mask, owner, &launches);
+        if (!plain_only && !(host_images && n_seg > 1) && launches <= GRAPH_MAX_LAUNCHES && seen_before(h, n))
+            graph = record_request(h, n, lanes, owner);
+    }
+    // one segment's images to the device, and the lanes' wait for them
+    const size_t image_floats = (size_t)h->base_h * h->base_w * 3;
+    auto bring_segment = [&](int64_t s) -> int {
+        const int64_t start = s * seg, end = std::min<int64_t>((s + 1) * seg, n);
+        HIP_TRY(hipMemcpyAsync((void*)(d_images + start * image_floats), host_images + start * image_floats,
+                               (size_t)(end - start) * image_floats * sizeof(float), hipMemcpyHostToDevice, h->main_stream));
+        while (h->copied.size() <= (size_t)s) {
+            hipEvent_t e = nullptr;
+            HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+            h->copied.push_back(e);
+        }
+        HIP_TRY(hipEventRecord(h->copied[s], h->main_stream));
+        for (int l = 0; l < lanes; l++) HIP_TRY(hipStreamWaitEvent(h->lanes[l], h->copied[s], 0));
+        return ENS_OK;
+    };
+    if (graph) {
+        if (host_images) {
+            rc = bring_segment(0);
+            if (rc != ENS_OK) return rc;
+        }
+        graph->used = h->requests;
+        for (int l = 0; l < lanes; l++) {
+            HIP_TRY(launch_bind_request(h->d_slots + l, d_images, d_probs, h->lanes[l]));
+            HIP_TRY(hipGraphLaunch(graph->exec[l], h->lanes[l]));
+        }
+        for (size_t w = 0; w < h->workers.size(); w++) h->workers[w].last_nb = graph->last_nb[w];
+        return ENS_OK;
+    }
+    int64_t here = host_images ? 0 : n_seg;                      // segments whose copies have been issued
+    rc = each_batch(h, n, mask, owner, [&](Gang& g, int64_t first, int nb, int64_t s) {
+        while (here <= s) {
+            const int e = bring_segment(here++);
+            if (e != ENS_OK) return e;
+        }
+        return forward_batch(h, g, first, nb, d_images, nullptr, h->lanes[g.lane]);
+    });
+    if (rc != ENS_OK) return rc;
+    if (mask == ~0ull || M == 1) {
+        CombineArgs c = combine_args(h, n, lanes);
+        c.y = d_probs;
+        for (int l = 0; l < lanes; l++) {
+            ProfRec r{prof_class(h, "combine_kernel"), nullptr, nullptr, 0.0, (double)n * h->classes * 4.0 * (M + 1)};
+            if (h->profiling && l == lanes - 1) {
+                r.start = take_event(h); r.stop = take_event(h);
+                if (!r.start || !r.stop) return ENS_E_HIP;
+                next_launch_events() = LaunchEvents{r.start, r.stop};
+            }
+            HIP_TRY(launch_combine(c, h->lanes[l]));
+            if (r.start) {
+                next_launch_events() = LaunchEvents{};
+                h->prof_recs.push_back(r);
+            }
         }
     }
     return ENS_OK;
+}
+
+// After a request that failed on the way: nothing of it is left in flight, and the arrivals are zeros again.
+static void recover(ens_handle* h) {
+    (void)hipDeviceSynchronize();
+    if (h->d_arrivals) (void)hipMemset(h->d_arrivals, 0, COMBINE_MAX_BLOCKS * sizeof(unsigned));
+    (void)hipGetLastError();
 }
 
 static int finish_profile(ens_handle* h) {
@@ -923,6 +1101,21 @@ static int ensure_calib(ens_handle* h, int64_t n) {
     return ENS_OK;
 }
 
+// Small requests from and to host memory: the staging kernels read the images in pinned host memory themselves (each
+// gang does, hence the product with their number) and the combination writes the probabilities there, instead of a
+// copy on a stream in front of the kernels and one behind them (10 us each, 20 and more from pageable memory).
+constexpr size_t DIRECT_IN_BYTES = 1280u << 10, DIRECT_OUT_BYTES = 256u << 10;
+
+static int grow_pinned(float** p, size_t* cap, size_t want_floats) {
+    if (want_floats <= *cap) return ENS_OK;
+    if (*p) (void)hipHostFree(*p);
+    *p = nullptr;
+    *cap = 0;
+    HIP_TRY(hipHostMalloc((void**)p, want_floats * sizeof(float), hipHostMallocNonCoherent));
+    *cap = want_floats;
+    return ENS_OK;
+}
+
 // Benchmark Mode on the installed allocation: median images/s of `repeats` runs after a warm-up.
 static int time_installed(ens_handle* h, int64_t n, int repeats, uint64_t mask, double* ips) {
     int rc = ensure_calib(h, n);
@@ -933,8 +1126,8 @@ static int time_installed(ens_handle* h, int64_t n, int repeats, uint64_t mask, 
     for (int i = 0; i < repeats + 1; i++) {
         const auto t0 = std::chrono::steady_clock::now();
         rc = run_device(h, h->d_calib, n, h->d_probs, mask);
-        if (rc != ENS_OK) return rc;
-        HIP_TRY(hipStreamSynchronize(h->main_stream));
+        if (rc != ENS_OK) { recover(h); return rc; }
+        HIP_TRY(wait_lanes(h));
         const auto t1 = std::chrono::steady_clock::now();
         if (i > 0) secs.push_back(std::chrono::duration<double>(t1 - t0).count());
     }
@@ -992,7 +1185,11 @@ int ens_load(const ens_member_spec* specs, int32_t n_members, uint64_t seed, ens
         }
     }
     if (hipStreamCreateWithFlags(&h->main_stream, hipStreamNonBlocking) != hipSuccess) return fail(ENS_E_HIP);
-    if (hipEventCreateWithFlags(&h->input_ready, hipEventDisableTiming) != hipSuccess) return fail(ENS_E_HIP);
+    if (acquire_lanes(h->lanes) != hipSuccess) return fail(ENS_E_HIP);
+    h->have_lanes = true;
+    if (hipMalloc((void**)&h->d_slots, LANES * sizeof(RequestSlot)) != hipSuccess) return fail(ENS_E_NOMEM);
+    if (hipMalloc((void**)&h->d_arrivals, COMBINE_MAX_BLOCKS * sizeof(unsigned)) != hipSuccess) return fail(ENS_E_NOMEM);
+    if (hipMemset(h->d_arrivals, 0, COMBINE_MAX_BLOCKS * sizeof(unsigned)) != hipSuccess) return fail(ENS_E_HIP);
     h->d_logits.assign(h->members.size(), nullptr);
     h->stage_klass = prof_class(h, "stage_kernel");
     *out = h;
@@ -1007,14 +1204,18 @@ void ens_free(ens_handle* h) {
         if (m.dev_params) (void)hipFree(m.dev_params);
     for (float* p : h->d_logits_heap)
         if (p) (void)hipFree(p);
-    if (h->d_logit_ptrs) (void)hipFree((void*)h->d_logit_ptrs);
+    if (h->d_slots) (void)hipFree(h->d_slots);
+    if (h->d_arrivals) (void)hipFree(h->d_arrivals);
+    if (h->pin_in) (void)hipHostFree(h->pin_in);
+    if (h->pin_out) (void)hipHostFree(h->pin_out);
     if (h->d_weights) (void)hipFree(h->d_weights);
     if (h->d_images) (void)hipFree(h->d_images);
     if (h->d_probs) (void)hipFree(h->d_probs);
     if (h->d_calib) (void)hipFree(h->d_calib);
     for (ProfRec& r : h->prof_recs) { (void)hipEventDestroy(r.start); (void)hipEventDestroy(r.stop); }
     for (hipEvent_t e : h->event_pool) (void)hipEventDestroy(e);
-    if (h->input_ready) (void)hipEventDestroy(h->input_ready);
+    for (hipEvent_t e : h->copied) (void)hipEventDestroy(e);
+    if (h->have_lanes) release_lanes(h->lanes);
     if (h->main_stream) (void)hipStreamDestroy(h->main_stream);
     delete h;
 }
@@ -1025,10 +1226,10 @@ int ens_set_io(ens_handle* h, int32_t base_h, int32_t base_w, int32_t images_on_
         if (h->d_calib) (void)hipFree(h->d_calib);
         h->d_calib = nullptr;
         h->d_calib_images = 0;
+        drop_graphs(h);                                          // the staging launches hold the image size
     }
     h->base_h = base_h;
     h->base_w = base_w;
-    h->bound_images = nullptr;
     h->images_on_device = images_on_device != 0;
     h->probs_on_device = probs_on_device != 0;
     return ENS_OK;
@@ -1047,26 +1248,38 @@ int ens_predict(ens_handle* h, const float* images, int64_t n, float* probs_out)
         if (rc != ENS_OK) return rc;
     }
     const auto t0 = std::chrono::steady_clock::now();
-    const size_t img_floats = (size_t)n * h->base_h * h->base_w * 3;
-    const float* d_in = images;
+    const size_t img_floats = (size_t)n * h->base_h * h->base_w * 3, out_floats = (size_t)n * h->classes;
+    const float *d_in = images, *host_in = nullptr;
     if (!h->images_on_device) {
-        int rc = grow(&h->d_images, &h->d_images_cap, img_floats);
-        if (rc != ENS_OK) return rc;
-        HIP_TRY(hipMemcpyAsync(h->d_images, images, img_floats * sizeof(float), hipMemcpyHostToDevice, h->main_stream));
-        d_in = h->d_images;
+        if (img_floats * sizeof(float) * h->gangs.size() <= DIRECT_IN_BYTES) {
+            int rc = grow_pinned(&h->pin_in, &h->pin_in_cap, img_floats);
+            if (rc != ENS_OK) return rc;
+            memcpy(h->pin_in, images, img_floats * sizeof(float));
+            d_in = h->pin_in;
+        } else {
+            int rc = grow(&h->d_images, &h->d_images_cap, img_floats);
+            if (rc != ENS_OK) return rc;
+            d_in = h->d_images;
+            host_in = images;
+        }
     }
     float* d_out = probs_out;
+    const bool direct_out = !h->probs_on_device && out_floats * sizeof(float) <= DIRECT_OUT_BYTES;
     if (!h->probs_on_device) {
-        int rc = grow(&h->d_probs, &h->d_probs_cap, (size_t)n * h->classes);
+        int rc = direct_out ? grow_pinned(&h->pin_out, &h->pin_out_cap, out_floats) : grow(&h->d_probs, &h->d_probs_cap, out_floats);
         if (rc != ENS_OK) return rc;
-        d_out = h->d_probs;
+        d_out = direct_out ? h->pin_out : h->d_probs;
     }
     if (h->profiling) reset_profile(h);
-    int rc = run_device(h, d_in, n, d_out, ~0ull);
-    if (rc != ENS_OK) { (void)hipDeviceSynchronize(); return rc; }
-    if (!h->probs_on_device)
-        HIP_TRY(hipMemcpyAsync(probs_out, d_out, (size_t)n * h->classes * sizeof(float), hipMemcpyDeviceToHost, h->main_stream));
-    HIP_TRY(hipStreamSynchronize(h->main_stream));
+    int rc = run_device(h, d_in, n, d_out, ~0ull, true, host_in);
+    if (rc != ENS_OK) { recover(h); return rc; }
+    HIP_TRY(wait_lanes(h));
+    if (direct_out) {
+        memcpy(probs_out, h->pin_out, out_floats * sizeof(float));
+    } else if (!h->probs_on_device) {
+        HIP_TRY(hipMemcpyAsync(probs_out, d_out, out_floats * sizeof(float), hipMemcpyDeviceToHost, h->main_stream));
+        HIP_TRY(hipStreamSynchronize(h->main_stream));
+    }
     if (h->profiling) finish_profile(h);
     h->last_n = n;
     h->last_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -1085,8 +1298,8 @@ int ens_predict_static(ens_handle* h, const float* d_images, int64_t n, float* d
     int rc = use_static_logits(h, n);
     if (rc != ENS_OK) return rc;
     rc = run_device(h, d_images, n, d_probs_out, ~0ull, false);
-    if (rc != ENS_OK) { (void)hipDeviceSynchronize(); return rc; }
-    HIP_TRY(hipStreamSynchronize(h->main_stream));
+    if (rc != ENS_OK) { recover(h); return rc; }
+    HIP_TRY(wait_lanes(h));
     h->last_n = n;
     h->last_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     return ENS_OK;
@@ -1312,6 +1525,7 @@ int ens_set_combination(ens_handle* h, int32_t rule, const float* weights) {
         HIP_TRY(hipMemcpy(h->d_weights, weights, h->members.size() * sizeof(float), hipMemcpyHostToDevice));
     }
     h->combine_rule = rule;
+    drop_graphs(h);                                              // they end in the combination
     return ENS_OK;
 }
 

@@ -136,13 +136,30 @@ struct Worker {
 struct Gang {
     std::vector<int> workers;      // indices into ens_handle::workers; [0] leads (its input tensor is shared)
     int rank = 0, of = 1;
-    hipStream_t stream = nullptr;
-    hipEvent_t done = nullptr;
+    int lane = 0;                  // lane of the request in flight
     std::vector<Launch> launches;
     StageArgs stage;
-    const StageArgs* d_stage = nullptr;
     char* d_args = nullptr;        // device block holding every argument array of the gang
     size_t d_args_bytes = 0;
+};
+
+// The streams that every handle of a process issues its kernels on, one set per GPU.  The runtime spreads ordinary
+// streams over four hardware queues in its own order, and streams that meet in a queue run one after the other: two of
+// an allocation's streams shared a queue while others stood empty (four streams in a row: two queues).  A stream made with
+// a compute-unit mask has a queue of its own; the mask names every unit.  Four of them: the GPU drains four queues
+// at once (eight take 1.8 times as long as four for the same work per queue, and many queues of short kernels are slower
+// than four), and gangs are dealt to them by estimated time.
+constexpr int LANES = 4;
+hipError_t acquire_lanes(hipStream_t* lanes);    // LANES streams; every successful call is paired with one of
+void release_lanes(const hipStream_t* lanes);    // these; the streams go with the last handle
+
+// A request of a size that came before, recorded: per lane every launch of it.
+struct RequestGraph {
+    int64_t n = 0;
+    uint64_t used = 0;             // for giving up the one used longest ago
+    int lanes = 0;
+    std::vector<int> last_nb;      // per worker: images of its last batch
+    hipGraphExec_t exec[LANES] = {nullptr, nullptr, nullptr, nullptr};
 };
 
 struct ProfClass {
@@ -167,23 +184,30 @@ struct ens_handle {
     int base_h = 0, base_w = 0, classes = 0;
     bool images_on_device = false, probs_on_device = false;
     uint64_t budget = 0;                         // 0: whatever the device has
-    hipStream_t main_stream = nullptr;
-    hipEvent_t input_ready = nullptr;
+    hipStream_t main_stream = nullptr;           // copies, and the recording of graphs
+    hipStream_t lanes[ens::LANES] = {nullptr, nullptr, nullptr, nullptr};
+    bool have_lanes = false;
+    std::vector<hipEvent_t> copied;              // per segment: its images are on the device
+    ens::RequestSlot* d_slots = nullptr;         // one per lane
+    unsigned* d_arrivals = nullptr;              // see CombineArgs
+    std::vector<ens::RequestGraph> graphs;
+    std::vector<std::pair<int64_t, uint64_t>> sizes_seen;   // request sizes and when they last came, not recorded (yet)
+    uint64_t requests = 0;
+    // pinned host memory for small requests: kernels read the images and write the probabilities there themselves
+    float* pin_in = nullptr;    size_t pin_in_cap = 0;
+    float* pin_out = nullptr;   size_t pin_out_cap = 0;
     // request buffers, grown on demand
     float* d_images = nullptr;  size_t d_images_cap = 0;
     float* d_probs = nullptr;   size_t d_probs_cap = 0;
-    // Per-member logits of the request in flight.  d_logits / d_logit_table are the buffers in use:
-    // either the library's own allocations (d_logits_heap, d_logit_ptrs; grown on demand) or, for the
+    // Per-member logits of the request in flight.  d_logits are the buffers in use:
+    // either the library's own allocations (d_logits_heap; grown on demand) or, for the
     // allocation-free entry point, slices of the fixed device array.
     std::vector<float*> d_logits; size_t d_logits_rows = 0;      // in use, and the rows they hold
     std::vector<float*> d_logits_heap; size_t d_logits_heap_rows = 0;
-    const float** d_logit_ptrs = nullptr;                        // device table of the heap pointers
-    const float** d_logit_table = nullptr;                       // device table of the pointers in use
     bool logits_static = false;
     int combine_rule = 0;                        // ENS_COMBINE_*
     float* d_weights = nullptr;                  // member weights of the weighted rule (device)
     float* d_calib = nullptr;   size_t d_calib_images = 0;
-    const float* bound_images = nullptr;         // request images the staging arguments point at
     int stage_klass = 0;
     int64_t last_n = 0;
     double last_ms = 0;

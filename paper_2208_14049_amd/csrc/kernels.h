@@ -106,8 +106,16 @@ __host__ __device__ inline int se_gate_offset(int c, int r, int cap) { return ca
 // Workgroups (of 256 lanes, one lane per 4 output columns x 8 channels) the summing depthwise kernel gives an image
 __host__ __device__ inline int dwconv_sums_blocks(int Ho, int Wo, int c) { return (Ho * ((Wo + 3) / 4) * (c / 8) + 255) / 256; }
 
+// Where a request's images and probabilities are.  Launches recorded into a graph read them from here (one block per
+// handle and lane, written by bind_request_kernel in front of the graph); others carry the pointers themselves.
+struct RequestSlot {
+    const float* src;
+    float* dst;
+};
+
 struct StageArgs {             // request images -> a worker's input tensor (convert, pad, resize)
-    const float* src;          // request images, n x sh x sw x 3 fp32
+    const float* src;          // request images, n x sh x sw x 3 fp32 (device memory, or pinned host memory)
+    const RequestSlot* slot;   // not null: the images are at slot->src instead
     void* dst;                 // nb x dh x dw x dc, dtype of the member; see s2d
     int nb, sh, sw, dh, dw, dc;
     // s2d != 0 (bf16, dc == 16): the dh x dw image is stored "space to depth", as
@@ -133,14 +141,25 @@ hipError_t launch_fc(const FcArgs& a, const FcArgs* argv, int G, int nb, long lo
 bool fc_mfma_applicable(const FcArgs& a);
 hipError_t launch_fc_mfma(const FcArgs& a, const FcArgs* argv, int G, int nb, long long first, hipStream_t s);
 hipError_t launch_se(const SeArgs& a, const SeArgs* argv, int G, int nb, bool bf16, hipStream_t s);
-hipError_t launch_stage(const StageArgs& a, const StageArgs* argv, int G, int nb, long long first, bool bf16, hipStream_t s);
-// Combination rule; logits: n_members pointers (device array).
+hipError_t launch_stage(const StageArgs& a, int nb, long long first, bool bf16, hipStream_t s);
+hipError_t launch_bind_request(RequestSlot* slot, const float* src, float* dst, hipStream_t s);
+// Combination rule over the members' logits.
 //   COMBINE_MEAN      Y[i, :] = sum_m softmax(logits_m[i, :]) / M
 //   COMBINE_WEIGHTED  Y[i, :] = sum_m weights[m] * softmax(logits_m[i, :])   (weights: device, n_members floats)
 //   COMBINE_VOTE      Y[i, c] = #{m : argmax logits_m[i, :] == c} / M        (lowest index on exact ties)
 enum { COMBINE_MEAN = 0, COMBINE_WEIGHTED = 1, COMBINE_VOTE = 2 };
-hipError_t launch_combine(const float* const* logits, const float* weights, int rule, int n_members, int64_t n,
-                          int classes, float* y, hipStream_t s);
+constexpr int COMBINE_MAX_MEMBERS = 64, COMBINE_MAX_BLOCKS = 1024;
+struct CombineArgs {
+    const float* logits[COMBINE_MAX_MEMBERS];
+    const float* weights;
+    float* y;                  // n x classes
+    const RequestSlot* slot;   // not null: y is slot->dst
+    unsigned* arrivals;        // COMBINE_MAX_BLOCKS zeros (left as zeros), used when lanes > 1
+    int lanes;                 // this many lanes issue the launch, each behind its share of the members
+    int n_members, classes, rule;
+    long long n;
+};
+hipError_t launch_combine(const CombineArgs& a, hipStream_t s);
 hipError_t launch_fill_noise(float* p, int64_t count, uint64_t seed, hipStream_t s);
 hipError_t launch_fill_zero(float* p, int64_t count, hipStream_t s);
 

@@ -92,9 +92,9 @@ __device__ __forceinline__ void stage_sample(const StageArgs& a, const float* __
 
 // One thread per destination pixel, written as dc channels (zero padded) in the member's dtype.
 template <bool BF16>
-__global__ void stage_kernel(const StageArgs* __restrict__ argv, const int nb_, const long long first) {
-    StageArgs a = argv[blockIdx.z];
+__global__ void stage_kernel(StageArgs a, const int nb_, const long long first) {
     a.nb = nb_;
+    if (a.slot) a.src = a.slot->src;
     a.src += first * a.sh * a.sw * 3;
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long total = (long long)a.nb * a.dh * a.dw;
@@ -121,9 +121,9 @@ __global__ void stage_kernel(const StageArgs* __restrict__ argv, const int nb_, 
 
 // Space-to-depth staging (bf16): one thread per destination pixel (r, q) gathers the 2x2 image
 // pixels (2r + by, 2q + bx) into channels (2*by + bx)*3 + c of a 16-channel pixel.
-__global__ void stage_s2d_kernel(const StageArgs* __restrict__ argv, const int nb_, const long long first) {
-    StageArgs a = argv[blockIdx.z];
+__global__ void stage_s2d_kernel(StageArgs a, const int nb_, const long long first) {
     a.nb = nb_;
+    if (a.slot) a.src = a.slot->src;
     a.src += first * a.sh * a.sw * 3;
     const int h2 = (a.dh + 1) / 2, w2 = (a.dw + 1) / 2;
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -148,18 +148,29 @@ __global__ void stage_s2d_kernel(const StageArgs* __restrict__ argv, const int n
     d[1] = pack8(f + 8);
 }
 
-hipError_t launch_stage(const StageArgs& a, const StageArgs* argv, int G, int nb, long long first, bool bf16, hipStream_t s) {
-    if (nb <= 0 || a.dc < 3 || G <= 0 || !argv) return hipErrorInvalidValue;
+hipError_t launch_stage(const StageArgs& a, int nb, long long first, bool bf16, hipStream_t s) {
+    if (nb <= 0 || a.dc < 3 || (!a.src && !a.slot)) return hipErrorInvalidValue;
     if (a.s2d) {
         if (!bf16 || a.dc != 16) return hipErrorInvalidValue;
         const long long px = (long long)nb * ((a.dh + 1) / 2) * ((a.dw + 1) / 2);
-        ENS_LAUNCH(stage_s2d_kernel, dim3(blocks_for(px, 256), 1, G), dim3(256), 0, s, argv, nb, first);
+        ENS_LAUNCH(stage_s2d_kernel, dim3(blocks_for(px, 256)), dim3(256), 0, s, a, nb, first);
         return hipGetLastError();
     }
     const long long total = (long long)nb * a.dh * a.dw;
-    const dim3 g(blocks_for(total, 256), 1, G);
-    if (bf16) ENS_LAUNCH(stage_kernel<true>, g, dim3(256), 0, s, argv, nb, first);
-    else ENS_LAUNCH(stage_kernel<false>, g, dim3(256), 0, s, argv, nb, first);
+    const dim3 g(blocks_for(total, 256));
+    if (bf16) ENS_LAUNCH(stage_kernel<true>, g, dim3(256), 0, s, a, nb, first);
+    else ENS_LAUNCH(stage_kernel<false>, g, dim3(256), 0, s, a, nb, first);
+    return hipGetLastError();
+}
+
+__global__ void bind_request_kernel(RequestSlot* slot, const float* src, float* dst) {
+    slot->src = src;
+    slot->dst = dst;
+}
+
+hipError_t launch_bind_request(RequestSlot* slot, const float* src, float* dst, hipStream_t s) {
+    if (!slot) return hipErrorInvalidValue;
+    ENS_LAUNCH(bind_request_kernel, dim3(1), dim3(1), 0, s, slot, src, dst);
     return hipGetLastError();
 }
 
@@ -1055,6 +1066,12 @@ hipError_t launch_se(const SeArgs& a, const SeArgs* argv, int G, int nb, bool bf
 // One wavefront per sample: for each member a max-subtracted softmax of its logits row
 // (wavefront shuffles for the maximum and the sum), each term divided by M and added in
 // member order, one write of the combined row.
+//
+// The members run on several lanes, and each lane ends with this launch.  A workgroup adds one to its place in
+// `arrivals` and goes on only if it is the last of the lanes' workgroups for those rows (it then puts the zero back);
+// the logits of the other lanes are in memory by then, since the kernels that wrote them ended before their lanes'
+// launch began, and none of their lines is in this workgroup's caches: nobody read them since.  That takes the place of
+// an event per lane and a wait for each of them in front of the combination (10 us of host time per lane).
 constexpr int COMBINE_MAX_PER_LANE = 32;    // classes <= 64 * 32
 
 __device__ __forceinline__ float wave_max(float v) {
@@ -1069,77 +1086,88 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 template <int PER, int RULE>
-__global__ __launch_bounds__(256) void combine_kernel(const float* const* logits, const float* __restrict__ weights,
-                                                      int n_members, long long n, int classes, float* y) {
-    const int lane = threadIdx.x & 63;
-    const long long row = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (row >= n) return;
-    float acc[PER];
-#pragma unroll
-    for (int e = 0; e < PER; e++) acc[e] = 0.f;
-    const float inv_m = 1.f / (float)n_members;
-    for (int m = 0; m < n_members; m++) {
-        const float* z = logits[m] + row * classes;
-        float v[PER];
-        float mx = -3.0e38f;
-        int arg = 0x7FFFFFFF;                        // class of this lane's maximum, lowest index first
-#pragma unroll
-        for (int e = 0; e < PER; e++) {
-            const int c = lane + 64 * e;
-            v[e] = c < classes ? z[c] : -3.0e38f;
-            if (RULE == COMBINE_VOTE && c < classes && (v[e] > mx || arg == 0x7FFFFFFF)) arg = c;
-            mx = fmaxf(mx, v[e]);
+__global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a) {
+    const int lane = threadIdx.x & 63, classes = a.classes, n_members = a.n_members;
+    if (a.lanes > 1) {
+        __shared__ unsigned before;
+        if (threadIdx.x == 0) {
+            before = __hip_atomic_fetch_add(&a.arrivals[blockIdx.x], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (before == (unsigned)a.lanes - 1u) __hip_atomic_store(&a.arrivals[blockIdx.x], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        if (RULE == COMBINE_VOTE) {
-            // arg-max over the wave: the larger value wins, the lower class on equal values
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                const float om = __shfl_xor(mx, off, 64);
-                const int oa = __shfl_xor(arg, off, 64);
-                if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
-            }
-#pragma unroll
-            for (int e = 0; e < PER; e++) acc[e] += lane + 64 * e == arg ? inv_m : 0.f;
-            continue;
-        }
-        mx = wave_max(mx);
-        float sum = 0.f;
-#pragma unroll
-        for (int e = 0; e < PER; e++) {
-            const int c = lane + 64 * e;
-            v[e] = c < classes ? expf(v[e] - mx) : 0.f;
-            sum += v[e];
-        }
-        sum = wave_sum(sum);
-        const float wm = RULE == COMBINE_WEIGHTED ? weights[m] : inv_m;
-#pragma unroll
-        for (int e = 0; e < PER; e++) acc[e] += (v[e] / sum) * wm;
+        __syncthreads();
+        if (before != (unsigned)a.lanes - 1u) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
+    float* __restrict__ const y = a.slot ? a.slot->dst : a.y;
+    const float* __restrict__ const weights = a.weights;
+    for (long long row = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); row < a.n; row += (long long)gridDim.x * (blockDim.x >> 6)) {
+        float acc[PER];
 #pragma unroll
-    for (int e = 0; e < PER; e++) {
-        const int c = lane + 64 * e;
-        if (c < classes) y[row * classes + c] = acc[e];
+        for (int e = 0; e < PER; e++) acc[e] = 0.f;
+        const float inv_m = 1.f / (float)n_members;
+        for (int m = 0; m < n_members; m++) {
+            const float* z = a.logits[m] + row * classes;
+            float v[PER];
+            float mx = -3.0e38f;
+            int arg = 0x7FFFFFFF;                        // class of this lane's maximum, lowest index first
+#pragma unroll
+            for (int e = 0; e < PER; e++) {
+                const int c = lane + 64 * e;
+                v[e] = c < classes ? z[c] : -3.0e38f;
+                if (RULE == COMBINE_VOTE && c < classes && (v[e] > mx || arg == 0x7FFFFFFF)) arg = c;
+                mx = fmaxf(mx, v[e]);
+            }
+            if (RULE == COMBINE_VOTE) {
+                // arg-max over the wave: the larger value wins, the lower class on equal values
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) {
+                    const float om = __shfl_xor(mx, off, 64);
+                    const int oa = __shfl_xor(arg, off, 64);
+                    if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
+                }
+#pragma unroll
+                for (int e = 0; e < PER; e++) acc[e] += lane + 64 * e == arg ? inv_m : 0.f;
+                continue;
+            }
+            mx = wave_max(mx);
+            float sum = 0.f;
+#pragma unroll
+            for (int e = 0; e < PER; e++) {
+                const int c = lane + 64 * e;
+                v[e] = c < classes ? expf(v[e] - mx) : 0.f;
+                sum += v[e];
+            }
+            sum = wave_sum(sum);
+            const float wm = RULE == COMBINE_WEIGHTED ? weights[m] : inv_m;
+#pragma unroll
+            for (int e = 0; e < PER; e++) acc[e] += (v[e] / sum) * wm;
+        }
+#pragma unroll
+        for (int e = 0; e < PER; e++) {
+            const int c = lane + 64 * e;
+            if (c < classes) y[row * classes + c] = acc[e];
+        }
     }
 }
 
 template <int RULE>
-static void launch_combine_rule(const float* const* logits, const float* weights, int n_members, int64_t n, int classes,
-                                float* y, hipStream_t s) {
-    const dim3 g((unsigned)((n + 3) / 4)), b(256);
-    const int per = (classes + 63) / 64;
-    if (per <= 1) ENS_LAUNCH((combine_kernel<1, RULE>), g, b, 0, s, logits, weights, n_members, (long long)n, classes, y);
-    else if (per <= 4) ENS_LAUNCH((combine_kernel<4, RULE>), g, b, 0, s, logits, weights, n_members, (long long)n, classes, y);
-    else if (per <= 16) ENS_LAUNCH((combine_kernel<16, RULE>), g, b, 0, s, logits, weights, n_members, (long long)n, classes, y);
-    else ENS_LAUNCH((combine_kernel<32, RULE>), g, b, 0, s, logits, weights, n_members, (long long)n, classes, y);
+static void launch_combine_rule(const CombineArgs& a, hipStream_t s) {
+    const long long blocks = (a.n + 3) / 4;
+    const dim3 g((unsigned)(blocks < COMBINE_MAX_BLOCKS ? blocks : COMBINE_MAX_BLOCKS)), b(256);
+    const int per = (a.classes + 63) / 64;
+    if (per <= 1) ENS_LAUNCH((combine_kernel<1, RULE>), g, b, 0, s, a);
+    else if (per <= 4) ENS_LAUNCH((combine_kernel<4, RULE>), g, b, 0, s, a);
+    else if (per <= 16) ENS_LAUNCH((combine_kernel<16, RULE>), g, b, 0, s, a);
+    else ENS_LAUNCH((combine_kernel<32, RULE>), g, b, 0, s, a);
 }
 
-hipError_t launch_combine(const float* const* logits, const float* weights, int rule, int n_members, int64_t n,
-                          int classes, float* y, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    if (n_members <= 0 || classes <= 0 || classes > 64 * COMBINE_MAX_PER_LANE) return hipErrorInvalidValue;
-    if (rule == COMBINE_MEAN) launch_combine_rule<COMBINE_MEAN>(logits, weights, n_members, n, classes, y, s);
-    else if (rule == COMBINE_WEIGHTED && weights) launch_combine_rule<COMBINE_WEIGHTED>(logits, weights, n_members, n, classes, y, s);
-    else if (rule == COMBINE_VOTE) launch_combine_rule<COMBINE_VOTE>(logits, weights, n_members, n, classes, y, s);
+hipError_t launch_combine(const CombineArgs& a, hipStream_t s) {
+    if (a.n <= 0) return hipSuccess;
+    if (a.n_members <= 0 || a.n_members > COMBINE_MAX_MEMBERS || a.classes <= 0 || a.classes > 64 * COMBINE_MAX_PER_LANE || a.lanes < 1) return hipErrorInvalidValue;
+    if ((!a.y && !a.slot) || (a.lanes > 1 && !a.arrivals)) return hipErrorInvalidValue;
+    if (a.rule == COMBINE_MEAN) launch_combine_rule<COMBINE_MEAN>(a, s);
+    else if (a.rule == COMBINE_WEIGHTED && a.weights) launch_combine_rule<COMBINE_WEIGHTED>(a, s);
+    else if (a.rule == COMBINE_VOTE) launch_combine_rule<COMBINE_VOTE>(a, s);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
