@@ -22,13 +22,15 @@ struct View {
 // Convolution (and its fused epilogue) over a batch of `nb` images.
 //   y[n, ho, wo, co] = act( scale[co] * sum_{kh,kw,ci} pre(x[n, ho*sh-pt+kh, wo*sw-pl+kw, ci]) * w[co][kh][kw][ci]
 //                           + bias[co] + res[n, ho, wo, co] )
-// Weights are stored [cout][kh][kw][cin] (K contiguous per output channel).  The batch-norm that
+// Weights are stored [cout][kh][kw][cin] (K contiguous per output channel) for bf16 members,
+// [kh][kw][cin][cout] for fp32 ones (conv_f32.hip).  The batch-norm that
 // follows the convolution is scale (gamma / sqrt(var + eps)) and bias (beta - mean * scale + the
 // layer's own bias * scale), both fp32 and applied to the fp32 sum: bf16 members keep the weights
 // exactly as given (folding the scale into them would round every weight a second time, an error
 // that is the same for all pixels of a channel and does not average out); fp32 members have the
 // scale folded into the weights and a scale of ones.  pre_scale / pre_shift (fp32, per input
 // channel) apply relu(x * scale + shift) to in-bounds inputs when non-null.
+constexpr int CONV_F32_TILE = 16;   // output channels of the widest fp32 tile: readable floats behind the fp32 weights
 struct ConvArgs {
     View x, y, res;            // res.p == nullptr: no residual
     const void* w;

@@ -1,4 +1,4 @@
-// Bandwidth-bound layers and the fp32 reference-precision convolution:
+// Bandwidth-bound layers:
 // input staging (convert / pad / bilinear resize), depthwise convolution, pooling, global
 // average pool, squeeze-excite, the FC head and the fused softmax-and-mean combination.
 // Activations are NHWC; the bf16 kernels move 8 channels (16 bytes) per lane so that a
@@ -14,12 +14,7 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
     u += 0x7FFFu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
 }
-// fp32 members: the exponential at full precision (the fast one is for results that are rounded to bf16)
-__device__ __forceinline__ float act_f(float v, int act) {
-    if (act == ACT_RELU) return fmaxf(v, 0.f);
-    if (act == ACT_SILU) return v / (1.f + expf(-v));
-    return v;
-}
+// FAST: for results that are rounded to bf16; fp32 members take the exponential at full precision
 template <bool FAST>
 __device__ __forceinline__ float exp_neg(float v) { return FAST ? __expf(-v) : expf(-v); }
 // SiLU of a value that is rounded to bf16 afterwards: fast exponential, hardware reciprocal (an IEEE division is ten
@@ -171,50 +166,6 @@ __global__ void bind_request_kernel(RequestSlot* slot, const float* src, float* 
 hipError_t launch_bind_request(RequestSlot* slot, const float* src, float* dst, hipStream_t s) {
     if (!slot) return hipErrorInvalidValue;
     ENS_LAUNCH(bind_request_kernel, dim3(1), dim3(1), 0, s, slot, src, dst);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ fp32 convolution
-// Reference-precision path (fp32 members): one thread per output element, taps and input
-// channels accumulated in the order kh, kw, ci.  Weights [cout][kh][kw][cin] fp32.
-__global__ void conv_f32_kernel(const ConvArgs* __restrict__ argv, const int nb_) {
-    ConvArgs a = argv[blockIdx.z];
-    a.nb = nb_;
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long total = (long long)a.nb * a.Ho * a.Wo * a.cout;
-    if (idx >= total) return;
-    const int co = (int)(idx % a.cout);
-    const long long p = idx / a.cout;
-    const int wo = (int)(p % a.Wo), ho = (int)((p / a.Wo) % a.Ho);
-    const long long n = p / ((long long)a.Wo * a.Ho);
-    const float* x = (const float*)a.x.p + n * (long long)a.H * a.W * a.x.stride + a.x.c0;
-    const float* w = (const float*)a.w + (long long)co * a.kh * a.kw * a.cin;
-    float acc = 0.f;
-    for (int kh = 0; kh < a.kh; kh++) {
-        const int hi = ho * a.sh - a.pt + kh;
-        if (hi < 0 || hi >= a.H) continue;
-        for (int kw = 0; kw < a.kw; kw++) {
-            const int wi = wo * a.sw - a.pl + kw;
-            if (wi < 0 || wi >= a.W) continue;
-            const float* px = x + ((long long)hi * a.W + wi) * a.x.stride;
-            const float* wk = w + (kh * a.kw + kw) * a.cin;
-            for (int ci = 0; ci < a.cin; ci++) {
-                float v = px[ci];
-                if (a.pre_scale) v = fmaxf(v * a.pre_scale[ci] + a.pre_shift[ci], 0.f);
-                acc = fmaf(v, wk[ci], acc);
-            }
-        }
-    }
-    acc = fmaf(acc, a.scale[co], a.bias[co]);        // fp32 members: the scale is in the weights and this one is 1
-    if (a.res.p) acc += ((const float*)a.res.p)[p * a.res.stride + a.res.c0 + co];
-    ((float*)a.y.p)[p * a.y.stride + a.y.c0 + co] = act_f(acc, a.act);
-}
-
-hipError_t launch_conv_f32(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s) {
-    if (nb <= 0 || a.cin <= 0 || a.cout <= 0 || !a.bias || G <= 0 || !argv) return hipErrorInvalidValue;
-    const long long total = (long long)nb * a.Ho * a.Wo * a.cout;
-    if (total >= (1LL << 31) * 256) return hipErrorInvalidValue;
-    ENS_LAUNCH(conv_f32_kernel, dim3(blocks_for(total, 256), 1, G), dim3(256), 0, s, argv, nb);
     return hipGetLastError();
 }
 

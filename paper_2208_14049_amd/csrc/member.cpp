@@ -247,6 +247,13 @@ int build_member(const ens_member_spec& spec, const float* params, Member* out) 
                                 wf[((size_t)co * o.kh * o.kw + k) * pl.cin_s + ci0 + ci] =
                                     w[((size_t)k * ig + ci) * o.cout + co] * wscale[co];
                     }
+                } else if (!m.bf16) {
+                    // fp32: the blob's own order, [kh][kw][cin][cout], with the scale folded in; what a tile of channels
+                    // past the last one reads behind them
+                    const int64_t rows = (int64_t)o.kh * o.kw * o.cin;
+                    wf.assign((size_t)(rows * o.cout + CONV_F32_TILE), 0.f);
+                    for (int64_t k = 0; k < rows; k++)
+                        for (int co = 0; co < o.cout; co++) wf[(size_t)(k * o.cout + co)] = w[k * o.cout + co] * wscale[co];
                 } else {
                     wf.assign((size_t)o.cout * o.kh * o.kw * pl.cin_s, 0.f);
                     for (int co = 0; co < o.cout; co++)
