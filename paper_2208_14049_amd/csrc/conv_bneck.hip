@@ -457,6 +457,7 @@ bool conv_bneck_applicable(const ConvArgs& a1, const ConvArgs& a2, const ConvArg
     // A workgroup runs its tile's three layers one after the other, so a handful of tiles leaves the
     // chip to a handful of workgroups; the separate kernels split the channels too.  Measured on a
     // ResNet-50-shaped member the one kernel wins from about two dozen tiles on (batch 4 at 28x28).
+    if (conv_small_layers(a1, nb, G)) return false;
     long long least = BNECK_MIN_TILES;
     return (long long)pl.tiles * G >= least;
 }

@@ -266,6 +266,14 @@ bool conv_pw_applicable(const ConvArgs& a, int nb, int G);
 const char* conv_pw_name(const ConvArgs& a, int G);
 hipError_t launch_conv_pw(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s);
 
+// Any convolution of few output pixels, K split over the wavefronts of small tiles; defined in conv_small.hip.
+// conv_small_pick returns the tile that runs the layer, or -1 when another kernel does; conv_small_layers says whether
+// layers on this many output pixels are better off one by one on it than fused with their neighbours.
+int conv_small_pick(const ConvArgs& a, int nb, int G);
+bool conv_small_layers(const ConvArgs& a, int nb, int G);
+const char* conv_small_name(const ConvArgs& a);
+hipError_t launch_conv_small(const ConvArgs& a, const ConvArgs* argv, int G, int nb, int variant, hipStream_t s);
+
 // 3x3 stride-1 kernel with the input window resident in LDS; defined in conv_halo.hip.
 // conv_halo_pick returns the variant that runs the layer, or -1 when the generic kernel does.
 int conv_halo_pick(const ConvArgs& a, int nb, int G);

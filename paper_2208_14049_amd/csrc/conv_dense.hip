@@ -390,6 +390,7 @@ static bool dense_plan(const ConvArgs& a1, const ConvArgs& a2, int nb, int G, De
 bool conv_dense_applicable(const ConvArgs& a1, const ConvArgs& a2, int nb, int G) {
     DensePlan pl;
     if (!dense_plan(a1, a2, nb, G, &pl)) return false;
+    if (conv_small_layers(a1, nb, G)) return false;
     long long least = DENSE_MIN_TILES;
     return (long long)pl.tiles * G >= least;
 }

@@ -461,7 +461,9 @@ static bool pre_in_dma_kernel(const ConvArgs& a) {
 
 const char* conv_bf16_variant_name(const ConvArgs& a, int G) {
     const long long P = (long long)a.nb * a.Ho * a.Wo;
+    if (conv_small_pick(a, a.nb, G) >= 0) return conv_small_name(a);
     if (a.pre_scale && !pre_in_dma_kernel(a)) return conv_regstage_name(a, (int)P);
+    if (a.pair) return VARIANTS[pick_variant(a, P, (long long)a.kh * a.kw * a.cin, G)].name;
     if (conv_pw_applicable(a, a.nb, G)) return conv_pw_name(a, G);
     if (conv_taps_applicable(a, a.nb)) return conv_taps_name(a);
     if (conv_wreg_applicable(a, a.nb, G)) return conv_wreg_name(a);
@@ -511,11 +513,14 @@ hipError_t launch_conv_bf16(const ConvArgs& a, const ConvArgs* argv, int G, int 
     if (P64 <= 0 || P64 >= (1LL << 31) || K64 >= (1LL << 31)) return hipErrorInvalidValue;
     const int P = (int)P64;
     if (a.gate && (a.pre_scale || !conv_pw_applicable(a, nb, G))) return hipErrorInvalidValue;   // only the 1x1 kernel applies a gate
+    if (const int sv = conv_small_pick(a, nb, G); sv >= 0) return launch_conv_small(a, argv, G, nb, sv, s);
     if (a.pre_scale && !pre_in_dma_kernel(a)) return launch_conv_regstage(a, argv, G, nb, P, s);
-    if (conv_pw_applicable(a, nb, G)) return launch_conv_pw(a, argv, G, nb, s);
-    if (conv_taps_applicable(a, nb)) return launch_conv_taps(a, argv, G, nb, s);
-    if (conv_wreg_applicable(a, nb, G)) return launch_conv_wreg(a, argv, G, nb, s);
-    if (const int hv = conv_halo_pick(a, nb, G); hv >= 0) return launch_conv_halo(a, argv, G, nb, hv, s);
+    if (!a.pair) {                                               // the generic kernel takes pairs
+        if (conv_pw_applicable(a, nb, G)) return launch_conv_pw(a, argv, G, nb, s);
+        if (conv_taps_applicable(a, nb)) return launch_conv_taps(a, argv, G, nb, s);
+        if (conv_wreg_applicable(a, nb, G)) return launch_conv_wreg(a, argv, G, nb, s);
+        if (const int hv = conv_halo_pick(a, nb, G); hv >= 0) return launch_conv_halo(a, argv, G, nb, hv, s);
+    }
     // byte offsets inside the kernel are unsigned 32-bit, 0xFFFFFFF0 stands for 'out of range'
     if ((long long)nb * a.H * a.W * a.x.stride >= 0x7FFFFF00LL || (long long)a.cout * K64 >= 0x70000000LL || a.kh > 16 || a.kw > 16) return hipErrorInvalidValue;
     int variant = pick_variant(a, P64, K64, G);

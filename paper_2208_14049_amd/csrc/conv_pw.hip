@@ -269,7 +269,7 @@ static bool pw_shape_ok(const ConvArgs& a, int nb) {
     if (a.kh != 1 || a.kw != 1 || a.pt != 0 || a.pl != 0 || a.sh < 1 || a.sw < 1) return false;
     if (a.Ho != (a.H - 1) / a.sh + 1 || a.Wo != (a.W - 1) / a.sw + 1) return false;
     if ((a.sh != 1 || a.sw != 1) && a.gate) return false;       // the gates are looked up by the input's image, which a tile finds from its output pixels
-    if (a.pre_scale || !a.wpk || a.cin % 8 || a.cout % 8) return false;
+    if (a.pre_scale || !a.wpk || a.pair || a.cin % 8 || a.cout % 8) return false;
     // 32-bit byte offsets with 2^31 standing for 'outside'
     const long long P = (long long)nb * a.Ho * a.Wo, Pin = (long long)nb * a.H * a.W;
     if (Pin * a.x.stride * 2 >= 0x7FFFFF00LL || P * a.y.stride * 2 >= 0x7FFFFF00LL) return false;

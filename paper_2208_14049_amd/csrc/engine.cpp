@@ -69,8 +69,9 @@ static bool same_network(const Member& a, const Member& b) {
 }
 
 // Fills one member's argument block for operation `pl`; `L` receives kind, class and work.
+// `images`: the batch size the launch is planned for (tile choices and names; work is counted at the worker's full batch).
 // `sub`: which of the operation's pl.sub argument blocks (sub-convolutions of a grouped convolution)
-static int fill_args(ens_handle* h, const Worker& w, const Worker& leader, int G, const OpPlan& pl, Launch& L, int sub = 0) {
+static int fill_args(ens_handle* h, const Worker& w, const Worker& leader, int G, int images, const OpPlan& pl, Launch& L, int sub = 0) {
     const Member& m = h->members[w.member];
     const int es = m.bf16 ? 2 : 4;
     const ens_op& o = pl.op;
@@ -93,13 +94,15 @@ static int fill_args(ens_handle* h, const Worker& w, const Worker& leader, int G
             a.pre_shift = pl.pre_shift != SIZE_MAX ? (const float*)(P + pl.pre_shift) : nullptr;
             a.ws = nullptr; a.ws_floats = 0;
             a.gate = nullptr; a.gate_stride = 0;
+            a.pair = 0;
+            a.few = 2 * images <= w.batch;
             a.zeros = P + m.zeros_off;
             a.wpk = pl.w_packed != SIZE_MAX ? P + pl.w_packed : nullptr;
             if (w.layout.scratch_offset != SIZE_MAX) {
                 a.ws = (float*)(w.arena + w.layout.scratch_offset);
                 a.ws_floats = (long long)SPLIT_WS_FLOATS;
             }
-            a.nb = w.batch; a.H = ts.h; a.W = ts.w; a.cin = pl.cin_s; a.Ho = td.h; a.Wo = td.w; a.cout = pl.sub_cout;
+            a.nb = images; a.H = ts.h; a.W = ts.w; a.cin = pl.cin_s; a.Ho = td.h; a.Wo = td.w; a.cout = pl.sub_cout;
             a.kh = o.kh; a.kw = o.kw; a.sh = o.sh; a.sw = o.sw; a.pt = o.pt; a.pl = o.pl; a.act = o.act;
             a.inv_hw = 1.0 / ((double)td.h * td.w); a.inv_w = 1.0 / (double)td.w;
             L.sub = pl.sub;
@@ -129,7 +132,7 @@ static int fill_args(ens_handle* h, const Worker& w, const Worker& leader, int G
             a.w = o.kind == ENS_OP_DWCONV ? P + pl.w : nullptr;
             a.bias = o.kind == ENS_OP_DWCONV ? (const float*)(P + pl.b) : nullptr;
             a.scale = o.kind == ENS_OP_DWCONV ? (const float*)(P + pl.scale) : nullptr;
-            a.nb = w.batch; a.H = ts.h; a.W = ts.w; a.c = o.cin; a.Ho = td.h; a.Wo = td.w;
+            a.nb = images; a.H = ts.h; a.W = ts.w; a.c = o.cin; a.Ho = td.h; a.Wo = td.w;
             a.kh = o.kh; a.kw = o.kw; a.sh = o.sh; a.sw = o.sw; a.pt = o.pt; a.pl = o.pl;
             a.act = o.kind == ENS_OP_DWCONV ? o.act : ACT_NONE;  // a pool has none of its own
             a.sums = nullptr; a.sums_stride = 0;
@@ -147,7 +150,7 @@ static int fill_args(ens_handle* h, const Worker& w, const Worker& leader, int G
             a.y = (float*)(w.arena + w.layout.offset[o.dst]) + o.dst_c0;
             a.pre_scale = pl.pre_scale != SIZE_MAX ? (const float*)(P + pl.pre_scale) : nullptr;
             a.pre_shift = pl.pre_shift != SIZE_MAX ? (const float*)(P + pl.pre_shift) : nullptr;
-            a.nb = w.batch; a.HW = ts.h * ts.w; a.c = o.cin;
+            a.nb = images; a.HW = ts.h * ts.w; a.c = o.cin;
             if (td.c != o.cin) return ENS_E_UNSUPPORTED;         // the pooled vector is dense
             L.bytes = nb * (double)ts.h * ts.w * o.cin * es;
             L.klass = prof_class(h, "gap_kernel");
@@ -161,7 +164,7 @@ static int fill_args(ens_handle* h, const Worker& w, const Worker& leader, int G
             a.wpk = pl.w_packed != SIZE_MAX ? P + pl.w_packed : nullptr;
             a.bias = (const float*)(P + pl.b);
             a.y = h->d_logits[w.member];                         // rows of the whole request
-            a.nb = w.batch; a.cin = o.cin; a.cout = o.cout; a.ldy = o.cout;
+            a.nb = images; a.cin = o.cin; a.cout = o.cout; a.ldy = o.cout;
             L.flop = 2.0 * nb * o.cin * o.cout;
             L.bytes = (double)o.cin * o.cout * es + nb * (o.cin + o.cout) * 4.0;
             L.klass = prof_class(h, m.bf16 && fc_mfma_applicable(a) ? "fc_mfma_bf16" : "fc_kernel");
@@ -175,7 +178,7 @@ static int fill_args(ens_handle* h, const Worker& w, const Worker& leader, int G
             a.w1 = (const float*)(P + pl.w); a.b1 = (const float*)(P + pl.b);
             a.w2 = (const float*)(P + pl.w2); a.b2 = (const float*)(P + pl.b2);
             a.scratch = (float*)(w.arena + w.layout.offset[pl.scratch]);
-            a.nb = w.batch; a.HW = ts.h * ts.w; a.c = o.cin; a.r = o.r;
+            a.nb = images; a.HW = ts.h * ts.w; a.c = o.cin; a.r = o.r;
             a.gate_only = 0;
             a.cap = pl.se_cap; a.have_sums = 0;
             L.flop = 4.0 * nb * o.cin * o.r;
@@ -189,25 +192,51 @@ static int fill_args(ens_handle* h, const Worker& w, const Worker& leader, int G
     return ENS_OK;
 }
 
-// Translates the gang's operations into kernel argument arrays in device memory.
-// may_alloc false: the device block of the gang must already be large enough (it is once the
-// allocation has been installed); the function then only rewrites it.
-static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
+// Which operations of a gang's member run together, for batches of up to `images` images.
+struct Fusions {
+    bool few = false;              // the batches do not fill half of the worker's batch size
+    std::vector<char> chain, fused, gated, summed, swapped;
+    bool operator==(const Fusions& o) const {
+        return few == o.few && chain == o.chain && fused == o.fused && gated == o.gated && summed == o.summed && swapped == o.swapped;
+    }
+};
+
+// The pooled output of a stem in the convolution's argument form.
+static ConvArgs pool_as_conv(ens_handle* h, const Worker& w, const OpPlan& pl, int images) {
+    const Member& mw = h->members[w.member];
+    ConvArgs p;
+    memset(&p, 0, sizeof(p));
+    p.y = view_of(w, w, mw, pl.op.dst, pl.op.dst_c0);
+    p.Ho = mw.tensors[pl.op.dst].h;
+    p.Wo = mw.tensors[pl.op.dst].w;
+    p.nb = images;
+    return p;
+}
+
+// Turns the arguments of a 1x1 convolution round: its input is the squeeze-excite block's, times the block's gates.
+static void gate_args(ens_handle* h, const Worker& w, const Worker& leader, const OpPlan& se, ConvArgs& c) {
+    const Member& mw = h->members[w.member];
+    c.x = view_of(w, leader, mw, se.op.src, se.op.src_c0);
+    c.gate = (const float*)(w.arena + w.layout.offset[se.scratch]) + se_gate_offset(se.op.cin, se.op.r, se.se_cap);
+    c.gate_stride = se_scratch_floats(se.op.cin, se.op.r, se.se_cap);
+}
+
+static Fusions decide_fusions(ens_handle* h, Gang& g, int images) {
     const Worker& leader = h->workers[g.workers[0]];
     const Member& m = h->members[leader.member];
     const int G = (int)g.workers.size();
-    const size_t slot = 512;                                     // bytes reserved per argument block
-    static_assert(sizeof(ConvArgs) <= 512 && sizeof(PoolArgs) <= 512 && sizeof(SeArgs) <= 512, "argument block");
+    Fusions F;
+    F.few = 2 * images <= leader.batch;
+    std::vector<char>&chain = F.chain, &fused = F.fused, &gated = F.gated, &summed = F.summed, &swapped = F.swapped;
+    auto fill = [&](size_t i, Launch& L) { return fill_args(h, leader, leader, G, images, m.ops[i], L) == ENS_OK; };
     // Which bottlenecks run as one kernel: planned as such and within the kernel's shapes at this batch
     // size.  The tensors in between are then not written (not wanted when they are to be read back).
-    std::vector<char> chain(m.ops.size(), 0);                    // 1: runs the next two operations too, 2: run by it
+    chain.assign(m.ops.size(), 0);                               // 1: runs the next two operations too, 2: run by it
     for (size_t i = 0; i + 2 < m.ops.size(); i++) {
         if (!m.ops[i].fuse_chain || h->keep_tensors) continue;
         Launch a, b, c;
-        if (fill_args(h, leader, leader, G, m.ops[i], a) != ENS_OK || fill_args(h, leader, leader, G, m.ops[i + 1], b) != ENS_OK ||
-            fill_args(h, leader, leader, G, m.ops[i + 2], c) != ENS_OK)
-            continue;
-        if (conv_bneck_applicable(a.conv, b.conv, c.conv, leader.batch, G)) {
+        if (!fill(i, a) || !fill(i + 1, b) || !fill(i + 2, c)) continue;
+        if (conv_bneck_applicable(a.conv, b.conv, c.conv, images, G)) {
             chain[i] = 1;
             chain[i + 1] = chain[i + 2] = 2;
         }
@@ -216,73 +245,61 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
     for (size_t i = 0; i + 1 < m.ops.size(); i++) {
         if (!m.ops[i].fuse_dense || h->keep_tensors || chain[i] || chain[i + 1]) continue;
         Launch a, b;
-        if (fill_args(h, leader, leader, G, m.ops[i], a) != ENS_OK || fill_args(h, leader, leader, G, m.ops[i + 1], b) != ENS_OK) continue;
-        if (conv_dense_applicable(a.conv, b.conv, leader.batch, G)) {
+        if (!fill(i, a) || !fill(i + 1, b)) continue;
+        if (conv_dense_applicable(a.conv, b.conv, images, G)) {
             chain[i] = 3;
             chain[i + 1] = 2;
         }
     }
     // The stem and the max-pool behind it as one kernel: chain[] 4 marks the stem, 2 the pool it runs
-    auto pool_as_conv = [&](const Worker& w, const OpPlan& pl) {   // the pooled output in the convolution's argument form
-        const Member& mw = h->members[w.member];
-        ConvArgs p;
-        memset(&p, 0, sizeof(p));
-        p.y = view_of(w, leader, mw, pl.op.dst, pl.op.dst_c0);
-        p.Ho = mw.tensors[pl.op.dst].h;
-        p.Wo = mw.tensors[pl.op.dst].w;
-        p.nb = w.batch;
-        return p;
-    };
     for (size_t i = 0; i + 1 < m.ops.size(); i++) {
         if (!m.ops[i].fuse_pool || h->keep_tensors || chain[i] || chain[i + 1]) continue;
         Launch a;
-        if (fill_args(h, leader, leader, G, m.ops[i], a) != ENS_OK) continue;
-        if (conv_stempool_applicable(a.conv, pool_as_conv(leader, m.ops[i + 1]), leader.batch, G)) {
+        if (!fill(i, a)) continue;
+        if (conv_stempool_applicable(a.conv, pool_as_conv(h, leader, m.ops[i + 1], images), images, G)) {
             chain[i] = 4;
             chain[i + 1] = 2;
         }
     }
-    // Which pairs of convolutions run as one launch: planned as such, and both on the generic kernel
-    // for this batch size (its workgroups read every field of their own argument block).
-    std::vector<char> fused(m.ops.size(), 0);                    // 1: takes the next operation along, 2: taken along
+    // Which pairs of convolutions run as one launch: planned as such, and both on the generic kernel or both on the one
+    // for few pixels at this batch size (their workgroups read every field of their own argument block).
+    fused.assign(m.ops.size(), 0);                               // 1: takes the next operation along, 2: taken along
     for (size_t i = 0; i + 1 < m.ops.size(); i++) {
         if (!m.ops[i].fuse_next || chain[i] || chain[i + 1]) continue;   // a bottleneck kernel takes precedence
         Launch a, b;
-        if (fill_args(h, leader, leader, G, m.ops[i], a) != ENS_OK || fill_args(h, leader, leader, G, m.ops[i + 1], b) != ENS_OK) continue;
-        a.conv.wpk = b.conv.wpk = nullptr;                       // a pair runs on the generic kernel
-        const char* generic = "conv_igemm_bf16";
-        if (strncmp(conv_bf16_variant_name(a.conv, 2 * G), generic, strlen(generic)) == 0 &&
-            strncmp(conv_bf16_variant_name(b.conv, 2 * G), generic, strlen(generic)) == 0) {
+        if (!fill(i, a) || !fill(i + 1, b)) continue;
+        auto both_on = [&](const char* kernel) {
+            return strncmp(conv_bf16_variant_name(a.conv, 2 * G), kernel, strlen(kernel)) == 0 &&
+                   strncmp(conv_bf16_variant_name(b.conv, 2 * G), kernel, strlen(kernel)) == 0;
+        };
+        a.conv.wpk = b.conv.wpk = nullptr;                       // the 1x1 kernel runs no pairs
+        bool pair = both_on("conv_igemm_bf16");
+        a.conv.pair = b.conv.pair = 1;
+        if (pair || both_on("conv_small_bf16")) {
             fused[i] = 1;
             fused[i + 1] = 2;
         }
     }
     // Squeeze-excite blocks that stop at the gates, which the 1x1 convolution behind them applies to its
-    // input: gated[] 1 marks the block, 2 the convolution.  gate_args turns the convolution's arguments round.
-    std::vector<char> gated(m.ops.size(), 0);
-    auto gate_args = [&](const Worker& w, const OpPlan& se, ConvArgs& c) {
-        const Member& mw = h->members[w.member];
-        c.x = view_of(w, leader, mw, se.op.src, se.op.src_c0);
-        c.gate = (const float*)(w.arena + w.layout.offset[se.scratch]) + se_gate_offset(se.op.cin, se.op.r, se.se_cap);
-        c.gate_stride = se_scratch_floats(se.op.cin, se.op.r, se.se_cap);
-    };
+    // input: gated[] 1 marks the block, 2 the convolution.
+    gated.assign(m.ops.size(), 0);
     for (size_t i = 0; i + 1 < m.ops.size(); i++) {
         if (!m.ops[i].fuse_gate || h->keep_tensors || chain[i] || chain[i + 1] || fused[i] || fused[i + 1]) continue;
         Launch c;
-        if (fill_args(h, leader, leader, G, m.ops[i + 1], c) != ENS_OK) continue;
-        gate_args(leader, m.ops[i], c.conv);
-        if (c.conv.wpk && conv_pw_applicable(c.conv, leader.batch, G)) {
+        if (!fill(i + 1, c)) continue;
+        gate_args(h, leader, leader, m.ops[i], c.conv);
+        if (c.conv.wpk && conv_pw_applicable(c.conv, images, G)) {
             gated[i] = 1;
             gated[i + 1] = 2;
         }
     }
     // Depthwise convolutions whose kernel leaves the channel sums for the squeeze-excite block behind them:
     // summed[] 1 marks the convolution, 2 the block.
-    std::vector<char> summed(m.ops.size(), 0);
+    summed.assign(m.ops.size(), 0);
     for (size_t i = 0; i + 1 < m.ops.size(); i++) {
         if (!m.ops[i].fuse_sums || h->keep_tensors || m.ops[i + 1].op.kind != ENS_OP_SE) continue;
         Launch d;
-        if (fill_args(h, leader, leader, G, m.ops[i], d) != ENS_OK) continue;
+        if (!fill(i, d)) continue;
         if (dwconv_sums_applicable(d.pool, m.bf16) && dwconv_sums_blocks(d.pool.Ho, d.pool.Wo, d.pool.c) <= m.ops[i + 1].se_cap) {
             summed[i] = 1;
             summed[i + 1] = 2;
@@ -290,7 +307,7 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
     }
     // Average pools that change places with the 1x1 convolution behind them: swapped[] 1 marks the pool's place
     // (the convolution runs there), 2 the convolution's (the pool runs there, on the convolution's channels).
-    std::vector<char> swapped(m.ops.size(), 0);
+    swapped.assign(m.ops.size(), 0);
     for (size_t i = 0; i + 1 < m.ops.size(); i++) {
         if (!m.ops[i].swap_pool || h->keep_tensors || chain[i] || chain[i + 1] || fused[i] || fused[i + 1] || gated[i + 1]) continue;
         swapped[i] = 1;
@@ -305,29 +322,41 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
         swapped[i] = 3;
         swapped[i + 1] = 4;
     }
+    return F;
+}
+
+constexpr size_t ARG_SLOT = 512;                                 // bytes reserved per argument block
+static_assert(sizeof(ConvArgs) <= ARG_SLOT && sizeof(PoolArgs) <= ARG_SLOT && sizeof(SeArgs) <= ARG_SLOT, "argument block");
+
+// The launches of a gang for batches of up to `images` images, their argument blocks appended to `blocks`; d_argv holds
+// offsets into `blocks` until the caller knows where they are on the device.
+static int build_plan(ens_handle* h, Gang& g, int images, const Fusions& F, std::vector<Launch>& launches, std::vector<char>& blocks) {
+    const Worker& leader = h->workers[g.workers[0]];
+    const Member& m = h->members[leader.member];
+    const int G = (int)g.workers.size();
+    const size_t slot = ARG_SLOT;
+    const std::vector<char>&chain = F.chain, &fused = F.fused, &gated = F.gated, &summed = F.summed, &swapped = F.swapped;
     std::vector<size_t> first_blk(m.ops.size() + 1, 0);          // argument blocks: G * sub per operation
     for (size_t i = 0; i < m.ops.size(); i++)
         first_blk[i + 1] = first_blk[i] + (fused[i] == 2 || chain[i] == 2 ? 0
                                            : (size_t)G * (chain[i] == 1 ? 3 : chain[i] == 3 || chain[i] == 4 || fused[i] == 1 ? 2 : (m.ops[i].sub > 1 ? m.ops[i].sub : 1)));
     const size_t n_blk = first_blk[m.ops.size()];
     std::vector<char> host(n_blk * slot, 0);
-    if (!may_alloc && (!g.d_args || g.d_args_bytes < host.size())) return ENS_E_INVALID;
-    if (g.d_args && g.d_args_bytes < host.size()) { (void)hipFree(g.d_args); g.d_args = nullptr; }
-    if (!g.d_args) { HIP_TRY(hipMalloc((void**)&g.d_args, host.size())); g.d_args_bytes = host.size(); }
-    g.launches.clear();
+    const size_t at = blocks.size();
+    launches.clear();
     for (size_t i = 0; i < m.ops.size(); i++) {
         Launch L;
         if (fused[i] == 2 || chain[i] == 2) {                    // its argument blocks are in an earlier launch
             L.kind = L_SKIP;
-            g.launches.push_back(L);
+            launches.push_back(L);
             continue;
         }
         if (chain[i] == 4) {                                     // stem and pool: G blocks of the convolution, then G of the pooled output
             for (int k = G - 1; k >= 0; k--) {
                 const Worker& wk = h->workers[g.workers[k]];
                 const Member& mk = h->members[wk.member];
-                const ConvArgs p = pool_as_conv(wk, mk.ops[i + 1]);
-                const int rc = fill_args(h, wk, leader, G, mk.ops[i], L);
+                const ConvArgs p = pool_as_conv(h, wk, mk.ops[i + 1], images);
+                const int rc = fill_args(h, wk, leader, G, images, mk.ops[i], L);
                 if (rc != ENS_OK) return rc;
                 L.conv.ws = nullptr;
                 L.conv.ws_floats = 0;
@@ -341,8 +370,8 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
             L.kind = L_STEMPOOL;
             L.sub = 2;
             L.klass = prof_class(h, conv_stempool_name());
-            L.d_argv = g.d_args + first_blk[i] * slot;
-            g.launches.push_back(L);
+            L.d_argv = (const void*)(at + first_blk[i] * slot);
+            launches.push_back(L);
             continue;
         }
         if (chain[i] == 3) {                                     // a layer of a dense block: G blocks of each of its two convolutions
@@ -350,7 +379,7 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
             for (int sub = 1; sub >= 0; sub--)
                 for (int k = G - 1; k >= 0; k--) {
                     const Member& mk = h->members[h->workers[g.workers[k]].member];
-                    const int rc = fill_args(h, h->workers[g.workers[k]], leader, G, mk.ops[i + sub], L);
+                    const int rc = fill_args(h, h->workers[g.workers[k]], leader, G, images, mk.ops[i + sub], L);
                     if (rc != ENS_OK) return rc;
                     L.conv.ws = nullptr;
                     L.conv.ws_floats = 0;
@@ -370,8 +399,8 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
             L.flop = flop;
             L.bytes = bytes;
             L.klass = prof_class(h, conv_dense_name());
-            L.d_argv = g.d_args + first_blk[i] * slot;
-            g.launches.push_back(L);
+            L.d_argv = (const void*)(at + first_blk[i] * slot);
+            launches.push_back(L);
             continue;
         }
         if (chain[i] == 1) {                                     // G blocks of each of the three convolutions
@@ -379,7 +408,7 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
             for (int sub = 2; sub >= 0; sub--)
                 for (int k = G - 1; k >= 0; k--) {
                     const Member& mk = h->members[h->workers[g.workers[k]].member];
-                    const int rc = fill_args(h, h->workers[g.workers[k]], leader, G, mk.ops[i + sub], L);
+                    const int rc = fill_args(h, h->workers[g.workers[k]], leader, G, images, mk.ops[i + sub], L);
                     if (rc != ENS_OK) return rc;
                     L.conv.ws = nullptr;
                     L.conv.ws_floats = 0;
@@ -399,8 +428,8 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
             L.flop = flop;
             L.bytes = px * 2.0 * (L.conv.cin + L.conv3.cout * (own_res ? 2 : 1)) + wbytes;
             L.klass = prof_class(h, conv_bneck_name(L.conv));
-            L.d_argv = g.d_args + first_blk[i] * slot;
-            g.launches.push_back(L);
+            L.d_argv = (const void*)(at + first_blk[i] * slot);
+            launches.push_back(L);
             continue;
         }
         const int nsub = fused[i] == 1 ? 2 : (m.ops[i].sub > 1 ? m.ops[i].sub : 1);
@@ -416,7 +445,7 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
                 const Member& mk = h->members[h->workers[g.workers[k]].member];
                 const OpPlan& pl = swapped[i] == 1 || swapped[i] == 3 ? mk.ops[i + 1] : swapped[i] == 2 || swapped[i] == 4 ? mk.ops[i - 1]
                                    : fused[i] == 1 && (sub == 1) != second_leads ? mk.ops[i + 1] : mk.ops[i];
-                const int rc = fill_args(h, h->workers[g.workers[k]], leader, G, pl, L, fused[i] == 1 ? 0 : sub);
+                const int rc = fill_args(h, h->workers[g.workers[k]], leader, G, images, pl, L, fused[i] == 1 ? 0 : sub);
                 if (rc != ENS_OK) return rc;
                 if (swapped[i] >= 3) {
                     // the pool first: pre-activation and average of the convolution's input into the convolution's output
@@ -490,11 +519,11 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
                     L.bytes -= 2.0 * se_pass;
                     if (summed[i] == 2) L.bytes = (double)L.se.nb * L.se.have_sums * L.se.c * sizeof(float);   // only the rows of sums
                 } else if (gated[i] == 2) {
-                    gate_args(h->workers[g.workers[k]], mk.ops[i - 1], L.conv);
+                    gate_args(h, h->workers[g.workers[k]], leader, mk.ops[i - 1], L.conv);
                     L.klass = prof_class(h, conv_bf16_variant_name(L.conv, G));
                 }
                 if (fused[i] == 1) {                             // no split of the depth: the two would share one workspace
-                    L.conv.wpk = nullptr;                        // the generic kernel runs both
+                    L.conv.pair = 1;                             // a kernel that can run both
                     L.conv.ws = nullptr;
                     L.conv.ws_floats = 0;
                     if (sub == 1) { flop2 = L.flop; bytes2 = L.bytes; }
@@ -516,12 +545,12 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
             L.bytes += bytes2;
             L.klass = prof_class(h, conv_bf16_variant_name(L.conv, 2 * G));
         }
-        L.d_argv = g.d_args + first_blk[i] * slot;
-        g.launches.push_back(L);
+        L.d_argv = (const void*)(at + first_blk[i] * slot);
+        launches.push_back(L);
     }
     // The device arrays are indexed by element size, so every block is re-packed densely.
     for (size_t i = 0; i < m.ops.size(); i++) {
-        const Launch& L = g.launches[i];
+        const Launch& L = launches[i];
         size_t sz = 0;
         switch (L.kind) {
             case L_CONV:
@@ -539,12 +568,44 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
         const size_t nb_i = first_blk[i + 1] - first_blk[i];
         for (size_t k = 1; k < nb_i; k++) memmove(base + k * sz, base + k * slot, sz);
     }
+    blocks.insert(blocks.end(), host.begin(), host.end());
+    return ENS_OK;
+}
+
+// Translates the gang's operations into kernel argument arrays in device memory, once for every range of batch sizes with
+// fusions of its own: a request smaller than a worker's batch size runs the layers as its own size wants them.  Ranges end at
+// powers of two, at half the worker's batch size and at the whole.
+// may_alloc false: the device block of the gang must already be large enough (it is once the
+// allocation has been installed); the function then only rewrites it.
+static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
+    const Worker& leader = h->workers[g.workers[0]];
+    const Member& m = h->members[leader.member];
+    std::vector<std::pair<int, Fusions>> ranges;
+    for (int images = 1;; images *= 2) {
+        const int most = 2 * images < leader.batch ? images : ranges.empty() || ranges.back().first < leader.batch / 2 ? std::max(1, leader.batch / 2) : leader.batch;
+        Fusions F = decide_fusions(h, g, most);
+        if (!ranges.empty() && ranges.back().second == F) ranges.back().first = most;
+        else ranges.emplace_back(most, std::move(F));
+        if (most == leader.batch) break;
+    }
+    g.plans.assign(ranges.size(), GangPlan());
+    std::vector<char> blocks;
+    for (size_t i = 0; i < ranges.size(); i++) {
+        g.plans[i].most = ranges[i].first;
+        const int rc = build_plan(h, g, ranges[i].first, ranges[i].second, g.plans[i].launches, blocks);
+        if (rc != ENS_OK) return rc;
+    }
+    if (!may_alloc && (!g.d_args || g.d_args_bytes < blocks.size())) return ENS_E_INVALID;
+    if (g.d_args && g.d_args_bytes < blocks.size()) { (void)hipFree(g.d_args); g.d_args = nullptr; }
+    if (!g.d_args) { HIP_TRY(hipMalloc((void**)&g.d_args, blocks.size())); g.d_args_bytes = blocks.size(); }
+    for (GangPlan& p : g.plans)
+        for (Launch& L : p.launches) L.d_argv = g.d_args + (size_t)L.d_argv;
     g.stage.src = nullptr;                                       // named per request
     g.stage.slot = nullptr;
     g.stage.dst = leader.arena + leader.layout.offset[0];
     g.stage.nb = leader.batch; g.stage.sh = h->base_h; g.stage.sw = h->base_w;
     g.stage.dh = m.in_h; g.stage.dw = m.in_w; g.stage.dc = m.tensors[0].cs; g.stage.s2d = m.stem_s2d ? 1 : 0;
-    HIP_TRY(hipMemcpy(g.d_args, host.data(), host.size(), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(g.d_args, blocks.data(), blocks.size(), hipMemcpyHostToDevice));
     return ENS_OK;
 }
 
@@ -559,7 +620,23 @@ static void drop_graphs(ens_handle* h) {
     h->sizes_seen.clear();
 }
 
+// A small request that is answered through pinned host memory ends in finish_kernel on every lane, and the last one to arrive
+// writes the request's number there too.  Waiting for that instead of for the streams saves 10 us and more per lane.
+// A request that takes longer than the spin is waited for the ordinary way, and so is one in SYNC_EVERY, which lets the runtime
+// give back what it holds for finished launches.  (Not for answers on the device: the caller's next synchronisation of a stream of its
+// own would pay for that, 0.6 us per launch.)
+constexpr double SPIN_S = 5e-3;
+constexpr uint64_t SYNC_EVERY = 64;
+
 static hipError_t wait_lanes(ens_handle* h) {
+    if (h->flagged && h->requests % SYNC_EVERY) {
+        const auto t0 = std::chrono::steady_clock::now();
+        for (unsigned i = 1;; i++) {
+            if (__atomic_load_n(h->flag, __ATOMIC_ACQUIRE) == (uint32_t)h->requests) return hipSuccess;
+            __builtin_ia32_pause();
+            if (i % 64 == 0 && std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > SPIN_S) break;
+        }
+    }
     for (int l = 0; l < LANES && h->have_lanes; l++) {
         const hipError_t e = hipStreamSynchronize(h->lanes[l]);
         if (e != hipSuccess) return e;
@@ -568,6 +645,7 @@ static hipError_t wait_lanes(ens_handle* h) {
 }
 
 static void destroy_workers(ens_handle* h) {
+    h->flagged = false;                                          // the streams themselves
     (void)wait_lanes(h);
     drop_graphs(h);
     for (Gang& g : h->gangs)
@@ -663,6 +741,7 @@ static int install_alloc(ens_handle* h, const ens_alloc& a, int segment_size) {
         if (rc0 != ENS_OK) { destroy_workers(h); return rc0; }
     }
     cu_budget() = stream_share(h);
+    lanes_busy() = std::min(LANES, std::max(1, (int)h->gangs.size()));
     for (Gang& g : h->gangs) {
         const int rc = build_launches(h, g);
         if (rc != ENS_OK) { destroy_workers(h); return rc; }
@@ -734,7 +813,7 @@ static int forward_batch(ens_handle* h, Gang& g, int64_t first, int nb, const fl
     g.stage.slot = slot;
     g.stage.sh = h->base_h; g.stage.sw = h->base_w;
     HIP_TRY(timed(h->stage_klass, 0.0, stage_bytes, [&] { return launch_stage(g.stage, nb, first, m.bf16, st); }));
-    for (const Launch& L : g.launches) {
+    for (const Launch& L : g.plan_for(nb).launches) {
         if (L.kind == L_SKIP) continue;
         HIP_TRY(timed(L.klass, L.flop * G, L.bytes * G, [&] { return issue(L, m.bf16, G, nb, first, st); }));
     }
@@ -802,7 +881,7 @@ static int grow(float** p, size_t* cap, size_t want_floats) {
     return ENS_OK;
 }
 
-// Calls fn(gang, first image, images, segment) for every batch of a request of n images, in the order of issue.
+// Calls fn(gang, first image, images) for every batch of a request of n images, in the order of issue.
 template <typename F>
 static int each_batch(ens_handle* h, int64_t n, uint64_t mask, const std::vector<std::vector<int32_t>>& owner, F&& fn) {
     const int seg = h->segment_size;
@@ -817,7 +896,7 @@ static int each_batch(ens_handle* h, int64_t n, uint64_t mask, const std::vector
             if (!wanted) continue;
             const int b = h->workers[g.workers[0]].batch;
             for (int64_t a = start; a < end; a += b) {
-                const int rc = fn(g, a, (int)std::min<int64_t>(b, end - a), s);
+                const int rc = fn(g, a, (int)std::min<int64_t>(b, end - a));
                 if (rc != ENS_OK) return rc;
             }
         }
@@ -825,29 +904,87 @@ static int each_batch(ens_handle* h, int64_t n, uint64_t mask, const std::vector
     return ENS_OK;
 }
 
-// Deals the gangs to the lanes for a request of n images: the longest first, each to the lane with the least so far.
-// The times are estimates that only have to rank: 4 us for a launch, or its work at a tenth of the chip's rates.
-// Returns the number of lanes in use, and in *launches how many launches the request takes.
-static int deal_lanes(ens_handle* h, int64_t n, uint64_t mask, const std::vector<std::vector<int32_t>>& owner, int64_t* launches) {
-    std::vector<double> est(h->gangs.size(), 0.0);
-    *launches = 0;
-    (void)each_batch(h, n, mask, owner, [&](Gang& g, int64_t, int nb, int64_t) {
-        const Worker& leader = h->workers[g.workers[0]];
-        const double share = (double)nb / leader.batch * (double)g.workers.size();
-        double t = 4e-6;
-        for (const Launch& L : g.launches) {
-            if (L.kind == L_SKIP) continue;
-            t += std::max(4e-6, share * std::max(L.flop / 4e14, L.bytes / 3e12));
-            ++*launches;
-        }
-        ++*launches;
-        est[&g - h->gangs.data()] += t;
+// Requests recorded as graphs (see below): the launches of a request that is still recorded, recorded requests and noted sizes that
+// a handle keeps; below three lanes the GPU takes as long for a launch as the host.  Average launch of the
+// requests that are handed out batch by batch instead.  What a graph costs the host per kernel in it, and what
+// it costs to start and to wait for one lane more (a graph's launch 30 us, a wait 10 to 20).
+constexpr int64_t GRAPH_MAX_LAUNCHES = 2048;
+constexpr size_t GRAPHS_KEPT = 8, SIZES_KEPT = 32;
+constexpr int GRAPH_MIN_LANES = 3;
+constexpr double HAND_OUT_LAUNCH_S = 9e-6, LANE_S = 30e-6, GRAPH_NODE_S = 0.4e-6;
+
+// What a launch takes whatever its batch (one image, other lanes busy): most are a chain of two or three round trips to memory.
+static double launch_floor(int kind) {
+    switch (kind) {
+        case L_SE: return 12e-6;
+        case L_DWCONV: return 9e-6;
+        case L_BNECK: return 25e-6;
+        case L_DENSE: return 17e-6;
+        case L_STEMPOOL: return 20e-6;
+        default: return 7e-6;
+    }
+}
+
+// What a launch of a large batch takes: its work at the rates the kernels reach (measured alone on batches of 128).
+static double launch_work(const Launch& L, double share) {
+    double tflops = 6e14, gbs = 3.1e12;
+    switch (L.kind) {
+        case L_CONV: tflops = L.conv.kh * L.conv.kw > 1 && L.conv.sh == 1 ? 8e14 : 5.5e14; break;
+        case L_DENSE: tflops = 2.8e14; break;
+        case L_BNECK: tflops = 5.6e14; break;
+        case L_STEMPOOL: tflops = 2.5e14; break;
+        case L_DWCONV: gbs = 2.7e12; break;
+        case L_SE: gbs = 1e12; break;
+        default: break;
+    }
+    return share * std::max(L.flop / tflops, L.bytes / gbs);
+}
+
+static double batch_estimate(ens_handle* h, const Gang& g, int nb) {
+    const double share = (double)nb / h->workers[g.workers[0]].batch * (double)g.workers.size();
+    double t = launch_floor(L_POOL);                             // input staging
+    for (const Launch& L : g.plan_for(nb).launches)
+        if (L.kind != L_SKIP) t += std::max(launch_floor(L.kind), launch_work(L, share));
+    return t;
+}
+
+// What a request comes to: its batches per gang, its launches and their estimated time one after the other.
+struct Batch { int64_t first; int nb; double estimate; };
+struct Work {
+    std::vector<std::vector<Batch>> batches;
+    std::vector<double> estimate;                                // per gang
+    int64_t launches = 0, most = 0;                              // most: batches of the gang that has the most of them
+    double total = 0;
+};
+static Work plan_work(ens_handle* h, int64_t n, uint64_t mask, const std::vector<std::vector<int32_t>>& owner) {
+    Work w;
+    w.batches.resize(h->gangs.size());
+    w.estimate.assign(h->gangs.size(), 0.0);
+    (void)each_batch(h, n, mask, owner, [&](Gang& g, int64_t first, int nb) {
+        const size_t i = &g - h->gangs.data();
+        std::vector<Batch>& all = w.batches[i];
+        const double t = !all.empty() && all.back().nb == nb ? all.back().estimate : batch_estimate(h, g, nb);
+        all.push_back(Batch{first, nb, t});
+        for (const Launch& L : g.plan_for(nb).launches) w.launches += L.kind != L_SKIP;
+        w.launches++;
+        w.estimate[i] += t;
+        w.total += t;
+        w.most = std::max<int64_t>(w.most, (int64_t)all.size());
         return ENS_OK;
     });
+    return w;
+}
+
+// Deals the gangs to the lanes: the longest first, each to the lane with the least so far.  The host
+// reaches a lane after it has issued those before it, which counts as load, and a lane more costs what LANE_S says.
+// Returns the number of lanes in use.
+static int deal_lanes(ens_handle* h, const Work& work) {
+    const std::vector<double>& est = work.estimate;
     std::vector<int> order(h->gangs.size());
     for (size_t i = 0; i < order.size(); i++) order[i] = (int)i;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return est[x] > est[y]; });
     double load[LANES] = {0};
+    for (int l = 0; l < LANES; l++) load[l] = l * (LANE_S + (work.launches <= GRAPH_MAX_LAUNCHES ? work.launches / LANES * GRAPH_NODE_S : 0.0));
     int used = 0;
     for (int i : order) {
         if (est[i] == 0.0) continue;
@@ -883,8 +1020,6 @@ static CombineArgs combine_args(ens_handle* h, int64_t n, int lanes) {
 // measured too: 2.2 us per launch.)  Recording takes 3 us per launch and is done the second time a size is seen; the recorded
 // launches find the request's buffers through a slot per lane.  Requests with more launches than this keep the GPU
 // busy for longer than the host needs to issue them.
-constexpr int64_t GRAPH_MAX_LAUNCHES = 2048;
-constexpr size_t GRAPHS_KEPT = 8, SIZES_KEPT = 32;
 
 static RequestGraph* find_graph(ens_handle* h, int64_t n) {
     for (RequestGraph& r : h->graphs)
@@ -915,7 +1050,7 @@ static RequestGraph* record_request(ens_handle* h, int64_t n, int lanes, const s
         ok = hipStreamBeginCapture(h->main_stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
         if (!ok) break;
         const RequestSlot* slot = h->d_slots + l;
-        int rc = each_batch(h, n, ~0ull, owner, [&](Gang& g, int64_t first, int nb, int64_t) {
+        int rc = each_batch(h, n, ~0ull, owner, [&](Gang& g, int64_t first, int nb) {
             return g.lane == l ? forward_batch(h, g, first, nb, nullptr, slot, h->main_stream) : ENS_OK;
         });
         CombineArgs c = combine_args(h, n, lanes);
@@ -952,6 +1087,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
                       const float* host_images = nullptr) {
     if (n == 0) return ENS_OK;
     cu_budget() = stream_share(h);
+    lanes_busy() = std::min(LANES, std::max(1, (int)h->gangs.size()));
     int rc = may_alloc ? ensure_buffers(h, n) : ENS_OK;
     if (rc != ENS_OK) return rc;
     if ((size_t)n > h->d_logits_rows) return ENS_E_INVALID;
@@ -973,6 +1109,8 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
     // would by taking them from one queue, the faster worker more of them (planner.cpp, hand_out)
     std::vector<std::vector<int32_t>> owner(M);
     int lanes = graph ? graph->lanes : 0;
+    Work work;
+    bool hand_out_batches = false;
     if (!graph) {
         for (int c = 0; c < M; c++) {
             std::vector<int32_t> batches;
@@ -985,55 +1123,135 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
             if (batches.size() <= 1 || !first) continue;
             double flop = 0;
             int launches = 1;
-            for (const Launch& L : first->launches)
+            for (const Launch& L : first->plans.back().launches)
                 if (L.kind != L_SKIP) { flop += L.flop; launches++; }
             const double launch_cost = launches * 8e-6;          // a kernel of a small batch lasts about this long whatever it does
             const double image_cost = flop / batches[0] / (h->members[c].bf16 ? 4e14 : 2e13);
             rc = hand_out(n, seg, batches.data(), (int)batches.size(), launch_cost, image_cost, &owner[c]);
             if (rc != ENS_OK) return rc;
         }
-        int64_t launches = 0;
-        lanes = deal_lanes(h, n, mask, owner, &launches);
-        if (!plain_only && !(host_images && n_seg > 1) && launches <= GRAPH_MAX_LAUNCHES && seen_before(h, n))
+        work = plan_work(h, n, mask, owner);
+        // More gangs than lanes with several batches each are handed out as the lanes come free (below), unless their launches are so
+        // short that the host has to be out of the way.
+        hand_out_batches = !h->one_stream && h->gangs.size() > LANES && work.most > 1 && work.total > HAND_OUT_LAUNCH_S * (double)work.launches;
+        lanes = hand_out_batches ? LANES : deal_lanes(h, work);
+        if (!plain_only && !(host_images && n_seg > 1) && !hand_out_batches && lanes >= GRAPH_MIN_LANES && work.launches <= GRAPH_MAX_LAUNCHES &&
+            seen_before(h, n))
             graph = record_request(h, n, lanes, owner);
     }
-    // one segment's images to the device, and the lanes' wait for them
+    // Host images go to the device in pieces of the smallest batch, beside the kernels; a lane waits for the last piece it needs.
     const size_t image_floats = (size_t)h->base_h * h->base_w * 3;
-    auto bring_segment = [&](int64_t s) -> int {
-        const int64_t start = s * seg, end = std::min<int64_t>((s + 1) * seg, n);
+    int64_t piece = seg;
+    for (const Worker& w : h->workers) piece = std::min<int64_t>(piece, w.batch);
+    piece = std::max<int64_t>(piece, 16);
+    const int64_t pieces = host_images ? (n + piece - 1) / piece : 0;
+    int64_t here = 0, waited[LANES] = {0};                       // pieces whose copies have been issued; that a lane has waited for
+    auto bring_piece = [&]() -> int {
+        const int64_t start = here * piece, end = std::min<int64_t>(start + piece, n);
         HIP_TRY(hipMemcpyAsync((void*)(d_images + start * image_floats), host_images + start * image_floats,
                                (size_t)(end - start) * image_floats * sizeof(float), hipMemcpyHostToDevice, h->main_stream));
-        while (h->copied.size() <= (size_t)s) {
+        while (h->copied.size() <= (size_t)here) {
             hipEvent_t e = nullptr;
             HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
             h->copied.push_back(e);
         }
-        HIP_TRY(hipEventRecord(h->copied[s], h->main_stream));
-        for (int l = 0; l < lanes; l++) HIP_TRY(hipStreamWaitEvent(h->lanes[l], h->copied[s], 0));
+        HIP_TRY(hipEventRecord(h->copied[here++], h->main_stream));
+        return ENS_OK;
+    };
+    auto need_images = [&](int l, int64_t end) -> int {          // lane l: images up to `end`
+        if (!host_images) return ENS_OK;
+        const int64_t p = (end + piece - 1) / piece;
+        while (here < p) {
+            const int e = bring_piece();
+            if (e != ENS_OK) return e;
+        }
+        if (waited[l] < p) HIP_TRY(hipStreamWaitEvent(h->lanes[l], h->copied[p - 1], 0));   // copies are in order
+        waited[l] = std::max(waited[l], p);
         return ENS_OK;
     };
     if (graph) {
-        if (host_images) {
-            rc = bring_segment(0);
-            if (rc != ENS_OK) return rc;
-        }
         graph->used = h->requests;
         for (int l = 0; l < lanes; l++) {
-            HIP_TRY(launch_bind_request(h->d_slots + l, d_images, d_probs, h->lanes[l]));
+            rc = need_images(l, n);
+            if (rc != ENS_OK) return rc;
+            HIP_TRY(launch_bind_request(h->d_slots + l, RequestSlot{d_images, d_probs}, h->lanes[l]));
             HIP_TRY(hipGraphLaunch(graph->exec[l], h->lanes[l]));
+            if (h->flagged) HIP_TRY(launch_finish(h->d_arrivals + COMBINE_MAX_BLOCKS, lanes, h->flag, (uint32_t)h->requests, h->lanes[l]));
         }
         for (size_t w = 0; w < h->workers.size(); w++) h->workers[w].last_nb = graph->last_nb[w];
         return ENS_OK;
     }
-    int64_t here = host_images ? 0 : n_seg;                      // segments whose copies have been issued
-    rc = each_batch(h, n, mask, owner, [&](Gang& g, int64_t first, int nb, int64_t s) {
-        while (here <= s) {
-            const int e = bring_segment(here++);
-            if (e != ENS_OK) return e;
+    if (hand_out_batches) {
+        // A lane holds two batches, the one that runs and the next; when one ends it gets the next batch of the gang that has the most
+        // left to do among those that have nothing on another lane.  (Dealt to the lanes beforehand by the estimates, the twelve-member
+        // ensemble's lanes ended between 151 and 191 ms.)
+        // A batch ends in finish_kernel, which writes its number to the lane's word in pinned memory (asking the runtime about events
+        // in a loop slowed the GPU's own queues down: 21.5 ms instead of 17.2 for three ResNet-18 over 1024 images).
+        struct InFlight { int gang = -1; uint32_t number = 0; };
+        InFlight flight[LANES][2];
+        std::vector<size_t> next(h->gangs.size(), 0);
+        std::vector<int> out(h->gangs.size(), 0), on(h->gangs.size(), -1);   // batches in flight, and their lane
+        std::vector<double> left = work.estimate;
+        uint32_t issued[LANES] = {0};
+        for (int l = 0; l < lanes; l++) __atomic_store_n(h->flag + 1 + l, 0u, __ATOMIC_RELEASE);
+        size_t remaining = 0;
+        for (const auto& b : work.batches) remaining += b.size();
+        auto t_moved = std::chrono::steady_clock::now();
+        while (remaining) {
+            bool moved = false;
+            for (int k = 0; k < 2; k++)                          // every lane one batch before any has two
+                for (int l = 0; l < lanes; l++) {
+                    InFlight& f = flight[l][k];
+                    if (f.gang >= 0) {
+                        if (__atomic_load_n(h->flag + 1 + l, __ATOMIC_ACQUIRE) < f.number) continue;
+                        out[f.gang]--;
+                        f.gang = -1;
+                    }
+                    int pick = -1;
+                    double pick_due = 0;
+                    for (size_t i = 0; i < h->gangs.size(); i++) {
+                        if (next[i] >= work.batches[i].size() || (out[i] > 0 && on[i] != l)) continue;
+                        if (host_images && work.batches[i][next[i]].first + work.batches[i][next[i]].nb > here * piece && here < pieces) continue;
+                        // a gang stays on its lane unless another has two batches more to do
+                        const double due = left[i] + (out[i] > 0 ? 2.0 * work.batches[i][next[i]].estimate : 0.0);
+                        if (pick < 0 || due > pick_due) { pick = (int)i; pick_due = due; }
+                    }
+                    if (pick < 0) continue;
+                    const Batch& b = work.batches[pick][next[pick]++];
+                    rc = need_images(l, b.first + b.nb);
+                    if (rc == ENS_OK) rc = forward_batch(h, h->gangs[pick], b.first, b.nb, d_images, nullptr, h->lanes[l]);
+                    if (rc != ENS_OK) return rc;
+                    f.number = ++issued[l];
+                    HIP_TRY(launch_finish(h->d_arrivals, 1, h->flag + 1 + l, f.number, h->lanes[l]));
+                    f.gang = pick;
+                    out[pick]++;
+                    on[pick] = l;
+                    left[pick] -= b.estimate;
+                    remaining--;
+                    moved = true;
+                }
+            if (moved) {
+                t_moved = std::chrono::steady_clock::now();
+                continue;
+            }
+            if (here < pieces) {
+                rc = bring_piece();
+                if (rc != ENS_OK) return rc;
+                continue;
+            }
+            for (int i = 0; i < 200; i++) __builtin_ia32_pause();       // some 5 us
+            if (std::chrono::steady_clock::now() - t_moved > std::chrono::seconds(2)) {   // a lane that is stuck: the runtime knows why
+                HIP_TRY(wait_lanes(h));
+                t_moved = std::chrono::steady_clock::now();
+            }
         }
-        return forward_batch(h, g, first, nb, d_images, nullptr, h->lanes[g.lane]);
-    });
-    if (rc != ENS_OK) return rc;
+    } else {
+        rc = each_batch(h, n, mask, owner, [&](Gang& g, int64_t first, int nb) {
+            const int e = need_images(g.lane, first + nb);
+            return e != ENS_OK ? e : forward_batch(h, g, first, nb, d_images, nullptr, h->lanes[g.lane]);
+        });
+        if (rc != ENS_OK) return rc;
+    }
     if (mask == ~0ull || M == 1) {
         CombineArgs c = combine_args(h, n, lanes);
         c.y = d_probs;
@@ -1045,6 +1263,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
                 next_launch_events() = LaunchEvents{r.start, r.stop};
             }
             HIP_TRY(launch_combine(c, h->lanes[l]));
+            if (h->flagged) HIP_TRY(launch_finish(h->d_arrivals + COMBINE_MAX_BLOCKS, lanes, h->flag, (uint32_t)h->requests, h->lanes[l]));
             if (r.start) {
                 next_launch_events() = LaunchEvents{};
                 h->prof_recs.push_back(r);
@@ -1057,7 +1276,8 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
 // After a request that failed on the way: nothing of it is left in flight, and the arrivals are zeros again.
 static void recover(ens_handle* h) {
     (void)hipDeviceSynchronize();
-    if (h->d_arrivals) (void)hipMemset(h->d_arrivals, 0, COMBINE_MAX_BLOCKS * sizeof(unsigned));
+    h->flagged = false;
+    if (h->d_arrivals) (void)hipMemset(h->d_arrivals, 0, (COMBINE_MAX_BLOCKS + 1) * sizeof(unsigned));
     (void)hipGetLastError();
 }
 
@@ -1106,12 +1326,12 @@ static int ensure_calib(ens_handle* h, int64_t n) {
 // copy on a stream in front of the kernels and one behind them (10 us each, 20 and more from pageable memory).
 constexpr size_t DIRECT_IN_BYTES = 1280u << 10, DIRECT_OUT_BYTES = 256u << 10;
 
-static int grow_pinned(float** p, size_t* cap, size_t want_floats) {
+static int grow_pinned(float** p, size_t* cap, size_t want_floats, unsigned flags) {
     if (want_floats <= *cap) return ENS_OK;
     if (*p) (void)hipHostFree(*p);
     *p = nullptr;
     *cap = 0;
-    HIP_TRY(hipHostMalloc((void**)p, want_floats * sizeof(float), hipHostMallocNonCoherent));
+    HIP_TRY(hipHostMalloc((void**)p, want_floats * sizeof(float), flags));
     *cap = want_floats;
     return ENS_OK;
 }
@@ -1188,8 +1408,10 @@ int ens_load(const ens_member_spec* specs, int32_t n_members, uint64_t seed, ens
     if (acquire_lanes(h->lanes) != hipSuccess) return fail(ENS_E_HIP);
     h->have_lanes = true;
     if (hipMalloc((void**)&h->d_slots, LANES * sizeof(RequestSlot)) != hipSuccess) return fail(ENS_E_NOMEM);
-    if (hipMalloc((void**)&h->d_arrivals, COMBINE_MAX_BLOCKS * sizeof(unsigned)) != hipSuccess) return fail(ENS_E_NOMEM);
-    if (hipMemset(h->d_arrivals, 0, COMBINE_MAX_BLOCKS * sizeof(unsigned)) != hipSuccess) return fail(ENS_E_HIP);
+    if (hipMalloc((void**)&h->d_arrivals, (COMBINE_MAX_BLOCKS + 1) * sizeof(unsigned)) != hipSuccess) return fail(ENS_E_NOMEM);
+    if (hipMemset(h->d_arrivals, 0, (COMBINE_MAX_BLOCKS + 1) * sizeof(unsigned)) != hipSuccess) return fail(ENS_E_HIP);
+    if (hipHostMalloc((void**)&h->flag, 64, hipHostMallocCoherent) != hipSuccess) return fail(ENS_E_NOMEM);
+    *h->flag = 0;
     h->d_logits.assign(h->members.size(), nullptr);
     h->stage_klass = prof_class(h, "stage_kernel");
     *out = h;
@@ -1208,6 +1430,7 @@ void ens_free(ens_handle* h) {
     if (h->d_arrivals) (void)hipFree(h->d_arrivals);
     if (h->pin_in) (void)hipHostFree(h->pin_in);
     if (h->pin_out) (void)hipHostFree(h->pin_out);
+    if (h->flag) (void)hipHostFree(h->flag);
     if (h->d_weights) (void)hipFree(h->d_weights);
     if (h->d_images) (void)hipFree(h->d_images);
     if (h->d_probs) (void)hipFree(h->d_probs);
@@ -1252,7 +1475,7 @@ int ens_predict(ens_handle* h, const float* images, int64_t n, float* probs_out)
     const float *d_in = images, *host_in = nullptr;
     if (!h->images_on_device) {
         if (img_floats * sizeof(float) * h->gangs.size() <= DIRECT_IN_BYTES) {
-            int rc = grow_pinned(&h->pin_in, &h->pin_in_cap, img_floats);
+            int rc = grow_pinned(&h->pin_in, &h->pin_in_cap, img_floats, hipHostMallocNonCoherent);
             if (rc != ENS_OK) return rc;
             memcpy(h->pin_in, images, img_floats * sizeof(float));
             d_in = h->pin_in;
@@ -1266,14 +1489,16 @@ int ens_predict(ens_handle* h, const float* images, int64_t n, float* probs_out)
     float* d_out = probs_out;
     const bool direct_out = !h->probs_on_device && out_floats * sizeof(float) <= DIRECT_OUT_BYTES;
     if (!h->probs_on_device) {
-        int rc = direct_out ? grow_pinned(&h->pin_out, &h->pin_out_cap, out_floats) : grow(&h->d_probs, &h->d_probs_cap, out_floats);
+        int rc = direct_out ? grow_pinned(&h->pin_out, &h->pin_out_cap, out_floats, hipHostMallocCoherent) : grow(&h->d_probs, &h->d_probs_cap, out_floats);
         if (rc != ENS_OK) return rc;
         d_out = direct_out ? h->pin_out : h->d_probs;
     }
     if (h->profiling) reset_profile(h);
+    h->flagged = direct_out && !h->profiling;
     int rc = run_device(h, d_in, n, d_out, ~0ull, true, host_in);
     if (rc != ENS_OK) { recover(h); return rc; }
     HIP_TRY(wait_lanes(h));
+    h->flagged = false;
     if (direct_out) {
         memcpy(probs_out, h->pin_out, out_floats * sizeof(float));
     } else if (!h->probs_on_device) {

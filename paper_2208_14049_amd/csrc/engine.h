@@ -130,6 +130,12 @@ struct Worker {
     int last_nb = 0;
 };
 
+// The launches of a gang for batches of up to `most` images.
+struct GangPlan {
+    int most = 0;
+    std::vector<Launch> launches;
+};
+
 // Workers that run the same network shape at the same batch size on the same segments (the
 // replicas of a homogeneous ensemble in one row of the allocation matrix) advance in lockstep:
 // one stream, and one kernel launch per operation whose grid spans all of them.
@@ -137,7 +143,12 @@ struct Gang {
     std::vector<int> workers;      // indices into ens_handle::workers; [0] leads (its input tensor is shared)
     int rank = 0, of = 1;
     int lane = 0;                  // lane of the request in flight
-    std::vector<Launch> launches;
+    std::vector<GangPlan> plans;   // by the batch sizes they are for, ascending; the last one ends at the workers' batch size
+    const GangPlan& plan_for(int images) const {
+        for (const GangPlan& p : plans)
+            if (images <= p.most) return p;
+        return plans.back();
+    }
     StageArgs stage;
     char* d_args = nullptr;        // device block holding every argument array of the gang
     size_t d_args_bytes = 0;
@@ -187,9 +198,12 @@ struct ens_handle {
     hipStream_t main_stream = nullptr;           // copies, and the recording of graphs
     hipStream_t lanes[ens::LANES] = {nullptr, nullptr, nullptr, nullptr};
     bool have_lanes = false;
-    std::vector<hipEvent_t> copied;              // per segment: its images are on the device
+    std::vector<hipEvent_t> copied;              // per piece of a host request: its images are on the device
     ens::RequestSlot* d_slots = nullptr;         // one per lane
-    unsigned* d_arrivals = nullptr;              // see CombineArgs
+    unsigned* d_arrivals = nullptr;              // see CombineArgs; one more for finish_kernel
+    uint32_t* flag = nullptr;                    // pinned: number of the last request that is complete (see wait_lanes), then
+                                                 // per lane the number of its last batch that is
+    bool flagged = false;                        // the request in flight will write it
     std::vector<ens::RequestGraph> graphs;
     std::vector<std::pair<int64_t, uint64_t>> sizes_seen;   // request sizes and when they last came, not recorded (yet)
     uint64_t requests = 0;

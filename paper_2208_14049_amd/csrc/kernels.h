@@ -51,6 +51,8 @@ struct ConvArgs {
     int nb, H, W, cin, Ho, Wo, cout;
     int kh, kw, sh, sw, pt, pl;
     int act;
+    int few;                   // host: planned for batches that do not fill half of the worker's batch size
+    int pair;                  // host: the launch also carries another operation's blocks, with a filter of their own
 };
 
 struct PoolArgs {              // max / average pooling, depthwise convolution
@@ -144,7 +146,7 @@ bool fc_mfma_applicable(const FcArgs& a);
 hipError_t launch_fc_mfma(const FcArgs& a, const FcArgs* argv, int G, int nb, long long first, hipStream_t s);
 hipError_t launch_se(const SeArgs& a, const SeArgs* argv, int G, int nb, bool bf16, hipStream_t s);
 hipError_t launch_stage(const StageArgs& a, int nb, long long first, bool bf16, hipStream_t s);
-hipError_t launch_bind_request(RequestSlot* slot, const float* src, float* dst, hipStream_t s);
+hipError_t launch_bind_request(RequestSlot* slot, const RequestSlot& request, hipStream_t s);
 // Combination rule over the members' logits.
 //   COMBINE_MEAN      Y[i, :] = sum_m softmax(logits_m[i, :]) / M
 //   COMBINE_WEIGHTED  Y[i, :] = sum_m weights[m] * softmax(logits_m[i, :])   (weights: device, n_members floats)
@@ -162,6 +164,9 @@ struct CombineArgs {
     long long n;
 };
 hipError_t launch_combine(const CombineArgs& a, hipStream_t s);
+// Behind the combination on every lane: the last of the lanes to arrive writes the request's number to *flag in coherent host
+// memory.  arrivals: a zero, left as a zero.
+hipError_t launch_finish(unsigned* arrivals, int lanes, uint32_t* flag, uint32_t number, hipStream_t s);
 hipError_t launch_fill_noise(float* p, int64_t count, uint64_t seed, hipStream_t s);
 hipError_t launch_fill_zero(float* p, int64_t count, hipStream_t s);
 
@@ -182,6 +187,8 @@ LaunchEvents& next_launch_events();                  // per thread
 // units against efficiency per workgroup by this number; the engine sets it (per thread) to the chip's
 // units divided by the number of streams of the installed allocation.
 int& cu_budget();
+// Lanes that issue launches at once (set with cu_budget): what the kernels for few pixels weigh their load traffic against.
+int& lanes_busy();
 
 }  // namespace ens
 

@@ -53,6 +53,11 @@ int& cu_budget() {
     return units;
 }
 
+int& lanes_busy() {
+    static thread_local int lanes = 1;
+    return lanes;
+}
+
 LaunchEvents& next_launch_events() {
     static thread_local LaunchEvents ev;
     return ev;
@@ -158,14 +163,25 @@ hipError_t launch_stage(const StageArgs& a, int nb, long long first, bool bf16, 
     return hipGetLastError();
 }
 
-__global__ void bind_request_kernel(RequestSlot* slot, const float* src, float* dst) {
-    slot->src = src;
-    slot->dst = dst;
+__global__ void bind_request_kernel(RequestSlot* slot, const RequestSlot request) { *slot = request; }
+
+hipError_t launch_bind_request(RequestSlot* slot, const RequestSlot& request, hipStream_t s) {
+    if (!slot) return hipErrorInvalidValue;
+    ENS_LAUNCH(bind_request_kernel, dim3(1), dim3(1), 0, s, slot, request);
+    return hipGetLastError();
 }
 
-hipError_t launch_bind_request(RequestSlot* slot, const float* src, float* dst, hipStream_t s) {
-    if (!slot) return hipErrorInvalidValue;
-    ENS_LAUNCH(bind_request_kernel, dim3(1), dim3(1), 0, s, slot, src, dst);
+__global__ void finish_kernel(unsigned* arrivals, const unsigned lanes, uint32_t* flag, const uint32_t number) {
+    if (lanes > 1) {
+        if (__hip_atomic_fetch_add(arrivals, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != lanes - 1u) return;
+        __hip_atomic_store(arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __hip_atomic_store(flag, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+hipError_t launch_finish(unsigned* arrivals, int lanes, uint32_t* flag, uint32_t number, hipStream_t s) {
+    if (!arrivals || !flag || lanes < 1) return hipErrorInvalidValue;
+    ENS_LAUNCH(finish_kernel, dim3(1), dim3(1), 0, s, arrivals, (unsigned)lanes, flag, number);
     return hipGetLastError();
 }
 

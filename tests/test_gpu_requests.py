@@ -1,0 +1,169 @@
+"""Requests that do not fill a worker's batch size, and requests that come again.
+
+The first run their layers on the kernel for few output pixels (and their bottlenecks and dense layers one by
+one), so each shape where its tiles, its split of K or its tables can go wrong is compared with the oracle; the second
+are replayed from recorded graphs, so replays are compared with the first, launch-by-launch answer bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from synth import nets as N
+from synth import weights as W
+
+from .test_gpu_parity import assert_after_bf16_layers, layer_net, oracle_tensor, prepared
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ens():
+    import torch
+    assert torch.cuda.is_available(), "this test needs the GPU"
+    import paper_2208_14049_amd as ens
+    ens.lib()
+    return ens
+
+
+# (H, W, cin, cout, k, stride, extra, images)
+FEW = [
+    (14, 14, 256, 256, 3, 1, {"res": True}, 1),                # 7 tiles, the last with 4 pixels; 36 chunks over 8 wavefronts
+    (7, 7, 512, 512, 3, 1, {}, 3),                             # 72 chunks: nine per wavefront, two in flight
+    (5, 5, 8, 72, 3, 1, {"act": None}, 1),                     # 8 channels in the last tile, K = 72: a chunk of 64 and one of 8
+    (9, 11, 24, 40, 3, 2, {}, 2),                              # taps that change inside a chunk, half-empty channel tile, odd strided map
+    (12, 12, 160, 192, (1, 7), 1, {}, 2),
+    (12, 12, 48, 72, (7, 1), 1, {"act": "silu"}, 3),
+    (13, 13, 16, 64, 5, 1, {}, 1),
+    (14, 14, 1024, 256, 1, 1, {}, 2),                          # two chunks per wavefront
+    (28, 28, 512, 128, 1, 1, {"act": "silu"}, 4),              # 392 tiles: one chunk at a time
+    (15, 15, 264, 520, 1, 2, {"act": None}, 3),                # strided shortcut, last chunk of 8 channels
+    (14, 14, 512, 128, 1, 1, {"pre": True}, 3),                # pre-activated
+    (7, 7, 904, 128, 1, 1, {"pre": True}, 7),
+    (28, 28, 128, 128, 3, 1, {}, 6),                           # 588 tiles of 32 x 32: four wavefronts
+    (14, 14, 512, 512, 1, 1, {"res": True}, 8),                # 784 tiles: 64 x 64 instead
+    (14, 14, 128, 256, 3, 1, {"groups": 2}, 2),
+]
+
+
+@pytest.mark.parametrize("case", FEW, ids=lambda c: "%dx%dx%d-%d-k%s-s%d_n%d" % (c[0], c[1], c[2], c[3], c[4], c[5], c[7]))
+def test_layers_on_few_images(ens, case):
+    h, w, cin, cout, k, stride, extra, nb = case
+    extra = dict(extra)
+    with_res = extra.pop("res", False)
+    net, t = layer_net(h, w, cin, lambda n, s: n.conv(s, cout, k, stride=stride, res=s if with_res else None, **extra), "bf16")
+    blobs, _ = prepared([net], 11, nb, h, bf16=True)
+    imgs = W.round_bf16(W.make_images(4, nb, h, w))
+    E = ens.Ensemble([net], blobs)
+    E.set_base_size(h, w)
+    E.ens_debug_keep_tensors()
+    E.ens_set_alloc([[2 * nb]])
+    E.ens_set_profiling(1)
+    E.ens_predict(imgs)
+    ran = {kk["name"]: kk["launches"] for kk in E.ens_profile() if kk["launches"]}
+    assert ran.get("conv_small_bf16", 0) >= 1, ran
+    src = net.ops[-3]["src"]
+    got, x = E.ens_debug_tensor(0, t, net.tensors[t], nb), E.ens_debug_tensor(0, src, net.tensors[src], nb)
+    E.close()
+    sub = N.Net("sub", h, w, 8, dtype="bf16", in_c=cin)
+    sub.ops, sub.params, sub.blob_size = [dict(net.ops[-3])], net.params, net.blob_size
+    sub.tensors = [net.tensors[src], net.tensors[t]]
+    sub.ops[0].update(src=0, dst=1)
+    if with_res:
+        sub.ops[0].update(res=0)
+    sub.out_tensor = 1
+    ref = oracle.forward_logits(sub, blobs[0], x, real="f64").reshape(got.shape)
+    scale = np.sqrt(np.mean(ref ** 2)) + 1e-6
+    err = np.abs(got - ref)
+    bound = 2.0 ** -7 * np.abs(ref) + scale * 2.0 ** -5 + 1e-6     # as for the same layers on full batches
+    assert (err <= bound).all(), (float(err.max()), float(scale), float((err / bound).max()))
+    assert err.mean() <= 2.0 ** -8 * scale
+
+
+@pytest.mark.parametrize("G", [1, 2])
+def test_blocks_on_few_images(ens, G):
+    """What runs fused or in pairs on full batches, on two images of a batch of 16: a bottleneck and a dense layer one by one, a strided
+    convolution and its shortcut as one launch, a gated projection."""
+    nets = []
+    for g in range(G):
+        n = N.Net("few%d" % g, 28, 28, 8, dtype="bf16")
+        x = n.conv(0, 256, 3)
+        u = n.conv(n.conv(x, 64, 1), 64, 3)
+        y = n.conv(u, 256, 1, res=x)                             # bottleneck
+        s = n.conv(y, 96, 1, stride=2, act=None)
+        b = n.conv(y, 96, 3, stride=2, act=None)                 # a pair
+        z = n.conv(b, 96, 1, res=s)
+        e = n.conv(n.se(n.dwconv(n.conv(z, 144, 1, act="silu"), 3), 6), 64, 1, act=None)   # gated projection
+        blk = n.tensor(14, 14, 64 + 32)
+        n.conv(e, 64, 1, dst=(blk, 0))
+        n.conv(n.conv(blk, 128, 1, pre=True, src_slice=(0, 64)), 32, 3, bn=False, act=None, bias=False, dst=(blk, 64))   # dense layer
+        n.fc(n.gap(blk, pre=True), 8)
+        nets.append(n)
+    nb = 2
+    blobs = [W.quantise_weights_bf16(n, W.make_blob(n, 151, i)) for i, n in enumerate(nets)]
+    imgs = W.round_bf16(W.make_images(152, nb, 28, 28))
+    E = ens.Ensemble(nets, blobs)
+    E.ens_set_alloc([[16] * G])
+    E.ens_set_profiling(1)
+    E.ens_predict(imgs)
+    ran = {k["name"]: k["launches"] for k in E.ens_profile() if k["launches"]}
+    got = [E.ens_debug_tensor(g, blk, nets[g].tensors[blk], nb) for g in range(G)]   # alive until the global pooling
+    E.close()
+    assert "bottleneck_bf16<c64>" not in ran and "dense_layer_bf16" not in ran and "conv_small_bf16<32x32,gate>" in ran, ran
+    for g in range(G):
+        ref = oracle_tensor(nets[g], blobs[g], imgs, blk)
+        # eleven bf16 layers from the image: twice the bound of three (errors grow with the root of the number)
+        err, scale = np.abs(got[g] - ref), np.sqrt(np.mean(ref ** 2))
+        assert err.max() <= 0.06 * scale + 2.0 ** -7 * np.abs(ref).max() and err.mean() <= 2.0 ** -6 * scale, (g, float(err.max()), float(scale))
+
+
+@pytest.mark.parametrize("cin,cout,k,stride,extra", [(3, 16, 3, 1, {}), (3, 8, 5, 1, {"act": "silu"}), (16, 32, 3, 1, {}), (5, 10, 3, 2, {"act": None}),
+                                                     (8, 20, (1, 7), 1, {}), (12, 3, 5, 1, {"res": True}), (6, 33, 1, 1, {"pre": True}), (20, 24, 3, 1, {"pre": True})])
+def test_fp32_convolutions(ens, cin, cout, k, stride, extra):
+    """The fp32 kernel: channel counts in fours, threes and neither, partly empty channel tiles, filters with and without an unrolled size."""
+    extra = dict(extra)
+    cout = cin if extra.get("res") else cout
+    with_res = extra.pop("res", False)
+    for h, nb in ((9, 1), (32, 70)):                             # four channels per lane, and eight or sixteen
+        net, t = layer_net(h, h + 2, cin, lambda n, s: n.conv(s, cout, k, stride=stride, res=s if with_res else None, **extra), "fp32")
+        blobs, _ = prepared([net], 17, nb, h, bf16=False)
+        imgs = W.make_images(5, nb, h, h + 2)
+        E = ens.Ensemble([net], blobs)
+        E.set_base_size(h, h + 2)
+        E.ens_debug_keep_tensors()
+        E.ens_set_alloc([[nb]])
+        E.ens_predict(imgs)
+        m = min(nb, 4)
+        got = E.ens_debug_tensor(0, t, net.tensors[t], nb)[-m:]
+        E.close()
+        ref = oracle_tensor(net, blobs[0], imgs[-m:], t)
+        assert np.abs(got - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max()), (h, float(np.abs(got - ref).max()))
+
+
+def test_repeated_requests_are_replayed(ens):
+    """Sizes that come again are replayed as graphs on several lanes: every answer equals the first one of its size, from device and
+    host buffers that change from call to call, between other sizes, eager GPU work and changes of the combination rule."""
+    import torch
+    nets = [N.resnet18(size=64, classes=100), N.efficientnet(0, size=64, classes=100), N.densenet121(size=64, classes=100), N.resnet18(size=48, classes=100)]
+    blobs = [W.quantise_weights_bf16(net, W.make_blob(net, synth.BASE_SEED + 3, i)) for i, net in enumerate(nets)]
+    imgs = W.round_bf16(W.make_images(synth.BASE_SEED + 1000, 70, 64, 64, varied=True))
+    d = torch.from_numpy(imgs).cuda()
+    E = ens.Ensemble(nets, blobs)
+    E.ens_set_alloc([[16, 8, 32, 16], [8, 0, 0, 16]], 32)
+    sizes = (1, 3, 70, 17)
+    first = {n: E.ens_predict(d[:n].contiguous()).cpu().numpy() for n in sizes}
+    junk = torch.randn(512, 512, device="cuda")
+    for rep in range(6):
+        for n in sizes:
+            x = d[:n].clone() if rep % 2 else imgs[:n].copy()
+            junk = junk @ junk * 1e-3
+            y = E.ens_predict(x)
+            y = y.cpu().numpy() if rep % 2 else y
+            assert np.array_equal(y, first[n]), (rep, n)
+    z = E.ens_member_logits(2, sizes[-1])
+    E.ens_set_combination("weighted", [0.7, 0.1, 0.1, 0.1])
+    w = [E.ens_predict(d[:3].contiguous()).cpu().numpy() for _ in range(3)]
+    assert np.array_equal(w[0], w[1]) and np.array_equal(w[0], w[2]) and np.abs(w[0] - first[3]).max() > 1e-4
+    E.ens_set_combination("mean")
+    assert np.array_equal(E.ens_predict(d[:17].contiguous()).cpu().numpy(), first[17])
+    assert np.array_equal(E.ens_member_logits(2, 17), z)
+    E.close()
