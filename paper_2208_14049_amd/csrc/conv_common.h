@@ -266,6 +266,11 @@ bool conv_pw_applicable(const ConvArgs& a, int nb, int G);
 const char* conv_pw_name(const ConvArgs& a, int G);
 hipError_t launch_conv_pw(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s);
 
+// Pre-activated 1x1 kernel with the weights from memory (a.wpk); defined in conv_pre.hip.
+bool conv_pre_applicable(const ConvArgs& a, int nb);
+const char* conv_pre_name();
+hipError_t launch_conv_pre(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s);
+
 // Any convolution of few output pixels, K split over the wavefronts of small tiles; defined in conv_small.hip.
 // conv_small_pick returns the tile that runs the layer, or -1 when another kernel does; conv_small_layers says whether
 // layers on this many output pixels are better off one by one on it than fused with their neighbours.

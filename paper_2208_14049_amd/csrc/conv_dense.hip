@@ -391,6 +391,11 @@ bool conv_dense_applicable(const ConvArgs& a1, const ConvArgs& a2, int nb, int G
     DensePlan pl;
     if (!dense_plan(a1, a2, nb, G, &pl)) return false;
     if (conv_small_layers(a1, nb, G)) return false;
+    // Among other lanes' launches the two layers one by one (conv_pre.hip and the 3x3 kernel) take less of the chip once the window
+    // costs more than the tensor in between: us per launch with four lanes busy at batch 128, fused / separate: 14x14 from 512 channels
+    // 10.8 / 10.7, 1024 16.8 / 14.1, 1760 26.2 / 19.3; 28x28 256 27.8 / 23.5; 56x56 160 100.7 / 87.2; batch 64, 14x14 512 7.2 / 8.6.
+    // Alone the one kernel stays ahead (14x14 512: 19.6 / 24.1).
+    if (lanes_busy() >= 3 && (double)nb * a1.H * a1.W * G * a1.cin >= 12e6 && conv_pre_applicable(a1, nb)) return false;
     long long least = DENSE_MIN_TILES;
     return (long long)pl.tiles * G >= least;
 }

@@ -462,6 +462,7 @@ static bool pre_in_dma_kernel(const ConvArgs& a) {
 const char* conv_bf16_variant_name(const ConvArgs& a, int G) {
     const long long P = (long long)a.nb * a.Ho * a.Wo;
     if (conv_small_pick(a, a.nb, G) >= 0) return conv_small_name(a);
+    if (conv_pre_applicable(a, a.nb)) return conv_pre_name();
     if (a.pre_scale && !pre_in_dma_kernel(a)) return conv_regstage_name(a, (int)P);
     if (a.pair) return VARIANTS[pick_variant(a, P, (long long)a.kh * a.kw * a.cin, G)].name;
     if (conv_pw_applicable(a, a.nb, G)) return conv_pw_name(a, G);
@@ -514,6 +515,7 @@ hipError_t launch_conv_bf16(const ConvArgs& a, const ConvArgs* argv, int G, int 
     const int P = (int)P64;
     if (a.gate && (a.pre_scale || !conv_pw_applicable(a, nb, G))) return hipErrorInvalidValue;   // only the 1x1 kernel applies a gate
     if (const int sv = conv_small_pick(a, nb, G); sv >= 0) return launch_conv_small(a, argv, G, nb, sv, s);
+    if (conv_pre_applicable(a, nb)) return launch_conv_pre(a, argv, G, nb, s);
     if (a.pre_scale && !pre_in_dma_kernel(a)) return launch_conv_regstage(a, argv, G, nb, P, s);
     if (!a.pair) {                                               // the generic kernel takes pairs
         if (conv_pw_applicable(a, nb, G)) return launch_conv_pw(a, argv, G, nb, s);

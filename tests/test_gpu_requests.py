@@ -167,3 +167,29 @@ def test_repeated_requests_are_replayed(ens):
     assert np.array_equal(E.ens_predict(d[:17].contiguous()).cpu().numpy(), first[17])
     assert np.array_equal(E.ens_member_logits(2, 17), z)
     E.close()
+
+
+@pytest.mark.parametrize("h,w,cin,nb", [(14, 14, 32, 50), (14, 14, 96, 50), (7, 9, 640, 160), (28, 28, 288, 13), (14, 14, 1888, 51)])
+def test_preactivated_layers_on_full_batches(ens, h, w, cin, nb):
+    """The pre-activated 1x1 layer of a dense block as a launch of its own: one input chunk (half of it padding) up to thirty, a ragged last tile."""
+    n = N.Net("pre", h, w, 8, dtype="bf16")
+    blk = n.tensor(h, w, cin + 32)
+    n.conv(0, cin, 1, dst=(blk, 0))
+    u = n.conv(blk, 128, 1, pre=True, src_slice=(0, cin))
+    n.conv(u, 32, 3, bn=False, act=None, bias=False, dst=(blk, cin))
+    n.fc(n.gap(blk, pre=True), 8)
+    blobs = [W.quantise_weights_bf16(n, W.make_blob(n, 161, 0))]
+    imgs = W.round_bf16(W.make_images(162, nb, h, w))
+    E = ens.Ensemble([n], blobs)
+    E.set_base_size(h, w)
+    E.ens_debug_keep_tensors()
+    E.ens_set_alloc([[nb]])
+    E.ens_set_profiling(1)
+    E.ens_predict(imgs)
+    ran = {k["name"]: k["launches"] for k in E.ens_profile() if k["launches"]}
+    got = E.ens_debug_tensor(0, u, n.tensors[u], nb)
+    E.close()
+    assert ran.get("conv1x1_pre_bf16<128x128>") == 1, ran
+    for i in (0, nb - 1):                                        # the first tile, and the ragged one
+        ref = oracle_tensor(n, blobs[0], imgs[i:i + 1], u)
+        assert_after_bf16_layers(got[i:i + 1], ref, (i,))
