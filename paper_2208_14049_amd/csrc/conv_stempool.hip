@@ -39,136 +39,125 @@ __device__ __forceinline__ void sp_for_each(F&& f, std::integer_sequence<int, T.
 constexpr int SP_BP = 128;        // positions per sub-tile
 constexpr int SP_KB = 2;          // pooled rows per band
 constexpr int SP_BROWS = 2 * SP_KB + 1;
+constexpr int SP_T = 512;         // threads: eight wavefronts, four along the positions of a sub-tile, two along the channels
+constexpr int SP_MAXW = 8;        // window loads per thread a band may take
 
 // argv: G blocks of the convolution, then G blocks that describe the pooled output (y, Ho, Wo)
+//
+// Two wavefronts per SIMD: with one (four wavefronts, each all 64 channels of its positions) nothing hid a wavefront's own vector
+// work, tables and LDS round trips, and the matrix cores were busy a quarter of a band's 20 000 clocks.  A wavefront
+// takes 32 of the 64 channels, which halves the filter's registers; where a band's window and outputs lie is the same for
+// every band but for the rows outside the image, so that each thread works its offsets out once.
 template <int KH, int KW>
-__global__ __launch_bounds__(256) void stem_pool_bf16(const ConvArgs* __restrict__ argv, const int nb_, const int hrows,
-                                                      const int gh, const int gw, const int nsub) {
+__global__ __launch_bounds__(SP_T) void stem_pool_bf16(const ConvArgs* __restrict__ argv, const int nb_, const int hrows,
+                                                       const int gh, const int gw, const int nsub) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const ConvArgs a = argv[blockIdx.z];
     const ConvArgs pool = argv[gridDim.z + blockIdx.z];
-    constexpr int BP = SP_BP, BC = 64, NT = KH * KW, TC = 2;
+    constexpr int BP = SP_BP, BC = 64, NT = KH * KW;
 
-    const int W1 = a.W + gw, H1 = a.H + gh;
-    const int PP = nb_ * H1 * W1;
+    const int W1 = a.W + gw;
+    const float inv_w1 = __builtin_amdgcn_rcpf((float)W1);
     const int PH = pool.Ho, PW = pool.Wo;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wp0 = wave * 32;
+    const int wp0 = (wave & 3) * 32, wc0 = (wave >> 2) * 32;     // this wave's positions of a sub-tile, and channels
     const int c0 = blockIdx.y * BC;
-    const int hbytes = hrows * 32, nhl = hrows / 128;            // bytes and load instructions per band window
-    const int orows = nsub * BP;                                 // positions a band is computed for
+    const int hbytes = hrows * 32, nhl = hrows / 256;            // bytes and load instructions per band window
     const int phb = (PH + SP_KB - 1) / SP_KB;                    // bands per image
     const int n_bands = nb_ * phb;
 
-    // LDS: window 0 | window 1 | window tables 0, 1 | output tables 0, 1 | the band's stem output
-    int* const tbls = (int*)(lds + 2 * hbytes);      // window row -> input pixel index, -1: no pixel
-    int* const owns = tbls + 2 * hrows;              // position of the band -> output pixel index, -1: none
-    unsigned char* const ctile = (unsigned char*)(owns + 2 * orows);
-    const int origin = a.pt * W1 + a.pl;             // window row 0 is tap (0, 0) of the band's first position
+    // LDS: window 0 | window 1 | the band's stem output
+    unsigned char* const ctile = lds + 2 * hbytes;
 
     constexpr unsigned OOBV = 0x80000000u;           // past the end of every buffer the launcher admits: zeros (loads), dropped (stores)
     const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
         (void*)a.x.p, 0, (int)((unsigned)nb_ * (unsigned)(a.H * a.W) * (unsigned)a.x.stride * 2u), 0x00020000);
-    const int r0 = t >> 1;                                       // window row k * 128 + r0, half t & 1
-    const unsigned xlane = (unsigned)(a.x.c0 * 2 + (((t & 1) ^ ((r0 >> 3) & 1)) * 16));
-    // first raster position of band b: one stem row above the centre row of its first pooled row
-    auto band_start = [&](int b) {
-        const int n = b / phb, jb = b - n * phb;
-        return (n * H1 + 2 * SP_KB * jb - 1) * W1;
-    };
-    auto make_tables = [&](int buf, int start) {
-        raster_table(tbls + buf * hrows, hrows, start - origin, PP, H1, W1, a.H, a.W);
-        raster_table(owns + buf * orows, orows, start, PP, H1, W1, a.Ho, a.Wo);
-    };
-    auto issue_window = [&](int buf) {
-        const int* tbl = tbls + buf * hrows;
-        unsigned char* dst = lds + buf * hbytes + wave * 1024;
-        for (int k0 = 0; k0 < nhl; k0 += 4) {
-            int p4[4];
+    // A band of image n starts at column 0 of stem row 2 KB jb - 1 (one above the centre row of its first pooled row).  Window row
+    // q is tap (0, 0) of position q: image row = that row + wrow, byte offset = the band's + wofs; wrow < -63: never a pixel.
+    const int r0 = t >> 1;                                       // window row k * 256 + r0, half t & 1
+    int wrow[SP_MAXW], wofs[SP_MAXW];
 #pragma unroll
-            for (int j = 0; j < 4; j++) p4[j] = tbl[min(k0 + j, nhl - 1) * 128 + r0];
+    for (int k = 0; k < SP_MAXW; k++) {
+        const int q = k * 256 + r0, u = q - (a.pt * W1 + a.pl) + 8 * W1;      // at most four rows up
+        const int dr = u / W1 - 8, c = u - (dr + 8) * W1;
+        wrow[k] = c < a.W ? dr : -1000;
+        wofs[k] = (dr * a.W + c) * a.x.stride * 2 + a.x.c0 * 2 + (((t & 1) ^ ((r0 >> 3) & 1)) * 16);
+    }
+    auto issue_window = [&](int buf, int n, int first_row) {
+        unsigned char* const dst = lds + buf * hbytes + wave * 1024;
+        const int base = (n * a.H + first_row) * a.W * a.x.stride * 2;
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                if (k0 + j >= nhl) break;
-                const unsigned vo = p4[j] >= 0 ? (unsigned)(p4[j] * a.x.stride * 2) + xlane : OOBV;
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (lds_ptr_t)(dst + (k0 + j) * 4096), LDS_LOAD_BYTES, vo, 0, 0, 0);
-            }
+        for (int k = 0; k < SP_MAXW; k++) {
+            if (k >= nhl) break;
+            const bool ok = (unsigned)(first_row + wrow[k]) < (unsigned)a.H;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (lds_ptr_t)(dst + k * 8192), LDS_LOAD_BYTES, ok ? (unsigned)(base + wofs[k]) : OOBV, 0, 0, 0);
         }
     };
     const TileWalk walk = tile_walk(n_bands, (blockIdx.y + blockIdx.z * gridDim.y) * gridDim.x);
     int band = walk.first;
     if (band >= walk.end) return;
-    make_tables(0, band_start(band));
-    __syncthreads();
-    issue_window(0);
+    auto band_of = [&](int b, int* n, int* jb) { *n = b / phb; *jb = b - *n * phb; };
+    int n, jb;
+    band_of(band, &n, &jb);
+    issue_window(0, n, 2 * SP_KB * jb - 1);
 
-    // ---- the filter stays in registers for the workgroup's whole life: fragment (tap, i) of this lane is
-    //      half lane / 32 of weight row 32 i + r', r' = lane % 32 with bits 2 and 3 swapped (a lane's 16
-    //      results of a block are then two runs of 8 consecutive channels); weights are [cout][tap][16]
+    // ---- the filter stays in registers for the workgroup's whole life: fragment `tap` of this lane is
+    //      half lane / 32 of weight row wc0 + r', r' = lane % 32 with bits 2 and 3 swapped (a lane's 16
+    //      results are then two runs of 8 consecutive channels); weights are [cout][tap][16]
     const int lrow = lane & 31, lhalf = lane >> 5;
     const int prow = (lrow & 0x13) | ((lrow & 4) << 1) | ((lrow & 8) >> 1);
-    bf16x8 wreg[NT][TC];
+    bf16x8 wreg[NT];
     {
         const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
             (void*)a.w, 0, (int)((unsigned)a.cout * (unsigned)(NT * 16) * 2u), 0x00020000);
+        const int co = c0 + wc0 + prow;
+        const unsigned base = co < a.cout ? (unsigned)(co * NT * 32 + lhalf * 16) : OOBV;
 #pragma unroll
-        for (int i = 0; i < TC; i++) {
-            const int co = c0 + 32 * i + prow;
-            const unsigned base = co < a.cout ? (unsigned)(co * NT * 32 + lhalf * 16) : OOBV;
-#pragma unroll
-            for (int tap = 0; tap < NT; tap++)
-                wreg[tap][i] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wres, base, tap * 32, 0));
-        }
+        for (int tap = 0; tap < NT; tap++) wreg[tap] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wres, base, tap * 32, 0));
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
     const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(
         (void*)pool.y.p, 0, (int)((unsigned)nb_ * (unsigned)(PH * PW) * (unsigned)pool.y.stride * 2u), 0x00020000);
 
-    // scale and bias of this lane's 4 runs of 8 channels (32 i + 16 k + 8 (lane / 32) + 0..7) stay in registers:
-    // with one wavefront per SIMD there are registers to spare and no second wavefront to hide an LDS round trip
-    f32x4 sq[TC][2][2], bq[TC][2][2];
+    // scale and bias of this lane's two runs of 8 channels (wc0 + 16 k + 8 (lane / 32) + 0..7)
+    f32x4 sq[2][2], bq[2][2];
 #pragma unroll
-    for (int i = 0; i < TC; i++)
+    for (int k = 0; k < 2; k++) {
+        const int cb = wc0 + 16 * k + 8 * lhalf;
+        const bool ok = c0 + cb < a.cout;                        // channel counts come in 8s: a run exists or does not
 #pragma unroll
-        for (int k = 0; k < 2; k++) {
-            const int cb = 32 * i + 16 * k + 8 * lhalf;
-            const bool ok = c0 + cb < a.cout;                    // channel counts come in 8s: a run exists or does not
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                sq[i][k][h] = ok ? *ENS_GLOBAL(f32x4, a.scale + c0 + cb + 4 * h) : f32x4{1.f, 1.f, 1.f, 1.f};
-                bq[i][k][h] = ok ? *ENS_GLOBAL(f32x4, a.bias + c0 + cb + 4 * h) : f32x4{0.f, 0.f, 0.f, 0.f};
-            }
+        for (int h = 0; h < 2; h++) {
+            sq[k][h] = ok ? *ENS_GLOBAL(f32x4, a.scale + c0 + cb + 4 * h) : f32x4{1.f, 1.f, 1.f, 1.f};
+            bq[k][h] = ok ? *ENS_GLOBAL(f32x4, a.bias + c0 + cb + 4 * h) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
-    // the maxima: task idx = t + 256 j is (pooled row idx / 8 / PW of the band, pooled column idx / 8 % PW, channels
+    }
+    // the maxima: task idx = t + 512 j is (pooled row idx / 8 / PW of the band, pooled column idx / 8 % PW, channels
     // 8 (idx % 8) ..); what does not depend on the band is worked out once
-    constexpr int NTASK = (SP_KB * 128 * 8 + 255) / 256;         // pooled rows of up to 128 columns
+    constexpr int NTASK = (SP_KB * 128 * 8 + SP_T - 1) / SP_T;   // pooled rows of up to 128 columns
     int task_q[NTASK], task_y[NTASK];                            // tile row of the window's top-left corner; output offset less the band's
-    bool task_ok[NTASK];
-    int task_jr[NTASK];                                          // pooled row of the band
+    int task_jr[NTASK];                                          // pooled row of the band, 1000: no task
     bool task_left[NTASK];                                       // the window's first column lies left of the image
 #pragma unroll
     for (int j = 0; j < NTASK; j++) {
-        const int idx = t + 256 * j;
-        const int g = idx & 7, pc = (idx >> 3) % PW, jr = (idx >> 3) / PW;
-        const bool ok = jr < SP_KB && c0 + 8 * g < a.cout;
-        task_ok[j] = ok;
+        const int idx = t + SP_T * j;
+        const int g = idx & 7, jr = (idx >> 3) / PW, pc = (idx >> 3) - jr * PW;
         task_q[j] = (2 * jr) * W1 + 2 * pc - 1;
         task_left[j] = pc == 0;
-        task_jr[j] = jr;
+        task_jr[j] = jr < SP_KB && c0 + 8 * g < a.cout ? jr : 1000;
         task_y[j] = ((jr * PW + pc) * pool.y.stride + pool.y.c0 + c0 + 8 * g) * 2;
     }
 
-    // Per band: its window has landed; ask for the next band's (tables first); run the sub-tiles, each wave on
-    // its own 32 positions of every sub-tile with no barrier in between; then the maxima.
+    // Per band: its window has landed; ask for the next band's; run the sub-tiles, each wave on
+    // its own 32 positions and channels of every sub-tile with no barrier in between; then the maxima.
     for (int buf = 0; band < walk.end; band += walk.step, buf ^= 1) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this band's window (and, the first time, the filter): this wave's part,
         __syncthreads();                                         // everybody's; the previous band's maxima have been taken from the tile
-        const bool has_next = band + walk.step < walk.end;
-        if (has_next) {
-            make_tables(buf ^ 1, band_start(band + walk.step));
-            __syncthreads();                                     // tables written; the other window was free since the barrier above
-            issue_window(buf ^ 1);
+        const int first_row = 2 * SP_KB * jb - 1;
+        int nn = 0, njb = 0;
+        if (band + walk.step < walk.end) {
+            band_of(band + walk.step, &nn, &njb);
+            issue_window(buf ^ 1, nn, 2 * SP_KB * njb - 1);      // everybody is past the taps of the band before
         }
         const uint32_t halo0 = lds0 + (uint32_t)(buf * hbytes);
         // Pixel fragments come through a ring of four registers, three taps ahead of their use (LDS returns in
@@ -180,66 +169,61 @@ __global__ __launch_bounds__(256) void stem_pool_bf16(const ConvArgs* __restrict
             const uint32_t q = (uint32_t)(sub * BP + wp0 + lrow + (tap / KW) * W1 + tap % KW);
             xf[tap & 3] = sp_lds_read<0>(halo0 + q * 32 + ((((uint32_t)lhalf) ^ ((q >> 3) & 1)) << 4));
         };
-        auto issue_first = [&](int sub) {
+        auto run_sub = [&](int sub) {
+            const int q0 = sub * BP + wp0 + lrow;                // this lane's position of the band
             issue_frag(sub, std::integral_constant<int, 0>{});
             issue_frag(sub, std::integral_constant<int, 1>{});
             issue_frag(sub, std::integral_constant<int, 2>{});
             issue_frag(sub, std::integral_constant<int, 3>{});
-        };
-        auto run_sub = [&](int sub) {
-            const int q0 = sub * BP + wp0 + lrow;                // this lane's position of the band
-            issue_first(sub);
-            f32x16 acc[TC];
+            f32x16 acc;
 #pragma unroll
-            for (int i = 0; i < TC; i++)
-#pragma unroll
-                for (int v = 0; v < 16; v++) acc[i][v] = 0.f;
+            for (int v = 0; v < 16; v++) acc[v] = 0.f;
             sp_for_each([&](auto tap_c) {
                 constexpr int tap = decltype(tap_c)::value;
                 constexpr int ahead = NT - 1 - tap < 3 ? NT - 1 - tap : 3;
                 asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(xf[tap & 3]) : "n"(ahead));
-#pragma unroll
-                for (int i = 0; i < TC; i++) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wreg[tap][i], xf[tap & 3], acc[i], 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wreg[tap], xf[tap & 3], acc, 0, 0, 0);
                 if constexpr (tap + 4 < NT) issue_frag(sub, std::integral_constant<int, (tap + 4 < NT ? tap + 4 : tap)>{});
             }, std::make_integer_sequence<int, NT>{});
-            const int pout = owns[buf * orows + q0];
+            // the stem row of this position, less the band's first: a float quotient (exact below 2^24 but for the last unit) and its correction
+            int dr = (int)((float)q0 * inv_w1);
+            int dc = q0 - dr * W1;
+            if (dc < 0) { dr--; dc += W1; } else if (dc >= W1) { dr++; dc -= W1; }
+            const bool live = (unsigned)(first_row + dr) < (unsigned)a.Ho && dc < a.Wo;
             // ---- this sub-tile's stem output into the band's tile: register v of a lane is channel
-            //      32i + 16(v/8) + 8(lane/32) + v%8 of its position; scale, bias, ReLU, bf16
+            //      wc0 + 16(v/8) + 8(lane/32) + v%8 of its position; scale, bias, ReLU, bf16
             unsigned char* const row = ctile + q0 * 128;
 #pragma unroll
-            for (int i = 0; i < TC; i++)
+            for (int k = 0; k < 2; k++) {
+                uint32_t o[4];
 #pragma unroll
-                for (int k = 0; k < 2; k++) {
-                    uint32_t o[4];
-#pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        const float v0 = fmaf(acc[i][8 * k + 2 * e], sq[i][k][e >> 1][(2 * e) & 3], bq[i][k][e >> 1][(2 * e) & 3]);
-                        const float v1 = fmaf(acc[i][8 * k + 2 * e + 1], sq[i][k][e >> 1][(2 * e + 1) & 3], bq[i][k][e >> 1][(2 * e + 1) & 3]);
-                        // ReLU on the rounded pair: a negative bf16 is a negative 16-bit integer
-                        typedef short s16x2 __attribute__((ext_vector_type(2)));
-                        const s16x2 z = {0, 0};
-                        o[e] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2, pack_bf16x2(v0, v1)), z));
-                    }
-                    const u32x4 val = pout >= 0 ? u32x4{o[0], o[1], o[2], o[3]} : u32x4{0u, 0u, 0u, 0u};
-                    *(u32x4*)(row + ((((4 * i + 2 * k + lhalf) ^ ((q0 >> 1) & 7))) << 4)) = val;
+                for (int e = 0; e < 4; e++) {
+                    const float v0 = fmaf(acc[8 * k + 2 * e], sq[k][e >> 1][(2 * e) & 3], bq[k][e >> 1][(2 * e) & 3]);
+                    const float v1 = fmaf(acc[8 * k + 2 * e + 1], sq[k][e >> 1][(2 * e + 1) & 3], bq[k][e >> 1][(2 * e + 1) & 3]);
+                    // ReLU on the rounded pair: a negative bf16 is a negative 16-bit integer
+                    typedef short s16x2 __attribute__((ext_vector_type(2)));
+                    const s16x2 z = {0, 0};
+                    o[e] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2, pack_bf16x2(v0, v1)), z));
                 }
+                const u32x4 val = live ? u32x4{o[0], o[1], o[2], o[3]} : u32x4{0u, 0u, 0u, 0u};
+                *(u32x4*)(row + (((wc0 / 8 + 2 * k + lhalf) ^ ((q0 >> 1) & 7)) << 4)) = val;
+            }
         };
+#pragma unroll 1
         for (int sub = 0; sub < nsub; sub++) run_sub(sub);
         __syncthreads();                                         // the band's tile is complete
         // ---- 3x3 / stride-2 maxima; to the right of an image lies a gap column, below it a gap row: zeros in the tile
-        const int n = band / phb, jb = band - n * phb;
         const int j0 = SP_KB * jb;
         const unsigned yband = (unsigned)((n * PH + j0) * PW) * (unsigned)pool.y.stride * 2u;
         typedef short s16x8 __attribute__((ext_vector_type(8)));
-        s16x8 mx[NTASK];
 #pragma unroll
         for (int j = 0; j < NTASK; j++) {
-            mx[j] = s16x8{0, 0, 0, 0, 0, 0, 0, 0};
-            if (!task_ok[j]) continue;
-            const int g = (t + 256 * j) & 7;
+            if (task_jr[j] >= SP_KB) continue;
+            s16x8 mx = s16x8{0, 0, 0, 0, 0, 0, 0, 0};
+            const int g = (t + SP_T * j) & 7;
             // neighbouring groups of 8 lanes read columns two apart: rows of the same bank half.  Every other
             // group takes the three columns of its window in rotated order, so that the two never meet.
-            const int rot = ((t + 256 * j) >> 3) & 1;
+            const int rot = ((t + SP_T * j) >> 3) & 1;
 #pragma unroll
             for (int dr = 0; dr < 3; dr++)
 #pragma unroll
@@ -248,14 +232,12 @@ __global__ __launch_bounds__(256) void stem_pool_bf16(const ConvArgs* __restrict
                     if (dc == 0 && task_left[j]) continue;       // left of the image: padding
                     const int q = task_q[j] + dr * W1 + dc;
                     const s16x8 v = *(const s16x8*)(ctile + q * 128 + ((g ^ ((q >> 1) & 7)) << 4));
-                    mx[j] = __builtin_elementwise_max(mx[j], v); // non-negative bf16 values order like 16-bit integers
+                    mx = __builtin_elementwise_max(mx, v);       // non-negative bf16 values order like 16-bit integers
                 }
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, mx), yres, j0 + task_jr[j] < PH ? yband + (unsigned)task_y[j] : OOBV, 0, 0);
         }
-#pragma unroll
-        for (int j = 0; j < NTASK; j++) {
-            const unsigned yo = task_ok[j] && j0 + task_jr[j] < PH ? yband + (unsigned)task_y[j] : OOBV;
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, mx[j]), yres, yo, 0, 0);
-        }
+        n = nn;
+        jb = njb;
     }
 }
 
@@ -284,8 +266,9 @@ static bool stempool_plan(const ConvArgs& a, const ConvArgs& pool, int nb, int G
     pl->nsub = (SP_BROWS * W1 + SP_BP - 1) / SP_BP;
     const int orows = pl->nsub * SP_BP;
     const int need = orows + (a.kh - 1) * W1 + a.kw;             // window of a whole band
-    pl->hrows = (need + 127) / 128 * 128;
-    pl->bytes = 2 * ((size_t)pl->hrows * 32 + (size_t)pl->hrows * 4 + (size_t)orows * 4) + (size_t)orows * 128;
+    pl->hrows = (need + 255) / 256 * 256;
+    pl->bytes = 2 * (size_t)pl->hrows * 32 + (size_t)orows * 128;
+    if (pl->hrows / 256 > SP_MAXW || a.pt > 4) return false;
     if (pool.Wo > 128) return false;                  // the maxima of a band are dealt to the threads once, for up to 128 columns
     if (pl->bytes > (size_t)SP_LDS_LIMIT) return false;
     // as many workgroups as the chip holds at once, shared by the gang and the channel tiles, and not one more
@@ -316,7 +299,7 @@ hipError_t launch_conv_stempool(const ConvArgs& a, const ConvArgs& pool, const C
         raised = true;
     }
     const dim3 grid((unsigned)pl.wgs, (unsigned)((a.cout + 63) / 64), G);
-    ENS_LAUNCH((stem_pool_bf16<4, 4>), grid, dim3(256), pl.bytes, s, argv, nb, pl.hrows, pl.gh, pl.gw, pl.nsub);
+    ENS_LAUNCH((stem_pool_bf16<4, 4>), grid, dim3(SP_T), pl.bytes, s, argv, nb, pl.hrows, pl.gh, pl.gw, pl.nsub);
     return hipGetLastError();
 }
 
