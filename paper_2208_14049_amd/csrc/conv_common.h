@@ -266,6 +266,10 @@ bool conv_pw_applicable(const ConvArgs& a, int nb, int G);
 const char* conv_pw_name(const ConvArgs& a, int G);
 hipError_t launch_conv_pw(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s);
 
+// The same layers with tiles of 256 output channels; defined in conv_wide.hip.
+bool conv_wide_wanted(const ConvArgs& a, int nb, int G);
+hipError_t launch_conv_wide(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s);
+
 // Pre-activated 1x1 kernel with the weights from memory (a.wpk); defined in conv_pre.hip.
 bool conv_pre_applicable(const ConvArgs& a, int nb);
 const char* conv_pre_name();

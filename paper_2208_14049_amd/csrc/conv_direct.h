@@ -93,6 +93,18 @@ __device__ __forceinline__ bf16x8 bn_wload(const __amdgpu_buffer_rsrc_t& r, unsi
     return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, vo, so, 0));
 }
 
+// Input pixel of output pixel p of a 1x1 layer with a stride: p -> (image, row, column) with one double multiply per division and a
+// correction step.
+__device__ __forceinline__ int strided_input_pixel(const ConvArgs& a, int p) {
+    int n = (int)((double)p * a.inv_hw);
+    int rem = p - n * (a.Ho * a.Wo);
+    if (rem < 0) { n--; rem += a.Ho * a.Wo; } else if (rem >= a.Ho * a.Wo) { n++; rem -= a.Ho * a.Wo; }
+    int ho = (int)((double)rem * a.inv_w);
+    int wo = rem - ho * a.Wo;
+    if (wo < 0) { ho--; wo += a.Wo; } else if (wo >= a.Wo) { ho++; wo -= a.Wo; }
+    return (n * a.H + ho * a.sh) * a.W + wo * a.sw;
+}
+
 template <int N>
 __device__ __forceinline__ void bn_wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 

@@ -121,17 +121,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int s = 0; s < XO; s++) {
         const int p = p0 + r8 + 32 * s;
-        int pin = p;                                 // the input pixel of output pixel p
-        if (strided && p < P) {
-            // p -> (image, row, column) with one double multiply per division and a correction step
-            int n = (int)((double)p * a.inv_hw);
-            int rem = p - n * (a.Ho * a.Wo);
-            if (rem < 0) { n--; rem += a.Ho * a.Wo; } else if (rem >= a.Ho * a.Wo) { n++; rem -= a.Ho * a.Wo; }
-            int ho = (int)((double)rem * a.inv_w);
-            int wo = rem - ho * a.Wo;
-            if (wo < 0) { ho--; wo += a.Wo; } else if (wo >= a.Wo) { ho++; wo -= a.Wo; }
-            pin = (n * a.H + ho * a.sh) * a.W + wo * a.sw;
-        }
+        const int pin = strided && p < P ? strided_input_pixel(a, p) : p;     // the input pixel of output pixel p
         xvo[s] = p < P ? (unsigned)(pin * a.x.stride * 2) + (unsigned)(a.x.c0 * 2 + c8 * 16) : OOBV;
     }
     // in the last chunk of a layer whose input channels are not a multiple of 64 this thread's 8 channels
@@ -322,6 +312,7 @@ static int pw_wpx(const ConvArgs& a, int nb, int G) {
 
 const char* conv_pw_name(const ConvArgs& a, int G) {
     if (a.gate) return pw_wpx(a, a.nb, G) == 2 ? "conv1x1_direct_bf16<128x64,gate>" : "conv1x1_direct_bf16<128x128,gate>";
+    if (conv_wide_wanted(a, a.nb, G)) return "conv1x1_direct_bf16<128x256>";
     return pw_wpx(a, a.nb, G) == 2 ? "conv1x1_direct_bf16<128x64>" : "conv1x1_direct_bf16<128x128>";
 }
 
@@ -331,6 +322,7 @@ hipError_t launch_conv_pw(const ConvArgs& a, const ConvArgs* argv, int G, int nb
         if (!conv_pw_applicable(a, nb, G)) return hipErrorInvalidValue;
         return pw_wpx(a, nb, G) == 2 ? launch_pw_variant<2, true>(a, argv, G, nb, s) : launch_pw_variant<1, true>(a, argv, G, nb, s);
     }
+    if (conv_wide_wanted(a, nb, G)) return launch_conv_wide(a, argv, G, nb, s);
     return pw_wpx(a, nb, G) == 2 ? launch_pw_variant<2, false>(a, argv, G, nb, s) : launch_pw_variant<1, false>(a, argv, G, nb, s);
 }
 

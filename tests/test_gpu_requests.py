@@ -193,3 +193,34 @@ def test_preactivated_layers_on_full_batches(ens, h, w, cin, nb):
     for i in (0, nb - 1):                                        # the first tile, and the ragged one
         ref = oracle_tensor(n, blobs[0], imgs[i:i + 1], u)
         assert_after_bf16_layers(got[i:i + 1], ref, (i,))
+
+
+@pytest.mark.parametrize("h,w,cin,cout,stride,res,nb", [
+    (39, 30, 136, 208, 1, False, 112),     # last chunk of 8 channels, last 48 of 256 columns missing, wavefront with 16 of its 64 channels
+    (31, 33, 320, 768, 1, False, 43),      # odd number of chunks, ragged last tile
+    (14, 14, 256, 1024, 1, True, 64),      # one round of tiles; residual behind an even number of chunks
+    (14, 15, 328, 984, 1, True, 57),       # residual behind an odd one, partly missing columns
+    (27, 29, 192, 1000, 2, False, 64),     # strided shortcut
+])
+def test_wide_pointwise_layers(ens, h, w, cin, cout, stride, res, nb):
+    """1x1 layers on tiles of 256 output channels."""
+    n = N.Net("wide", h, w, 8, dtype="bf16")
+    u = n.conv(0, cin, 1)
+    r = n.conv(0, cout, 1) if res else None
+    y = n.conv(u, cout, 1, stride=stride, res=r)
+    n.fc(n.gap(y), 8)
+    blobs = [W.quantise_weights_bf16(n, W.make_blob(n, 171, 0))]
+    imgs = W.round_bf16(W.make_images(172, nb, h, w))
+    E = ens.Ensemble([n], blobs)
+    E.set_base_size(h, w)
+    E.ens_debug_keep_tensors()
+    E.ens_set_alloc([[nb]])
+    E.ens_set_profiling(1)
+    E.ens_predict(imgs)
+    ran = {k["name"]: k["launches"] for k in E.ens_profile() if k["launches"]}
+    got = E.ens_debug_tensor(0, y, n.tensors[y], nb)
+    E.close()
+    assert ran.get("conv1x1_direct_bf16<128x256>") == 1, ran
+    for i in (0, nb // 2, nb - 1):
+        ref = oracle_tensor(n, blobs[0], imgs[i:i + 1], y)
+        assert_after_bf16_layers(got[i:i + 1], ref, (i,))
