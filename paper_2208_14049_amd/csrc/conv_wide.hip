@@ -174,7 +174,7 @@ bool conv_wide_wanted(const ConvArgs& a, int nb, int G) {
     const int ctiles = (a.cout + WD_BC - 1) / WD_BC;
     const long long tiles = ((long long)nb * a.Ho * a.Wo + WD_BP - 1) / WD_BP * ctiles * G;
     if (a.gate || a.cin <= 128 || 4 * a.cout < 3 * ctiles * WD_BC) return false;
-    return lanes_busy() >= 3 ? tiles >= 128 : (tiles > 343 && tiles <= 512) || tiles >= 1024;
+    return lanes_in_use() >= 3 ? tiles >= 128 : (tiles > 343 && tiles <= 512) || tiles >= 1024;
 }
 
 hipError_t launch_conv_wide(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s) {

@@ -651,6 +651,7 @@ static void destroy_workers(ens_handle* h) {
     for (Gang& g : h->gangs)
         if (g.d_args) (void)hipFree(g.d_args);
     h->gangs.clear();
+    h->own_gangs = 0;
     for (Worker& w : h->workers)
         if (w.arena) (void)hipFree(w.arena);
     h->workers.clear();
@@ -668,8 +669,48 @@ static int64_t alloc_bytes(const ens_handle* h, const ens_alloc& a) {
 
 // The worker streams of an allocation run at once: each launch counts on its share of the chip.
 static int stream_share(const ens_handle* h) {
-    const int streams = (int)std::max<size_t>(1, h->gangs.size());
+    const int streams = std::max(1, h->own_gangs);
     return std::max(32, 256 / streams);
+}
+
+// Copies of the gangs (see Gang): LANES - 1 of a single gang, one each of two; of three or four, which have lanes enough, one of
+// those with batches of up to 64 images (see takes_turns).  They are an extra: no more than a quarter of the memory that is free,
+// nothing that a budget does not have room for, none while every tensor is kept for inspection.
+static void copy_gangs(ens_handle* h, int64_t need) {
+    const int own = h->own_gangs;
+    if (own > LANES || h->keep_tensors) return;
+    std::vector<int> copies(own);
+    size_t extra = 0, free_bytes = 0, total = 0;
+    for (int i = 0; i < own; i++) {
+        copies[i] = own == 1 ? LANES - 1 : own == 2 || h->workers[h->gangs[i].workers[0]].batch <= 64 ? 1 : 0;
+        for (int wi : h->gangs[i].workers) extra += copies[i] * std::max<size_t>(h->workers[wi].arena_bytes, 256);
+    }
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess || extra > free_bytes / 4) { (void)hipGetLastError(); return; }
+    if (h->budget && (uint64_t)need + extra > h->budget) return;
+    for (int k = 0; k < LANES - 1; k++)
+        for (int i = 0; i < own; i++) {
+            if (k >= copies[i]) continue;
+            Gang g = h->gangs[i];
+            g.copy = true;
+            g.copies.clear();
+            const size_t had = h->workers.size();
+            for (int& wi : g.workers) {
+                Worker w = h->workers[wi];
+                w.copy = true;
+                w.gang = (int)h->gangs.size();
+                w.arena = nullptr;
+                if (hipMalloc((void**)&w.arena, std::max<size_t>(w.arena_bytes, 256)) != hipSuccess) {
+                    (void)hipGetLastError();
+                    for (size_t j = had; j < h->workers.size(); j++) (void)hipFree(h->workers[j].arena);
+                    h->workers.resize(had);
+                    return;
+                }
+                wi = (int)h->workers.size();
+                h->workers.push_back(w);
+            }
+            h->gangs[i].copies.push_back((int)h->gangs.size());
+            h->gangs.push_back(g);
+        }
 }
 
 static int install_alloc(ens_handle* h, const ens_alloc& a, int segment_size) {
@@ -733,15 +774,18 @@ static int install_alloc(ens_handle* h, const ens_alloc& a, int segment_size) {
             g.workers.push_back((int)i);
             g.rank = w.rank; g.of = w.of;
             w.gang = (int)h->gangs.size();
+            g.copies.push_back(w.gang);
             h->gangs.push_back(g);
         }
     }
+    h->own_gangs = (int)h->gangs.size();
+    copy_gangs(h, need);
     if (!h->d_logits.empty() && !h->d_logits[0]) {               // argument blocks hold the logits pointers
         const int rc0 = ensure_buffers(h, 1);
         if (rc0 != ENS_OK) { destroy_workers(h); return rc0; }
     }
     cu_budget() = stream_share(h);
-    lanes_busy() = std::min(LANES, std::max(1, (int)h->gangs.size()));
+    lanes_busy() = lanes_in_use() = std::min(LANES, std::max(1, h->own_gangs));
     for (Gang& g : h->gangs) {
         const int rc = build_launches(h, g);
         if (rc != ENS_OK) { destroy_workers(h); return rc; }
@@ -881,22 +925,36 @@ static int grow(float** p, size_t* cap, size_t want_floats) {
     return ENS_OK;
 }
 
-// Calls fn(gang, first image, images) for every batch of a request of n images, in the order of issue.
+// Does a gang with `batches` batches in a request share them with its copies?  One or two gangs always: 512 images through a
+// ResNet-50 in batches of 128, 64 and 32 8.7 -> 7.4, 10.4 -> 7.7 and 12.6 -> 8.9 ms.  Three or four from four batches on: four members,
+// 256 images in batches of 64, 32 and 16 16.2 -> 15.5, 20.7 -> 18.2 and 28.9 -> 23.4 ms; with two batches each (100 images,
+// batches of 64) the lanes were loaded less evenly than by one gang each, 10.1 -> 10.5 ms, and with batches of 128 images three lanes
+// fill the GPU: 38.5 -> 39.1 ms.
+static bool takes_turns(const ens_handle* h, const Gang& g, int64_t batches) {
+    return !h->one_stream && g.copies.size() > 1 && (h->own_gangs <= 2 || batches >= 4);
+}
+
+// Calls fn(gang, first image, images) for every batch of a request of n images, in the order of issue.  A gang's copies take its
+// batches in turn.
 template <typename F>
 static int each_batch(ens_handle* h, int64_t n, uint64_t mask, const std::vector<std::vector<int32_t>>& owner, F&& fn) {
     const int seg = h->segment_size;
     const int64_t n_seg = (n + seg - 1) / seg;
+    std::vector<size_t> turn(h->own_gangs, 0);
     for (int64_t s = 0; s < n_seg; s++) {
         const int64_t start = s * seg, end = std::min<int64_t>((s + 1) * seg, n);
-        for (Gang& g : h->gangs) {
+        for (int i = 0; i < h->own_gangs; i++) {
+            Gang& g = h->gangs[i];
             const int member0 = h->workers[g.workers[0]].member;
             if (g.of > 1 && owner[member0][s] != g.rank) continue;
             bool wanted = false;
             for (int wi : g.workers) wanted = wanted || ((mask >> h->workers[wi].member) & 1);
             if (!wanted) continue;
             const int b = h->workers[g.workers[0]].batch;
+            const bool turns = takes_turns(h, g, (n + b - 1) / b / g.of);
             for (int64_t a = start; a < end; a += b) {
-                const int rc = fn(g, a, (int)std::min<int64_t>(b, end - a));
+                Gang& taker = turns ? h->gangs[g.copies[turn[i]++ % g.copies.size()]] : g;
+                const int rc = fn(taker, a, (int)std::min<int64_t>(b, end - a));
                 if (rc != ENS_OK) return rc;
             }
         }
@@ -1087,7 +1145,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
                       const float* host_images = nullptr) {
     if (n == 0) return ENS_OK;
     cu_budget() = stream_share(h);
-    lanes_busy() = std::min(LANES, std::max(1, (int)h->gangs.size()));
+    lanes_busy() = std::min(LANES, std::max(1, h->own_gangs));
     int rc = may_alloc ? ensure_buffers(h, n) : ENS_OK;
     if (rc != ENS_OK) return rc;
     if ((size_t)n > h->d_logits_rows) return ENS_E_INVALID;
@@ -1096,10 +1154,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
     const int64_t n_seg = (n + seg - 1) / seg;
     if (h->args_stale) {                                         // the logits moved
         drop_graphs(h);
-        for (Gang& g : h->gangs) {
-            rc = build_launches(h, g, may_alloc);
-            if (rc != ENS_OK) return rc;
-        }
+        for (Gang& g : h->gangs) g.stale = true;
         h->args_stale = false;
     }
     h->requests++;
@@ -1116,7 +1171,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
             std::vector<int32_t> batches;
             const Gang* first = nullptr;
             for (const Worker& w : h->workers)                   // in slot order = rank order
-                if (w.member == c) {
+                if (w.member == c && !w.copy) {
                     batches.push_back(w.batch);
                     if (w.rank == 0) first = &h->gangs[w.gang];
                 }
@@ -1134,7 +1189,13 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
         // More gangs than lanes with several batches each are handed out as the lanes come free (below), unless their launches are so
         // short that the host has to be out of the way.
         hand_out_batches = !h->one_stream && h->gangs.size() > LANES && work.most > 1 && work.total > HAND_OUT_LAUNCH_S * (double)work.launches;
-        lanes = hand_out_batches ? LANES : deal_lanes(h, work);
+        lanes = lanes_in_use() = hand_out_batches ? LANES : deal_lanes(h, work);
+        for (size_t i = 0; i < h->gangs.size(); i++) {
+            if (!h->gangs[i].stale || work.batches[i].empty()) continue;
+            rc = build_launches(h, h->gangs[i], may_alloc);
+            if (rc != ENS_OK) return rc;
+            h->gangs[i].stale = false;
+        }
         if (!plain_only && !(host_images && n_seg > 1) && !hand_out_batches && lanes >= GRAPH_MIN_LANES && work.launches <= GRAPH_MAX_LAUNCHES &&
             seen_before(h, n))
             graph = record_request(h, n, lanes, owner);
@@ -1474,7 +1535,7 @@ int ens_predict(ens_handle* h, const float* images, int64_t n, float* probs_out)
     const size_t img_floats = (size_t)n * h->base_h * h->base_w * 3, out_floats = (size_t)n * h->classes;
     const float *d_in = images, *host_in = nullptr;
     if (!h->images_on_device) {
-        if (img_floats * sizeof(float) * h->gangs.size() <= DIRECT_IN_BYTES) {
+        if (img_floats * sizeof(float) * h->own_gangs <= DIRECT_IN_BYTES) {
             int rc = grow_pinned(&h->pin_in, &h->pin_in_cap, img_floats, hipHostMallocNonCoherent);
             if (rc != ENS_OK) return rc;
             memcpy(h->pin_in, images, img_floats * sizeof(float));

@@ -124,6 +124,7 @@ struct Worker {
     int member = 0, batch = 0, slot = 0;
     int rank = 0, of = 1;          // this is worker `rank` of the member's `of` workers
     int gang = -1;
+    bool copy = false;             // the arena of a gang's copy (see Gang)
     char* arena = nullptr;
     size_t arena_bytes = 0;
     ArenaLayout layout;
@@ -139,10 +140,17 @@ struct GangPlan {
 // Workers that run the same network shape at the same batch size on the same segments (the
 // replicas of a homogeneous ensemble in one row of the allocation matrix) advance in lockstep:
 // one stream, and one kernel launch per operation whose grid spans all of them.
+//
+// Where there are few of them a gang has copies, gangs of their own over the same members with an arena more each, and its
+// batches go to the copies in turn: the batches of one gang ran one after the other on one lane, and its kernels leave compute
+// units idle at the end of every launch and wait for memory at its beginning.
 struct Gang {
     std::vector<int> workers;      // indices into ens_handle::workers; [0] leads (its input tensor is shared)
     int rank = 0, of = 1;
     int lane = 0;                  // lane of the request in flight
+    bool copy = false;
+    std::vector<int> copies;       // of the gang they were made from: itself and its copies, indices into ens_handle::gangs
+    bool stale = false;            // its argument blocks name request buffers that have moved
     std::vector<GangPlan> plans;   // by the batch sizes they are for, ascending; the last one ends at the workers' batch size
     const GangPlan& plan_for(int images) const {
         for (const GangPlan& p : plans)
@@ -186,7 +194,8 @@ struct ProfRec { int klass; hipEvent_t start, stop; double flop, bytes; };
 struct ens_handle {
     std::vector<ens::Member> members;
     std::vector<ens::Worker> workers;
-    std::vector<ens::Gang> gangs;
+    std::vector<ens::Gang> gangs;                // the copies last
+    int own_gangs = 0;                           // without the copies
     bool gangs_enabled = true;                   // false: every worker is a gang of its own
     bool args_stale = false;                     // request buffers moved: argument arrays need rebuilding
     ens_alloc alloc;

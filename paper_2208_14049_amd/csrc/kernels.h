@@ -187,8 +187,11 @@ LaunchEvents& next_launch_events();                  // per thread
 // units against efficiency per workgroup by this number; the engine sets it (per thread) to the chip's
 // units divided by the number of streams of the installed allocation.
 int& cu_budget();
-// Lanes that issue launches at once (set with cu_budget): what the kernels for few pixels weigh their load traffic against.
+// Lanes that issue launches at once (set with cu_budget, the same for every request of an allocation, so that what was planned
+// together also runs together): what the kernels for few pixels weigh their load traffic against.
 int& lanes_busy();
+// Lanes that the request in flight is spread over; for choices that are made launch by launch.
+int& lanes_in_use();
 
 }  // namespace ens
 

@@ -58,6 +58,11 @@ int& lanes_busy() {
     return lanes;
 }
 
+int& lanes_in_use() {
+    static thread_local int lanes = 1;
+    return lanes;
+}
+
 LaunchEvents& next_launch_events() {
     static thread_local LaunchEvents ev;
     return ev;

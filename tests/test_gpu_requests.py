@@ -224,3 +224,36 @@ def test_wide_pointwise_layers(ens, h, w, cin, cout, stride, res, nb):
     for i in (0, nb // 2, nb - 1):
         ref = oracle_tensor(n, blobs[0], imgs[i:i + 1], y)
         assert_after_bf16_layers(got[i:i + 1], ref, (i,))
+
+
+def tiny_member(i):
+    n = N.Net("turns%d" % i, 12, 12, 8, dtype="bf16")
+    n.fc(n.gap(n.conv(n.conv(0, 16 + 8 * i, 3), 32, 3)), 8)
+    return n
+
+
+@pytest.mark.parametrize("members,rows,batch,images", [
+    (1, 1, 4, 23),             # six batches of one gang over four arenas, the last one short
+    (1, 2, 4, 23),             # two instances: two arenas each
+    (3, 1, 4, 11),             # three gangs with three batches each: one arena each
+    (3, 1, 4, 17),             # with five: two arenas each
+])
+def test_batches_take_turns(ens, members, rows, batch, images):
+    """Batches of one gang on arenas of its own and its copies': the answer is that of one stream, which uses no copy, and stays it when
+    the logits move to the fixed device array and back."""
+    import torch
+    nets = [tiny_member(i) for i in range(members)]
+    blobs = [W.quantise_weights_bf16(n, W.make_blob(n, 181 + i, 0)) for i, n in enumerate(nets)]
+    x = torch.from_numpy(W.round_bf16(W.make_images(182, images, 12, 12))).cuda()
+    E = ens.Ensemble(nets, blobs)
+    E.set_base_size(12, 12)
+    E.ens_set_alloc([[batch] * members] * rows, 8)
+    E.ens_debug_one_stream(1)
+    want = E.ens_predict(x)
+    E.ens_debug_one_stream(0)
+    out = torch.empty_like(want)
+    for _ in range(4):
+        assert torch.equal(E.ens_predict(x), want)
+        E.ens_predict_static(x, out)
+        assert torch.equal(out, want)
+    E.close()
