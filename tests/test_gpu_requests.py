@@ -257,3 +257,21 @@ def test_batches_take_turns(ens, members, rows, batch, images):
         E.ens_predict_static(x, out)
         assert torch.equal(out, want)
     E.close()
+
+
+def test_small_host_requests_see_their_own_images(ens):
+    """Small requests from host memory go through one pinned buffer, and are waited for without synchronising a stream: requests of one
+    size with other images each time give the answers that the same images give from device memory."""
+    import torch
+    nets = [tiny_member(i) for i in range(3)]
+    blobs = [W.quantise_weights_bf16(n, W.make_blob(n, 191 + i, 0)) for i, n in enumerate(nets)]
+    imgs = W.round_bf16(W.make_images(192, 40, 12, 12, varied=True))
+    E = ens.Ensemble(nets, blobs)
+    E.set_base_size(12, 12)
+    E.ens_set_alloc([[4] * 3], 8)
+    want = [E.ens_predict(torch.from_numpy(imgs[4 * i:4 * i + 4]).cuda()).cpu().numpy() for i in range(10)]
+    assert np.abs(want[0] - want[1]).max() > 1e-4
+    for rep in range(20):
+        i = rep * 7 % 10
+        assert np.array_equal(E.ens_predict(imgs[4 * i:4 * i + 4].copy()), want[i]), rep
+    E.close()
