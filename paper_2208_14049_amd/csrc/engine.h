@@ -167,7 +167,8 @@ struct Gang {
 // an allocation's streams shared a queue while others stood empty (four streams in a row: two queues).  A stream made with
 // a compute-unit mask has a queue of its own; the mask names every unit.  Four of them: the GPU drains four queues
 // at once (eight take 1.8 times as long as four for the same work per queue, and many queues of short kernels are slower
-// than four), and gangs are dealt to them by estimated time.
+// than four), and gangs are dealt to them by estimated time.  Streams of this kind order themselves with the null
+// stream, so that a request waits for work that another thread has in flight there.
 constexpr int LANES = 4;
 hipError_t acquire_lanes(hipStream_t* lanes);    // LANES streams; every successful call is paired with one of
 void release_lanes(const hipStream_t* lanes);    // these; the streams go with the last handle
