@@ -41,6 +41,7 @@ constexpr int SP_KB = 2;          // pooled rows per band
 constexpr int SP_BROWS = 2 * SP_KB + 1;
 constexpr int SP_T = 512;         // threads: eight wavefronts, four along the positions of a sub-tile, two along the channels
 constexpr int SP_MAXW = 8;        // window loads per thread a band may take
+constexpr int SP_NO_PIXEL = -(1 << 30);
 
 // argv: G blocks of the convolution, then G blocks that describe the pooled output (y, Ho, Wo)
 //
@@ -74,14 +75,15 @@ __global__ __launch_bounds__(SP_T) void stem_pool_bf16(const ConvArgs* __restric
     const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
         (void*)a.x.p, 0, (int)((unsigned)nb_ * (unsigned)(a.H * a.W) * (unsigned)a.x.stride * 2u), 0x00020000);
     // A band of image n starts at column 0 of stem row 2 KB jb - 1 (one above the centre row of its first pooled row).  Window row
-    // q is tap (0, 0) of position q: image row = that row + wrow, byte offset = the band's + wofs; wrow < -63: never a pixel.
+    // q is tap (0, 0) of position q: image row = that row + wrow, byte offset = the band's + wofs.  The gap columns between rows hold no
+    // pixel: their wrow keeps the sum below zero for every row that an image can have.
     const int r0 = t >> 1;                                       // window row k * 256 + r0, half t & 1
     int wrow[SP_MAXW], wofs[SP_MAXW];
 #pragma unroll
     for (int k = 0; k < SP_MAXW; k++) {
         const int q = k * 256 + r0, u = q - (a.pt * W1 + a.pl) + 8 * W1;      // at most four rows up
         const int dr = u / W1 - 8, c = u - (dr + 8) * W1;
-        wrow[k] = c < a.W ? dr : -1000;
+        wrow[k] = c < a.W ? dr : SP_NO_PIXEL;
         wofs[k] = (dr * a.W + c) * a.x.stride * 2 + a.x.c0 * 2 + (((t & 1) ^ ((r0 >> 3) & 1)) * 16);
     }
     auto issue_window = [&](int buf, int n, int first_row) {

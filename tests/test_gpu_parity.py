@@ -363,6 +363,30 @@ def test_stem_and_max_pool_in_one_kernel(ens, h, w, cout, G, nb):
         assert err.mean() <= 2.0 ** -8 * scale
 
 
+@pytest.mark.parametrize("h,w,nb", [(2016, 224, 1), (2500, 46, 2)], ids=["2016x224", "2500x46_two_images"])
+def test_stem_and_max_pool_of_tall_images(ens, h, w, nb):
+    """Stem maps of more than a thousand rows: the gap columns between rows are padding in every band of the image, the last
+    ones among them.  Compared row by row, since a fault of one band would drown in a mean over the map."""
+    n = N.Net("tall", h, w, 8, dtype="bf16")
+    pooled = n.maxpool(n.conv(0, 64, 7, stride=2), 3, 2, 1)
+    n.fc(n.gap(pooled), 8)
+    blobs = [W.quantise_weights_bf16(n, W.make_blob(n, 93, 0))]
+    imgs = W.round_bf16(W.make_images(94, nb, h, w))
+    E = ens.Ensemble([n], blobs)
+    E.set_base_size(h, w)
+    E.ens_set_alloc([[nb]])
+    E.ens_set_profiling(1)
+    E.ens_predict(imgs)
+    ran = {k["name"]: k["launches"] for k in E.ens_profile() if k["launches"]}
+    got = E.ens_debug_tensor(0, pooled, n.tensors[pooled], nb)
+    E.close()
+    assert ran.get("stem_pool_bf16<4x4>") == 1, ran
+    ref = oracle_tensor(n, blobs[0], imgs, pooled)
+    scale = np.sqrt(np.mean(ref ** 2)) + 1e-6
+    ratio = np.abs(got - ref) / (2.0 ** -7 * np.abs(ref) + scale * 2.0 ** -5 + 1e-6)   # the bound of the test above
+    assert (ratio <= 1.0).all(), np.argwhere(ratio.max(axis=(2, 3)) > 1.0)[:10]
+
+
 # (C, H, W, cin, cout, residual, activation of the last convolution, members in the gang, images, batch)
 BOTTLENECKS = [
     (64, 24, 24, 256, 256, "input", "relu", 1, 56, 64),        # identity block, short last batch
