@@ -637,7 +637,7 @@ static hipError_t wait_lanes(ens_handle* h) {
             if (i % 64 == 0 && std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > SPIN_S) break;
         }
     }
-    for (int l = 0; l < LANES && h->have_lanes; l++) {
+    for (int l = 0; l < h->lanes_used; l++) {
         const hipError_t e = hipStreamSynchronize(h->lanes[l]);
         if (e != hipSuccess) return e;
     }
@@ -1200,6 +1200,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
             seen_before(h, n))
             graph = record_request(h, n, lanes, owner);
     }
+    h->lanes_used = lanes;
     // Host images go to the device in pieces of the smallest batch, beside the kernels; a lane waits for the last piece it needs.
     const size_t image_floats = (size_t)h->base_h * h->base_w * 3;
     int64_t piece = seg;

@@ -170,6 +170,8 @@ struct Gang {
 // than four), and gangs are dealt to them by estimated time.  Streams of this kind order themselves with the null
 // stream, so that a request waits for work that another thread has in flight there.
 constexpr int LANES = 4;
+// Handles share them, each beginning with another one: a request waits for the lanes that it uses itself, and queues behind another
+// handle's work only where the two meet on a lane.
 hipError_t acquire_lanes(hipStream_t* lanes);    // LANES streams; every successful call is paired with one of
 void release_lanes(const hipStream_t* lanes);    // these; the streams go with the last handle
 
@@ -208,6 +210,7 @@ struct ens_handle {
     hipStream_t main_stream = nullptr;           // copies, and the recording of graphs
     hipStream_t lanes[ens::LANES] = {nullptr, nullptr, nullptr, nullptr};
     bool have_lanes = false;
+    int lanes_used = 0;                          // by the last request: the first ones of `lanes`
     std::vector<hipEvent_t> copied;              // per piece of a host request: its images are on the device
     ens::RequestSlot* d_slots = nullptr;         // one per lane
     unsigned* d_arrivals = nullptr;              // see CombineArgs; one more for finish_kernel

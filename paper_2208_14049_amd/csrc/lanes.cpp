@@ -9,6 +9,7 @@ namespace {
 constexpr int MAX_DEVICES = 64;
 struct LaneSet {
     int users = 0;
+    int first = 0;                 // of the next handle: those with work for one lane do not all meet on the same one
     hipStream_t s[LANES] = {nullptr, nullptr, nullptr, nullptr};
 };
 std::mutex g_lock;
@@ -44,17 +45,19 @@ hipError_t acquire_lanes(hipStream_t* lanes) {
         }
     }
     set.users++;
-    for (int i = 0; i < LANES; i++) lanes[i] = set.s[i];
+    for (int i = 0; i < LANES; i++) lanes[i] = set.s[(set.first + i) % LANES];
+    set.first = (set.first + 1) % LANES;
     return hipSuccess;
 }
 
 void release_lanes(const hipStream_t* lanes) {
     std::lock_guard<std::mutex> hold(g_lock);
     for (LaneSet& set : g_sets)
-        if (set.users > 0 && set.s[0] == lanes[0]) {
-            if (--set.users == 0) destroy(set);
-            return;
-        }
+        for (const hipStream_t s : set.s)
+            if (set.users > 0 && s == lanes[0]) {
+                if (--set.users == 0) destroy(set);
+                return;
+            }
 }
 
 }  // namespace ens

@@ -275,3 +275,81 @@ def test_small_host_requests_see_their_own_images(ens):
         i = rep * 7 % 10
         assert np.array_equal(E.ens_predict(imgs[4 * i:4 * i + 4].copy()), want[i]), rep
     E.close()
+
+
+def run_beside(work):
+    """Starts work() on a thread of its own; returns the thread and a list that gets the time of its end."""
+    import threading
+    import time
+    end = []
+
+    def body():
+        work()
+        end.append(time.perf_counter())
+    th = threading.Thread(target=body)
+    th.start()
+    return th, end
+
+
+def test_a_request_does_not_wait_for_another_handles_lanes(ens):
+    """A request of microseconds on one lane, sent while another handle's request of some hundred milliseconds runs on one lane of its own, is
+    answered long before that one.  (Through the C entry point with device buffers: torch's own synchronisation of the null stream, which the
+    binding does for device tensors, waits for every lane.)"""
+    import time
+    import torch
+    long = N.Net("long", 128, 128, 8, dtype="fp32")
+    t = 0
+    for _ in range(16):
+        t = long.conv(t, 64, 3)
+    long.fc(long.gap(t), 8)
+    short = tiny_member(0)
+    B = ens.Ensemble([long], [W.make_blob(long, 201, 0)])
+    B.ens_set_alloc([[256]], 256)                                # one batch: one lane
+    A = ens.Ensemble([short], [W.quantise_weights_bf16(short, W.make_blob(short, 202, 0))])
+    A.ens_set_alloc([[8]])
+    xb, yb = torch.randn(256, 128, 128, 3, device="cuda"), torch.empty(256, 8, device="cuda")
+    xa, ya = torch.randn(4, 12, 12, 3, device="cuda"), torch.empty(4, 8, device="cuda")
+    B.ens_predict(xb, yb)
+    want = A.ens_predict(xa, ya).clone()
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    B.ens_predict(xb, yb)
+    alone = time.perf_counter() - t0
+    L = ens.lib()
+    th, end = run_beside(lambda: L.ens_predict(B._h, xb.data_ptr(), 256, yb.data_ptr()))
+    time.sleep(0.1 * alone)
+    t0 = time.perf_counter()
+    assert L.ens_predict(A._h, xa.data_ptr(), 4, ya.data_ptr()) == 0
+    t1 = time.perf_counter()
+    th.join()
+    assert t0 < end[0] and t1 - t0 < 0.4 * alone and t1 < end[0], (alone, t1 - t0, end[0] - t0)
+    assert torch.equal(ya, want)
+    A.close()
+    B.close()
+
+
+def test_two_handles_in_two_threads(ens):
+    """Two handles that share the lanes, one of them with recorded requests, each in a thread of its own: the answers are those that each gives alone."""
+    nets = [[N.resnet18(size=64, classes=100), N.efficientnet(0, size=64, classes=100), N.densenet121(size=64, classes=100)], [tiny_member(i) for i in range(4)]]
+    sizes, requests = ((1, 5, 40), (2, 9, 33)), []
+    for k, members in enumerate(nets):
+        blobs = [W.quantise_weights_bf16(n, W.make_blob(n, 211 + k, i)) for i, n in enumerate(members)]
+        imgs = W.round_bf16(W.make_images(213 + k, 40, members[0].in_h, members[0].in_w, varied=True))
+        E = ens.Ensemble(members, blobs)
+        E.ens_set_alloc([[8] * len(members)], 16)
+        requests.append((E, imgs, {n: E.ens_predict(imgs[:n]) for n in sizes[k]}))
+    wrong = []
+
+    def serve(k):
+        E, imgs, want = requests[k]
+        for rep in range(40):
+            for n in sizes[k]:
+                if not np.array_equal(E.ens_predict(imgs[:n]), want[n]):
+                    wrong.append((k, rep, n))
+    threads = [run_beside(lambda k=k: serve(k)) for k in range(2)]
+    for th, end in threads:
+        th.join()
+        assert end, "a request failed"
+    assert not wrong, wrong[:5]
+    for E, _, _ in requests:
+        E.close()
