@@ -226,6 +226,17 @@ int ens_member_logits(ens_handle* h, int32_t member, int64_t n, float* logits_ou
 int ens_debug_keep_tensors(ens_handle* h, int32_t on);
 int ens_debug_tensor(ens_handle* h, int32_t member, int32_t tensor, int32_t n_images, float* out);
 
+/* What the handle has done since it was loaded, and what it holds now; for tests and for tuning. */
+typedef struct {
+    int64_t recorded;    /* requests recorded as graphs                                          */
+    int64_t replayed;    /* requests run from a graph (the one that was recorded included)       */
+    int64_t graphs;      /* recorded requests held                                               */
+    int64_t handed_out;  /* batches handed out one by one as streams came free                   */
+    int64_t copies;      /* copies of groups of workers with an arena more each (ens_set_alloc)  */
+    int64_t copy_bytes;  /* device memory of those arenas                                        */
+} ens_stats;
+int ens_debug_stats(const ens_handle* h, ens_stats* out);
+
 /* ---- queries -------------------------------------------------------------------------------*/
 int ens_classes(const ens_handle* h);
 int ens_n_members(const ens_handle* h);

@@ -611,11 +611,19 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
 
 static int ensure_buffers(ens_handle* h, int64_t n);
 
+// The last replay may have been waited for on the flag alone (see wait_lanes): the runtime is done with it when its lanes are synchronised.
+static void destroy_graph(ens_handle* h, RequestGraph& r) {
+    for (int l = 0; l < r.lanes; l++)
+        if (r.exec[l]) (void)hipStreamSynchronize(h->lanes[l]);
+    for (hipGraphExec_t& e : r.exec) {
+        if (e) (void)hipGraphExecDestroy(e);
+        e = nullptr;
+    }
+}
+
 // Recorded requests hold launch geometry, argument block addresses and the batches' sizes.
 static void drop_graphs(ens_handle* h) {
-    for (RequestGraph& r : h->graphs)
-        for (hipGraphExec_t& e : r.exec)
-            if (e) (void)hipGraphExecDestroy(e);
+    for (RequestGraph& r : h->graphs) destroy_graph(h, r);
     h->graphs.clear();
     h->sizes_seen.clear();
 }
@@ -963,11 +971,12 @@ static int each_batch(ens_handle* h, int64_t n, uint64_t mask, const std::vector
 }
 
 // Requests recorded as graphs (see below): the launches of a request that is still recorded, recorded requests and noted sizes that
-// a handle keeps; below three lanes the GPU takes as long for a launch as the host.  Average launch of the
+// a handle keeps, and requests from one recording that takes another's place to the next (see worth_recording); below three lanes the GPU takes as long for a launch as the host.  Average launch of the
 // requests that are handed out batch by batch instead.  What a graph costs the host per kernel in it, and what
 // it costs to start and to wait for one lane more (a graph's launch 30 us, a wait 10 to 20).
 constexpr int64_t GRAPH_MAX_LAUNCHES = 2048;
-constexpr size_t GRAPHS_KEPT = 8, SIZES_KEPT = 32;
+constexpr size_t GRAPHS_KEPT = 16, SIZES_KEPT = 32;
+constexpr uint64_t RECORD_EVERY = 32;
 constexpr int GRAPH_MIN_LANES = 3;
 constexpr double HAND_OUT_LAUNCH_S = 9e-6, LANE_S = 30e-6, GRAPH_NODE_S = 0.4e-6;
 
@@ -1085,20 +1094,31 @@ static RequestGraph* find_graph(ens_handle* h, int64_t n) {
     return nullptr;
 }
 
-// Has a request of this size come before?  Notes that it has.
-static bool seen_before(ens_handle* h, int64_t n) {
-    for (auto& s : h->sizes_seen)
-        if (s.first == n) {
-            s.second = h->requests;
-            return true;
+static RequestGraph* oldest_graph(ens_handle* h) {
+    return &*std::min_element(h->graphs.begin(), h->graphs.end(), [](const RequestGraph& x, const RequestGraph& y) { return x.used < y.used; });
+}
+
+// Is a request of this size to be recorded?  When it comes again, while there is room.  After that only if it came last time since the
+// recorded size that would make room for it was used, and once in RECORD_EVERY requests: a front end with more sizes than
+// are kept would otherwise pay for a recording (3 us a launch, as much as issuing it) with most of its requests and see it given up
+// before it is replayed.  (One to 12 and one to 24 images in turn through twelve members: 5.7 and 6.8 ms a request with each size
+// recorded again whenever it came, 4.1 and 5.2 ms now; 5.6 and 6.3 ms launch by launch on a stream per gang.)  Sixteen of them hold some 13 MB of device memory there.  Notes that the size has come.
+static bool worth_recording(ens_handle* h, int64_t n) {
+    for (SeenSize& s : h->sizes_seen)
+        if (s.n == n) {
+            const uint64_t before = s.when;
+            s.when = h->requests;
+            if (s.failed) return false;
+            return h->graphs.size() < GRAPHS_KEPT || (before > oldest_graph(h)->used && h->requests - h->last_recorded >= RECORD_EVERY);
         }
     if (h->sizes_seen.size() >= SIZES_KEPT)
-        h->sizes_seen.erase(std::min_element(h->sizes_seen.begin(), h->sizes_seen.end(), [](auto& x, auto& y) { return x.second < y.second; }));
-    h->sizes_seen.emplace_back(n, h->requests);
+        h->sizes_seen.erase(std::min_element(h->sizes_seen.begin(), h->sizes_seen.end(), [](auto& x, auto& y) { return x.when < y.when; }));
+    h->sizes_seen.push_back(SeenSize{n, h->requests, false});
     return false;
 }
 
-// Records the request on the handle's own stream; nothing runs.  Failure leaves no graph: the request is then issued launch by launch.
+// Records the request on the handle's own stream; nothing runs.  Failure leaves no graph: the request is then issued launch by launch,
+// and so are those of its size that follow.
 static RequestGraph* record_request(ens_handle* h, int64_t n, int lanes, const std::vector<std::vector<int32_t>>& owner) {
     RequestGraph r;
     r.n = n;
@@ -1119,18 +1139,21 @@ static RequestGraph* record_request(ens_handle* h, int64_t n, int lanes, const s
         ok = ok && hipGraphInstantiate(&r.exec[l], graph, nullptr, nullptr, 0) == hipSuccess;
         if (graph) (void)hipGraphDestroy(graph);
     }
+    auto seen = std::find_if(h->sizes_seen.begin(), h->sizes_seen.end(), [&](const SeenSize& x) { return x.n == n; });
     if (!ok) {
         (void)hipGetLastError();
-        for (hipGraphExec_t& e : r.exec)
-            if (e) (void)hipGraphExecDestroy(e);
+        destroy_graph(h, r);
+        if (seen != h->sizes_seen.end()) seen->failed = true;
         return nullptr;
     }
     if (h->graphs.size() >= GRAPHS_KEPT) {
-        auto old = std::min_element(h->graphs.begin(), h->graphs.end(), [](const RequestGraph& x, const RequestGraph& y) { return x.used < y.used; });
-        for (hipGraphExec_t& e : old->exec)
-            if (e) (void)hipGraphExecDestroy(e);
-        h->graphs.erase(old);
+        RequestGraph* const old = oldest_graph(h);
+        destroy_graph(h, *old);
+        h->graphs.erase(h->graphs.begin() + (old - h->graphs.data()));
     }
+    if (seen != h->sizes_seen.end()) h->sizes_seen.erase(seen);      // to be seen twice again once it has been given up
+    h->last_recorded = h->requests;
+    h->stats.recorded++;
     for (const Worker& w : h->workers) r.last_nb.push_back(w.last_nb);
     h->graphs.push_back(r);
     return &h->graphs.back();
@@ -1197,7 +1220,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
             h->gangs[i].stale = false;
         }
         if (!plain_only && !(host_images && n_seg > 1) && !hand_out_batches && lanes >= GRAPH_MIN_LANES && work.launches <= GRAPH_MAX_LAUNCHES &&
-            seen_before(h, n))
+            worth_recording(h, n))
             graph = record_request(h, n, lanes, owner);
     }
     h->lanes_used = lanes;
@@ -1233,6 +1256,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
     };
     if (graph) {
         graph->used = h->requests;
+        h->stats.replayed++;
         for (int l = 0; l < lanes; l++) {
             rc = need_images(l, n);
             if (rc != ENS_OK) return rc;
@@ -1283,6 +1307,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
                     rc = need_images(l, b.first + b.nb);
                     if (rc == ENS_OK) rc = forward_batch(h, h->gangs[pick], b.first, b.nb, d_images, nullptr, h->lanes[l]);
                     if (rc != ENS_OK) return rc;
+                    h->stats.handed_out++;
                     f.number = ++issued[l];
                     HIP_TRY(launch_finish(h->d_arrivals, 1, h->flag + 1 + l, f.number, h->lanes[l]));
                     f.gang = pick;
@@ -1823,6 +1848,17 @@ int ens_debug_one_stream(ens_handle* h, int32_t on) {
     if (!h) return ENS_E_INVALID;
     (void)hipDeviceSynchronize();
     h->one_stream = on != 0;
+    return ENS_OK;
+}
+
+int ens_debug_stats(const ens_handle* h, ens_stats* out) {
+    if (!h || !out) return ENS_E_INVALID;
+    *out = h->stats;
+    out->graphs = (int64_t)h->graphs.size();
+    out->copies = (int64_t)h->gangs.size() - h->own_gangs;
+    out->copy_bytes = 0;
+    for (const Worker& w : h->workers)
+        if (w.copy) out->copy_bytes += (int64_t)w.arena_bytes;
     return ENS_OK;
 }
 

@@ -184,6 +184,13 @@ struct RequestGraph {
     hipGraphExec_t exec[LANES] = {nullptr, nullptr, nullptr, nullptr};
 };
 
+// A request size that has come and is not recorded (yet).
+struct SeenSize {
+    int64_t n = 0;
+    uint64_t when = 0;             // number of the request that last had it
+    bool failed = false;           // its recording did: not tried again
+};
+
 struct ProfClass {
     std::string name;
     double ms = 0, flop = 0, bytes = 0;
@@ -218,8 +225,9 @@ struct ens_handle {
                                                  // per lane the number of its last batch that is
     bool flagged = false;                        // the request in flight will write it
     std::vector<ens::RequestGraph> graphs;
-    std::vector<std::pair<int64_t, uint64_t>> sizes_seen;   // request sizes and when they last came, not recorded (yet)
-    uint64_t requests = 0;
+    std::vector<ens::SeenSize> sizes_seen;
+    uint64_t requests = 0, last_recorded = 0;    // requests so far, and the one that was recorded last
+    ens_stats stats = {};
     // pinned host memory for small requests: kernels read the images and write the probabilities there themselves
     float* pin_in = nullptr;    size_t pin_in_cap = 0;
     float* pin_out = nullptr;   size_t pin_out_cap = 0;

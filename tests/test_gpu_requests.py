@@ -159,6 +159,10 @@ def test_repeated_requests_are_replayed(ens):
             y = E.ens_predict(x)
             y = y.cpu().numpy() if rep % 2 else y
             assert np.array_equal(y, first[n]), (rep, n)
+    # the small sizes were recorded the second time they came after the logits buffers had grown for the largest; the large ones have
+    # several batches for more gangs than lanes and are handed out batch by batch
+    ran = E.ens_debug_stats()
+    assert ran["recorded"] == ran["graphs"] >= 2 and ran["replayed"] == 5 * ran["recorded"] and ran["handed_out"] > 0, ran
     z = E.ens_member_logits(2, sizes[-1])
     E.ens_set_combination("weighted", [0.7, 0.1, 0.1, 0.1])
     w = [E.ens_predict(d[:3].contiguous()).cpu().numpy() for _ in range(3)]
@@ -226,6 +230,38 @@ def test_wide_pointwise_layers(ens, h, w, cin, cout, stride, res, nb):
         assert_after_bf16_layers(got[i:i + 1], ref, (i,))
 
 
+def test_sizes_in_turn_are_recorded_within_bounds(ens):
+    """More request sizes in turn than recorded requests are kept: what is kept is replayed, the others are issued, and a recording takes
+    another's place at most once in 32 requests; sizes that come instead of the first ones are recorded in the end."""
+    nets = [tiny_member(i) for i in range(4)]
+    blobs = [W.quantise_weights_bf16(n, W.make_blob(n, 175 + i, 0)) for i, n in enumerate(nets)]
+    imgs = W.round_bf16(W.make_images(176, 64, 12, 12, varied=True))
+    E = ens.Ensemble(nets, blobs)
+    E.set_base_size(12, 12)
+    E.ens_set_alloc([[64] * 4])                                  # four gangs with one batch: four lanes
+    first = {n: E.ens_predict(imgs[:n]) for n in range(1, 25)}
+    requests = 24
+    for rep in range(6):
+        for n in range(1, 25):
+            assert np.array_equal(E.ens_predict(imgs[:n]), first[n]), (rep, n)
+            requests += 1
+    a = E.ens_debug_stats()
+    assert a["graphs"] == 16 and a["recorded"] <= 16 + requests // 32, a
+    assert a["replayed"] >= 6 * 12, a                            # more than half of the requests that came again
+    rng = np.random.default_rng(3)
+    for n in rng.integers(1, 25, 200):
+        assert np.array_equal(E.ens_predict(imgs[:n]), first[n]), n
+    b = E.ens_debug_stats()
+    assert b["recorded"] - a["recorded"] <= 1 + 200 // 32 and b["graphs"] == 16, (a, b)
+    for rep in range(100):                                       # two new sizes and nothing else
+        n = 40 + rep % 2
+        first.setdefault(n, E.ens_predict(imgs[:n]))
+        assert np.array_equal(E.ens_predict(imgs[:n]), first[n]), (rep, n)
+    c = E.ens_debug_stats()
+    assert c["recorded"] - b["recorded"] >= 2 and c["replayed"] - b["replayed"] >= 20, (b, c)
+    E.close()
+
+
 def tiny_member(i):
     n = N.Net("turns%d" % i, 12, 12, 8, dtype="bf16")
     n.fc(n.gap(n.conv(n.conv(0, 16 + 8 * i, 3), 32, 3)), 8)
@@ -251,6 +287,7 @@ def test_batches_take_turns(ens, members, rows, batch, images):
     E.ens_debug_one_stream(1)
     want = E.ens_predict(x)
     E.ens_debug_one_stream(0)
+    assert E.ens_debug_stats()["copies"] == {1: 3 if rows == 1 else 2, 3: 3}[members]
     out = torch.empty_like(want)
     for _ in range(4):
         assert torch.equal(E.ens_predict(x), want)
