@@ -233,7 +233,7 @@ static Fusions decide_fusions(ens_handle* h, Gang& g, int images) {
     // size.  The tensors in between are then not written (not wanted when they are to be read back).
     chain.assign(m.ops.size(), 0);                               // 1: runs the next two operations too, 2: run by it
     for (size_t i = 0; i + 2 < m.ops.size(); i++) {
-        if (!m.ops[i].fuse_chain || h->keep_tensors) continue;
+        if (!m.ops[i].fuse_chain || h->keeps) continue;
         Launch a, b, c;
         if (!fill(i, a) || !fill(i + 1, b) || !fill(i + 2, c)) continue;
         if (conv_bneck_applicable(a.conv, b.conv, c.conv, images, G)) {
@@ -243,7 +243,7 @@ static Fusions decide_fusions(ens_handle* h, Gang& g, int images) {
     }
     // Which layers of dense blocks run as one kernel: chain[] 3 marks the head (two operations), 2 the one it runs
     for (size_t i = 0; i + 1 < m.ops.size(); i++) {
-        if (!m.ops[i].fuse_dense || h->keep_tensors || chain[i] || chain[i + 1]) continue;
+        if (!m.ops[i].fuse_dense || h->keeps || chain[i] || chain[i + 1]) continue;
         Launch a, b;
         if (!fill(i, a) || !fill(i + 1, b)) continue;
         if (conv_dense_applicable(a.conv, b.conv, images, G)) {
@@ -253,7 +253,7 @@ static Fusions decide_fusions(ens_handle* h, Gang& g, int images) {
     }
     // The stem and the max-pool behind it as one kernel: chain[] 4 marks the stem, 2 the pool it runs
     for (size_t i = 0; i + 1 < m.ops.size(); i++) {
-        if (!m.ops[i].fuse_pool || h->keep_tensors || chain[i] || chain[i + 1]) continue;
+        if (!m.ops[i].fuse_pool || h->keeps || chain[i] || chain[i + 1]) continue;
         Launch a;
         if (!fill(i, a)) continue;
         if (conv_stempool_applicable(a.conv, pool_as_conv(h, leader, m.ops[i + 1], images), images, G)) {
@@ -284,7 +284,7 @@ static Fusions decide_fusions(ens_handle* h, Gang& g, int images) {
     // input: gated[] 1 marks the block, 2 the convolution.
     gated.assign(m.ops.size(), 0);
     for (size_t i = 0; i + 1 < m.ops.size(); i++) {
-        if (!m.ops[i].fuse_gate || h->keep_tensors || chain[i] || chain[i + 1] || fused[i] || fused[i + 1]) continue;
+        if (!m.ops[i].fuse_gate || h->keeps || chain[i] || chain[i + 1] || fused[i] || fused[i + 1]) continue;
         Launch c;
         if (!fill(i + 1, c)) continue;
         gate_args(h, leader, leader, m.ops[i], c.conv);
@@ -297,7 +297,7 @@ static Fusions decide_fusions(ens_handle* h, Gang& g, int images) {
     // summed[] 1 marks the convolution, 2 the block.
     summed.assign(m.ops.size(), 0);
     for (size_t i = 0; i + 1 < m.ops.size(); i++) {
-        if (!m.ops[i].fuse_sums || h->keep_tensors || m.ops[i + 1].op.kind != ENS_OP_SE) continue;
+        if (!m.ops[i].fuse_sums || h->keeps || m.ops[i + 1].op.kind != ENS_OP_SE) continue;
         Launch d;
         if (!fill(i, d)) continue;
         if (dwconv_sums_applicable(d.pool, m.bf16) && dwconv_sums_blocks(d.pool.Ho, d.pool.Wo, d.pool.c) <= m.ops[i + 1].se_cap) {
@@ -309,14 +309,14 @@ static Fusions decide_fusions(ens_handle* h, Gang& g, int images) {
     // (the convolution runs there), 2 the convolution's (the pool runs there, on the convolution's channels).
     swapped.assign(m.ops.size(), 0);
     for (size_t i = 0; i + 1 < m.ops.size(); i++) {
-        if (!m.ops[i].swap_pool || h->keep_tensors || chain[i] || chain[i + 1] || fused[i] || fused[i + 1] || gated[i + 1]) continue;
+        if (!m.ops[i].swap_pool || h->keeps || chain[i] || chain[i + 1] || fused[i] || fused[i + 1] || gated[i + 1]) continue;
         swapped[i] = 1;
         swapped[i + 1] = 2;
     }
     // ... and pre-activated 1x1 convolutions that let the 2x2 average pool behind them go first: 3 marks the
     // convolution's place (the pool runs there, on the convolution's input), 4 the pool's (the convolution, on the pooled map)
     for (size_t i = 0; i + 1 < m.ops.size(); i++) {
-        if (!m.ops[i].swap_conv || h->keep_tensors || chain[i] || chain[i + 1] || fused[i] || fused[i + 1] || gated[i] || swapped[i] ||
+        if (!m.ops[i].swap_conv || h->keeps || chain[i] || chain[i + 1] || fused[i] || fused[i + 1] || gated[i] || swapped[i] ||
             swapped[i + 1])
             continue;
         swapped[i] = 3;
@@ -605,7 +605,10 @@ static int build_launches(ens_handle* h, Gang& g, bool may_alloc = true) {
     g.stage.dst = leader.arena + leader.layout.offset[0];
     g.stage.nb = leader.batch; g.stage.sh = h->base_h; g.stage.sw = h->base_w;
     g.stage.dh = m.in_h; g.stage.dw = m.in_w; g.stage.dc = m.tensors[0].cs; g.stage.s2d = m.stem_s2d ? 1 : 0;
-    HIP_TRY(hipMemcpy(g.d_args, blocks.data(), blocks.size(), hipMemcpyHostToDevice));
+    // (not on the null stream, which would wait for the lanes of every handle)
+    HIP_TRY(hipMemcpyAsync(g.d_args, blocks.data(), blocks.size(), hipMemcpyHostToDevice, h->main_stream));
+    HIP_TRY(hipStreamSynchronize(h->main_stream));
+    g.stale = false;
     return ENS_OK;
 }
 
@@ -621,7 +624,9 @@ static void destroy_graph(ens_handle* h, RequestGraph& r) {
     }
 }
 
-// Recorded requests hold launch geometry, argument block addresses and the batches' sizes.
+// Recorded requests hold launch geometry, argument block addresses, the batches' sizes and the addresses of the library's own logits
+// buffers.  What the argument blocks name may change beneath them and back: a request that runs on the fixed device array leaves
+// them as they are, and the next one of ens_predict has the blocks of its gangs rewritten before it replays one.
 static void drop_graphs(ens_handle* h) {
     for (RequestGraph& r : h->graphs) destroy_graph(h, r);
     h->graphs.clear();
@@ -794,6 +799,7 @@ static int install_alloc(ens_handle* h, const ens_alloc& a, int segment_size) {
     }
     cu_budget() = stream_share(h);
     lanes_busy() = lanes_in_use() = std::min(LANES, std::max(1, h->own_gangs));
+    h->keeps = h->keep_tensors;
     for (Gang& g : h->gangs) {
         const int rc = build_launches(h, g);
         if (rc != ENS_OK) { destroy_workers(h); return rc; }
@@ -887,6 +893,7 @@ static int ensure_buffers(ens_handle* h, int64_t n) {
             HIP_TRY(hipMalloc((void**)&h->d_logits_heap[m], rows * h->members[m].classes * sizeof(float)));
         h->d_logits_heap_rows = rows;
         moved = true;
+        drop_graphs(h);                                        // they end in a combination of the old ones
     }
     if (moved || h->logits_static) {                           // (back) to the library's own buffers
         h->d_logits = h->d_logits_heap;
@@ -1129,7 +1136,10 @@ static RequestGraph* record_request(ens_handle* h, int64_t n, int lanes, const s
         if (!ok) break;
         const RequestSlot* slot = h->d_slots + l;
         int rc = each_batch(h, n, ~0ull, owner, [&](Gang& g, int64_t first, int nb) {
-            return g.lane == l ? forward_batch(h, g, first, nb, nullptr, slot, h->main_stream) : ENS_OK;
+            if (g.lane != l) return (int)ENS_OK;
+            const int i = (int)(&g - h->gangs.data());
+            if (std::find(r.gangs.begin(), r.gangs.end(), i) == r.gangs.end()) r.gangs.push_back(i);
+            return forward_batch(h, g, first, nb, nullptr, slot, h->main_stream);
         });
         CombineArgs c = combine_args(h, n, lanes);
         c.slot = slot;
@@ -1175,11 +1185,11 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
     const int M = (int)h->members.size();
     const int seg = h->segment_size;
     const int64_t n_seg = (n + seg - 1) / seg;
-    if (h->args_stale) {                                         // the logits moved
-        drop_graphs(h);
+    if (h->args_stale) {                                         // other logits than those that the argument blocks name
         for (Gang& g : h->gangs) g.stale = true;
         h->args_stale = false;
     }
+    auto refresh = [&](int i) { return h->gangs[i].stale ? build_launches(h, h->gangs[i], may_alloc) : ENS_OK; };
     h->requests++;
     const bool plain_only = !may_alloc || h->profiling || h->fake_predictor || h->one_stream || mask != ~0ull;
     RequestGraph* graph = plain_only || (host_images && n_seg > 1) ? nullptr : find_graph(h, n);
@@ -1214,10 +1224,9 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
         hand_out_batches = !h->one_stream && h->gangs.size() > LANES && work.most > 1 && work.total > HAND_OUT_LAUNCH_S * (double)work.launches;
         lanes = lanes_in_use() = hand_out_batches ? LANES : deal_lanes(h, work);
         for (size_t i = 0; i < h->gangs.size(); i++) {
-            if (!h->gangs[i].stale || work.batches[i].empty()) continue;
-            rc = build_launches(h, h->gangs[i], may_alloc);
+            if (work.batches[i].empty()) continue;
+            rc = refresh((int)i);
             if (rc != ENS_OK) return rc;
-            h->gangs[i].stale = false;
         }
         if (!plain_only && !(host_images && n_seg > 1) && !hand_out_batches && lanes >= GRAPH_MIN_LANES && work.launches <= GRAPH_MAX_LAUNCHES &&
             worth_recording(h, n))
@@ -1255,6 +1264,10 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
         return ENS_OK;
     };
     if (graph) {
+        for (int i : graph->gangs) {
+            rc = refresh(i);
+            if (rc != ENS_OK) return rc;
+        }
         graph->used = h->requests;
         h->stats.replayed++;
         for (int l = 0; l < lanes; l++) {

@@ -181,6 +181,7 @@ struct RequestGraph {
     uint64_t used = 0;             // for giving up the one used longest ago
     int lanes = 0;
     std::vector<int> last_nb;      // per worker: images of its last batch
+    std::vector<int> gangs;        // that it runs: indices into ens_handle::gangs
     hipGraphExec_t exec[LANES] = {nullptr, nullptr, nullptr, nullptr};
 };
 
@@ -207,7 +208,7 @@ struct ens_handle {
     std::vector<ens::Gang> gangs;                // the copies last
     int own_gangs = 0;                           // without the copies
     bool gangs_enabled = true;                   // false: every worker is a gang of its own
-    bool args_stale = false;                     // request buffers moved: argument arrays need rebuilding
+    bool args_stale = false;                     // other logits buffers are in use: argument arrays need rebuilding
     ens_alloc alloc;
     bool have_alloc = false;
     int segment_size = 128;
@@ -249,6 +250,7 @@ struct ens_handle {
     // profiling
     bool profiling = false;
     bool keep_tensors = false;                   // debug: no reuse of arena regions
+    bool keeps = false;                          // the installed workers were laid out that way
     bool fake_predictor = false;                 // overhead experiment: forward passes replaced by zeros
     bool one_stream = false;                     // measurement: every worker issues on the main stream, one kernel at a time
     std::vector<ens::ProfClass> prof;

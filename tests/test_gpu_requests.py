@@ -230,6 +230,42 @@ def test_wide_pointwise_layers(ens, h, w, cin, cout, stride, res, nb):
         assert_after_bf16_layers(got[i:i + 1], ref, (i,))
 
 
+def test_recorded_requests_outlive_the_allocation_free_entry_point(ens):
+    """ens_predict_static frees nothing: requests recorded before it are replayed after it, with the answers they gave."""
+    import torch
+    nets = [tiny_member(i) for i in range(4)]
+    blobs = [W.quantise_weights_bf16(n, W.make_blob(n, 177 + i, 0)) for i, n in enumerate(nets)]
+    x = torch.from_numpy(W.round_bf16(W.make_images(178, 24, 12, 12, varied=True))).cuda()
+    E = ens.Ensemble(nets, blobs)
+    E.set_base_size(12, 12)
+    E.ens_set_alloc([[8] * 4])
+    parts = {n: x[:n].contiguous() for n in (24, 3, 7)}
+    first = {n: E.ens_predict(v).clone() for n, v in parts.items()}
+    outs = {n: torch.empty_like(v) for n, v in first.items()}
+    for _ in range(2):
+        for n, v in parts.items():
+            assert torch.equal(E.ens_predict(v, outs[n]), first[n])
+    E.ens_predict_static(parts[24], outs[24])
+    a = E.ens_debug_stats()
+    assert a["recorded"] == a["graphs"] >= 2, a
+    for rep in range(4):
+        for n, v in parts.items():
+            m = (24, 3, 7)[rep % 3]
+            outs[m].zero_()
+            free = torch.cuda.mem_get_info()[0]
+            E.ens_predict_static(parts[m], outs[m])
+            assert rep == 0 or torch.cuda.mem_get_info()[0] == free, (rep, m)      # (the runtime's own buffers come with the first calls)
+            assert torch.equal(outs[m], first[m]), (rep, m)
+            outs[n].zero_()
+            assert torch.equal(E.ens_predict(v, outs[n]), first[n]), (rep, n)
+    z = E.ens_member_logits(1, 7)
+    E.ens_predict_static(parts[7], outs[7])
+    assert np.array_equal(E.ens_member_logits(1, 7), z)
+    b = E.ens_debug_stats()
+    assert b["recorded"] == a["recorded"] and b["graphs"] == a["graphs"] and b["replayed"] == a["replayed"] + 4 * a["graphs"], (a, b)
+    E.close()
+
+
 def test_sizes_in_turn_are_recorded_within_bounds(ens):
     """More request sizes in turn than recorded requests are kept: what is kept is replayed, the others are issued, and a recording takes
     another's place at most once in 32 requests; sizes that come instead of the first ones are recorded in the end."""
