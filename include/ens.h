@@ -101,7 +101,8 @@ typedef struct {
 typedef struct {
     int32_t rows, cols;
     int32_t batch[ENS_MAX_SLOTS][ENS_MAX_MEMBERS];
-    int64_t bytes;      /* out: device memory the matrix needs (weights + arenas)             */
+    int64_t bytes;      /* out: device memory of the matrix as installed (weights, arenas and
+                           those of the copies, see ens_set_alloc)                            */
     double  score;      /* out: images per second measured for it, 0 if never benchmarked     */
     int32_t n_bench;    /* out: number of benchmarks the optimizer ran                        */
 } ens_alloc;
@@ -158,7 +159,11 @@ int ens_plan(ens_handle* h, uint64_t mem_budget_bytes, const ens_plan_opts* opts
 
 /* Installs a caller-made matrix, or one kept from an earlier ens_plan (section "The allocation
  * optimizer" keeps the best matrix for reuse).  ENS_E_INVALID for a zero column or a non-positive size, ENS_E_NOMEM when the
- * workers do not fit.  Builds one stream and one activation arena per non-zero cell. */
+ * workers do not fit.  Builds one activation arena per non-zero cell; kernels are issued on four streams
+ * that all handles of the process share (see ens_predict).  Where the matrix has up to four groups of workers (workers of one row with
+ * networks of the same shape form a group) the library adds arenas for copies of them, up to three per worker, on which a group's
+ * batches overlap: as many as take a quarter of the free device memory at most and, after ens_plan, fit into its budget beside the
+ * workers and the request buffers.  They are given back when a later call of the handle finds too little memory. */
 int ens_set_alloc(ens_handle* h, const ens_alloc* a, int32_t segment_size);
 
 /* "Benchmark Mode" of section "The inference system": installs `a`, predicts n_calib synthetic
@@ -232,7 +237,7 @@ typedef struct {
     int64_t replayed;    /* requests run from a graph (the one that was recorded included)       */
     int64_t graphs;      /* recorded requests held                                               */
     int64_t handed_out;  /* batches handed out one by one as streams came free                   */
-    int64_t copies;      /* copies of groups of workers with an arena more each (ens_set_alloc)  */
+    int64_t copies;      /* copies of groups of workers with arenas of their own (ens_set_alloc) */
     int64_t copy_bytes;  /* device memory of those arenas                                        */
 } ens_stats;
 int ens_debug_stats(const ens_handle* h, ens_stats* out);

@@ -686,26 +686,67 @@ static int stream_share(const ens_handle* h) {
     return std::max(32, 256 / streams);
 }
 
+static int64_t copy_bytes(const ens_handle* h) {
+    int64_t total = 0;
+    for (const Worker& w : h->workers)
+        if (w.copy) total += (int64_t)std::max<size_t>(w.arena_bytes, 256);
+    return total;
+}
+
+// Gives the copies up.  Recorded requests run on them.
+static void drop_copies(ens_handle* h) {
+    h->flagged = false;                                          // the streams themselves
+    (void)wait_lanes(h);
+    drop_graphs(h);
+    h->alloc.bytes -= copy_bytes(h);
+    while ((int)h->gangs.size() > h->own_gangs) {
+        if (h->gangs.back().d_args) (void)hipFree(h->gangs.back().d_args);
+        h->gangs.pop_back();
+    }
+    while (!h->workers.empty() && h->workers.back().copy) {
+        (void)hipFree(h->workers.back().arena);
+        h->workers.pop_back();
+    }
+    for (size_t i = 0; i < h->gangs.size(); i++) h->gangs[i].copies.assign(1, (int)i);
+    (void)hipGetLastError();
+}
+
+// fn, which allocates device memory; once more without the copies if there is not enough of it.
+template <typename F>
+static int with_room(ens_handle* h, F&& fn) {
+    int rc = fn();
+    if (rc != ENS_E_NOMEM) return rc;
+    (void)hipGetLastError();
+    if ((int)h->gangs.size() == h->own_gangs) return rc;
+    drop_copies(h);
+    rc = fn();
+    if (rc == ENS_E_NOMEM) (void)hipGetLastError();
+    return rc;
+}
+
 // Copies of the gangs (see Gang): LANES - 1 of a single gang, one each of two; of three or four, which have lanes enough, one of
 // those with batches of up to 64 images (see takes_turns).  They are an extra: no more than a quarter of the memory that is free,
-// nothing that a budget does not have room for, none while every tensor is kept for inspection.
-static void copy_gangs(ens_handle* h, int64_t need) {
+// nothing that a budget does not have room for beside the workers and the request buffers, none while every tensor is kept for
+// inspection; and they go when something else finds no memory (with_room).
+static int copy_gangs(ens_handle* h, int64_t need) {
     const int own = h->own_gangs;
-    if (own > LANES || h->keep_tensors) return;
+    if (own > LANES || h->keep_tensors) return ENS_OK;
     std::vector<int> copies(own);
     size_t extra = 0, free_bytes = 0, total = 0;
     for (int i = 0; i < own; i++) {
         copies[i] = own == 1 ? LANES - 1 : own == 2 || h->workers[h->gangs[i].workers[0]].batch <= 64 ? 1 : 0;
         for (int wi : h->gangs[i].workers) extra += copies[i] * std::max<size_t>(h->workers[wi].arena_bytes, 256);
     }
-    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess || extra > free_bytes / 4) { (void)hipGetLastError(); return; }
-    if (h->budget && (uint64_t)need + extra > h->budget) return;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess || extra > free_bytes / 4) { (void)hipGetLastError(); return ENS_OK; }
+    if (h->budget && (uint64_t)need + extra + (uint64_t)h->reserve > h->budget) return ENS_OK;
     for (int k = 0; k < LANES - 1; k++)
         for (int i = 0; i < own; i++) {
             if (k >= copies[i]) continue;
             Gang g = h->gangs[i];
             g.copy = true;
             g.copies.clear();
+            g.d_args = nullptr;
+            g.d_args_bytes = 0;
             const size_t had = h->workers.size();
             for (int& wi : g.workers) {
                 Worker w = h->workers[wi];
@@ -716,14 +757,17 @@ static void copy_gangs(ens_handle* h, int64_t need) {
                     (void)hipGetLastError();
                     for (size_t j = had; j < h->workers.size(); j++) (void)hipFree(h->workers[j].arena);
                     h->workers.resize(had);
-                    return;
+                    return ENS_OK;
                 }
                 wi = (int)h->workers.size();
                 h->workers.push_back(w);
             }
             h->gangs[i].copies.push_back((int)h->gangs.size());
             h->gangs.push_back(g);
+            const int rc = build_launches(h, h->gangs.back());
+            if (rc != ENS_OK) return rc;
         }
+    return ENS_OK;
 }
 
 static int install_alloc(ens_handle* h, const ens_alloc& a, int segment_size) {
@@ -792,7 +836,6 @@ static int install_alloc(ens_handle* h, const ens_alloc& a, int segment_size) {
         }
     }
     h->own_gangs = (int)h->gangs.size();
-    copy_gangs(h, need);
     if (!h->d_logits.empty() && !h->d_logits[0]) {               // argument blocks hold the logits pointers
         const int rc0 = ensure_buffers(h, 1);
         if (rc0 != ENS_OK) { destroy_workers(h); return rc0; }
@@ -807,6 +850,8 @@ static int install_alloc(ens_handle* h, const ens_alloc& a, int segment_size) {
     h->args_stale = false;
     h->alloc = a;
     h->alloc.bytes = need;
+    if (copy_gangs(h, need) != ENS_OK) drop_copies(h);
+    h->alloc.bytes = need + copy_bytes(h);
     h->segment_size = segment_size;
     h->have_alloc = true;
     return ENS_OK;
@@ -1179,7 +1224,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
     if (n == 0) return ENS_OK;
     cu_budget() = stream_share(h);
     lanes_busy() = std::min(LANES, std::max(1, h->own_gangs));
-    int rc = may_alloc ? ensure_buffers(h, n) : ENS_OK;
+    int rc = may_alloc ? with_room(h, [&] { return ensure_buffers(h, n); }) : ENS_OK;
     if (rc != ENS_OK) return rc;
     if ((size_t)n > h->d_logits_rows) return ENS_E_INVALID;
     const int M = (int)h->members.size();
@@ -1441,9 +1486,9 @@ static int grow_pinned(float** p, size_t* cap, size_t want_floats) {
 
 // Benchmark Mode on the installed allocation: median images/s of `repeats` runs after a warm-up.
 static int time_installed(ens_handle* h, int64_t n, int repeats, uint64_t mask, double* ips) {
-    int rc = ensure_calib(h, n);
+    int rc = with_room(h, [&] { return ensure_calib(h, n); });
     if (rc != ENS_OK) return rc;
-    rc = grow(&h->d_probs, &h->d_probs_cap, (size_t)n * h->classes);
+    rc = with_room(h, [&] { return grow(&h->d_probs, &h->d_probs_cap, (size_t)n * h->classes); });
     if (rc != ENS_OK) return rc;
     std::vector<double> secs;
     for (int i = 0; i < repeats + 1; i++) {
@@ -1583,7 +1628,7 @@ int ens_predict(ens_handle* h, const float* images, int64_t n, float* probs_out)
             memcpy(h->pin_in, images, img_floats * sizeof(float));
             d_in = h->pin_in;
         } else {
-            int rc = grow(&h->d_images, &h->d_images_cap, img_floats);
+            int rc = with_room(h, [&] { return grow(&h->d_images, &h->d_images_cap, img_floats); });
             if (rc != ENS_OK) return rc;
             d_in = h->d_images;
             host_in = images;
@@ -1592,7 +1637,7 @@ int ens_predict(ens_handle* h, const float* images, int64_t n, float* probs_out)
     float* d_out = probs_out;
     const bool direct_out = !h->probs_on_device && out_floats * sizeof(float) <= DIRECT_OUT_BYTES;
     if (!h->probs_on_device) {
-        int rc = direct_out ? grow_pinned(&h->pin_out, &h->pin_out_cap, out_floats) : grow(&h->d_probs, &h->d_probs_cap, out_floats);
+        int rc = direct_out ? grow_pinned(&h->pin_out, &h->pin_out_cap, out_floats) : with_room(h, [&] { return grow(&h->d_probs, &h->d_probs_cap, out_floats); });
         if (rc != ENS_OK) return rc;
         d_out = direct_out ? h->pin_out : h->d_probs;
     }
@@ -1672,8 +1717,6 @@ int ens_plan(ens_handle* h, uint64_t mem_budget_bytes, const ens_plan_opts* opts
         HIP_TRY(hipMemGetInfo(&fr, &tot));
         mem_budget_bytes = tot;
     }
-    h->budget = mem_budget_bytes;
-
     std::vector<int64_t> wbytes(M), abytes((size_t)M * o.n_domain);
     for (int m = 0; m < M; m++) {
         wbytes[m] = (int64_t)h->members[m].weight_bytes();
@@ -1684,6 +1727,8 @@ int ens_plan(ens_handle* h, uint64_t mem_budget_bytes, const ens_plan_opts* opts
     int64_t reserve = (int64_t)o.n_calib * ((int64_t)h->base_h * h->base_w * 3 + (int64_t)h->classes * (M + 1)) * 4;
     int64_t cap = (int64_t)mem_budget_bytes - reserve;
     if (cap < 0) cap = 0;
+    h->budget = mem_budget_bytes;
+    h->reserve = reserve;
     ens_plan_problem p;
     p.n_models = M; p.n_rows = o.slots; p.n_pools = 1; p.n_domain = o.n_domain;
     p.domain = o.domain; p.default_batch = o.default_batch;
@@ -1869,9 +1914,7 @@ int ens_debug_stats(const ens_handle* h, ens_stats* out) {
     *out = h->stats;
     out->graphs = (int64_t)h->graphs.size();
     out->copies = (int64_t)h->gangs.size() - h->own_gangs;
-    out->copy_bytes = 0;
-    for (const Worker& w : h->workers)
-        if (w.copy) out->copy_bytes += (int64_t)w.arena_bytes;
+    out->copy_bytes = copy_bytes(h);
     return ENS_OK;
 }
 

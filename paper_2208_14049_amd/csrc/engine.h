@@ -215,6 +215,7 @@ struct ens_handle {
     int base_h = 0, base_w = 0, classes = 0;
     bool images_on_device = false, probs_on_device = false;
     uint64_t budget = 0;                         // 0: whatever the device has
+    int64_t reserve = 0;                         // of the budget for request buffers (ens_plan)
     hipStream_t main_stream = nullptr;           // copies, and the recording of graphs
     hipStream_t lanes[ens::LANES] = {nullptr, nullptr, nullptr, nullptr};
     bool have_lanes = false;

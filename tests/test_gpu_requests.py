@@ -332,6 +332,21 @@ def test_batches_take_turns(ens, members, rows, batch, images):
     E.close()
 
 
+def test_copies_leave_the_request_buffers_their_room(ens):
+    """After ens_plan copies of a group come out of the budget beside the workers and the buffers of a request, and are counted."""
+    net = tiny_member(0)
+    E = ens.Ensemble([net], [W.quantise_weights_bf16(net, W.make_blob(net, 221, 0))])
+    weights, arena = E.ens_member_bytes(0, 8)
+    images = 4 * arena // (12 * 12 * 3 * 4)                      # buffers of a calibration request larger than three arenas
+    reserve = images * (12 * 12 * 3 + 2 * 8) * 4
+    opts = dict(domain=[8], slots=1, strategy=1, n_calib=images, repeats=1)
+    for budget, copies in ((weights + arena + reserve, 0), (weights + 4 * arena + reserve - 1, 0), (weights + 4 * arena + reserve, 3)):
+        a = E.ens_plan(budget, **opts)
+        s = E.ens_debug_stats()
+        assert s["copies"] == copies and s["copy_bytes"] == copies * arena and a.bytes == weights + (1 + copies) * arena, (budget, s, a.bytes)
+    E.close()
+
+
 def test_small_host_requests_see_their_own_images(ens):
     """Small requests from host memory go through one pinned buffer, and are waited for without synchronising a stream: requests of one
     size with other images each time give the answers that the same images give from device memory."""

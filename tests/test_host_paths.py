@@ -1,0 +1,82 @@
+"""Host paths of the library where device memory runs short, on the CPU: the library runs in a process of its own in front of fake_hip.cpp,
+whose device memory is host memory with a limit and whose launches do nothing."""
+import ctypes
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def fake_hip(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-o", lib, os.path.join(ROOT, "tests", "fake_hip.cpp")])
+    return lib
+
+
+def beside_fake_hip(lib, call):
+    """Runs `call` (an expression over this module) in a process with the fake runtime in front."""
+    p = subprocess.run([sys.executable, "-c", "import tests.test_host_paths as t; t.%s" % call], cwd=ROOT, env=dict(os.environ, LD_PRELOAD=lib),
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, timeout=100)
+    assert p.returncode == 0, p.stdout.decode()[-3000:]
+
+
+def fake():
+    L = ctypes.CDLL(None)
+    L.fake_limit.argtypes = [ctypes.c_size_t]
+    for f in ("fake_used", "fake_launches", "fake_null_copies"):
+        getattr(L, f).restype = ctypes.c_size_t
+    return L
+
+
+def tiny_ensemble(members):
+    import paper_2208_14049_amd as ens
+    from synth import nets as N, weights as W
+    nets = []
+    for i in range(members):
+        n = N.Net("tiny%d" % i, 12, 12, 8, dtype="bf16")
+        n.fc(n.gap(n.conv(n.conv(0, 16 + 8 * i, 3), 32, 3)), 8)
+        nets.append(n)
+    return ens.Ensemble(nets, [W.make_blob(n, 231, i) for i, n in enumerate(nets)])
+
+
+def copies_go(members, rows, copies):
+    import paper_2208_14049_amd as ens
+    F, x = fake(), np.zeros((64, 12, 12, 3), np.float32)
+    E = tiny_ensemble(members)
+    arena, start = E.ens_member_bytes(0, 64)[1], F.fake_used()
+    limit = start + 16 * members * rows * arena
+    F.fake_limit(limit)
+    E.ens_set_alloc([[64] * members] * rows, 64)
+    for n in (64, 8, 64, 8, 64):
+        E.ens_predict(x[:n])
+    s = E.ens_debug_stats()
+    assert s["copies"] == copies and s["copy_bytes"] > 0, s
+    assert s["graphs"] == (2 if members == 4 else 0), s          # four lanes: recorded requests, which run on the copies' lanes too
+    # images that fit without the copies only
+    n = (limit - F.fake_used() + s["copy_bytes"] // 2) // (12 * 12 * 3 * 4 + (members + 1) * 8 * 4)
+    held, before = F.fake_used(), F.fake_launches()
+    E.ens_predict(np.zeros((n, 12, 12, 3), np.float32))
+    t = E.ens_debug_stats()
+    assert t["copies"] == t["copy_bytes"] == t["graphs"] == 0 and F.fake_launches() > before, t
+    assert F.fake_used() <= limit and F.fake_used() > held
+    for m in (64, 8, 64, 8):
+        E.ens_predict(x[:m])
+    # images that fit nowhere: refused, and the next request is answered
+    E.ens_set_alloc([[64] * members] * rows, 64)
+    out = np.empty((8, 8), np.float32)
+    assert ens.lib().ens_predict(E._h, x.ctypes.data, 1 << 40, out.ctypes.data) == -2
+    for m in (64, 8):
+        E.ens_predict(x[:m])
+    E.close()
+    assert F.fake_used() == 0
+
+
+@pytest.mark.parametrize("members,rows,copies", [(1, 1, 3), (1, 2, 2), (2, 1, 2), (4, 1, 4)])
+def test_copies_go_when_a_request_finds_no_memory(fake_hip, members, rows, copies):
+    """A request whose buffers do not fit beside the copies of the gangs is answered without them, as it was before there were copies."""
+    beside_fake_hip(fake_hip, "copies_go(%d, %d, %d)" % (members, rows, copies))
