@@ -885,6 +885,15 @@ static hipError_t issue(const Launch& L, bool bf16, int G, int nb, long long fir
     return hipErrorInvalidValue;
 }
 
+static void note_batch(ens_handle* h, const Gang& g, int64_t first, int nb) {
+    for (int wi : g.workers) {
+        Worker& w = h->workers[wi];
+        w.last_nb = nb;
+        w.last_request = h->requests;
+        w.last_first = first;
+    }
+}
+
 // One batch of one gang: stage the images into the leader's arena, run every member, write the
 // logits rows of the batch.
 // The images are at `src`, or where `slot` says when the launches are being recorded.
@@ -907,8 +916,8 @@ static int forward_batch(ens_handle* h, Gang& g, int64_t first, int nb, const fl
         for (int wi : g.workers) {
             const Worker& w = h->workers[wi];
             HIP_TRY(launch_fill_zero(h->d_logits[w.member] + first * h->classes, (int64_t)nb * h->classes, st));
-            h->workers[wi].last_nb = nb;
         }
+        note_batch(h, g, first, nb);
         return ENS_OK;
     }
     const double stage_bytes = (double)leader.batch * (h->base_h * h->base_w * 12.0 + (double)m.tensors[0].h * m.tensors[0].w * g.stage.dc * (m.bf16 ? 2 : 4));
@@ -920,7 +929,7 @@ static int forward_batch(ens_handle* h, Gang& g, int64_t first, int nb, const fl
         if (L.kind == L_SKIP) continue;
         HIP_TRY(timed(L.klass, L.flop * G, L.bytes * G, [&] { return issue(L, m.bf16, G, nb, first, st); }));
     }
-    for (int wi : g.workers) h->workers[wi].last_nb = nb;
+    note_batch(h, g, first, nb);
     return ENS_OK;
 }
 
@@ -1209,7 +1218,10 @@ static RequestGraph* record_request(ens_handle* h, int64_t n, int lanes, const s
     if (seen != h->sizes_seen.end()) h->sizes_seen.erase(seen);      // to be seen twice again once it has been given up
     h->last_recorded = h->requests;
     h->stats.recorded++;
-    for (const Worker& w : h->workers) r.last_nb.push_back(w.last_nb);
+    for (int i : r.gangs) {
+        const Worker& w = h->workers[h->gangs[i].workers[0]];
+        r.last_batch.emplace_back(w.last_first, w.last_nb);
+    }
     h->graphs.push_back(r);
     return &h->graphs.back();
 }
@@ -1322,7 +1334,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
             HIP_TRY(hipGraphLaunch(graph->exec[l], h->lanes[l]));
             if (h->flagged) HIP_TRY(launch_finish(h->d_arrivals + COMBINE_MAX_BLOCKS, lanes, h->flag, (uint32_t)h->requests, h->lanes[l]));
         }
-        for (size_t w = 0; w < h->workers.size(); w++) h->workers[w].last_nb = graph->last_nb[w];
+        for (size_t i = 0; i < graph->gangs.size(); i++) note_batch(h, h->gangs[graph->gangs[i]], graph->last_batch[i].first, graph->last_batch[i].second);
         return ENS_OK;
     }
     if (hand_out_batches) {
@@ -1829,7 +1841,14 @@ int ens_debug_tensor(ens_handle* h, int32_t member, int32_t tensor, int32_t n_im
     const Worker* w = nullptr;
     for (const Worker& x : h->workers)
         if (x.member == member) { w = &x; break; }
-    if (!w || n_images <= 0 || n_images > w->last_nb) return ENS_E_INVALID;
+    if (!w) return ENS_E_INVALID;
+    const Gang& own = h->gangs[w->gang];                         // its batches may have gone to copies of its gang
+    const size_t place = std::find(own.workers.begin(), own.workers.end(), (int)(w - h->workers.data())) - own.workers.begin();
+    for (int i : own.copies) {
+        const Worker& x = h->workers[h->gangs[i].workers[place]];
+        if (x.last_request > w->last_request || (x.last_request == w->last_request && x.last_first > w->last_first)) w = &x;
+    }
+    if (n_images <= 0 || n_images > w->last_nb) return ENS_E_INVALID;
     if (tensor == 0) w = &h->workers[h->gangs[w->gang].workers[0]];   // the staged input lives with the gang's leader
     const TensorInfo& ti = m.tensors[tensor];
     const size_t elems = (size_t)n_images * ti.elems_per_image();

@@ -128,7 +128,9 @@ struct Worker {
     char* arena = nullptr;
     size_t arena_bytes = 0;
     ArenaLayout layout;
-    int last_nb = 0;
+    int last_nb = 0;               // images of its last batch
+    uint64_t last_request = 0;     // and which one that was: the number of the request, its first image
+    int64_t last_first = 0;
 };
 
 // The launches of a gang for batches of up to `most` images.
@@ -180,8 +182,8 @@ struct RequestGraph {
     int64_t n = 0;
     uint64_t used = 0;             // for giving up the one used longest ago
     int lanes = 0;
-    std::vector<int> last_nb;      // per worker: images of its last batch
     std::vector<int> gangs;        // that it runs: indices into ens_handle::gangs
+    std::vector<std::pair<int64_t, int>> last_batch;   // of each of them: first image, images
     hipGraphExec_t exec[LANES] = {nullptr, nullptr, nullptr, nullptr};
 };
 

@@ -332,6 +332,26 @@ def test_batches_take_turns(ens, members, rows, batch, images):
     E.close()
 
 
+@pytest.mark.parametrize("members", [1, 3])
+def test_tensors_of_the_last_batch(ens, members):
+    """ens_debug_tensor gives a tensor of the last batch of a request, also where batches are dealt to copies of a gang or replayed."""
+    nets = [tiny_member(i) for i in range(members)]
+    blobs = [W.quantise_weights_bf16(n, W.make_blob(n, 231 + i, 0)) for i, n in enumerate(nets)]
+    x = W.round_bf16(W.make_images(232, 61, 12, 12, varied=True))
+    E = ens.Ensemble(nets, blobs)
+    E.ens_set_alloc([[8] * members], 64)
+    for n in (29, 61, 16, 29, 2, 29):
+        E.ens_predict(x[:n])
+        last = (n - 1) % 8 + 1
+        got = [E.ens_debug_tensor(m, 3, (1, 1, 32), last) for m in range(members)]
+        E.ens_debug_one_stream(1)                                # no copies take part
+        E.ens_predict(x[:n])
+        E.ens_debug_one_stream(0)
+        for m in range(members):
+            assert np.array_equal(got[m], E.ens_debug_tensor(m, 3, (1, 1, 32), last)), (n, m)
+    E.close()
+
+
 def test_copies_leave_the_request_buffers_their_room(ens):
     """After ens_plan copies of a group come out of the budget beside the workers and the buffers of a request, and are counted."""
     net = tiny_member(0)

@@ -80,3 +80,23 @@ def copies_go(members, rows, copies):
 def test_copies_go_when_a_request_finds_no_memory(fake_hip, members, rows, copies):
     """A request whose buffers do not fit beside the copies of the gangs is answered without them, as it was before there were copies."""
     beside_fake_hip(fake_hip, "copies_go(%d, %d, %d)" % (members, rows, copies))
+
+
+def last_batch():
+    import paper_2208_14049_amd as ens
+    x, out = np.zeros((64, 12, 12, 3), np.float32), np.empty((8, 1, 1, 32), np.float32)
+    for members, n in ((1, 29), (4, 29), (1, 8), (4, 61)):       # three copies of the one, one of each of the four
+        E = tiny_ensemble(members)
+        E.ens_set_alloc([[8] * members], 64)
+        for size in (16, n, 2, 16, n, n):                        # what comes again runs from a graph with four members
+            E.ens_predict(x[:size])
+            in_last = (size - 1) % 8 + 1
+            for m in range(members):
+                rc = [ens.lib().ens_debug_tensor(E._h, m, 3, k, out.ctypes.data) for k in range(1, 9)]
+                assert rc == [0] * in_last + [-1] * (8 - in_last), (members, size, m, rc)
+        E.close()
+
+
+def test_a_worker_tells_of_its_last_batch(fake_hip):
+    """ens_debug_tensor is about the last batch of the member's first worker, whichever copy of its gang took it."""
+    beside_fake_hip(fake_hip, "last_batch()")
