@@ -18,12 +18,12 @@ namespace ens {
 // K: filter size of both axes, 0 = any.  S: input channels fetched together: 4 (16-byte loads; channel count, stride and
 // offset in fours), 3 (an image of three channels) or 1.
 template <int CT, int K, int S>
-__global__ __launch_bounds__(256) void conv_f32_kernel(const ConvArgs* __restrict__ argv, const int nb_) {
+__global__ __launch_bounds__(256) void conv_f32_kernel(const ConvArgs* __restrict__ argv, const int nb_, const int tile0) {
     const ConvArgs a = argv[blockIdx.z];
     const unsigned P = (unsigned)nb_ * (unsigned)(a.Ho * a.Wo);
     const unsigned p = blockIdx.x * 256u + threadIdx.x;
     if (p >= P) return;
-    const int co0 = (int)blockIdx.y * CT;
+    const int co0 = (tile0 + (int)blockIdx.y) * CT;
     const unsigned row = p / (unsigned)a.Wo, n = row / (unsigned)a.Ho;
     const int wo = (int)(p - row * (unsigned)a.Wo), ho = (int)(row - n * (unsigned)a.Ho);
     const float* __restrict__ const x = (const float*)a.x.p + (long long)n * a.H * a.W * a.x.stride + a.x.c0;
@@ -105,10 +105,15 @@ __global__ __launch_bounds__(256) void conv_f32_kernel(const ConvArgs* __restric
 
 template <int CT, int K>
 static void launch_f32_variant(const ConvArgs& a, const ConvArgs* argv, int G, int nb, long long P, hipStream_t s) {
-    const dim3 grid((unsigned)((P + 255) / 256), (unsigned)((a.cout + CT - 1) / CT), (unsigned)G);
-    if (a.cin % 4 == 0 && a.x.stride % 4 == 0 && a.x.c0 % 4 == 0) ENS_LAUNCH((conv_f32_kernel<CT, K, 4>), grid, dim3(256), 0, s, argv, nb);
-    else if (a.cin == 3) ENS_LAUNCH((conv_f32_kernel<CT, K, 3>), grid, dim3(256), 0, s, argv, nb);
-    else ENS_LAUNCH((conv_f32_kernel<CT, K, 1>), grid, dim3(256), 0, s, argv, nb);
+    constexpr int MOST = 65535;                                  // channel tiles that a grid can hold: wider layers take more launches
+    const int tiles = (a.cout + CT - 1) / CT;
+    for (int t0 = 0; t0 < tiles; t0 += MOST) {
+        const dim3 grid((unsigned)((P + 255) / 256), (unsigned)(tiles - t0 < MOST ? tiles - t0 : MOST), (unsigned)G);
+        const bool first = t0 == 0, last = tiles - t0 <= MOST;
+        if (a.cin % 4 == 0 && a.x.stride % 4 == 0 && a.x.c0 % 4 == 0) ENS_LAUNCH_EV(first, last, (conv_f32_kernel<CT, K, 4>), grid, dim3(256), 0, s, argv, nb, t0);
+        else if (a.cin == 3) ENS_LAUNCH_EV(first, last, (conv_f32_kernel<CT, K, 3>), grid, dim3(256), 0, s, argv, nb, t0);
+        else ENS_LAUNCH_EV(first, last, (conv_f32_kernel<CT, K, 1>), grid, dim3(256), 0, s, argv, nb, t0);
+    }
 }
 template <int CT>
 static void launch_f32_channels(const ConvArgs& a, const ConvArgs* argv, int G, int nb, long long P, hipStream_t s) {
@@ -121,7 +126,7 @@ hipError_t launch_conv_f32(const ConvArgs& a, const ConvArgs* argv, int G, int n
     if (nb <= 0 || a.cin <= 0 || a.cout <= 0 || !a.bias || !a.scale || G <= 0 || !argv) return hipErrorInvalidValue;
     if ((a.pre_scale == nullptr) != (a.pre_shift == nullptr)) return hipErrorInvalidValue;
     const long long P = (long long)nb * a.Ho * a.Wo;
-    if (P >= (1LL << 31) - 256 || (a.cout + 3) / 4 > 65535) return hipErrorInvalidValue;
+    if (P >= (1LL << 32) - 256) return hipErrorInvalidValue;     // the kernel's pixel numbers, and the threads that a launch can have
     // More channels per lane make more of a fetched value, fewer make more wavefronts: as many channels as leave two
     // wavefronts per SIMD (1024 of them).  A lane's channels past the last one are worked out and dropped.
     const long long waves = (P + 63) / 64 * G;

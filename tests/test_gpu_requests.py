@@ -230,6 +230,24 @@ def test_wide_pointwise_layers(ens, h, w, cin, cout, stride, res, nb):
         assert_after_bf16_layers(got[i:i + 1], ref, (i,))
 
 
+def test_fp32_layer_wider_than_a_grid(ens):
+    """An fp32 convolution with more than 65535 tiles of four output channels takes two launches.  Sums of three products in fp32."""
+    net = N.Net("wide", 2, 2, 8, dtype="fp32")
+    t = net.conv(0, 262160, 1, act=None)
+    net.fc(net.gap(t), 8)
+    blob = W.make_blob(net, 245, 0)
+    imgs = W.make_images(246, 2, 2, 2)
+    E = ens.Ensemble([net], [blob])
+    E.ens_debug_keep_tensors()
+    E.ens_set_alloc([[2]])
+    E.ens_predict(imgs)
+    got = E.ens_debug_tensor(0, t, net.tensors[t], 2)
+    E.close()
+    ref = oracle_tensor(net, blob, imgs, t)
+    # scale folded into the weight, three products and sums, the shift: six roundings of 2^-24 of terms of a few times the tensor's rms
+    assert np.abs(got - ref).max() <= 8 * 2.0 ** -24 * np.abs(ref).max() * 4
+
+
 def test_recorded_requests_outlive_the_allocation_free_entry_point(ens):
     """ens_predict_static frees nothing: requests recorded before it are replayed after it, with the answers they gave."""
     import torch

@@ -100,3 +100,24 @@ def last_batch():
 def test_a_worker_tells_of_its_last_batch(fake_hip):
     """ens_debug_tensor is about the last batch of the member's first worker, whichever copy of its gang took it."""
     beside_fake_hip(fake_hip, "last_batch()")
+
+
+def large_fp32_layers():
+    import ctypes as C
+    import paper_2208_14049_amd as ens
+    from synth import nets as N, weights as W
+    fake().fake_limit(90 << 30)                                  # nothing is written there; no room for copies
+    for side, cout, nb in ((2, 262160, 1), (32768, 1, 2)):       # wider than 65535 tiles of four channels; 2^31 output pixels
+        n = N.Net("large", side, side, 8, dtype="fp32")
+        n.fc(n.gap(n.conv(0, cout, 1)), 8)
+        E = ens.Ensemble([n], [W.make_blob(n, 241, 0)])
+        E.ens_set_alloc([[nb]])
+        L, some = ens.lib(), np.empty(64, np.float32)
+        assert L.ens_set_io(E._h, side, side, 1, 1) == 0
+        assert L.ens_predict(E._h, C.c_void_p(some.ctypes.data), nb, C.c_void_p(some.ctypes.data)) == 0, (side, cout)
+        E.close()
+
+
+def test_fp32_layers_of_any_width(fake_hip):
+    """The fp32 convolution is launched for every number of output channels, and for as many pixels as a launch can have threads."""
+    beside_fake_hip(fake_hip, "large_fp32_layers()")
