@@ -1,12 +1,12 @@
 """Throughput of the ensemble hot path on one MI355X.
 
-A step is one pass of the whole hot path (input staging, every member's forward pass on its
-worker streams, fused softmax-and-mean) over one request of n synthetic images resident in HBM.
+A step is one pass of the whole hot path (input staging, every member's forward pass on the
+library's streams, fused softmax-and-mean) over one request of n synthetic images resident in HBM.
 The headline workload is the heavy 12-member ensemble (the largest of the workload configurations
 that one GPU holds); the other bf16 configurations are measured in the same run as sub-records.
 Prints one JSON line: images per second (whole K steps), median and relative standard deviation of
 the single steps, the rate with the images coming from pinned host memory, the roofline figures of
-the dominant kernel (durations from HIP events attached to the dispatches on the worker streams),
+the dominant kernel (durations from HIP events attached to the dispatches),
 per-kernel-class rates, and the CPU oracle's rate on the host cores.
 """
 import argparse

@@ -143,9 +143,11 @@ void ens_free(ens_handle* h);
  * centres, edge clamp).  images_on_device / probs_on_device: the pointers given to ens_predict
  * are device pointers.  Default: base size = member 0's input size, host pointers.
  * Device buffers are read and written on the library's own streams, which are not ordered against
- * any stream of the caller: the images must be complete in device memory before ens_predict is
+ * the caller's: the images must be complete in device memory before ens_predict is
  * called (synchronise the producing stream first), and the probabilities are complete when it
- * returns. */
+ * returns.  The null stream alone is ordered with them, both ways: work that any thread of the process puts there runs
+ * before or after a request's kernels, never beside them (other work of a serving process is better put on non-blocking
+ * streams). */
 int ens_set_io(ens_handle* h, int32_t base_h, int32_t base_w, int32_t images_on_device,
                int32_t probs_on_device);
 
@@ -180,23 +182,27 @@ int ens_bench(ens_handle* h, const ens_alloc* a, int32_t segment_size, int64_t n
  *   images   : n x base_h x base_w x 3 fp32 (host or device, see ens_set_io)
  *   probs_out: n x classes fp32, written completely before the call returns
  * Needs an installed allocation (ens_plan or ens_set_alloc); without one, every member gets one
- * worker of batch size 8.  A call with a larger n than any before it (or with another device
- * image pointer) allocates device memory and rewrites argument blocks before it starts;
- * ens_predict_static below never allocates.
+ * worker of batch size 8.  A call with a larger n than any before it allocates device memory and
+ * rewrites argument blocks before it starts, one behind ens_predict_static rewrites them; a size that comes again may be
+ * recorded as graphs, up to sixteen sizes of them (some 0.8 MB of device memory each with twelve members).  ens_predict_static below
+ * never allocates.
+ * The kernels go to four streams, one set per GPU and process: handles that are used at once share them, and a request waits for
+ * those that it uses.  The calling thread spins while it waits for a small request, and while it hands out the batches of a request
+ * with more groups of workers than streams.
  */
 int ens_predict(ens_handle* h, const float* images, int64_t n, float* probs_out);
 
 /* ens_predict for callers that cannot allocate device memory (code under HIP graph capture set-up,
  * tight serving loops, harnesses that forbid hipMalloc): the same computation as ens_predict with
- * the per-request scratch of the call (the members' logits, members x n x classes fp32, and the
- * device table of their pointers), which ens_predict grows with hipMalloc, placed in a fixed device
+ * the per-request scratch of the call (the members' logits, members x n x classes fp32, behind a
+ * reserved head of 4 KiB), which ens_predict grows with hipMalloc, placed in a fixed device
  * array inside the library (ens_static_scratch_bytes() bytes, 32 MiB, held by every GPU the
  * library is loaded on until the process ends).  The call allocates and frees nothing.
  *   d_images   : DEVICE, n x base_h x base_w x 3 fp32, complete before the call
  *   d_probs_out: DEVICE, n x classes fp32, complete when the call returns
  * Needs an installed allocation (ens_plan / ens_set_alloc: they allocate the workers' arenas) and
  * per-kernel profiling switched off; ENS_E_INVALID otherwise.  ENS_E_TOOBIG, with a message on
- * stderr, when members x n x classes x 4 bytes exceed the array less its 4 KiB table (3 members of
+ * stderr, when members x n x classes x 4 bytes exceed the array less its head (3 members of
  * 1000 classes: n <= 2795).  The array is shared by every handle and call on a GPU and keeps the last
  * call's contents; a call writes every value it later reads, so nothing needs clearing, but calls
  * that overlap in time on one GPU race.  ens_member_logits reads the array after such a call. */
@@ -215,7 +221,7 @@ int ens_set_combination(ens_handle* h, int32_t rule, const float* weights);
 
 /* Overhead experiment of section "Overhead of the inference system": with the fake predictor on,
  * every member's forward pass (input staging included) is replaced by a prediction of zeros; the
- * partition into segments and batches, the workers' streams, the event join and the combination
+ * partition into segments and batches, their dealing to the streams and the combination
  * rule still run.  The wall time of such an ens_predict is the system's own overhead. */
 int ens_debug_fake_predictor(ens_handle* h, int32_t on);
 

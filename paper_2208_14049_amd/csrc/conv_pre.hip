@@ -148,7 +148,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             bn_unroll<TP>([&](auto j) { xf[b][decltype(j)::value] = bn_lds_read<decltype(j)::value * 4096>(xa); });
         };
         read_frags(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
-        // the loads of chunk kc + 1 have landed: issued behind them are those of chunks kc + 2 and kc + 3 and the weights of chunk kc + 2
+        // The input of chunk kc + 1 has landed.  Issued behind it are the inputs of chunks kc + 2 and kc + 3 and the weights of chunks kc + 1
+        // and kc + 2, 2 (XO + WO) loads in the steady loop and XO + 2 WO where kc + 2 is the last chunk.  The waits allow XO (WO) fewer:
+        // the input of chunk kc + 2 has landed as well.  Not measured with the looser ones.
         if (steady) bn_wait_vm<2 * XO + WO>();
         else if (kc + 2 < nk) bn_wait_vm<XO + WO>();
         else bn_wait_vm<0>();

@@ -1,10 +1,11 @@
 // The inference-system core (section "The inference system") on one GPU and its C interface.
 //
 // The paper's processes become: the segment broadcaster -> a host loop that hands every segment
-// once to every member; a worker (batcher, predictor, prediction sender) -> a HIP stream plus an
-// activation arena whose kernels write logits straight into the member's row block, so there
-// is nothing to reassemble; the prediction accumulator -> one fused softmax-and-mean kernel
-// after an event join of all worker streams (fixed member order, no atomics).
+// once to every member; a worker (batcher, predictor, prediction sender) -> an activation arena
+// and the launches of a gang on one of the process's four streams (lanes), whose kernels write
+// logits straight into the member's row block, so there is nothing to reassemble; the prediction
+// accumulator -> one fused softmax-and-mean kernel behind every lane, of which the last to arrive
+// for a row does the work (members in a fixed order).
 #include "engine.h"
 
 #include <algorithm>
@@ -680,7 +681,8 @@ static int64_t alloc_bytes(const ens_handle* h, const ens_alloc& a) {
     return total;
 }
 
-// The worker streams of an allocation run at once: each launch counts on its share of the chip.
+// What a launch counts on of the chip: its gang's share.  (Of the gangs at most LANES run at once, and the copies of a single gang do so
+// too: the share that a launch has can be twice this, or a quarter.  The kernels' thresholds were measured with this number.)
 static int stream_share(const ens_handle* h) {
     const int streams = std::max(1, h->own_gangs);
     return std::max(32, 256 / streams);

@@ -183,9 +183,9 @@ struct LaunchEvents {
 LaunchEvents& next_launch_events();                  // per thread
 
 // Compute units a launch may count on: all 256 when its stream has the GPU to itself, a share of them
-// when several worker streams run at once.  The launchers' tile and split choices weigh idle compute
+// when several gangs run at once.  The launchers' tile and split choices weigh idle compute
 // units against efficiency per workgroup by this number; the engine sets it (per thread) to the chip's
-// units divided by the number of streams of the installed allocation.
+// units divided by the number of gangs of the installed allocation, 32 at least.
 int& cu_budget();
 // Lanes that issue launches at once (set with cu_budget, the same for every request of an allocation, so that what was planned
 // together also runs together): what the kernels for few pixels weigh their load traffic against.

@@ -6,7 +6,7 @@
 namespace ens {
 
 // 32 MiB per GPU: per-member logits of one request (members x n x classes fp32) behind a
-// 4 KiB table of the members' logits pointers.
+// reserved head of 4 KiB (it once held a table of their addresses; requests' sizes are bounded with it).
 constexpr size_t STATIC_SCRATCH_BYTES = 32u << 20;
 constexpr size_t STATIC_SCRATCH_TABLE_BYTES = 4096;
 
