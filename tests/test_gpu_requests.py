@@ -316,6 +316,32 @@ def test_sizes_in_turn_are_recorded_within_bounds(ens):
     E.close()
 
 
+@pytest.mark.parametrize("rows,images", [([[8, 8, 8, 8], [8, 0, 0, 16]], 75), ([[8, 8, 8]], 83)], ids=["six_gangs", "copies_of_three"])
+def test_handed_out_batches(ens, rows, images):
+    """Several batches each for more gangs than lanes, handed out as lanes come free: bit for bit what one stream gives, whether the images are on
+    the device or come from pinned or ordinary host memory in pieces beside the kernels."""
+    import torch
+    nets = [N.resnet18(size=64, classes=100), N.efficientnet(0, size=64, classes=100), N.densenet121(size=64, classes=100), N.resnet18(size=48, classes=100)][:len(rows[0])]
+    blobs = [W.quantise_weights_bf16(net, W.make_blob(net, synth.BASE_SEED + 7, i)) for i, net in enumerate(nets)]
+    imgs = W.round_bf16(W.make_images(synth.BASE_SEED + 1001, images, 64, 64, varied=True))
+    d, pinned = torch.from_numpy(imgs).cuda(), torch.from_numpy(imgs).pin_memory()
+    out = torch.empty((images, 100), dtype=torch.float32, pin_memory=True)
+    E = ens.Ensemble(nets, blobs)
+    E.ens_set_alloc(rows, 16)
+    E.ens_debug_one_stream(1)
+    want = E.ens_predict(imgs)
+    z = [E.ens_member_logits(m, images) for m in range(len(nets))]
+    E.ens_debug_one_stream(0)
+    assert E.ens_debug_stats()["handed_out"] == 0
+    for rep in range(3):
+        for k, ask in enumerate((lambda: E.ens_predict(d.clone()).cpu().numpy(), lambda: E.ens_predict(pinned, out).numpy().copy(), lambda: E.ens_predict(imgs.copy()))):
+            before = E.ens_debug_stats()["handed_out"]
+            assert np.array_equal(ask(), want), (rep, k)
+            assert E.ens_debug_stats()["handed_out"] - before >= len(nets) * (images // 16), (rep, k)
+            assert all(np.array_equal(E.ens_member_logits(m, images), z[m]) for m in range(len(nets))), (rep, k)
+    E.close()
+
+
 def tiny_member(i):
     n = N.Net("turns%d" % i, 12, 12, 8, dtype="bf16")
     n.fc(n.gap(n.conv(n.conv(0, 16 + 8 * i, 3), 32, 3)), 8)
