@@ -695,7 +695,7 @@ static int64_t copy_bytes(const ens_handle* h) {
     return total;
 }
 
-// Gives the copies up.  Recorded requests run on them.
+// Gives the copies up, and the recorded requests, which run on them.
 static void drop_copies(ens_handle* h) {
     h->flagged = false;                                          // the streams themselves
     (void)wait_lanes(h);
@@ -713,13 +713,13 @@ static void drop_copies(ens_handle* h) {
     (void)hipGetLastError();
 }
 
-// fn, which allocates device memory; once more without the copies if there is not enough of it.
+// fn, which allocates device memory; once more without the copies and the recorded requests if there is not enough of it.
 template <typename F>
 static int with_room(ens_handle* h, F&& fn) {
     int rc = fn();
     if (rc != ENS_E_NOMEM) return rc;
     (void)hipGetLastError();
-    if ((int)h->gangs.size() == h->own_gangs) return rc;
+    if ((int)h->gangs.size() == h->own_gangs && h->graphs.empty()) return rc;
     drop_copies(h);
     rc = fn();
     if (rc == ENS_E_NOMEM) (void)hipGetLastError();

@@ -20,7 +20,8 @@ def fake_hip(tmp_path_factory):
 
 def beside_fake_hip(lib, call):
     """Runs `call` (an expression over this module) in a process with the fake runtime in front."""
-    p = subprocess.run([sys.executable, "-c", "import tests.test_host_paths as t; t.%s" % call], cwd=ROOT, env=dict(os.environ, LD_PRELOAD=lib),
+    preload = ":".join([lib] + [p for p in (os.environ.get("LD_PRELOAD"),) if p])
+    p = subprocess.run([sys.executable, "-c", "import tests.test_host_paths as t; t.%s" % call], cwd=ROOT, env=dict(os.environ, LD_PRELOAD=preload),
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, timeout=100)
     assert p.returncode == 0, p.stdout.decode()[-3000:]
 
@@ -121,3 +122,27 @@ def large_fp32_layers():
 def test_fp32_layers_of_any_width(fake_hip):
     """The fp32 convolution is launched for every number of output channels, and for as many pixels as a launch can have threads."""
     beside_fake_hip(fake_hip, "large_fp32_layers()")
+
+
+def graphs_go():
+    F, x = fake(), np.zeros((64, 12, 12, 3), np.float32)
+    E = tiny_ensemble(6)                                         # more groups than streams: no copies
+    E.ens_set_alloc([[64] * 6], 64)
+    for n in (64, 8, 3, 8, 3):
+        E.ens_predict(x[:n])
+    s = E.ens_debug_stats()
+    assert s["graphs"] == 2 and s["copies"] == 0, s
+    # room for larger buffers of a request once they, or its recordings, are gone
+    F.fake_limit(F.fake_used() + (2 << 20))
+    n = (5 << 20) // (12 * 12 * 3 * 4 + 7 * 8 * 4)
+    E.ens_predict(np.zeros((n, 12, 12, 3), np.float32))
+    assert E.ens_debug_stats()["graphs"] == 0
+    for n in (64, 8, 3, 8):
+        E.ens_predict(x[:n])
+    E.close()
+    assert F.fake_used() == 0
+
+
+def test_recorded_requests_go_when_a_request_finds_no_memory(fake_hip):
+    """The memory of recorded requests is given back to a request whose buffers do not fit beside them."""
+    beside_fake_hip(fake_hip, "graphs_go()")
