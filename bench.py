@@ -37,10 +37,10 @@ CPU_SAMPLE = {2: 16, 3: 16, 4: 12, 5: 16}      # images the oracle is timed on (
 # profiles/ (scaled by the plain-copy calibration given there).  An entry describes the kernel sources
 # with the digest recorded with it; with any other sources the figure is withheld (null).
 TRAFFIC = {
-    (4, "conv1x1_direct_bf16<128x128>"): dict(
-        bytes_per_launch=97.2e6,                 # read + written (profiles/bench_config4_12members_b128.md)
-        sources=["conv_pw.hip", "conv_direct.h", "conv_common.h", "kernels.h"],
-        sha256="5119a20acf9c0b64cb2ad90a1e8a33ccbd2747c48b7645bd7fba83864d033d63"),
+    (4, "conv1x1_direct_bf16<128x256>"): dict(
+        bytes_per_launch=94.9e6,                 # read + written (profiles/bench_config4_12members_b128.md)
+        sources=["conv_wide.hip", "conv_direct.h", "conv_common.h", "kernels.h"],
+        sha256="76c7072b892c2e9f09ed86410fd274e57eac4526f99c530435a491392d43f706"),
 }
 
 
