@@ -102,7 +102,7 @@ typedef struct {
     int32_t rows, cols;
     int32_t batch[ENS_MAX_SLOTS][ENS_MAX_MEMBERS];
     int64_t bytes;      /* out: device memory of the matrix as installed (weights, arenas and
-                           those of the copies, see ens_set_alloc)                            */
+                           those of the copies and chains, see ens_set_alloc)                 */
     double  score;      /* out: images per second measured for it, 0 if never benchmarked     */
     int32_t n_bench;    /* out: number of benchmarks the optimizer ran                        */
 } ens_alloc;
@@ -165,7 +165,9 @@ int ens_plan(ens_handle* h, uint64_t mem_budget_bytes, const ens_plan_opts* opts
  * that all handles of the process share (see ens_predict).  Where the matrix has up to four groups of workers (workers of one row with
  * networks of the same shape form a group) the library adds arenas for copies of them, up to three per worker, on which a group's
  * batches overlap: as many as take a quarter of the free device memory at most and, after ens_plan, fit into its budget beside the
- * workers and the request buffers.  They are given back when a later call of the handle finds too little memory. */
+ * workers and the request buffers.  They are given back when a later call of the handle finds too little memory.  So is, under the same
+ * conditions, what an ensemble of deep bf16 members keeps for requests of a few images (ens_predict): the steps of its members and a copy of
+ * their convolutions' weights in the order of the matrix cores' operands, up to the size of the weights. */
 int ens_set_alloc(ens_handle* h, const ens_alloc* a, int32_t segment_size);
 
 /* "Benchmark Mode" of section "The inference system": installs `a`, predicts n_calib synthetic
@@ -186,6 +188,9 @@ int ens_bench(ens_handle* h, const ens_alloc* a, int32_t segment_size, int64_t n
  * rewrites argument blocks before it starts, one behind ens_predict_static rewrites them; a size that comes again may be
  * recorded as graphs, up to sixteen sizes of them (some 0.8 MB of device memory each with twelve members).  ens_predict_static below
  * never allocates.
+ * A request of a few images to deep bf16 members, no more than the batch size of any worker, may run as one launch in which the compute units
+ * of an XCD take a member through all its layers (both entry points; estimates decide, by the members and the number of images); such a
+ * request is not recorded.
  * The kernels go to four streams, one set per GPU and process: handles that are used at once share them, and a request waits for
  * those that it uses.  The calling thread spins while it waits for a small request, and while it hands out the batches of a request
  * with more groups of workers than streams.
@@ -245,6 +250,7 @@ typedef struct {
     int64_t handed_out;  /* batches handed out one by one as streams came free                   */
     int64_t copies;      /* copies of groups of workers with arenas of their own (ens_set_alloc) */
     int64_t copy_bytes;  /* device memory of those arenas                                        */
+    int64_t chained;     /* requests of a few images that ran in one launch, as chains           */
 } ens_stats;
 int ens_debug_stats(const ens_handle* h, ens_stats* out);
 

@@ -52,7 +52,7 @@ class EnsAlloc(ctypes.Structure):
 
 
 class EnsStats(ctypes.Structure):
-    _fields_ = [(f, ctypes.c_int64) for f in ("recorded", "replayed", "graphs", "handed_out", "copies", "copy_bytes")]
+    _fields_ = [(f, ctypes.c_int64) for f in ("recorded", "replayed", "graphs", "handed_out", "copies", "copy_bytes", "chained")]
 
 
 class EnsPlanOpts(ctypes.Structure):
@@ -341,7 +341,7 @@ class Ensemble:
         _check(lib().ens_debug_one_stream(self._h, int(on)), "ens_debug_one_stream")
 
     def ens_debug_stats(self):
-        """{recorded, replayed, graphs, handed_out, copies, copy_bytes} of the handle."""
+        """{recorded, replayed, graphs, handed_out, copies, copy_bytes, chained} of the handle."""
         s = EnsStats()
         _check(lib().ens_debug_stats(self._h, ctypes.byref(s)), "ens_debug_stats")
         return {f: getattr(s, f) for f, _ in EnsStats._fields_}

@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstring>
 
+#include "chain.h"
 #include "planner.h"
 #include "seedgen.h"
 #include "static_scratch.h"
@@ -639,6 +640,7 @@ static void drop_graphs(ens_handle* h) {
 // A request that takes longer than the spin is waited for the ordinary way, and so is one in SYNC_EVERY, which lets the runtime
 // give back what it holds for finished launches.  (Not for answers on the device: the caller's next synchronisation of a stream of its
 // own would pay for that, 0.6 us per launch.)
+constexpr int CHAIN_FAILED_WORD = 8;                             // of the flag's 64 bytes
 constexpr double SPIN_S = 5e-3;
 constexpr uint64_t SYNC_EVERY = 64;
 
@@ -658,6 +660,15 @@ static hipError_t wait_lanes(ens_handle* h) {
     return hipSuccess;
 }
 
+static void drop_chains(ens_handle* h) {
+    h->chains.clear();
+    if (h->d_chain) (void)hipFree(h->d_chain);
+    h->d_chain = nullptr;
+    h->chain_bytes = 0;
+    h->chain_plans.clear();
+    for (Worker& w : h->workers) w.last_programs.clear();
+}
+
 static void destroy_workers(ens_handle* h) {
     h->flagged = false;                                          // the streams themselves
     (void)wait_lanes(h);
@@ -669,6 +680,7 @@ static void destroy_workers(ens_handle* h) {
     for (Worker& w : h->workers)
         if (w.arena) (void)hipFree(w.arena);
     h->workers.clear();
+    drop_chains(h);
     h->have_alloc = false;
 }
 
@@ -695,12 +707,13 @@ static int64_t copy_bytes(const ens_handle* h) {
     return total;
 }
 
-// Gives the copies up, and the recorded requests, which run on them.
+// Gives the copies up, and the recorded requests, which run on them, and the chains.
 static void drop_copies(ens_handle* h) {
     h->flagged = false;                                          // the streams themselves
     (void)wait_lanes(h);
     drop_graphs(h);
-    h->alloc.bytes -= copy_bytes(h);
+    h->alloc.bytes -= copy_bytes(h) + h->chain_bytes;
+    drop_chains(h);
     while ((int)h->gangs.size() > h->own_gangs) {
         if (h->gangs.back().d_args) (void)hipFree(h->gangs.back().d_args);
         h->gangs.pop_back();
@@ -719,7 +732,7 @@ static int with_room(ens_handle* h, F&& fn) {
     int rc = fn();
     if (rc != ENS_E_NOMEM) return rc;
     (void)hipGetLastError();
-    if ((int)h->gangs.size() == h->own_gangs && h->graphs.empty()) return rc;
+    if ((int)h->gangs.size() == h->own_gangs && h->graphs.empty() && h->chains.empty()) return rc;
     drop_copies(h);
     rc = fn();
     if (rc == ENS_E_NOMEM) (void)hipGetLastError();
@@ -770,6 +783,87 @@ static int copy_gangs(ens_handle* h, int64_t need) {
             if (rc != ENS_OK) return rc;
         }
     return ENS_OK;
+}
+
+// The members' chains, for requests of a few images (run_chains).  For ensembles of deep bf16 members: a chain saves a launch per layer,
+// and one of a few layers has little to save.  They run in the arenas of the members' first workers; a matrix whose workers of one member
+// differ in batch size is left alone, since which of them takes a batch is what it is about (hand_out).
+constexpr size_t CHAIN_MIN_OPS = 16;
+
+static void install_chains(ens_handle* h, int64_t need) {
+    std::vector<Chain> chains(h->members.size());
+    if (h->keeps || !h->gangs_enabled) return;
+    for (const Worker& w : h->workers)
+        if (w.batch != h->workers[0].batch && w.rank > 0) {
+            for (const Worker& u : h->workers)
+                if (u.member == w.member && u.batch != w.batch) return;
+        }
+    size_t steps = 0;
+    std::vector<size_t> at;
+    for (size_t c = 0; c < h->members.size(); c++) {
+        const Member& m = h->members[c];
+        if (!m.bf16 || m.ops.size() < CHAIN_MIN_OPS) return;
+        const Worker* own = nullptr;
+        for (const Worker& w : h->workers)
+            if (w.member == (int)c && w.rank == 0 && !w.copy) own = &w;
+        if (!own) return;
+        Worker w = *own;                                         // its tensors apart, and every operation for itself
+        w.layout = plan_arena(m, 1, true);
+        w.batch = 1;
+        const size_t arena_bytes = own->arena_bytes;
+        const int batch = own->batch;
+        char* const arena = own->arena;
+        Fusions F;
+        F.chain.assign(m.ops.size(), 0);
+        F.fused = F.gated = F.summed = F.swapped = F.chain;
+        for (size_t i = 0; i + 1 < m.ops.size(); i++)
+            if (!F.swapped[i] && (m.ops[i].swap_pool || m.ops[i].swap_conv)) {
+                F.swapped[i] = m.ops[i].swap_pool ? 1 : 3;
+                F.swapped[i + 1] = m.ops[i].swap_pool ? 2 : 4;
+            }
+        Gang g;
+        g.workers.push_back((int)h->workers.size());
+        std::vector<Launch> launches;
+        std::vector<char> blocks;
+        const std::vector<size_t> places = w.layout.offset;
+        h->workers.push_back(w);
+        const int rc = build_plan(h, g, 1, F, launches, blocks);
+        h->workers.pop_back();
+        if (rc != ENS_OK || !build_chain(m, launches, arena, places, arena_bytes, batch, &chains[c])) return;
+        at.push_back(steps);
+        steps += chains[c].steps.size();
+    }
+    // the steps, and behind them the weights that are not in operand order elsewhere
+    size_t bytes = steps * sizeof(ChainStep);
+    for (const Chain& c : chains) bytes += c.pack_bytes;
+    size_t free_bytes = 0, total = 0;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess || bytes > free_bytes / 4) { (void)hipGetLastError(); return; }
+    if (h->budget && (uint64_t)need + bytes + (uint64_t)h->reserve > h->budget) return;
+    if (hipMalloc((void**)&h->d_chain, bytes) != hipSuccess) { h->d_chain = nullptr; (void)hipGetLastError(); return; }
+    bool ok = true;
+    char* packed = (char*)(h->d_chain + steps);
+    for (size_t c = 0; c < chains.size() && ok; c++) {
+        for (const Chain::Pack& p : chains[c].packs) {
+            ChainStep& s = chains[c].steps[p.step];
+            ok = ok && launch_chain_pack(s.w, packed + p.at, p.groups, p.rows, p.K, h->main_stream) == hipSuccess;
+            for (ChainStep& q : chains[c].steps)
+                for (int k = 0; k < 2; k++)
+                    if (q.ahead[k] == s.w) q.ahead[k] = packed + p.at;
+            s.w = packed + p.at;
+        }
+        packed += chains[c].pack_bytes;
+        ok = ok && hipMemcpyAsync(h->d_chain + at[c], chains[c].steps.data(), chains[c].steps.size() * sizeof(ChainStep), hipMemcpyHostToDevice, h->main_stream) == hipSuccess;
+    }
+    ok = hipStreamSynchronize(h->main_stream) == hipSuccess && ok;
+    if (!ok) {
+        (void)hipGetLastError();
+        (void)hipFree(h->d_chain);
+        h->d_chain = nullptr;
+        return;
+    }
+    h->chain_bytes = (int64_t)bytes;
+    h->chain_at = at;
+    h->chains = std::move(chains);
 }
 
 static int install_alloc(ens_handle* h, const ens_alloc& a, int segment_size) {
@@ -852,8 +946,9 @@ static int install_alloc(ens_handle* h, const ens_alloc& a, int segment_size) {
     h->args_stale = false;
     h->alloc = a;
     h->alloc.bytes = need;
-    if (copy_gangs(h, need) != ENS_OK) drop_copies(h);
-    h->alloc.bytes = need + copy_bytes(h);
+    install_chains(h, need);
+    if (copy_gangs(h, need + h->chain_bytes) != ENS_OK) drop_copies(h);
+    h->alloc.bytes = need + h->chain_bytes + copy_bytes(h);
     h->segment_size = segment_size;
     h->have_alloc = true;
     return ENS_OK;
@@ -891,6 +986,7 @@ static void note_batch(ens_handle* h, const Gang& g, int64_t first, int nb) {
     for (int wi : g.workers) {
         Worker& w = h->workers[wi];
         w.last_nb = nb;
+        w.last_programs.clear();
         w.last_request = h->requests;
         w.last_first = first;
     }
@@ -1228,6 +1324,131 @@ static RequestGraph* record_request(ens_handle* h, int64_t n, int lanes, const s
     return &h->graphs.back();
 }
 
+// ---- requests as chains -----------------------------------------------------------------------------
+
+// A program's estimate from those of the numbers of images around it.
+static double program_seconds(const Chain& c, int images) {
+    const int z = chain_size(images);
+    if (images >= 1 << z) return c.seconds[z] * images / (1 << z);
+    const double lo = 1 << (z - 1), hi = 1 << z;
+    return c.seconds[z - 1] + (c.seconds[z] - c.seconds[z - 1]) * (images - lo) / (hi - lo);
+}
+
+// Cuts a request into programs for the eight groups: every member's images in the number of parts that ends first by the estimates, the
+// longest program first.  None: the request is not one for chains.
+static ChainPlan plan_programs(const ens_handle* h, int64_t n) {
+    ChainPlan best;
+    constexpr int GROUPS = 8;                                    // XCDs
+    for (int parts = 1; parts <= GROUPS && parts <= n; parts++) {
+        std::vector<std::pair<double, ChainProgram>> all;
+        const int most = (int)((n + parts - 1) / parts);
+        if (parts > 1 && most == (int)((n + parts - 2) / (parts - 1))) continue;
+        for (size_t c = 0; c < h->chains.size(); c++)
+            for (int first = 0; first < n; first += most) {
+                const int images = (int)std::min<int64_t>(most, n - first);
+                all.emplace_back(program_seconds(h->chains[c], images), ChainProgram{(short)c, (short)first, (short)images, (short)chain_size(images)});
+            }
+        if (all.size() > CHAIN_MAX_PROGRAMS) break;
+        std::stable_sort(all.begin(), all.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+        double load[GROUPS] = {0}, end = 0;
+        for (const auto& p : all) {
+            double& l = *std::min_element(load, load + GROUPS);
+            l += p.first;
+            end = std::max(end, l);
+        }
+        if (end < best.seconds) {
+            best.seconds = end;
+            best.programs.clear();
+            for (const auto& p : all) best.programs.push_back(p.second);
+        }
+    }
+    return best;
+}
+
+// What the launches of the request come to: a launch is a chain of round trips however little it does, one after the other on a lane, and
+// the work of all of them takes the GPU besides.
+static double launches_seconds(ens_handle* h, int64_t n) {
+    const std::vector<std::vector<int32_t>> owner(h->members.size(), std::vector<int32_t>(1, 0));   // (one segment: the first worker's)
+    std::vector<double> floors(h->gangs.size(), 0.0);
+    double work = 0;
+    (void)each_batch(h, n, ~0ull, owner, [&](Gang& g, int64_t, int nb) {
+        const double share = (double)nb / h->workers[g.workers[0]].batch * (double)g.workers.size();
+        floors[&g - h->gangs.data()] += launch_floor(L_POOL);    // input staging
+        for (const Launch& L : g.plan_for(nb).launches)
+            if (L.kind != L_SKIP) {
+                floors[&g - h->gangs.data()] += launch_floor(L.kind);
+                work += launch_work(L, share);
+            }
+        return ENS_OK;
+    });
+    std::sort(floors.begin(), floors.end(), [](double x, double y) { return x > y; });
+    double load[LANES] = {0};
+    for (double t : floors) *std::min_element(load, load + LANES) += t;
+    // (the floors are those of a launch among others' on four lanes: on a lane of its own a gang is faster, and twelve on four are slower)
+    const bool crowded = std::count_if(floors.begin(), floors.end(), [](double t) { return t > 0.0; }) > LANES;
+    return *std::max_element(load, load + LANES) * (crowded ? 1.08 : 0.85) + work;
+}
+
+// How a request of n images is cut into programs, or null when it goes launch by launch.  Measured both ways over six ensembles on 1 to 12
+// images (us, launches / chains): twelve members on 1, 2, 4 and 8 images 2967 / 1269, 3171 / 1712, 3637 / 2537 and 4414 / 4444; four members
+// 825 / 637, 885 / 650, 1032 / 781 and 1338 / 1185; a ResNet-50 alone 334 / 394, 348 / 391, 385 / 391 and 469 / 426; three ResNet-18, whose launches
+// carry all three, 188 / 201 and 337 / 356 (1 and 8 images).  The estimates of chains are 10 to 20 % low: hence the margin, which leaves to the
+// launches what comes out even.
+constexpr double CHAIN_MARGIN = 1.25;
+
+static const ChainPlan* chain_plan(ens_handle* h, int64_t n) {
+    if (h->chains.empty()) return nullptr;
+    for (const Chain& c : h->chains)
+        if (n > c.cap) return nullptr;
+    if (h->chain_plans.size() <= (size_t)n) h->chain_plans.resize((size_t)n + 1);
+    ChainPlan& p = h->chain_plans[(size_t)n];
+    if (!p.known) {
+        p = plan_programs(h, n);
+        p.known = true;
+        if (p.seconds * CHAIN_MARGIN > launches_seconds(h, n)) p.programs.clear();
+    }
+    return p.programs.empty() ? nullptr : &p;
+}
+
+// The request in one launch and the combination behind it, on the first lane.
+static int run_chains(ens_handle* h, const float* d_images, int64_t n, float* d_probs, const ChainPlan& plan, const float* host_images) {
+    const std::vector<ChainProgram>& programs = plan.programs;
+    if (host_images)
+        HIP_TRY(hipMemcpyAsync((void*)d_images, host_images, (size_t)n * h->base_h * h->base_w * 3 * sizeof(float), hipMemcpyHostToDevice, h->lanes[0]));
+    ChainArgs a;
+    memset(&a, 0, sizeof(a));
+    for (size_t c = 0; c < h->members.size(); c++) {
+        a.steps[c] = h->d_chain + h->chain_at[c];
+        a.phases[c] = (short)h->chains[c].phases;
+        a.image_bytes[c] = (unsigned)h->chains[c].image_bytes;
+        a.logits[c] = h->d_logits[c];
+    }
+    for (Worker& w : h->workers)
+        if (w.rank == 0 && !w.copy) {
+            a.arena[w.member] = w.arena;
+            w.last_nb = (int)n;
+            w.last_request = h->requests;
+            w.last_first = 0;
+            w.last_programs.clear();
+            for (const ChainProgram& p : programs)
+                if (p.member == w.member) w.last_programs.push_back(p);
+        }
+    std::copy(programs.begin(), programs.end(), a.programs);
+    a.n_programs = (int)programs.size();
+    a.sync = h->d_chain_sync;
+    a.failed = h->flag + CHAIN_FAILED_WORD;
+    a.src = d_images;
+    a.base_h = h->base_h; a.base_w = h->base_w; a.classes = h->classes;
+    HIP_TRY(launch_chain(a, h->lanes[0]));
+    h->stats.chained++;
+    h->lanes_used = 1;
+    CombineArgs c = combine_args(h, n, 1);
+    c.y = d_probs;
+    HIP_TRY(launch_combine(c, h->lanes[0]));
+    if (h->flagged) HIP_TRY(launch_finish(h->d_arrivals + COMBINE_MAX_BLOCKS, 1, h->flag, (uint32_t)h->requests, h->lanes[0]));
+    return ENS_OK;
+}
+
 // f(X, A) -> Y with Y on the device (or in pinned host memory).  The images are at d_images; when host_images is
 // given they are still to be copied there from host memory, segment by segment beside the kernels of the segments before.
 // `mask` selects the members that take part (all members for a real request; a single member when the BBS baseline
@@ -1251,6 +1472,10 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
     auto refresh = [&](int i) { return h->gangs[i].stale ? build_launches(h, h->gangs[i], may_alloc) : ENS_OK; };
     h->requests++;
     const bool plain_only = !may_alloc || h->profiling || h->fake_predictor || h->one_stream || mask != ~0ull;
+    if (!h->chains.empty() && !h->profiling && !h->fake_predictor && !h->one_stream && mask == ~0ull) {
+        const ChainPlan* plan = chain_plan(h, n);
+        if (plan) return run_chains(h, d_images, n, d_probs, *plan, host_images);
+    }
     RequestGraph* graph = plain_only || (host_images && n_seg > 1) ? nullptr : find_graph(h, n);
     // every segment id goes once to every member; a member's workers share its segments as they
     // would by taking them from one queue, the faster worker more of them (planner.cpp, hand_out)
@@ -1437,7 +1662,16 @@ static void recover(ens_handle* h) {
     (void)hipDeviceSynchronize();
     h->flagged = false;
     if (h->d_arrivals) (void)hipMemset(h->d_arrivals, 0, (COMBINE_MAX_BLOCKS + 1) * sizeof(unsigned));
+    if (h->d_chain_sync) (void)hipMemset(h->d_chain_sync, 0, sizeof(ChainSync));
     (void)hipGetLastError();
+}
+
+// A chain's group that waited for seconds has said so and left.
+static int chains_ended(ens_handle* h) {
+    if (!__atomic_load_n(h->flag + CHAIN_FAILED_WORD, __ATOMIC_ACQUIRE)) return ENS_OK;
+    __atomic_store_n(h->flag + CHAIN_FAILED_WORD, 0u, __ATOMIC_RELEASE);
+    recover(h);
+    return ENS_E_HIP;
 }
 
 static int finish_profile(ens_handle* h) {
@@ -1510,6 +1744,8 @@ static int time_installed(ens_handle* h, int64_t n, int repeats, uint64_t mask, 
         rc = run_device(h, h->d_calib, n, h->d_probs, mask);
         if (rc != ENS_OK) { recover(h); return rc; }
         HIP_TRY(wait_lanes(h));
+        rc = chains_ended(h);
+        if (rc != ENS_OK) return rc;
         const auto t1 = std::chrono::steady_clock::now();
         if (i > 0) secs.push_back(std::chrono::duration<double>(t1 - t0).count());
     }
@@ -1573,7 +1809,9 @@ int ens_load(const ens_member_spec* specs, int32_t n_members, uint64_t seed, ens
     if (hipMalloc((void**)&h->d_arrivals, (COMBINE_MAX_BLOCKS + 1) * sizeof(unsigned)) != hipSuccess) return fail(ENS_E_NOMEM);
     if (hipMemset(h->d_arrivals, 0, (COMBINE_MAX_BLOCKS + 1) * sizeof(unsigned)) != hipSuccess) return fail(ENS_E_HIP);
     if (hipHostMalloc((void**)&h->flag, 64, hipHostMallocCoherent) != hipSuccess) return fail(ENS_E_NOMEM);
-    *h->flag = 0;
+    memset(h->flag, 0, 64);
+    if (hipMalloc((void**)&h->d_chain_sync, sizeof(ChainSync)) != hipSuccess) return fail(ENS_E_NOMEM);
+    if (hipMemset(h->d_chain_sync, 0, sizeof(ChainSync)) != hipSuccess) return fail(ENS_E_HIP);
     h->d_logits.assign(h->members.size(), nullptr);
     h->stage_klass = prof_class(h, "stage_kernel");
     *out = h;
@@ -1590,6 +1828,7 @@ void ens_free(ens_handle* h) {
         if (p) (void)hipFree(p);
     if (h->d_slots) (void)hipFree(h->d_slots);
     if (h->d_arrivals) (void)hipFree(h->d_arrivals);
+    if (h->d_chain_sync) (void)hipFree(h->d_chain_sync);
     if (h->pin_in) (void)hipHostFree(h->pin_in);
     if (h->pin_out) (void)hipHostFree(h->pin_out);
     if (h->flag) (void)hipHostFree(h->flag);
@@ -1661,6 +1900,8 @@ int ens_predict(ens_handle* h, const float* images, int64_t n, float* probs_out)
     if (rc != ENS_OK) { recover(h); return rc; }
     HIP_TRY(wait_lanes(h));
     h->flagged = false;
+    rc = chains_ended(h);
+    if (rc != ENS_OK) return rc;
     if (direct_out) {
         memcpy(probs_out, h->pin_out, out_floats * sizeof(float));
     } else if (!h->probs_on_device) {
@@ -1687,6 +1928,8 @@ int ens_predict_static(ens_handle* h, const float* d_images, int64_t n, float* d
     rc = run_device(h, d_images, n, d_probs_out, ~0ull, false);
     if (rc != ENS_OK) { recover(h); return rc; }
     HIP_TRY(wait_lanes(h));
+    rc = chains_ended(h);
+    if (rc != ENS_OK) return rc;
     h->last_n = n;
     h->last_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     return ENS_OK;
@@ -1851,11 +2094,20 @@ int ens_debug_tensor(ens_handle* h, int32_t member, int32_t tensor, int32_t n_im
         if (x.last_request > w->last_request || (x.last_request == w->last_request && x.last_first > w->last_first)) w = &x;
     }
     if (n_images <= 0 || n_images > w->last_nb) return ENS_E_INVALID;
-    if (tensor == 0) w = &h->workers[h->gangs[w->gang].workers[0]];   // the staged input lives with the gang's leader
     const TensorInfo& ti = m.tensors[tensor];
-    const size_t elems = (size_t)n_images * ti.elems_per_image();
-    std::vector<uint8_t> raw(elems * (ti.f32 ? 4 : 2));
-    HIP_TRY(hipMemcpy(raw.data(), w->arena + w->layout.offset[tensor], raw.size(), hipMemcpyDeviceToHost));
+    std::vector<uint8_t> raw(ti.bytes(n_images));
+    if (!w->last_programs.empty()) {
+        const Chain& c = h->chains[member];
+        if (c.place[tensor] == SIZE_MAX) return ENS_E_INVALID;
+        for (const ChainProgram& p : w->last_programs) {
+            const int images = std::min((int)p.images, n_images - p.first);
+            if (images <= 0) continue;
+            HIP_TRY(hipMemcpy(raw.data() + ti.bytes(p.first), w->arena + p.first * c.image_bytes + p.images * c.place[tensor], ti.bytes(images), hipMemcpyDeviceToHost));
+        }
+    } else {
+        if (tensor == 0) w = &h->workers[h->gangs[w->gang].workers[0]];   // the staged input lives with the gang's leader
+        HIP_TRY(hipMemcpy(raw.data(), w->arena + w->layout.offset[tensor], raw.size(), hipMemcpyDeviceToHost));
+    }
     const size_t pixels = (size_t)n_images * ti.h * ti.w;
     for (size_t p = 0; p < pixels; p++)
         for (int c = 0; c < ti.c; c++) {

@@ -12,6 +12,11 @@
 
 namespace ens {
 
+struct ChainStep;
+struct ChainSync;
+// Images [first, first + images) of one member, as a chain (chain.h); size: for what number of images its tiles were chosen.
+struct alignas(8) ChainProgram { short member, first, images, size; };
+
 struct TensorInfo {
     int h, w, c;
     int cs;          // stored channels (bf16 tensors are padded to a multiple of 8)
@@ -129,6 +134,7 @@ struct Worker {
     size_t arena_bytes = 0;
     ArenaLayout layout;
     int last_nb = 0;               // images of its last batch
+    std::vector<ChainProgram> last_programs;   // not empty: it ran as these (chain.h)
     uint64_t last_request = 0;     // and which one that was: the number of the request, its first image
     int64_t last_first = 0;
 };
@@ -176,6 +182,25 @@ constexpr int LANES = 4;
 // handle's work only where the two meet on a lane.
 hipError_t acquire_lanes(hipStream_t* lanes);    // LANES streams; every successful call is paired with one of
 void release_lanes(const hipStream_t* lanes);    // these; the streams go with the last handle
+
+constexpr int CHAIN_SIZES = 6;               // numbers of images that a chain's tiles are chosen for: up to 1, 2, 4, 8, 16, 32 and more
+// The chain of one member, worked out when an allocation is installed.
+struct Chain {
+    std::vector<ChainStep> steps;
+    int phases = 0, cap = 0;                 // images that the worker's arena holds in the chain's layout
+    struct Pack { int step, groups, rows, K; size_t at, bytes; };   // weights to be put into operand order, and where among all of them
+    std::vector<Pack> packs;
+    size_t pack_bytes = 0;
+    std::vector<size_t> place;               // of every tensor, for one image
+    size_t image_bytes = 0;
+    double seconds[CHAIN_SIZES] = {};        // estimate of a program of 1, 2, 4 ... images
+};
+// A request cut into programs, and its estimate.
+struct ChainPlan {
+    bool known = false;
+    std::vector<ChainProgram> programs;      // the longest first
+    double seconds = 1e30;
+};
 
 // A request of a size that came before, recorded: per lane every launch of it.
 struct RequestGraph {
@@ -228,6 +253,13 @@ struct ens_handle {
     uint32_t* flag = nullptr;                    // pinned: number of the last request that is complete (see wait_lanes), then
                                                  // per lane the number of its last batch that is
     bool flagged = false;                        // the request in flight will write it
+    // small requests as chains (chain.h): one per member, or none at all; their steps in device memory, and where in it each begins
+    std::vector<ens::Chain> chains;
+    ens::ChainStep* d_chain = nullptr;           // and behind them weights in operand order
+    int64_t chain_bytes = 0;
+    std::vector<size_t> chain_at;
+    std::vector<ens::ChainPlan> chain_plans;     // by the number of images
+    ens::ChainSync* d_chain_sync = nullptr;
     std::vector<ens::RequestGraph> graphs;
     std::vector<ens::SeenSize> sizes_seen;
     uint64_t requests = 0, last_recorded = 0;    // requests so far, and the one that was recorded last

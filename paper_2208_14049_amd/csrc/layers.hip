@@ -3,7 +3,7 @@
 // average pool, squeeze-excite, the FC head and the fused softmax-and-mean combination.
 // Activations are NHWC; the bf16 kernels move 8 channels (16 bytes) per lane so that a
 // wavefront reads and writes whole 128-byte lines; all arithmetic is fp32.
-#include "kernels.h"
+#include "stage.h"
 
 namespace ens {
 
@@ -71,30 +71,6 @@ LaunchEvents& next_launch_events() {
 static inline int blocks_for(long long work, int threads) { return (int)((work + threads - 1) / threads); }
 
 // ------------------------------------------------------------------ input staging
-// Bilinear sample (half-pixel centres, edge clamp) of the three source channels at destination
-// pixel (y, x) of a dh x dw image; a plain copy when the sizes agree.
-__device__ __forceinline__ void stage_sample(const StageArgs& a, const float* __restrict__ src, int y, int x, float* v) {
-    if (a.sh == a.dh && a.sw == a.dw) {
-        const float* p = src + ((long long)y * a.sw + x) * 3;
-        v[0] = p[0]; v[1] = p[1]; v[2] = p[2];
-        return;
-    }
-    float fy = (y + 0.5f) * ((float)a.sh / (float)a.dh) - 0.5f;
-    float fx = (x + 0.5f) * ((float)a.sw / (float)a.dw) - 0.5f;
-    fy = fminf(fmaxf(fy, 0.f), (float)(a.sh - 1));
-    fx = fminf(fmaxf(fx, 0.f), (float)(a.sw - 1));
-    const int y0 = (int)floorf(fy), x0 = (int)floorf(fx);
-    const int y1 = min(y0 + 1, a.sh - 1), x1 = min(x0 + 1, a.sw - 1);
-    const float wy = fy - y0, wx = fx - x0;
-#pragma unroll
-    for (int c = 0; c < 3; c++) {
-        const float p00 = src[((long long)y0 * a.sw + x0) * 3 + c], p01 = src[((long long)y0 * a.sw + x1) * 3 + c];
-        const float p10 = src[((long long)y1 * a.sw + x0) * 3 + c], p11 = src[((long long)y1 * a.sw + x1) * 3 + c];
-        const float top = p00 * (1.f - wx) + p01 * wx, bot = p10 * (1.f - wx) + p11 * wx;
-        v[c] = top * (1.f - wy) + bot * wy;
-    }
-}
-
 // One thread per destination pixel, written as dc channels (zero padded) in the member's dtype.
 template <bool BF16>
 __global__ void stage_kernel(StageArgs a, const int nb_, const long long first) {
@@ -109,7 +85,7 @@ __global__ void stage_kernel(StageArgs a, const int nb_, const long long first) 
     const long long n = idx / ((long long)a.dw * a.dh);
     const float* src = a.src + n * (long long)a.sh * a.sw * 3;
     float v[3];
-    stage_sample(a, src, y, x, v);
+    stage_sample(a.sh, a.sw, a.dh, a.dw, src, y, x, v);
     if (BF16) {
         uint16_t* d = (uint16_t*)a.dst + idx * a.dc;
         if (a.dc == 8) {
@@ -146,7 +122,7 @@ __global__ void stage_s2d_kernel(StageArgs a, const int nb_, const long long fir
 #pragma unroll
         for (int bx = 0; bx < 2; bx++) {
             const int y = 2 * r + by, x = 2 * q + bx;
-            if (y < a.dh && x < a.dw) stage_sample(a, src, y, x, &f[(by * 2 + bx) * 3]);
+            if (y < a.dh && x < a.dw) stage_sample(a.sh, a.sw, a.dh, a.dw, src, y, x, &f[(by * 2 + bx) * 3]);
         }
     uint4* d = (uint4*)((uint16_t*)a.dst + idx * 16);
     d[0] = pack8(f);

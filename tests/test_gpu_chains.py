@@ -1,0 +1,105 @@
+"""Requests of a few images that run in one launch, a member per XCD (csrc/chain.hip): against the oracle, for every family of members and for
+layers at the edges of what the kernel's steps take."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from synth import nets as N
+from synth import weights as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ens():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_2208_14049_amd as e
+    e.lib()
+    return e
+
+
+def ask_all_ways(ens, nets, blobs, imgs, base, batch, sizes, bound):
+    """Every size of `sizes`, from device and host memory and through the allocation-free entry point, in one order and another, beside the oracle's logits."""
+    import torch
+    x = [oracle.resize_bilinear(imgs, net.in_h, net.in_w) for net in nets]
+    z_ref = [oracle.forward_logits(net, b, xi, real="f32") for net, b, xi in zip(nets, blobs, x)]
+    d = torch.from_numpy(imgs).cuda()
+    E = ens.Ensemble(nets, blobs)
+    E.set_base_size(base[0], base[1])
+    E.ens_set_alloc([[batch] * len(nets)])
+    first = {}
+    for n in sizes:
+        first[n] = E.ens_predict(d[:n].clone()).cpu().numpy()
+        for m, net in enumerate(nets):
+            z, ref = E.ens_member_logits(m, n), z_ref[m][:n]
+            err = float(np.abs(z - ref).max() / z_ref[m].std())
+            print("%s, %d images: logits max-abs err / std %.4f" % (net.name, n, err), flush=True)
+            assert np.isfinite(z).all() and err <= bound, (net.name, n, err)
+    assert E.ens_debug_stats()["chained"] == len(sizes) and E.ens_debug_stats()["recorded"] == 0, E.ens_debug_stats()
+    out = {n: torch.empty((n, E.classes), device="cuda") for n in sizes}
+    for n in tuple(reversed(sizes)) + tuple(sizes):
+        assert np.array_equal(E.ens_predict(imgs[:n].copy()), first[n]), n
+        E.ens_predict_static(d[:n].contiguous(), out[n])
+        assert np.array_equal(out[n].cpu().numpy(), first[n]), n
+    ran = E.ens_debug_stats()
+    assert ran["chained"] == 5 * len(sizes) and ran["graphs"] == 0, ran
+    # the pooled features of the last request, and what launches leave of them
+    n = sizes[-1]
+    pooled = [net.ops[-1]["src"] for net in nets]
+    got = [E.ens_debug_tensor(m, pooled[m], net.tensors[pooled[m]], n) for m, net in enumerate(nets)]
+    E.ens_debug_one_stream(1)
+    plain = E.ens_predict(imgs[:n].copy())
+    E.ens_debug_one_stream(0)
+    assert E.ens_debug_stats()["chained"] == ran["chained"] and np.abs(plain - first[n]).max() <= 2e-2
+    for m, net in enumerate(nets):
+        want = E.ens_debug_tensor(m, pooled[m], net.tensors[pooled[m]], n)
+        assert np.abs(got[m] - want).max() <= bound * want.std(), net.name
+    E.close()
+
+
+def test_families_of_members(ens):
+    """Residual, dense, inception, inverted-residual, separable, grouped and plain members at reduced size, two of them at another resolution than the
+    request; one image, and several per program.  The bound on the logits is that of each family's own test."""
+    nets = [N.resnet18(size=64, classes=200), N.resnet50(size=64, classes=200), N.densenet121(size=64, classes=200), N.efficientnet(0, size=64, classes=200),
+            N.inception_v3(size=107, classes=200), N.resnext50(size=64, classes=200), N.xception(size=107, classes=200), N.mobilenet_v2(size=64, classes=200),
+            N.vgg(16, size=64, classes=200)]
+    blobs = [W.quantise_weights_bf16(net, W.make_blob(net, synth.BASE_SEED + 41, i)) for i, net in enumerate(nets)]
+    imgs = W.round_bf16(W.make_images(synth.BASE_SEED + 1041, 5, 64, 64, varied=True))
+    ask_all_ways(ens, nets, blobs, imgs, (64, 64), 16, (1, 3, 5), 0.08)
+
+
+def edges(i):
+    """Layers at the edges of the chain's steps: K of 8 and of a chunk and 8, taps that change inside a chunk, odd maps, strides, filters along one
+    axis, slices of a concatenation, groups, a squeeze-excite block with and without a depthwise layer in front, pools of every kind."""
+    n = N.Net("edges%d" % i, 45, 37, 24, dtype="bf16")
+    t = n.conv(0, 24 + 8 * i, 3)                                  # the image itself, 8 channels stored
+    t = n.conv(t, 40, 3, stride=2, act="silu")
+    a = n.conv(t, 72, 1)
+    b = n.conv(a, 72, (1, 7), act=None)
+    t = n.conv(b, 72, (7, 1), res=a)
+    t = n.maxpool(t, 3, 2, 1)
+    h, w, _ = n.tensors[t]
+    cat = n.tensor(h, w, 40 + 48 + 72)                            # three branches into slices
+    n.conv(t, 40, 1, dst=(cat, 0))
+    n.conv(n.conv(t, 16, 5), 48, 3, dst=(cat, 40))
+    n.avgpool(t, 3, 1, 1, dst=(cat, 88))
+    t = n.conv(cat, 136, 1, pre=True)
+    t = n.dwconv(t, 5, stride=1)
+    t = n.conv(n.se(t, 10), 64, 1, act=None)
+    t = n.dwconv(t, 3, stride=2, act="relu")
+    t = n.se(n.conv(t, 64, 3, groups=2, act=None), 3)             # no depthwise layer in front of this one
+    t = n.avgpool(n.conv(t, 128, 1, pre=True, act=None), 2, 2)
+    t = n.conv(t, 200, 1, stride=2)
+    n.fc(n.gap(t, pre=True), 24)
+    return n
+
+
+@pytest.mark.parametrize("sizes", [(1, 2), (3, 5, 7)], ids=str)
+def test_layers_at_the_edges(ens, sizes):
+    nets = [edges(i) for i in range(4)]
+    blobs = [W.quantise_weights_bf16(net, W.make_blob(net, synth.BASE_SEED + 43, i)) for i, net in enumerate(nets)]
+    imgs = W.round_bf16(W.make_images(synth.BASE_SEED + 1043, sizes[-1], 45, 37, varied=True))
+    # some 20 bf16 roundings of 2^-9 from the image to the logits, as for the members above
+    ask_all_ways(ens, nets, blobs, imgs, (45, 37), 16, sizes, 0.08)
