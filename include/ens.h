@@ -190,7 +190,8 @@ int ens_bench(ens_handle* h, const ens_alloc* a, int32_t segment_size, int64_t n
  * never allocates.
  * A request of a few images to deep bf16 members, no more than the batch size of any worker, may run as one launch in which the compute units
  * of an XCD take a member through all its layers (both entry points; estimates decide, by the members and the number of images); such a
- * request is not recorded.
+ * request is not recorded.  Neither is one of small fp32 members (convolutions, pooling and a head whose tensors and weights fit 160 KB), of
+ * which a compute unit takes an image at a time.
  * The kernels go to four streams, one set per GPU and process: handles that are used at once share them, and a request waits for
  * those that it uses.  The calling thread spins while it waits for a small request, and while it hands out the batches of a request
  * with more groups of workers than streams.
@@ -250,7 +251,7 @@ typedef struct {
     int64_t handed_out;  /* batches handed out one by one as streams came free                   */
     int64_t copies;      /* copies of groups of workers with arenas of their own (ens_set_alloc) */
     int64_t copy_bytes;  /* device memory of those arenas                                        */
-    int64_t chained;     /* requests of a few images that ran in one launch, as chains           */
+    int64_t chained;     /* requests whose members ran in one launch (see ens_predict)           */
 } ens_stats;
 int ens_debug_stats(const ens_handle* h, ens_stats* out);
 

@@ -134,6 +134,7 @@ struct Worker {
     size_t arena_bytes = 0;
     ArenaLayout layout;
     int last_nb = 0;               // images of its last batch
+    bool input_only = false;       // of which its arena holds the input and nothing else (ens_debug_tensor runs the layers)
     std::vector<ChainProgram> last_programs;   // not empty: it ran as these (chain.h)
     uint64_t last_request = 0;     // and which one that was: the number of the request, its first image
     int64_t last_first = 0;
@@ -195,6 +196,15 @@ struct Chain {
     size_t image_bytes = 0;
     double seconds[CHAIN_SIZES] = {};        // estimate of a program of 1, 2, 4 ... images
 };
+// A small fp32 member that runs in a compute unit's LDS (resident.h), worked out when an allocation is installed.
+struct Resident {
+    std::vector<float> fixed;                // what LDS begins with
+    int lds_floats = 0;
+    int in = 0, in_p = 0, in_r = 0;          // the input tensor in LDS: pixel (0, 0), floats a pixel and a row
+    int n_ops = 0;
+    double seconds = 0;                      // estimate of an image
+};
+
 // A request cut into programs, and its estimate.
 struct ChainPlan {
     bool known = false;
@@ -260,6 +270,10 @@ struct ens_handle {
     std::vector<size_t> chain_at;
     std::vector<ens::ChainPlan> chain_plans;     // by the number of images
     ens::ChainSync* d_chain_sync = nullptr;
+    // fp32 members that fit LDS (resident.h): one per member, or none at all; what LDS begins with in device memory, and where each begins
+    std::vector<ens::Resident> residents;
+    float* d_resident = nullptr;
+    std::vector<size_t> resident_at;
     std::vector<ens::RequestGraph> graphs;
     std::vector<ens::SeenSize> sizes_seen;
     uint64_t requests = 0, last_recorded = 0;    // requests so far, and the one that was recorded last

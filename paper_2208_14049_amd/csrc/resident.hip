@@ -1,0 +1,292 @@
+// A small fp32 member from the request's images to its logits in one launch: a workgroup takes an image at a time, every tensor in LDS.
+//
+// Launch by launch such a member costs five launches a batch that leave the GPU idle (8 images: 66 us, of which a few are work) and fetches
+// every tap through the vector memory path (14 TFLOP/s over 8 100 images).  A 32 x 32 x 16 map is 64 KB: the whole network fits the 160 KB of a
+// compute unit.  Weights come once per workgroup, which then walks its share of the images.
+//
+// Convolutions run on the matrix cores in fp32 (v_mfma_f32_16x16x4: fp32 products, fp32 sums): 16 channels x 16 pixels, K = taps x input
+// channels in steps of four.  The value a lane needs for its k is at a distance from the first tap's that is the same for every pixel: a
+// table in LDS.  Tensors that a padded convolution reads have a border of zeros of their own, so that no tap is outside.
+//
+// Measured, two members of 32 x 32 images: 8 images 61 -> 33 us, 1 000 images in batches of 8 2.5 ms -> 117 us, 8 192 images 2.84 -> 0.71 ms.  A first
+// form kept every map in LDS (convolution, barrier, pooling): one workgroup a compute unit, 1.50 ms; with windows and means taken in
+// registers and the next image's pixels asked for ahead two of them fit.  What bounds it now: LDS reads, a value a lane for each step of four.
+#include "resident.h"
+#include "conv_common.h"
+#include "stage.h"
+
+#include <cstddef>
+
+namespace ens {
+
+#define RS(f) __builtin_amdgcn_readlane(op, offsetof(ResidentOp, f) / 4)
+
+__device__ __forceinline__ float rs_act(float v, int act) {
+    return act == ACT_RELU ? fmaxf(v, 0.f) : act == ACT_SILU ? v / (1.f + expf(-v)) : v;   // the exponential at full precision
+}
+
+// p / d for 0 <= p < 2^24
+__device__ __forceinline__ int rs_div(int p, int d, float inv) {
+    int q = (int)((float)p * inv);
+    const int r = p - q * d;
+    return q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
+}
+
+// PT x 16 pixels times CT x 16 channels at a time.  POOL: a lane's pixels are the four of a 2 x 2 window, whose maximum or mean is what leaves the
+// registers; MEAN: the sums over a unit's pixels are, added up at the end.  So the widest maps never are in LDS.
+enum { RS_PLAIN, RS_POOL, RS_MEAN };
+template <int PT, int CT, int FORM>
+__device__ __forceinline__ void rs_conv(const int op, float* const lds) {
+    const int t = threadIdx.x, lane = t & 63, l16 = lane & 15, kq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    // outputs: pixels, or windows of four
+    const int Wo = RS(Wo), P = RS(Ho) * Wo, cout = RS(cout), steps = RS(steps), K = RS(kh) * RS(kw) * RS(cin), xs = RS(xp) * RS(sw), xrs = RS(xr) * RS(sh), act = RS(act);
+    constexpr int EACH = FORM == RS_POOL ? 16 : 16 * PT;
+    const int cts = (cout + 16 * CT - 1) / (16 * CT), units = ((P + EACH - 1) / EACH) * cts;
+    const float inv = __builtin_amdgcn_rcpf((float)Wo);
+    const int* const taps = (const int*)lds + RS(taps) + kq;
+    for (int u = wave; u < units; u += RESIDENT_THREADS / 64) {
+        const int pt = u / cts, ct = u - pt * cts;
+        const float* x[PT];
+        int yo[PT];
+#pragma unroll
+        for (int j = 0; j < PT; j++) {
+            if constexpr (FORM == RS_POOL) {
+                static_assert(PT == 4, "a window");
+                const int p = pt * 16 + l16, pc = min(p, P - 1), ho = rs_div(pc, Wo, inv), wo = pc - ho * Wo;
+                x[j] = lds + RS(x) + (2 * ho + (j >> 1)) * xrs + (2 * wo + (j & 1)) * xs;
+                yo[j] = p < P ? RS(y) + ho * RS(yr) + wo * RS(yp) : -1;
+            } else {
+                const int p = (pt * PT + j) * 16 + l16, pc = min(p, P - 1), ho = rs_div(pc, Wo, inv), wo = pc - ho * Wo;
+                x[j] = lds + RS(x) + ho * xrs + wo * xs;
+                yo[j] = p < P ? RS(y) + ho * RS(yr) + wo * RS(yp) : -1;
+            }
+        }
+        const float* const w = lds + RS(w) + (ct * CT * 4 * steps + kq) * 16 + l16;
+        f32x4 acc[CT][PT];
+#pragma unroll
+        for (int i = 0; i < CT; i++)
+#pragma unroll
+            for (int j = 0; j < PT; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // four steps at a time, the places of the next four on their way
+        constexpr int U = 4;
+        const int whole = K / (4 * U) * U;
+        int off[U];
+#pragma unroll
+        for (int q = 0; q < U; q++) off[q] = taps[4 * q];        // (behind the table lie other words of LDS)
+        for (int s = 0; s < whole; s += U) {
+            float a[U][CT], b[U][PT];
+#pragma unroll
+            for (int q = 0; q < U; q++) {
+#pragma unroll
+                for (int j = 0; j < PT; j++) b[q][j] = x[j][off[q]];
+#pragma unroll
+                for (int i = 0; i < CT; i++) a[q][i] = w[(i * steps + s + q) * 64];
+            }
+#pragma unroll
+            for (int q = 0; q < U; q++) off[q] = taps[4 * (s + U + q)];
+#pragma unroll
+            for (int q = 0; q < U; q++)
+#pragma unroll
+                for (int i = 0; i < CT; i++)
+#pragma unroll
+                    for (int j = 0; j < PT; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][i], b[q][j], acc[i][j], 0, 0, 0);
+        }
+        for (int s = whole; s < steps; s++) {                    // (behind K: a weight of zero times what is there could be a NaN)
+            const bool ok = 4 * s + kq < K;
+            const int o = taps[4 * s];
+            float a[CT], b[PT];
+#pragma unroll
+            for (int j = 0; j < PT; j++) b[j] = x[j][ok ? o : 0];
+#pragma unroll
+            for (int i = 0; i < CT; i++) a[i] = w[(i * steps + s) * 64];
+#pragma unroll
+            for (int i = 0; i < CT; i++)
+#pragma unroll
+                for (int j = 0; j < PT; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], ok ? b[j] : 0.f, acc[i][j], 0, 0, 0);
+        }
+        // register v of a lane: channel 4 (lane / 16) + v of pixel lane % 16; whole fours are written (a pixel has room for them)
+#pragma unroll
+        for (int i = 0; i < CT; i++) {
+            const int c = (ct * CT + i) * 16 + 4 * kq;
+            const f32x4 b = *(const f32x4*)(lds + RS(bias) + min(c, cout - 1) / 4 * 4);
+            f32x4 v[PT];
+#pragma unroll
+            for (int j = 0; j < PT; j++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[j][e] = rs_act(acc[i][j][e] + b[e], act);
+            if constexpr (FORM == RS_POOL) {
+                const bool is_max = RS(pool) == RS_MAX_POOL;
+                f32x4 r;
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const float most = fmaxf(fmaxf(fmaxf(v[0][e], v[1][e]), fmaxf(v[2][e], v[3][e])), -3.0e38f);   // as rs_pool begins
+                    r[e] = is_max ? most : (v[0][e] + v[1][e] + v[2][e] + v[3][e]) * 0.25f;
+                }
+                if (yo[0] >= 0 && c < cout) *(f32x4*)(lds + yo[0] + c) = r;
+            } else if constexpr (FORM == RS_MEAN) {
+                f32x4 r{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < PT; j++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) r[e] += yo[j] >= 0 ? v[j][e] : 0.f;
+#pragma unroll
+                for (int off = 8; off > 0; off >>= 1)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) r[e] += __shfl_xor(r[e], off, 64);
+                if (l16 == 0 && c < cout) *(f32x4*)(lds + RS(sums) + pt * RS(sums_p) + c) = r;
+            } else if (c < cout) {
+#pragma unroll
+                for (int j = 0; j < PT; j++)
+                    if (yo[j] >= 0) *(f32x4*)(lds + yo[j] + c) = v[j];
+            }
+        }
+    }
+    if constexpr (FORM == RS_MEAN) {                 // the units' sums in order
+        __syncthreads();
+        const int n = (P + EACH - 1) / EACH;
+        for (int c = t; c < cout; c += RESIDENT_THREADS) {
+            float sum = 0.f;
+            for (int q = 0; q < n; q++) sum += lds[RS(sums) + q * RS(sums_p) + c];
+            lds[RS(y) + c] = sum / (float)P;
+        }
+    }
+}
+
+__device__ __forceinline__ void rs_pool(const int op, float* const lds, const bool is_max) {
+    const int c4 = (RS(cin) + 3) / 4, Wo = RS(Wo), H = RS(H), W = RS(W), items = RS(Ho) * Wo * c4;
+    const float inv_c = __builtin_amdgcn_rcpf((float)c4), inv_w = __builtin_amdgcn_rcpf((float)Wo);
+    for (int it = threadIdx.x; it < items; it += RESIDENT_THREADS) {
+        const int p = rs_div(it, c4, inv_c), c = (it - p * c4) * 4, ho = rs_div(p, Wo, inv_w), wo = p - ho * Wo;
+        const int h0 = ho * RS(sh) - RS(pt), w0 = wo * RS(sw) - RS(pl);
+        f32x4 acc = is_max ? f32x4{-3.0e38f, -3.0e38f, -3.0e38f, -3.0e38f} : f32x4{0.f, 0.f, 0.f, 0.f};
+        int cnt = 0;
+        for (int h = max(h0, 0); h < min(h0 + RS(kh), H); h++)
+            for (int w = max(w0, 0); w < min(w0 + RS(kw), W); w++) {
+                const f32x4 v = *(const f32x4*)(lds + RS(x) + h * RS(xr) + w * RS(xp) + c);
+#pragma unroll
+                for (int e = 0; e < 4; e++) acc[e] = is_max ? fmaxf(acc[e], v[e]) : acc[e] + v[e];
+                cnt++;
+            }
+        if (!is_max) {
+#pragma unroll
+            for (int e = 0; e < 4; e++) acc[e] /= (float)max(cnt, 1);
+        }
+        *(f32x4*)(lds + RS(y) + ho * RS(yr) + wo * RS(yp) + c) = acc;
+    }
+}
+
+// mean over the pixels, a wavefront per channel
+__device__ __forceinline__ void rs_gap(const int op, float* const lds) {
+    const int t = threadIdx.x, lane = t & 63, W = RS(W), HW = RS(H) * W;
+    const float inv = __builtin_amdgcn_rcpf((float)W);
+    for (int c = t >> 6; c < RS(cin); c += RESIDENT_THREADS / 64) {
+        float sum = 0.f;
+        for (int p = lane; p < HW; p += 64) {
+            const int h = rs_div(p, W, inv);
+            sum += lds[RS(x) + h * RS(xr) + (p - h * W) * RS(xp) + c];
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+        if (lane == 0) lds[RS(y) + c] = sum / (float)HW;
+    }
+}
+
+// a wavefront per class
+__device__ __forceinline__ void rs_fc(const int op, float* const lds, float* const logits) {
+    const int t = threadIdx.x, lane = t & 63, K = RS(cin), classes = RS(cout);
+    for (int c = t >> 6; c < classes; c += RESIDENT_THREADS / 64) {
+        float sum = 0.f;
+        for (int k = lane; k < K; k += 64) sum = fmaf(lds[RS(x) + k], lds[RS(w) + k * classes + c], sum);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+        if (lane == 0) logits[c] = sum + lds[RS(bias) + c];
+    }
+}
+
+__global__ __launch_bounds__(RESIDENT_THREADS) void resident_kernel(const ResidentArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) float rlds[];
+    const int t = threadIdx.x;
+    int m = 0;
+    while (m + 1 < a.n_members && (int)blockIdx.x >= a.member[m + 1].first_block) m++;
+    const ResidentMember& mb = a.member[m];
+    const int px = mb.in_h * mb.in_w;
+    const float inv_w = __builtin_amdgcn_rcpf((float)mb.in_w);
+    // the next image's pixels are asked for a network ahead, where a thread has no more than two of them and they are only copied
+    constexpr int AHEAD = 2;
+    const bool ahead = px <= AHEAD * RESIDENT_THREADS && a.base_h == mb.in_h && a.base_w == mb.in_w;
+    float v[AHEAD][3];
+    auto ask = [&](int image) {
+        const float* const src = a.src + (size_t)image * px * 3;
+#pragma unroll
+        for (int q = 0; q < AHEAD; q++)
+#pragma unroll
+            for (int c = 0; c < 3; c++) v[q][c] = t + q * RESIDENT_THREADS < px ? src[(t + q * RESIDENT_THREADS) * 3 + c] : 0.f;
+    };
+    int image = a.first + (int)blockIdx.x - mb.first_block;
+    const int end = a.first + a.n;
+    if (ahead && image < end) ask(image);
+    for (int i = t; i < mb.lds_floats / 4; i += RESIDENT_THREADS)
+        ((f32x4*)rlds)[i] = i < mb.fixed_floats / 4 ? ((const f32x4*)mb.fixed)[i] : f32x4{0.f, 0.f, 0.f, 0.f};   // and the borders' zeros
+    const int* const ops = (const int*)rlds;         // the operations lie first
+    __syncthreads();
+    for (; image < end; image += mb.blocks) {
+        auto put = [&](int i, const float* p) {
+            const int y = rs_div(i, mb.in_w, inv_w), x = i - y * mb.in_w;
+            float* const d = rlds + mb.in + y * mb.in_r + x * mb.in_p;
+            d[0] = p[0]; d[1] = p[1]; d[2] = p[2];
+            if (image >= mb.last_first && image < mb.last_first + mb.last_n) {
+                float* const k = mb.input + ((size_t)(image - mb.last_first) * px + i) * 3;
+                k[0] = p[0]; k[1] = p[1]; k[2] = p[2];
+            }
+        };
+        if (ahead) {
+#pragma unroll
+            for (int q = 0; q < AHEAD; q++)
+                if (t + q * RESIDENT_THREADS < px) put(t + q * RESIDENT_THREADS, v[q]);
+            if (image + mb.blocks < end) ask(image + mb.blocks);
+        } else {
+            const float* const src = a.src + (size_t)image * a.base_h * a.base_w * 3;
+            for (int i = t; i < px; i += RESIDENT_THREADS) {
+                const int y = rs_div(i, mb.in_w, inv_w), x = i - y * mb.in_w;
+                float p[3];
+                stage_sample(a.base_h, a.base_w, mb.in_h, mb.in_w, src, y, x, p);
+                put(i, p);
+            }
+        }
+        __syncthreads();
+        for (int i = 0; i < mb.n_ops; i++) {
+            const int op = ops[i * 64 + (t & 63)];
+            switch (RS(kind)) {
+                case RS_CONV:
+                    if (RS(pool) == RS_NO_POOL) {
+                        if (RS(cout) > 16) rs_conv<2, 2, RS_PLAIN>(op, rlds); else rs_conv<4, 1, RS_PLAIN>(op, rlds);
+                    } else if (RS(pool) == RS_MEAN_POOL) {
+                        if (RS(cout) > 16) rs_conv<2, 2, RS_MEAN>(op, rlds); else rs_conv<2, 1, RS_MEAN>(op, rlds);
+                    } else {
+                        if (RS(cout) > 16) rs_conv<4, 2, RS_POOL>(op, rlds); else rs_conv<4, 1, RS_POOL>(op, rlds);
+                    }
+                    break;
+                case RS_GAP: rs_gap(op, rlds); break;
+                case RS_FC: rs_fc(op, rlds, mb.logits + (size_t)image * a.classes); break;
+                default: rs_pool(op, rlds, RS(kind) == RS_MAXPOOL);
+            }
+            __syncthreads();
+        }
+    }
+}
+
+hipError_t launch_resident(const ResidentArgs& a, int lds_bytes, hipStream_t s) {
+    if (!a.src || a.n <= 0 || a.n_members <= 0 || a.n_members > RESIDENT_MAX_MEMBERS || lds_bytes > RESIDENT_LDS) return hipErrorInvalidValue;
+    static const hipError_t raised = hipFuncSetAttribute((const void*)&resident_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, RESIDENT_LDS);
+    if (raised != hipSuccess) return raised;
+    int blocks = 0;
+    for (int m = 0; m < a.n_members; m++) {
+        if (a.member[m].blocks <= 0 || a.member[m].first_block != blocks || a.member[m].lds_floats * 4 > lds_bytes || !a.member[m].logits) return hipErrorInvalidValue;
+        blocks += a.member[m].blocks;
+    }
+    ENS_LAUNCH(resident_kernel, dim3((unsigned)blocks), dim3(RESIDENT_THREADS), (size_t)lds_bytes, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace ens

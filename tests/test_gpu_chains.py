@@ -96,9 +96,9 @@ def edges(i):
     return n
 
 
-@pytest.mark.parametrize("sizes", [(1, 2), (3, 5, 7)], ids=str)
-def test_layers_at_the_edges(ens, sizes):
-    nets = [edges(i) for i in range(4)]
+@pytest.mark.parametrize("members,sizes", [(4, (1, 2)), (8, (3, 5, 7))], ids=str)   # (more images take more members for the rule to chain them)
+def test_layers_at_the_edges(ens, members, sizes):
+    nets = [edges(i) for i in range(members)]
     blobs = [W.quantise_weights_bf16(net, W.make_blob(net, synth.BASE_SEED + 43, i)) for i, net in enumerate(nets)]
     imgs = W.round_bf16(W.make_images(synth.BASE_SEED + 1043, sizes[-1], 45, 37, varied=True))
     # some 20 bf16 roundings of 2^-9 from the image to the logits, as for the members above

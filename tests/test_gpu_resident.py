@@ -1,0 +1,97 @@
+"""Requests of small fp32 members that run with every tensor in LDS (csrc/resident.hip): against the oracle in float64 and beside the launches."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from synth import nets as N
+from synth import weights as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ens():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_2208_14049_amd as e
+    e.lib()
+    return e
+
+
+def windows(classes=7):
+    """Convolutions that take 2 x 2 windows or the mean along: fewer and more channels than a tile of 16, a pair of tiles and one channel more, K of
+    no whole step, an image of another size than the request's."""
+    n = N.Net("windows", 26, 20, classes, dtype="fp32")
+    t = n.maxpool(n.conv(0, 5, 5, act="silu"), 2, 2)
+    t = n.avgpool(n.conv(t, 33, (1, 7)), 2, 2)                   # 13 rows: the last belongs to no window
+    t = n.conv(t, 16, 1, act=None)
+    n.fc(n.gap(n.conv(t, 35, 3)), classes)
+    return n
+
+
+def plain(classes=7):
+    """What runs by itself: pools of three with padding, strides, a layer without padding, a tensor that two layers read, a mean over a pool."""
+    n = N.Net("plain", 19, 23, classes, dtype="fp32")
+    t = n.maxpool(n.conv(0, 17, 3, stride=2, bn=False), 3, 2, 1)
+    t = n.conv(t, 20, 2, pad="valid", act="silu")
+    t = n.avgpool(n.conv(t, 3, 3), 3, 1, 1)
+    n.fc(n.gap(n.maxpool(n.conv(t, 40, 1), 2, 1)), classes)
+    return n
+
+
+# one image; fewer than workgroups; pieces of 1024 of a host's images and part of one; several batches a worker and members with two workers
+@pytest.mark.parametrize("n,rows", [(1, [[8, 8, 8, 8]]), (37, [[8, 8, 8, 8], [8, 16, 0, 8]]), (1061, [[32, 16, 32, 32]])], ids=str)
+def test_members_in_lds(ens, n, rows):
+    import torch
+    nets = [N.tiny_a(classes=7), N.tiny_b(classes=7), windows(), plain()]
+    blobs = [W.make_blob(net, synth.BASE_SEED + 51, i) for i, net in enumerate(nets)]
+    imgs = W.make_images(synth.BASE_SEED + 1051, n, 32, 32, varied=True)
+    z_ref = [oracle.forward_logits(net, b, oracle.resize_bilinear(imgs, net.in_h, net.in_w), real="f64") for net, b in zip(nets, blobs)]
+    E = ens.Ensemble(nets, blobs)
+    E.set_base_size(32, 32)
+    E.ens_set_alloc(rows)
+    d = torch.from_numpy(imgs).cuda()
+    first = E.ens_predict(d.clone()).cpu().numpy()
+    z = [E.ens_member_logits(m, n) for m in range(len(nets))]
+    assert np.array_equal(E.ens_predict(imgs), first)
+    out = torch.empty((n, E.classes), device="cuda")
+    E.ens_predict_static(d, out)
+    assert np.array_equal(out.cpu().numpy(), first)
+    assert E.ens_debug_stats()["chained"] == 3, E.ens_debug_stats()
+    kept = [op["dst"] for op in nets[3].ops[:-1]]
+    got = {t: E.ens_debug_tensor(3, t, nets[3].tensors[t], 1) for t in (0, kept[-1])}
+    E.ens_debug_one_stream(1)
+    assert np.abs(E.ens_predict(imgs) - first).max() <= 1e-6
+    for t in got:
+        assert np.abs(E.ens_debug_tensor(3, t, nets[3].tensors[t], 1) - got[t]).max() <= 1e-5, t
+    assert E.ens_debug_stats()["chained"] == 3
+    for m, net in enumerate(nets):
+        # sums of K <= 300 products leave some sqrt(K) 2^-24 = 1e-6 of a value each, over six layers and the largest of many: 4e-5
+        std = z_ref[m].std() if n > 1 else 1.0
+        err, launches = (float(np.abs(x - z_ref[m]).max() / std) for x in (z[m], E.ens_member_logits(m, n)))
+        print("%s: logits max-abs err / std %.2e, by launches %.2e" % (net.name, err, launches), flush=True)
+        assert err <= 4e-5, (net.name, err)
+    E.close()
+
+
+def test_values_that_are_no_numbers(ens):
+    """An infinity, a NaN and the largest numbers in some images leave the others alone, and what they give is what the launches give."""
+    nets = [N.tiny_a(classes=7), windows(), plain()]
+    blobs = [W.make_blob(net, synth.BASE_SEED + 53, i) for i, net in enumerate(nets)]
+    imgs = W.make_images(synth.BASE_SEED + 1053, 9, 32, 32, varied=True)
+    E = ens.Ensemble(nets, blobs)
+    E.set_base_size(32, 32)
+    E.ens_set_alloc([[8, 8, 8]])
+    E.ens_predict(imgs)
+    clean = [E.ens_member_logits(m, 9) for m in range(3)]
+    imgs[2, 5, 7, 1], imgs[4, 31, 31, :], imgs[6, :, 3, 0] = np.inf, np.nan, -3.4e38
+    E.ens_predict(imgs)
+    z = [E.ens_member_logits(m, 9) for m in range(3)]
+    assert E.ens_debug_stats()["chained"] == 2
+    E.ens_debug_one_stream(1)
+    E.ens_predict(imgs)
+    for m, net in enumerate(nets):
+        assert np.array_equal(z[m][[0, 1, 3, 5, 7, 8]], clean[m][[0, 1, 3, 5, 7, 8]]), net.name
+        np.testing.assert_allclose(z[m], E.ens_member_logits(m, 9), rtol=1e-4, atol=1e-4, err_msg=net.name)
+    E.close()
