@@ -14,14 +14,15 @@
 //      layout the 3x3 kernel reads its window in, with zeros at the positions that hold no pixel
 //      (the 3x3 padding is zero in t1, not act(b1));
 //   2. t2 = act(W2 * t1 + b2), nine taps over the window in LDS; the result replaces t1 in LDS;
-//   3. y = act(W3 t2 + b3 + residual), 128 output channels at a time, stored from the accumulators.
+//   3. y = act(W3 t2 + b3 + residual), 128 output channels at a time, stored from the accumulators or, among other
+//      lanes' launches, turned into rows in LDS on the way.
 // The weights do not pass through LDS: the member keeps a second copy of them in the order of the
 // matrix-core operands (blocks of 32 rows x 16 columns, 16 bytes per lane), so a wavefront fetches
 // a fragment as 1 KB in a row straight into registers, several steps ahead of its use.  Phases 2
 // and 3 therefore run without a barrier; their only LDS traffic is the pixel fragments.
 // The weight rows are handed to the matrix cores with bits 2 and 3 of the row number swapped, so
 // that a lane of a 32x32 result block holds two runs of 8 consecutive channels of one position:
-// 16-byte LDS writes in phases 1 and 2, 16-byte global stores in phase 3.  The price of the fusion
+// 16-byte LDS writes.  The price of the fusion
 // is phase 1 on the R - 128 extra positions; the gain is the traffic of t1 and t2 and the second
 // pass over x (the residual is re-read while its lines are still in a cache).
 #include "conv_direct.h"
@@ -38,7 +39,7 @@ template <int C, int R>
 constexpr int bn_big() { return bn_max3(BN_NXB * R * 64, (C / 64) * R * 128, (C / 64) * BN_BP * 128); }
 
 // argv: the argument blocks of the three convolutions, gridDim.z of each (one per member of the gang)
-template <int C, int R>
+template <int C, int R, bool ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void bottleneck_bf16(const ConvArgs* __restrict__ argv, const int nb_) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const int G = gridDim.z;
@@ -244,25 +245,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc((void*)a3.y.p, 0, (int)(npix * (unsigned)a3.y.stride * 2u), 0x00020000);
     const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(has_res ? a3.res.p : a3.y.p), 0, (int)(npix * (unsigned)(has_res ? a3.res.stride : a3.y.stride) * 2u), 0x00020000);
-    unsigned yo[2], ro[2];
+    // ROWS: residual and output come and go in rows of the wavefront's 64 channels (bn_row), piece (j, i) being position 32 j + 8 i + lane / 8, channels
+    // 8 (lane % 8) ...; otherwise straight from the accumulators, position 32 j + lane % 32, channels 16 i + 8 (lane / 32) ...
+    int pout[2][4];
     {
-        const int* own = tbl + W1 + 1 + wp0 + lrow;              // the centre tap's rows: this tile's outputs
+        const int* own = tbl + W1 + 1 + wp0 + (ROWS ? lane >> 3 : lrow);   // the centre tap's rows: this tile's outputs
 #pragma unroll
-        for (int j = 0; j < 2; j++) {
-            const int pout = own[32 * j];
-            yo[j] = pout >= 0 ? (unsigned)(pout * a3.y.stride * 2) + (unsigned)((a3.y.c0 + wc3 + 8 * lhalf) * 2) : OOBV;
-            ro[j] = pout >= 0 ? (unsigned)(pout * a3.res.stride * 2) + (unsigned)((a3.res.c0 + wc3 + 8 * lhalf) * 2) : OOBV;
-        }
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) pout[j][i] = own[32 * j + (ROWS ? 8 * i : 0)];
     }
-    u32x4 resn[2][2][2];
+    auto piece = [&](int j, int i, const View& v) {
+        return pout[j][i] >= 0 ? (unsigned)(pout[j][i] * v.stride * 2) + (unsigned)((v.c0 + wc3 + (ROWS ? 8 * (lane & 7) : 8 * lhalf + 16 * i)) * 2) : OOBV;
+    };
+    u32x4 resn[2][4];
     auto load_res = [&](int nc) {
 #pragma unroll
         for (int j = 0; j < 2; j++)
 #pragma unroll
-            for (int i = 0; i < 2; i++)
-#pragma unroll
-                for (int k = 0; k < 2; k++)
-                    resn[j][i][k] = __builtin_amdgcn_raw_buffer_load_b128(rres, ro[j], (nc * NCH + 32 * i + 16 * k) * 2, 0);
+            for (int i = 0; i < 4; i++)
+                resn[j][i] = __builtin_amdgcn_raw_buffer_load_b128(rres, piece(j, i, a3.res), nc * NCH * 2, 0);
     };
     if (has_res) load_res(0);
     // ---- phase 2: t2 = 3x3 over t1.  No barrier and no LDS traffic but the pixel fragments: the
@@ -335,17 +337,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int xr = wp0 + lrow;
         const uint32_t xs3 = lds0 + (uint32_t)(xr * 128 + ((lhalf ^ ((xr >> 1) & 7)) << 4));
         const int nch = cout3 / NCH;
+        // behind t2, where t1 was: both blocks of 32 positions at a time or, with 128 channels, one
+        constexpr int TJ = C == 64 ? 2 : 1;
+        static_assert((C / 64) * T2B + 4 * TJ * 4096 <= BIG, "room for the rows on their way out");
+        unsigned char* const turn = big + (C / 64) * T2B + wave * (TJ * 4096);
         const bool relu = a3.act == ACT_RELU;
         // weight fragments PW3 steps ahead, on into the next pass
         __syncthreads();                                         // t2 is complete
         for (int nc = 0; nc < nch; nc++) {
-            u32x4 res[2][2][2];
+            u32x4 res[2][4];
 #pragma unroll
             for (int j = 0; j < 2; j++)
 #pragma unroll
-                for (int i = 0; i < 2; i++)
-#pragma unroll
-                    for (int k = 0; k < 2; k++) res[j][i][k] = resn[j][i][k];
+                for (int i = 0; i < 4; i++) res[j][i] = resn[j][i];
             if (has_res && nc + 1 < nch) load_res(nc + 1);
             f32x16 acc[2][2];
 #pragma unroll
@@ -383,15 +387,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     for (int j = 0; j < 2; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wc[i], xf[b][j], acc[i][j], 0, 0, 0);
             });
 #pragma unroll
-            for (int j = 0; j < 2; j++)
+            for (int j0 = 0; j0 < 2; j0 += TJ) {
+                auto row = [&](int j, int i) { return (u32x4*)(turn + bn_row<128>(32 * (j - j0) + 8 * i + (lane >> 3), lane & 7)); };
+                if (ROWS && has_res) {
+#pragma unroll
+                    for (int j = j0; j < j0 + TJ; j++)
+#pragma unroll
+                        for (int i = 0; i < 4; i++) *row(j, i) = res[j][i];
+                    bn_turn();
+                }
+#pragma unroll
+                for (int j = j0; j < j0 + TJ; j++)
 #pragma unroll
                 for (int i = 0; i < 2; i++)
 #pragma unroll
                     for (int k = 0; k < 2; k++) {
+                        u32x4* const at = (u32x4*)(turn + bn_row<128>(32 * (j - j0) + lrow, 4 * i + 2 * k + lhalf));
                         float v[8];
                         bn_affine8(v, acc[i][j], k, b3l + nc * NCH + wc3 + 32 * i + 8 * lhalf, SBS);
                         if (has_res) {
-                            const uint32_t rr[4] = {res[j][i][k].x, res[j][i][k].y, res[j][i][k].z, res[j][i][k].w};
+                            u32x4 r = res[j][2 * i + k];
+                            if constexpr (ROWS) r = *at;
+                            const uint32_t rr[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
                             for (int q = 0; q < 4; q++) {
                                 v[2 * q] += bf16_to_f32((uint16_t)(rr[q] & 0xFFFF));
@@ -409,8 +426,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                                 o[q] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2, o[q]), z));
                             }
                         }
-                        __builtin_amdgcn_raw_buffer_store_b128(u32x4{o[0], o[1], o[2], o[3]}, yres, yo[j], (nc * NCH + 32 * i + 16 * k) * 2, 0);
+                        if constexpr (ROWS) *at = u32x4{o[0], o[1], o[2], o[3]};
+                        else __builtin_amdgcn_raw_buffer_store_b128(u32x4{o[0], o[1], o[2], o[3]}, yres, piece(j, 2 * i + k, a3.y), nc * NCH * 2, 0);
                     }
+                if constexpr (!ROWS) continue;
+                bn_turn();
+#pragma unroll
+                for (int j = j0; j < j0 + TJ; j++)
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    __builtin_amdgcn_raw_buffer_store_b128(*row(j, i), yres, piece(j, i, a3.y), nc * NCH * 2, 0);
+                bn_turn();
+            }
         }
     }
 }
@@ -464,22 +491,23 @@ bool conv_bneck_applicable(const ConvArgs& a1, const ConvArgs& a2, const ConvArg
 
 const char* conv_bneck_name(const ConvArgs& a1) { return a1.cout == 64 ? "bottleneck_bf16<c64>" : "bottleneck_bf16<c128>"; }
 
-template <int C, int R>
+template <int C, int R, bool ROWS>
 static hipError_t launch_bneck_variant(const ConvArgs* argv, int G, int nb, const BneckPlan& pl, hipStream_t s) {
     static bool raised = false;                                  // LDS above 64 KB has to be asked for once
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)&bottleneck_bf16<C, R>, hipFuncAttributeMaxDynamicSharedMemorySize, BNECK_LDS_LIMIT);
+        hipError_t e = hipFuncSetAttribute((const void*)&bottleneck_bf16<C, R, ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, BNECK_LDS_LIMIT);
         if (e != hipSuccess) return e;
         raised = true;
     }
-    ENS_LAUNCH((bottleneck_bf16<C, R>), dim3((unsigned)pl.tiles, 1, G), dim3(256), pl.bytes, s, argv, nb);
+    ENS_LAUNCH((bottleneck_bf16<C, R, ROWS>), dim3((unsigned)pl.tiles, 1, G), dim3(256), pl.bytes, s, argv, nb);
     return hipGetLastError();
 }
 
 hipError_t launch_conv_bneck(const ConvArgs& a1, const ConvArgs& a2, const ConvArgs& a3, const ConvArgs* argv, int G, int nb, hipStream_t s) {
     BneckPlan pl;
     if (!bneck_plan(a1, a2, a3, nb, &pl)) return hipErrorInvalidValue;
-    return pl.c == 64 ? launch_bneck_variant<64, 256>(argv, G, nb, pl, s) : launch_bneck_variant<128, 192>(argv, G, nb, pl, s);
+    if (rows_wanted()) return pl.c == 64 ? launch_bneck_variant<64, 256, true>(argv, G, nb, pl, s) : launch_bneck_variant<128, 192, true>(argv, G, nb, pl, s);
+    return pl.c == 64 ? launch_bneck_variant<64, 256, false>(argv, G, nb, pl, s) : launch_bneck_variant<128, 192, false>(argv, G, nb, pl, s);
 }
 
 }  // namespace ens

@@ -96,6 +96,22 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // an LDS operation, so the next LDS read would wait for the store to leave the wave.
 #define ENS_GLOBAL_W(T, p) ((__attribute__((address_space(1))) T*)(p))
 
+// The way out of the kernels that multiply in blocks of 32 x 32.  In the accumulators a lane holds 16 bytes of a pixel and the lanes beside it those of other pixels: stored (or a residual loaded) in that
+// order, an instruction is 64 accesses of the L1, one a clock, and 64 writes of 16 bytes to the L2.  With whole rows of a wavefront's channels, 64 or
+// 128 bytes in neighbouring lanes, it is 16 of each.  A wavefront turns one order into the other in LDS, in a piece of its own: 16 bytes
+// `piece` of pixel `px` lie at bn_row; lane l of instruction i has pixel i * 1024 / ROW + l / (ROW / 16), piece l % (ROW / 16).
+template <int ROW>
+__device__ __forceinline__ int bn_row(int px, int piece) {
+    return px * ROW + ((piece ^ ((ROW == 64 ? px >> 2 : px >> 1) & (ROW / 16 - 1))) << 4);   // either order of 16 lanes covers the banks once
+}
+// Taken among the launches of other lanes, whose accesses these are in the way of: 1 024 images of a ResNet-50 in batches of 128, streamed, 17.1 -> 16.7 ms,
+// three ResNet-18 15.8 -> 15.3, a grouped, a separable and an inverted-residual member 16.5 -> 16.0, twelve members 204 -> 201.  Alone a
+// workgroup has the L1 nearly to itself and the turn is a microsecond more at its end: 9.6 -> 10.6 us (56x56 bottleneck of 8 images
+// 18.3 -> 19.9, of 128 144.5 -> 141.8).
+inline bool rows_wanted() { return lanes_in_use() >= 3; }
+// between the one order and the other: the wavefront's own LDS operations have ended
+__device__ __forceinline__ void bn_turn() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
 // Pixels in a padded raster: image n, row hi, column wi sits at position (n * H1 + hi) * W1 + wi
 // with H1 >= H, W1 >= W; the positions with hi >= H or wi >= W hold no pixel.  Fills
 // tbl[q] for q in [0, rows) with the pixel index (n * H + hi) * W + wi of position first + q,

@@ -15,6 +15,7 @@ namespace ens {
 
 constexpr int PR_BP = 128, PR_BC = 128, PR_NXB = 4, PR_XS = PR_BP * 128;
 
+template <bool ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv1x1_pre_bf16(const ConvArgs* __restrict__ argv, const int nb_) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const ConvArgs a = argv[blockIdx.z];
@@ -191,14 +192,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     // ---- output: register v of a lane is channel wc + 16(v/8) + 8(lane/32) + v%8 of its pixel
     const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc((void*)a.y.p, 0, (int)((unsigned)P * (unsigned)a.y.stride * 2u), 0x00020000);
-    const int ch0 = wc + 8 * lhalf;
+    //      and leaves straight from the accumulators or, ROWS, in rows (bn_row), turned in the ring, which everybody is done with since the last barrier
+    unsigned char* const turn = lds + wave * (TP * 32 * 64);
+    auto store = [&](const u32x4& v, int px, int c) {
+        const int p = p0 + px;
+        __builtin_amdgcn_raw_buffer_store_b128(v, yres, p < P && c < a.cout ? (unsigned)(p * a.y.stride * 2) + (unsigned)((a.y.c0 + c) * 2) : OOBV, 0, 0);
+    };
 #pragma unroll
-    for (int j = 0; j < TP; j++) {
-        const int p = p0 + 32 * j + lrow;
+    for (int j = 0; j < TP; j++)
 #pragma unroll
         for (int k = 0; k < 2; k++) {
-            const unsigned yo = p < P && ch0 + 16 * k < a.cout ? (unsigned)(p * a.y.stride * 2) + (unsigned)((a.y.c0 + ch0) * 2) : OOBV;
-            __builtin_amdgcn_raw_buffer_store_b128(bn_pack(acc[j], k, a.act, sbl + ch0, PR_BC), yres, yo, 32 * k, 0);
+            const u32x4 o = bn_pack(acc[j], k, a.act, sbl + wc + 8 * lhalf, PR_BC);
+            if constexpr (ROWS) *(u32x4*)(turn + bn_row<64>(32 * j + lrow, 2 * k + lhalf)) = o;
+            else store(o, 32 * j + lrow, wc + 8 * lhalf + 16 * k);
+        }
+    if constexpr (ROWS) {
+        bn_turn();
+#pragma unroll
+        for (int i = 0; i < 2 * TP; i++) {
+            const int px = 16 * i + (lane >> 2);
+            store(*(const u32x4*)(turn + bn_row<64>(px, lane & 3)), px, wc + 8 * (lane & 3));
         }
     }
 }
@@ -217,17 +230,22 @@ bool conv_pre_applicable(const ConvArgs& a, int nb) {
 
 const char* conv_pre_name() { return "conv1x1_pre_bf16<128x128>"; }
 
-hipError_t launch_conv_pre(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s) {
-    if (!conv_pre_applicable(a, nb)) return hipErrorInvalidValue;
+template <bool ROWS>
+static hipError_t launch_pre_variant(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s) {
     static bool raised = false;                                  // LDS above 64 KB has to be asked for once
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)&conv1x1_pre_bf16, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        hipError_t e = hipFuncSetAttribute((const void*)&conv1x1_pre_bf16<ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         raised = true;
     }
     const long long P = (long long)nb * a.H * a.W;
-    ENS_LAUNCH(conv1x1_pre_bf16, dim3((unsigned)((P + PR_BP - 1) / PR_BP), 1, (unsigned)G), dim3(256), pre_lds_bytes(a), s, argv, nb);
+    ENS_LAUNCH(conv1x1_pre_bf16<ROWS>, dim3((unsigned)((P + PR_BP - 1) / PR_BP), 1, (unsigned)G), dim3(256), pre_lds_bytes(a), s, argv, nb);
     return hipGetLastError();
+}
+
+hipError_t launch_conv_pre(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s) {
+    if (!conv_pre_applicable(a, nb)) return hipErrorInvalidValue;
+    return rows_wanted() ? launch_pre_variant<true>(a, argv, G, nb, s) : launch_pre_variant<false>(a, argv, G, nb, s);
 }
 
 }  // namespace ens

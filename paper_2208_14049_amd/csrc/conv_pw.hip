@@ -13,7 +13,7 @@
 // the pixel fragments is read from LDS, and the one barrier per chunk covers 16 or 8 matrix-core
 // instructions per wavefront where the generic kernel's covers 4 to 8 and also waits for its
 // weights.  The output leaves from the accumulators as 16-byte runs of 8 channels after the
-// per-channel scale and bias (which wait in LDS); the residual is asked for before the loop.
+// per-channel scale and bias (which wait in LDS), turned into rows on the way where that pays; the residual is asked for before the loop.
 //
 // Wavefront roles: WPX along the pixels, 4 / WPX along blocks of 32 channels.  WPX = 1: a wavefront
 // has all 128 pixels of 32 channels (a weight fragment serves four matrix-core instructions and is
@@ -30,7 +30,7 @@ constexpr int PW_BP = 128, PW_NXB = 3, PW_XS = PW_BP * 128;
 // (the rescaling of a squeeze-excite block folded into the projection that follows it): product in fp32,
 // rounded to bf16 as the separate rescaling kernel would have stored it.  The gates of the images a tile
 // touches wait in LDS behind the ring, gimg images of nk * 64 floats.
-template <int WPX, bool GATE>
+template <int WPX, bool GATE, bool ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv1x1_direct_bf16(const ConvArgs* __restrict__ argv,
                                                                                                      const int nb_, const int gimg) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -71,27 +71,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const bool has_res = a.res.p != nullptr;
     const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(has_res ? a.res.p : a.y.p), 0, (int)(npix * (unsigned)(has_res ? a.res.stride : a.y.stride) * 2u), 0x00020000);
-    // this lane's two runs of 8 channels, wc + 8 (lane / 32) + 16 k: each exists as a whole or not at all
-    const int ch0 = wc + 8 * lhalf;
-    const bool run_ok[2] = {ch0 < a.cout, ch0 + 16 < a.cout};
-    unsigned yo[TP][2], ro[TP][2];
+    // ROWS: residual and output come and go in rows (bn_row), piece (j, k) of them being pixel rp + 32 j + 16 k, channels rc ... rc + 7 (which exist
+    // as a whole or not at all).  Otherwise straight from the accumulators, pixel rp + 32 j, channels rc + 16 k.
+    const int rp = p0 + wp0 + (ROWS ? lane >> 2 : lrow), rc = wc + 8 * (ROWS ? lane & 3 : lhalf);
+    auto piece = [&](int j, int k, const View& v) {
+        const int p = rp + 32 * j + (ROWS ? 16 * k : 0), c = rc + (ROWS ? 0 : 16 * k);
+        return p < P && c < a.cout ? (unsigned)(p * v.stride * 2) + (unsigned)((v.c0 + c) * 2) : OOBV;
+    };
+    unsigned yo[TP][2];
 #pragma unroll
-    for (int j = 0; j < TP; j++) {
-        const int p = p0 + wp0 + 32 * j + lrow;
+    for (int j = 0; j < TP; j++)
 #pragma unroll
-        for (int k = 0; k < 2; k++) {
-            const bool ok = p < P && run_ok[k];
-            yo[j][k] = ok ? (unsigned)(p * a.y.stride * 2) + (unsigned)((a.y.c0 + ch0) * 2) : OOBV;
-            ro[j][k] = ok ? (unsigned)(p * a.res.stride * 2) + (unsigned)((a.res.c0 + ch0) * 2) : OOBV;
-        }
-    }
+        for (int k = 0; k < 2; k++) yo[j][k] = piece(j, k, a.y);
     u32x4 res[TP][2];
     if (has_res) {
 #pragma unroll
-        for (int j = 0; j < TP; j++) {
-            res[j][0] = __builtin_amdgcn_raw_buffer_load_b128(rres, ro[j][0], 0, 0);
-            res[j][1] = __builtin_amdgcn_raw_buffer_load_b128(rres, ro[j][1], 32, 0);
-        }
+        for (int j = 0; j < TP; j++)
+#pragma unroll
+            for (int k = 0; k < 2; k++) res[j][k] = __builtin_amdgcn_raw_buffer_load_b128(rres, piece(j, k, a.res), 0, 0);
     }
     f32x16 acc[TP];
 #pragma unroll
@@ -242,16 +239,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (kc < nk) chunk(std::integral_constant<int, 0>{}, w0, w2, kc);
     if (kc + 1 < nk) chunk(std::integral_constant<int, 1>{}, w1, w0, kc + 1);
 
-    // ---- output: register v of a lane is channel wc + 16(v/8) + 8(lane/32) + v%8 of its pixel.  Stores
-    //      to rows past the last pixel carry the out-of-range offset and are dropped by the hardware.
+    // ---- output: register v of a lane is channel wc + 16(v/8) + 8(lane/32) + v%8 of its pixel.  The rows are turned in the two buffers of the
+    //      ring that the last chunk is not in: everybody is done with them since its barrier.  Stores to rows past the last pixel
+    //      carry the out-of-range offset and are dropped by the hardware.
+    unsigned char* const turn = lds + ((wave < 2 ? nk : nk + 1) % 3) * XS + (wave & 1) * 8192;
+    auto row = [&](int j, int k) { return (u32x4*)(turn + bn_row<64>(32 * j + 16 * k + (lane >> 2), lane & 3)); };
+    if (ROWS && has_res) {
+#pragma unroll
+        for (int j = 0; j < TP; j++)
+#pragma unroll
+            for (int k = 0; k < 2; k++) *row(j, k) = res[j][k];
+        bn_turn();
+    }
+    const float* const sb = sbl + (wc + 8 * lhalf - c0);
 #pragma unroll
     for (int j = 0; j < TP; j++)
 #pragma unroll
         for (int k = 0; k < 2; k++) {
-            const float* sb = sbl + (ch0 - c0);
+            u32x4* const at = (u32x4*)(turn + bn_row<64>(32 * j + lrow, 2 * k + lhalf));
+            if (ROWS && has_res) res[j][k] = *at;
             const u32x4 o = has_res ? bn_pack_res<true>(acc[j], k, res[j][k], a.act, sb, BC) : bn_pack_res<false>(acc[j], k, res[j][k], a.act, sb, BC);
-            __builtin_amdgcn_raw_buffer_store_b128(o, yres, yo[j][k], 32 * k, 0);
+            if constexpr (ROWS) *at = o;
+            else __builtin_amdgcn_raw_buffer_store_b128(o, yres, yo[j][k], 0, 0);
         }
+    if constexpr (ROWS) {
+        bn_turn();
+#pragma unroll
+        for (int j = 0; j < TP; j++)
+#pragma unroll
+            for (int k = 0; k < 2; k++) __builtin_amdgcn_raw_buffer_store_b128(*row(j, k), yres, yo[j][k], 0, 0);
+    }
 }
 
 // ---- host side -----------------------------------------------------------------------------
@@ -283,7 +300,7 @@ bool conv_pw_applicable(const ConvArgs& a, int nb, int G) {
 
 
 
-template <int WPX, bool GATE>
+template <int WPX, bool GATE, bool ROWS = false>
 static hipError_t launch_pw_variant(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s) {
     constexpr int BC = 32 * (4 / WPX);
     const long long P = (long long)nb * a.Ho * a.Wo;
@@ -292,12 +309,12 @@ static hipError_t launch_pw_variant(const ConvArgs& a, const ConvArgs* argv, int
     if (bytes > 64 * 1024) {                                     // LDS above 64 KB has to be asked for once
         static bool raised = false;
         if (!raised) {
-            hipError_t e = hipFuncSetAttribute((const void*)&conv1x1_direct_bf16<WPX, GATE>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            hipError_t e = hipFuncSetAttribute((const void*)&conv1x1_direct_bf16<WPX, GATE, ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
             if (e != hipSuccess) return e;
             raised = true;
         }
     }
-    ENS_LAUNCH((conv1x1_direct_bf16<WPX, GATE>), grid, dim3(256), bytes, s, argv, nb, GATE ? pw_gate_images(a) : 0);
+    ENS_LAUNCH((conv1x1_direct_bf16<WPX, GATE, ROWS>), grid, dim3(256), bytes, s, argv, nb, GATE ? pw_gate_images(a) : 0);
     return hipGetLastError();
 }
 
@@ -323,7 +340,9 @@ hipError_t launch_conv_pw(const ConvArgs& a, const ConvArgs* argv, int G, int nb
         return pw_wpx(a, nb, G) == 2 ? launch_pw_variant<2, true>(a, argv, G, nb, s) : launch_pw_variant<1, true>(a, argv, G, nb, s);
     }
     if (conv_wide_wanted(a, nb, G)) return launch_conv_wide(a, argv, G, nb, s);
-    return pw_wpx(a, nb, G) == 2 ? launch_pw_variant<2, false>(a, argv, G, nb, s) : launch_pw_variant<1, false>(a, argv, G, nb, s);
+    if (pw_wpx(a, nb, G) == 2) return launch_pw_variant<2, false>(a, argv, G, nb, s);
+    // (the smaller tile and the gated layers have little output to turn)
+    return rows_wanted() ? launch_pw_variant<1, false, true>(a, argv, G, nb, s) : launch_pw_variant<1, false>(a, argv, G, nb, s);
 }
 
 }  // namespace ens

@@ -15,7 +15,7 @@ namespace ens {
 constexpr int WD_BP = 128, WD_BC = 256, WD_NXB = 3, WD_XS = WD_BP * 128;
 constexpr size_t WD_LDS = (size_t)WD_NXB * WD_XS + 2 * WD_BC * sizeof(float);
 
-template <bool RES>
+template <bool RES, bool ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv1x1_wide_bf16(const ConvArgs* __restrict__ argv, const int nb_) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const ConvArgs a = argv[blockIdx.z];
@@ -83,17 +83,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const uint32_t xs0 = lds0 + (uint32_t)(lrow * 128 + ((lhalf ^ ((lrow >> 1) & 7)) << 4));
     const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(RES ? a.res.p : a.y.p), 0, (int)(npix * (unsigned)(RES ? a.res.stride : a.y.stride) * 2u), 0x00020000);
-    const int ch0 = wc + 8 * lhalf;
-    const int left = a.cout - ch0;               // a run of 8 channels exists as a whole or not at all
-    auto load_res = [&](bf16x8 (&res)[CB][4], int q, int pl) {
-#pragma unroll
-        for (int j = 0; j < TP; j++) {
-            const unsigned o = pl + 32 * j < P ? (unsigned)((pl + 32 * j) * a.res.stride * 2) + (unsigned)((a.res.c0 + ch0) * 2) : OOBV;
-#pragma unroll
-            for (int k = 0; k < 2; k++) res[k][j] = bn_wload(rres, left > 32 * q + 16 * k ? o : OOBV, 64 * q + 32 * k);
-        }
+    // Residual and output come and go half the tile's pixels at a time, in 8 pieces of 8 channels, which exist as a whole or not at all.  ROWS: in rows
+    // (bn_row), piece m being pixel pl + 8 m, channels rc ...; otherwise straight from the accumulators, pixel pl + 32 (m / 4), channels rc + 16 (m % 4).
+    const int rc = wc + 8 * (ROWS ? lane & 7 : lhalf);
+    auto piece = [&](int h, int m, int pl, const View& v) {
+        const int p = pl + 64 * h + (ROWS ? 8 * m : m / 4 * 32), c = rc + (ROWS ? 0 : m % 4 * 16);
+        return p < P && c < a.cout ? (unsigned)(p * v.stride * 2) + (unsigned)((v.c0 + c) * 2) : OOBV;
     };
-    int pl = p0 + lrow;
+    auto load_res = [&](bf16x8 (&res)[CB][4], int h, int pl) {
+#pragma unroll
+        for (int m = 0; m < 8; m++) res[m / 4][m % 4] = bn_wload(rres, piece(h, m, pl, a.res), 0);
+    };
+    int pl = p0 + (ROWS ? lane >> 3 : lrow);
     int buf = 0;
     // Order of issue: x(0) w(0) x(1), then w(kc + 1) x(kc + 2) in chunk kc; when chunk kc begins only x(kc + 1) may be outstanding.
     auto chunk = [&](bf16x8 (&wc_)[CB][4], bf16x8 (&wl)[CB][4], const int kc) {
@@ -148,18 +149,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
         load_res(r1, 1, pl);
     }
+    // turned in the two buffers of the ring that the last chunk is not in: everybody is done with them since its barrier
+    unsigned char* const turn = lds + ((wave < 2 ? nk : nk + 1) % 3) * XS + (wave & 1) * 8192;
 #pragma unroll
-    for (int q = 0; q < CB; q++)
+    for (int h = 0; h < 2; h++) {
+        auto row = [&](int m) { return (u32x4*)(turn + bn_row<128>(8 * m + (lane >> 3), lane & 7)); };
+        auto res = [&](int m) { return __builtin_bit_cast(u32x4, h ? r1[m / 4][m % 4] : w0[m / 4][m % 4]); };
+        if constexpr (RES && ROWS) {
 #pragma unroll
-        for (int j = 0; j < TP; j++) {
-            const unsigned o = pl + 32 * j < P ? (unsigned)((pl + 32 * j) * a.y.stride * 2) + (unsigned)((a.y.c0 + ch0) * 2) : OOBV;
-#pragma unroll
-            for (int k = 0; k < 2; k++) {
-                const float* sb = sbl + (ch0 + 32 * q - c0);
-                const u32x4 v = bn_pack_res<RES>(acc[q][j], k, __builtin_bit_cast(u32x4, q ? r1[k][j] : w0[k][j]), a.act, sb, BC);
-                __builtin_amdgcn_raw_buffer_store_b128(v, yres, left > 32 * q + 16 * k ? o : OOBV, 64 * q + 32 * k, 0);
-            }
+            for (int m = 0; m < 8; m++) *row(m) = res(m);
+            bn_turn();
         }
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int q = 0; q < CB; q++)
+#pragma unroll
+                for (int k = 0; k < 2; k++) {
+                    u32x4* const at = (u32x4*)(turn + bn_row<128>(32 * j + lrow, 4 * q + 2 * k + lhalf));
+                    u32x4 r = {0u, 0u, 0u, 0u};
+                    if constexpr (RES && ROWS) r = *at;
+                    else if constexpr (RES) r = res(4 * j + 2 * q + k);
+                    r = bn_pack_res<RES>(acc[q][2 * h + j], k, r, a.act, sbl + (wc + 8 * lhalf + 32 * q - c0), BC);
+                    if constexpr (ROWS) *at = r;
+                    else __builtin_amdgcn_raw_buffer_store_b128(r, yres, piece(h, 4 * j + 2 * q + k, pl, a.y), 0, 0);
+                }
+        if constexpr (ROWS) {
+            bn_turn();
+#pragma unroll
+            for (int m = 0; m < 8; m++) __builtin_amdgcn_raw_buffer_store_b128(*row(m), yres, piece(h, m, pl, a.y), 0, 0);
+            bn_turn();
+        }
+    }
 }
 // ---- host side -----------------------------------------------------------------------------
 // The shape has passed conv_pw_applicable.  Wide tiles are taken
@@ -180,8 +201,13 @@ bool conv_wide_wanted(const ConvArgs& a, int nb, int G) {
 hipError_t launch_conv_wide(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s) {
     const long long P = (long long)nb * a.Ho * a.Wo;
     const dim3 grid((unsigned)(((P + WD_BP - 1) / WD_BP) * ((a.cout + WD_BC - 1) / WD_BC)), 1, G);
-    if (a.res.p) ENS_LAUNCH(conv1x1_wide_bf16<true>, grid, dim3(256), WD_LDS, s, argv, nb);
-    else ENS_LAUNCH(conv1x1_wide_bf16<false>, grid, dim3(256), WD_LDS, s, argv, nb);
+    if (rows_wanted()) {
+        if (a.res.p) ENS_LAUNCH((conv1x1_wide_bf16<true, true>), grid, dim3(256), WD_LDS, s, argv, nb);
+        else ENS_LAUNCH((conv1x1_wide_bf16<false, true>), grid, dim3(256), WD_LDS, s, argv, nb);
+    } else {
+        if (a.res.p) ENS_LAUNCH((conv1x1_wide_bf16<true, false>), grid, dim3(256), WD_LDS, s, argv, nb);
+        else ENS_LAUNCH((conv1x1_wide_bf16<false, false>), grid, dim3(256), WD_LDS, s, argv, nb);
+    }
     return hipGetLastError();
 }
 

@@ -44,7 +44,7 @@ __device__ __forceinline__ void wreg_for_each(F&& f, std::integer_sequence<int, 
     (f(std::integral_constant<int, T>{}), ...);
 }
 
-template <int BP, int WPX, int WCG>
+template <int BP, int WPX, int WCG, bool ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const int hrows) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -211,7 +211,7 @@ void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const i
     const bool has_res = a.res.p != nullptr;
     const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(has_res ? a.res.p : a.y.p), 0, (int)(npix * (unsigned)(has_res ? a.res.stride : a.y.stride) * 2u), 0x00020000);
-    const unsigned ylane = (unsigned)((a.y.c0 + c0 + cl) * 2), rlane = (unsigned)((a.res.c0 + c0 + cl) * 2);
+    const unsigned ylane = (unsigned)((a.y.c0 + c0 + wc0 + 8 * (ROWS ? lane & 3 : lhalf)) * 2), rlane = (unsigned)((a.res.c0 + c0 + wc0 + 8 * (ROWS ? lane & 3 : lhalf)) * 2);
 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the first window has landed: this wave's part,
     __builtin_amdgcn_s_barrier();                                // and with the barrier everybody's
@@ -225,21 +225,21 @@ void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const i
         if (ptile + step_tiles < walk.end) issue_window(buf ^ 1, slot1);
         // slot2 held the previous tile's table, which every wave has read before that tile's barrier
         make_table(slot2);
-        const int* own = tblp + slot * hrows + W1 + 1 + wp0 + lrow;   // the centre tap's rows: this tile's outputs
-        unsigned yo[TP], ro[TP];
+        // The centre tap's rows: this tile's outputs.  ROWS: residual and output come and go in rows (bn_row), piece i being position 16 i + lane / 4,
+        // channels 8 (lane % 4) ...; otherwise straight from the accumulators, position 32 (i / 2) + lane % 32, channels 16 (i % 2) + 8 (lane / 32) ...
+        const int* own = tblp + slot * hrows + W1 + 1 + wp0 + (ROWS ? lane >> 2 : lrow);
+        constexpr int NO = ROWS ? 2 * TP : TP;                   // positions; their pieces without ROWS: 32 bytes from one to the next
+        unsigned yo[NO], ro[NO];
 #pragma unroll
-        for (int j = 0; j < TP; j++) {
-            const int pout = own[j * 32];
-            yo[j] = pout >= 0 && wave_ok ? (unsigned)(pout * a.y.stride * 2) + ylane : OOBV;
-            ro[j] = pout >= 0 && wave_ok ? (unsigned)(pout * a.res.stride * 2) + rlane : OOBV;
+        for (int i = 0; i < NO; i++) {
+            const int pout = own[i * (ROWS ? 16 : 32)];
+            yo[i] = pout >= 0 && wave_ok ? (unsigned)(pout * a.y.stride * 2) + ylane : OOBV;
+            ro[i] = pout >= 0 && wave_ok ? (unsigned)(pout * a.res.stride * 2) + rlane : OOBV;
         }
-        u32x4 res[TP][2];
+        u32x4 res[2 * TP];
         if (has_res) {
 #pragma unroll
-            for (int j = 0; j < TP; j++) {
-                res[j][0] = __builtin_amdgcn_raw_buffer_load_b128(rres, ro[j], 0, 0);
-                res[j][1] = __builtin_amdgcn_raw_buffer_load_b128(rres, ro[j], 32, 0);
-            }
+            for (int i = 0; i < 2 * TP; i++) res[i] = __builtin_amdgcn_raw_buffer_load_b128(rres, ro[ROWS ? i : i / 2], ROWS ? 0 : i % 2 * 32, 0);
         }
 
         f32x16 acc[TP];
@@ -281,8 +281,16 @@ void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const i
         // ---- output: register v of a lane is channel cl + 16(v/8) + v%8 of its position, scaled and
         //      biased per channel.  Stores to positions without a pixel carry the out-of-range offset
         //      and are dropped by the hardware.
+        //      ROWS: turned in this window, in the pieces that this wavefront's own loads fill: nobody else writes there.
+        unsigned char* const turn = lds + buf * hbytes + wave * 1024;
+        auto at_row = [&](int pos, int piece) { return (u32x4*)(turn + (pos >> 4) * 4096 + bn_row<64>(pos & 15, piece)); };
         auto emit = [&](auto res_c, auto relu_c) {
             constexpr bool RES = decltype(res_c)::value, RELU = decltype(relu_c)::value;
+            if constexpr (RES && ROWS) {
+#pragma unroll
+                for (int i = 0; i < 2 * TP; i++) *at_row(16 * i + (lane >> 2), lane & 3) = res[i];
+                bn_turn();
+            }
 #pragma unroll
             for (int k = 0; k < 2; k++) {
                 const f32x4 sq[2] = {*(const f32x4*)&scalel[cl + 16 * k], *(const f32x4*)&scalel[cl + 16 * k + 4]};
@@ -293,7 +301,9 @@ void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const i
 #pragma unroll
                     for (int e = 0; e < 8; e++) v[e] = fmaf(acc[j][8 * k + e], sq[e >> 2][e & 3], bq[e >> 2][e & 3]);
                     if constexpr (RES) {
-                        const uint32_t rr[4] = {res[j][k].x, res[j][k].y, res[j][k].z, res[j][k].w};
+                        u32x4 r = res[2 * j + k];
+                        if constexpr (ROWS) r = *at_row(32 * j + lrow, 2 * k + lhalf);
+                        const uint32_t rr[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
                         for (int q = 0; q < 4; q++) {
                             v[2 * q] += bf16_to_f32((uint16_t)(rr[q] & 0xFFFF));
@@ -312,8 +322,15 @@ void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const i
                             o[q] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2, o[q]), z));
                         }
                     }
-                    __builtin_amdgcn_raw_buffer_store_b128(u32x4{o[0], o[1], o[2], o[3]}, yres, yo[j], 32 * k, 0);
+                    if constexpr (ROWS) *at_row(32 * j + lrow, 2 * k + lhalf) = u32x4{o[0], o[1], o[2], o[3]};
+                    else __builtin_amdgcn_raw_buffer_store_b128(u32x4{o[0], o[1], o[2], o[3]}, yres, yo[ROWS ? 2 * j + k : j], 32 * k, 0);
                 }
+            }
+            if constexpr (ROWS) {
+                bn_turn();
+#pragma unroll
+                for (int i = 0; i < 2 * TP; i++) __builtin_amdgcn_raw_buffer_store_b128(*at_row(16 * i + (lane >> 2), lane & 3), yres, yo[i], 0, 0);
+                bn_turn();
             }
         };
         if (a.act == ACT_RELU) {
@@ -366,22 +383,26 @@ bool conv_wreg_applicable(const ConvArgs& a, int nb, int G) {
 
 const char* conv_wreg_name(const ConvArgs&) { return "conv3x3_wreg_bf16<128,c64>"; }
 
+template <bool ROWS>
+static hipError_t launch_wreg_variant(const ConvArgs& a, const ConvArgs* argv, int G, int nb, const WregPlan& pl, hipStream_t s) {
+    static bool raised = false;                                  // LDS above 64 KB has to be asked for once
+    if (!raised) {
+        hipError_t e = hipFuncSetAttribute((const void*)&conv3x3_wreg_bf16<128, 2, 2, ROWS>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, WREG_LDS_LIMIT);
+        if (e != hipSuccess) return e;
+        raised = true;
+    }
+    const dim3 grid((unsigned)pl.wgs, (unsigned)((a.cout + 63) / 64), G);
+    ENS_LAUNCH((conv3x3_wreg_bf16<128, 2, 2, ROWS>), grid, dim3(256), pl.bytes, s, argv, nb, pl.hrows);
+    return hipGetLastError();
+}
+
 hipError_t launch_conv_wreg(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s) {
     WregPlan pl;
     if (!wreg_plan(a, nb, G, &pl)) return hipErrorInvalidValue;
     if (a.x.stride % 8 || a.x.c0 % 8 || a.y.stride % 8 || a.y.c0 % 8) return hipErrorInvalidValue;
     if (a.res.p && (a.res.stride % 8 || a.res.c0 % 8)) return hipErrorInvalidValue;
-    static bool raised = false;                                  // LDS above 64 KB has to be asked for once
-    if (!raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)&conv3x3_wreg_bf16<128, 2, 2>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, WREG_LDS_LIMIT);
-        if (e != hipSuccess) return e;
-        raised = true;
-    }
-    int wgs = pl.wgs;
-    const dim3 grid((unsigned)wgs, (unsigned)((a.cout + 63) / 64), G);
-    ENS_LAUNCH((conv3x3_wreg_bf16<128, 2, 2>), grid, dim3(256), pl.bytes, s, argv, nb, pl.hrows);
-    return hipGetLastError();
+    return rows_wanted() ? launch_wreg_variant<true>(a, argv, G, nb, pl, s) : launch_wreg_variant<false>(a, argv, G, nb, pl, s);
 }
 
 }  // namespace ens
