@@ -187,7 +187,8 @@ __device__ __forceinline__ void chain_conv(const Step s, const Step s0_, char* c
         const int off = ((n * H + hi) * W + wi) * xs * 2 + (int)x_at;
         unsigned mask = ~0u;
         if (ST(padded)) {
-            const unsigned cols = ((1u << min(kw_n, W - wi)) - 1u) & (~0u << max(0, -wi));
+            // (a filter of up to 32 taps in a row, or a window up to 255 columns outside: counts of 32 are no shifts of 32 bits)
+            const unsigned cols = (unsigned)((1ull << min(kw_n, W - wi)) - (1ull << min(kw_n, max(0, -wi))));
             const int kh_n = window & 255;
             mask = 0;
             for (int kh = 0; kh < kh_n; kh++) mask |= (unsigned)(hi + kh) < (unsigned)H ? cols << (kh * kw_n) : 0u;

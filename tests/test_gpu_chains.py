@@ -103,3 +103,29 @@ def test_layers_at_the_edges(ens, members, sizes):
     imgs = W.round_bf16(W.make_images(synth.BASE_SEED + 1043, sizes[-1], 45, 37, varied=True))
     # some 20 bf16 roundings of 2^-9 from the image to the logits, as for the members above
     ask_all_ways(ens, nets, blobs, imgs, (45, 37), 16, sizes, 0.08)
+
+
+def long_filters(i):
+    """Filters of 32 taps in a row or in two, in a column, of 31, windows that begin 33 columns outside the image, and 49 taps that are never outside."""
+    n = N.Net("long%d" % i, 45, 37, 24, dtype="bf16")
+    t = n.conv(0, 16 + 8 * i, 3)
+    t = n.conv(t, 32, (1, 32), pad=(0, 15))
+    t = n.conv(t, 32, (1, 31))
+    t = n.conv(t, 32, (2, 16), pad=(1, 8), act="silu")
+    t = n.conv(t, 24, (32, 1), pad=(16, 0), stride=2)
+    h, w, _ = n.tensors[t]
+    t = n.conv(t, 40, (1, 3), pad=(0, 33))
+    n.tensors[t] = (h, w + 31, 40)                                # the last window ends in the image's last columns
+    t = n.conv(n.avgpool(t, 2, 2), 32, 7, pad="valid")
+    for _ in range(9):
+        t = n.conv(t, 32, 1)
+    n.fc(n.gap(t), 24)
+    return n
+
+
+def test_long_filters(ens):
+    nets = [long_filters(i) for i in range(8)]
+    blobs = [W.quantise_weights_bf16(net, W.make_blob(net, synth.BASE_SEED + 45, i)) for i, net in enumerate(nets)]
+    imgs = W.round_bf16(W.make_images(synth.BASE_SEED + 1045, 3, 45, 37, varied=True))
+    # some 17 bf16 roundings of 2^-9 from the image to the logits, as for the members above; a dropped tap is an error of the size of the values
+    ask_all_ways(ens, nets, blobs, imgs, (45, 37), 16, (1, 3), 0.08)
