@@ -41,6 +41,13 @@ static_assert(sizeof(ChainStep) == 256, "a dword for each lane");
 constexpr int CH_POOL = 2;                   // outputs of a pooling layer that a lane works on at a time
 constexpr int CHAIN_PHASE_STEPS = 7;         // of a phase at most
 
+// Where in a 1 KB fragment of block i of channel tile cs (`side` blocks of 32 output channels each) a lane's weights lie.  The last tile has a block
+// less than others when the number of blocks is odd: what it asks for there lies past the end of every buffer and comes as zeros.  (The
+// range check is about this offset alone, not about the place of the block, which is a scalar.)
+__host__ __device__ inline unsigned chain_weight_lane(int cs, int side, int i, int blocks, int lane) {
+    return cs * side + i < blocks ? (unsigned)lane * 16u : 0x80000000u;
+}
+
 // Words that the groups of one launch meet at; zeros before a launch, and again after it.
 struct ChainSync {
     // (what workgroups of one XCD count at their L2 has a line of its own, is never set back, and is used by nobody else)

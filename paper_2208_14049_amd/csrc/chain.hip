@@ -151,11 +151,14 @@ __device__ __forceinline__ void chain_conv(const Step s, const Step s0_, char* c
 
     const __amdgpu_buffer_rsrc_t wres = ch_rsrc(ST_P(w), (unsigned)ST(wsize));
     bf16x8 wf[NST][4][TC];
+    unsigned wv[TC];
+#pragma unroll
+    for (int i = 0; i < TC; i++) wv[i] = i == 0 ? lane * 16u : chain_weight_lane(cs, TC, i, ST(ctiles[0]), lane);
     auto ask_w = [&](auto buf, int m) {
 #pragma unroll
         for (int st = 0; st < 4; st++)
 #pragma unroll
-            for (int i = 0; i < TC; i++) wf[decltype(buf)::value][st][i] = bn_wload(wres, lane * 16, (((cs * TC + i) * chunks + m) * 4 + st) * 1024);
+            for (int i = 0; i < TC; i++) wf[decltype(buf)::value][st][i] = bn_wload(wres, wv[i], (((cs * TC + i) * chunks + m) * 4 + st) * 1024);
     };
     if (m0 < m1) ask_w(std::integral_constant<int, 0>{}, m0);
     if (m0 + 1 < m1) ask_w(std::integral_constant<int, 1>{}, m0 + 1);

@@ -1,0 +1,34 @@
+// What the host works out for the chains of a loaded ensemble (csrc/chain.h), for tests on a machine without a GPU.
+#include "chain.h"
+
+using namespace ens;
+
+extern "C" {
+
+int chain_steps(ens_handle* h, int member) { return h->chains.empty() ? 0 : (int)h->chains[member].steps.size(); }
+
+// The weights that the convolutions of a member ask for, with every tile that is chosen for some number of images: the number of
+// fragments of which a lane lies outside the layer's weights, and of those that are asked for and do not exist (`none`).
+int chain_weights_outside(ens_handle* h, int member, int* none) {
+    int outside = 0;
+    *none = 0;
+    for (const ChainStep& s : h->chains[member].steps) {
+        if (s.kind > CH_CONV_PRE) continue;
+        const int chunks = (s.K + 63) / 64;
+        bool sides[3] = {false, false, false};
+        for (int z = 0; z < CHAIN_SIZES; z++) sides[s.choice[z] & 255] = true;
+        for (int side = 1; side <= 2; side++)
+            for (int cs = 0; sides[side] && cs < s.ctiles[side - 1]; cs++)
+                for (int i = 0; i < side; i++)
+                    for (int m = 0; m < chunks; m++)
+                        for (int st = 0; st < 4; st++) {
+                            const unsigned at = chain_weight_lane(cs, side, i, s.ctiles[0], 63);
+                            const size_t block = (size_t)(((cs * side + i) * chunks + m) * 4 + st) * 1024;
+                            if (at >= 0x80000000u) (*none)++;    // zeros
+                            else outside += block + at + 16 > (size_t)s.wsize;
+                        }
+    }
+    return outside;
+}
+
+}

@@ -146,3 +146,37 @@ def graphs_go():
 def test_recorded_requests_go_when_a_request_finds_no_memory(fake_hip):
     """The memory of recorded requests is given back to a request whose buffers do not fit beside them."""
     beside_fake_hip(fake_hip, "graphs_go()")
+
+
+@pytest.fixture(scope="module")
+def chain_view(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("view") / "libchain_view.so")
+    subprocess.check_call(["hipcc", "-O1", "-std=c++17", "-fPIC", "-shared", "-x", "hip", "--offload-arch=gfx950", "-I" + os.path.join(ROOT, "paper_2208_14049_amd", "csrc"),
+                           "-o", lib, os.path.join(ROOT, "tests", "chain_view.cpp")])
+    return lib
+
+
+def odd_blocks(view):
+    import paper_2208_14049_amd as ens
+    from synth import nets as N, weights as W
+    V, none = ctypes.CDLL(view), 0
+    for i, (h, c) in enumerate(((112, 96), (96, 48), (75, 32), (40, 328))):
+        n = N.Net("odd%d" % i, h, h, 16, dtype="bf16")
+        t = n.conv(n.conv(0, c, 3), 16, 1)
+        t = n.conv(n.conv(t, c, 3), 2 * c, 1, pre=True)
+        for _ in range(13):
+            t = n.conv(t, 32, 3, stride=1 + (n.tensors[t][0] > 16))
+        n.fc(n.gap(t), 16)
+        E = ens.Ensemble([n], [W.make_blob(n, 251, i)])
+        E.ens_set_alloc([[32]])
+        assert V.chain_steps(E._h, 0) > 16
+        beyond = ctypes.c_int()
+        assert V.chain_weights_outside(E._h, 0, ctypes.byref(beyond)) == 0, (h, c)
+        none += beyond.value
+        E.close()
+    assert none > 0                                              # wide tiles of which half has no channels were among them
+
+
+def test_chains_read_no_weights_behind_a_layers_own(fake_hip, chain_view):
+    """Output channels in an odd number of blocks of 32: the second half of the last wide tile has no weights to ask for."""
+    beside_fake_hip(fake_hip, "odd_blocks(%r)" % chain_view)
