@@ -219,7 +219,8 @@ __device__ __forceinline__ void chain_conv(const Step s, const Step s0_, char* c
 #pragma unroll
             for (int i = 0; i < 4 * TP; i++) __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (lds_ptr_t)(d + i * 1024), LDS_LOAD_BYTES, xo[i] + to, 0, 0, SC1);
         } else {
-            const unsigned to = (unsigned)(at + c * 2), bit = kok ? 1u << tap : 0u;
+            // (more than 32 taps are taken by layers only of which none is outside: all bits are set)
+            const unsigned to = (unsigned)(at + c * 2), bit = kok ? 1u << (tap & 31) : 0u;
 #pragma unroll
             for (int i = 0; i < 4 * TP; i++)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (lds_ptr_t)(d + i * 1024), LDS_LOAD_BYTES, taps[i] & bit ? xo[i] + to : OOBV, 0, 0, SC1);
