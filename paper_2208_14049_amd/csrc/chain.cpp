@@ -355,8 +355,10 @@ bool build_chain(const Member& m, const std::vector<Launch>& launches, char* bas
         out->cap = (int)std::min({(double)out->cap, 2147483000.0 / std::max(1.0, bytes), 8388607.0 / std::max(1.0, items)});
         if (s.kind == CH_FC && (double)((s.cout + 31) / 32) * ((s.cin + 63) / 64) * 4096 >= 0x7FFFFF00LL) return false;
     }
+    // what a launch is told of a program in 32 and in 16 bits
+    if (out->image_bytes > UINT32_MAX) return false;
+    out->cap = std::min(out->cap, (int)INT16_MAX);
     if (out->cap < 1) return false;
-    if (out->image_bytes * (size_t)out->cap >= (size_t)1 << 40) return false;
     out->steps.clear();
     out->packs.clear();
     out->pack_bytes = 0;

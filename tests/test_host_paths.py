@@ -180,3 +180,36 @@ def odd_blocks(view):
 def test_chains_read_no_weights_behind_a_layers_own(fake_hip, chain_view):
     """Output channels in an odd number of blocks of 32: the second half of the last wide tile has no weights to ask for."""
     beside_fake_hip(fake_hip, "odd_blocks(%r)" % chain_view)
+
+
+def wide_programs(view):
+    import paper_2208_14049_amd as ens
+    from synth import nets as N, weights as W
+    V = ctypes.CDLL(view)
+    fake().fake_limit(90 << 30)                                  # nothing is written there
+    # more images in a batch than a program's 16 bits count
+    n = N.Net("many", 6, 6, 8, dtype="bf16")
+    t = n.conv(0, 8, 3)
+    for _ in range(15):
+        t = n.conv(t, 8, 3)
+    n.fc(n.gap(t), 8)
+    E = ens.Ensemble([n], [W.make_blob(n, 261, 0)])
+    E.ens_set_alloc([[40000]], 40000)
+    assert V.chain_steps(E._h, 0) > 16 and V.chain_cap(E._h, 0) == 32767, V.chain_cap(E._h, 0)
+    E.close()
+    # three tensors of 2.0 GB at a time: more bytes for an image than 32 bits count
+    n = N.Net("large", 2880, 2880, 8, dtype="bf16")
+    a = n.conv(0, 128, 1)
+    t = n.conv(n.conv(a, 128, 1), 128, 1, res=a)
+    for _ in range(14):
+        t = n.conv(t, 8, 3, stride=2)
+    n.fc(n.gap(t), 8)
+    E = ens.Ensemble([n], [W.make_blob(n, 262, 0)])
+    E.ens_set_alloc([[2]])
+    assert V.chain_steps(E._h, 0) == 0
+    E.close()
+
+
+def test_chains_within_the_widths_of_a_program(fake_hip, chain_view):
+    """The first image of a program has 16 bits and the bytes of an image 32: larger batches and images are left to the launches."""
+    beside_fake_hip(fake_hip, "wide_programs(%r)" % chain_view)
