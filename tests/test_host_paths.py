@@ -197,12 +197,14 @@ def wide_programs(view):
     E.ens_set_alloc([[40000]], 40000)
     assert V.chain_steps(E._h, 0) > 16 and V.chain_cap(E._h, 0) == 32767, V.chain_cap(E._h, 0)
     E.close()
-    # three tensors of 2.0 GB at a time: more bytes for an image than 32 bits count
-    n = N.Net("large", 2880, 2880, 8, dtype="bf16")
-    a = n.conv(0, 128, 1)
-    t = n.conv(n.conv(a, 128, 1), 128, 1, res=a)
-    for _ in range(14):
-        t = n.conv(t, 8, 3, stride=2)
+    # 36 tensors of 128 MB at a time: more bytes for an image than 32 bits count
+    n = N.Net("large", 1000, 1000, 8, dtype="bf16")
+    held = [n.conv(0, 64, 1)]
+    for _ in range(36):
+        held.append(n.conv(held[-1], 64, 1))
+    t = held[-1]
+    for a in reversed(held[:-1]):
+        t = n.conv(t, 64, 1, res=a)
     n.fc(n.gap(t), 8)
     E = ens.Ensemble([n], [W.make_blob(n, 262, 0)])
     E.ens_set_alloc([[2]])
