@@ -798,10 +798,8 @@ static void install_chains(ens_handle* h, int64_t need) {
     std::vector<Chain> chains(h->members.size());
     if (h->keeps || !h->gangs_enabled) return;
     for (const Worker& w : h->workers)
-        if (w.batch != h->workers[0].batch && w.rank > 0) {
-            for (const Worker& u : h->workers)
-                if (u.member == w.member && u.batch != w.batch) return;
-        }
+        for (const Worker& u : h->workers)
+            if (u.member == w.member && u.batch != w.batch) return;
     size_t steps = 0;
     std::vector<size_t> at;
     for (size_t c = 0; c < h->members.size(); c++) {

@@ -215,3 +215,26 @@ def wide_programs(view):
 def test_chains_within_the_widths_of_a_program(fake_hip, chain_view):
     """The first image of a program has 16 bits and the bytes of an image 32: larger batches and images are left to the launches."""
     beside_fake_hip(fake_hip, "wide_programs(%r)" % chain_view)
+
+
+def unequal_workers(view):
+    import paper_2208_14049_amd as ens
+    from synth import nets as N, weights as W
+    V, nets = ctypes.CDLL(view), []
+    for i in range(2):
+        n = N.Net("deep%d" % i, 12, 12, 8, dtype="bf16")
+        t = n.conv(0, 16, 3)
+        for _ in range(15):
+            t = n.conv(t, 16, 3)
+        n.fc(n.gap(t), 8)
+        nets.append(n)
+    E = ens.Ensemble(nets, [W.make_blob(n, 271, i) for i, n in enumerate(nets)])
+    for matrix, chains in (([[8, 16]], True), ([[8, 16], [8, 16]], True), ([[8, 16], [8, 0]], True), ([[8, 8], [16, 8]], False), ([[8, 16], [0, 8]], False), ([[16, 8], [0, 16]], False)):
+        E.ens_set_alloc(matrix)
+        assert [V.chain_steps(E._h, m) > 0 for m in range(2)] == [chains] * 2, matrix
+    E.close()
+
+
+def test_chains_leave_unequal_workers_alone(fake_hip, chain_view):
+    """Workers of one member with different batch sizes: which of them takes a batch is what such a matrix is about, so that its requests go launch by launch."""
+    beside_fake_hip(fake_hip, "unequal_workers(%r)" % chain_view)
