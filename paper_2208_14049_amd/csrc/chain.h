@@ -10,6 +10,7 @@ constexpr int CHAIN_THREADS = 512, CHAIN_WAVES = CHAIN_THREADS / 64;
 constexpr int CHAIN_GROUPS = 16;             // XCDs that the kernel has a group word for (the GPU has 8)
 constexpr int CHAIN_MAX_PROGRAMS = 192;
 constexpr int CHAIN_TABLE_FLOATS = 4096;     // of LDS: pre-activation (scale and shift of up to 2048 channels), means, hidden values
+constexpr int CHAIN_FAILED_WORD = 8;         // of the 16 words of ens_handle::flag: ChainArgs::failed
 constexpr int CHAIN_DW_SLOTS = 880;          // pixels (of 64 channels) of a depthwise layer's strip that LDS holds beside the sums
 
 // One operation; the steps of a phase follow each other, read nothing that another one of them writes and run side by side.

@@ -641,7 +641,6 @@ static void drop_graphs(ens_handle* h) {
 // A request that takes longer than the spin is waited for the ordinary way, and so is one in SYNC_EVERY, which lets the runtime
 // give back what it holds for finished launches.  (Not for answers on the device: the caller's next synchronisation of a stream of its
 // own would pay for that, 0.6 us per launch.)
-constexpr int CHAIN_FAILED_WORD = 8;                             // of the flag's 64 bytes
 constexpr double SPIN_S = 5e-3;
 constexpr uint64_t SYNC_EVERY = 64;
 
@@ -796,6 +795,7 @@ constexpr size_t CHAIN_MIN_OPS = 16;
 
 static void install_chains(ens_handle* h, int64_t need) {
     std::vector<Chain> chains(h->members.size());
+    h->chains_off = false;
     if (h->keeps || !h->gangs_enabled) return;
     for (const Worker& w : h->workers)
         for (const Worker& u : h->workers)
@@ -1562,7 +1562,7 @@ static double launches_seconds(ens_handle* h, int64_t n) {
 constexpr double CHAIN_MARGIN = 1.25;
 
 static const ChainPlan* chain_plan(ens_handle* h, int64_t n) {
-    if (h->chains.empty()) return nullptr;
+    if (h->chains.empty() || h->chains_off) return nullptr;
     for (const Chain& c : h->chains)
         if (n > c.cap) return nullptr;
     if (h->chain_plans.size() <= (size_t)n) h->chain_plans.resize((size_t)n + 1);
@@ -1817,12 +1817,22 @@ static void recover(ens_handle* h) {
     (void)hipGetLastError();
 }
 
-// A chain's group that waited for seconds has said so and left.
-static int chains_ended(ens_handle* h) {
-    if (!__atomic_load_n(h->flag + CHAIN_FAILED_WORD, __ATOMIC_ACQUIRE)) return ENS_OK;
-    __atomic_store_n(h->flag + CHAIN_FAILED_WORD, 0u, __ATOMIC_RELEASE);
-    recover(h);
-    return ENS_E_HIP;
+// A request from its launches to its end.  A chain's group that waited for seconds has said so and left: the launches answer that request,
+// and those after it until the next allocation is installed.
+static int answer(ens_handle* h, const float* d_images, int64_t n, float* d_probs, uint64_t mask = ~0ull, bool may_alloc = true, const float* host_images = nullptr) {
+    const bool flagged = h->flagged;
+    for (;;) {
+        const int rc = run_device(h, d_images, n, d_probs, mask, may_alloc, host_images);
+        if (rc != ENS_OK) { recover(h); return rc; }
+        HIP_TRY(wait_lanes(h));
+        if (!__atomic_load_n(h->flag + CHAIN_FAILED_WORD, __ATOMIC_ACQUIRE)) break;
+        recover(h);
+        __atomic_store_n(h->flag + CHAIN_FAILED_WORD, 0u, __ATOMIC_RELEASE);
+        h->chains_off = true;
+        h->flagged = flagged;
+    }
+    h->flagged = false;
+    return ENS_OK;
 }
 
 static int finish_profile(ens_handle* h) {
@@ -1892,10 +1902,7 @@ static int time_installed(ens_handle* h, int64_t n, int repeats, uint64_t mask, 
     std::vector<double> secs;
     for (int i = 0; i < repeats + 1; i++) {
         const auto t0 = std::chrono::steady_clock::now();
-        rc = run_device(h, h->d_calib, n, h->d_probs, mask);
-        if (rc != ENS_OK) { recover(h); return rc; }
-        HIP_TRY(wait_lanes(h));
-        rc = chains_ended(h);
+        rc = answer(h, h->d_calib, n, h->d_probs, mask);
         if (rc != ENS_OK) return rc;
         const auto t1 = std::chrono::steady_clock::now();
         if (i > 0) secs.push_back(std::chrono::duration<double>(t1 - t0).count());
@@ -2047,11 +2054,7 @@ int ens_predict(ens_handle* h, const float* images, int64_t n, float* probs_out)
     }
     if (h->profiling) reset_profile(h);
     h->flagged = direct_out && !h->profiling;
-    int rc = run_device(h, d_in, n, d_out, ~0ull, true, host_in);
-    if (rc != ENS_OK) { recover(h); return rc; }
-    HIP_TRY(wait_lanes(h));
-    h->flagged = false;
-    rc = chains_ended(h);
+    const int rc = answer(h, d_in, n, d_out, ~0ull, true, host_in);
     if (rc != ENS_OK) return rc;
     if (direct_out) {
         memcpy(probs_out, h->pin_out, out_floats * sizeof(float));
@@ -2076,10 +2079,7 @@ int ens_predict_static(ens_handle* h, const float* d_images, int64_t n, float* d
     const auto t0 = std::chrono::steady_clock::now();
     int rc = use_static_logits(h, n);
     if (rc != ENS_OK) return rc;
-    rc = run_device(h, d_images, n, d_probs_out, ~0ull, false);
-    if (rc != ENS_OK) { recover(h); return rc; }
-    HIP_TRY(wait_lanes(h));
-    rc = chains_ended(h);
+    rc = answer(h, d_images, n, d_probs_out, ~0ull, false);
     if (rc != ENS_OK) return rc;
     h->last_n = n;
     h->last_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();

@@ -270,6 +270,7 @@ struct ens_handle {
     std::vector<size_t> chain_at;
     std::vector<ens::ChainPlan> chain_plans;     // by the number of images
     ens::ChainSync* d_chain_sync = nullptr;
+    bool chains_off = false;                     // one of them gave up waiting: no more of them with this allocation
     // fp32 members that fit LDS (resident.h): one per member, or none at all; what LDS begins with in device memory, and where each begins
     std::vector<ens::Resident> residents;
     float* d_resident = nullptr;

@@ -9,6 +9,9 @@ int chain_steps(ens_handle* h, int member) { return h->chains.empty() ? 0 : (int
 
 int chain_cap(ens_handle* h, int member) { return h->chains.empty() ? 0 : h->chains[member].cap; }
 
+// What a group leaves that gave up waiting.
+void chain_gave_up(ens_handle* h) { h->flag[CHAIN_FAILED_WORD] = 1; }
+
 // The weights that the convolutions of a member ask for, with every tile that is chosen for some number of images: the number of
 // fragments of which a lane lies outside the layer's weights, and of those that are asked for and do not exist (`none`).
 int chain_weights_outside(ens_handle* h, int member, int* none) {

@@ -217,18 +217,47 @@ def test_chains_within_the_widths_of_a_program(fake_hip, chain_view):
     beside_fake_hip(fake_hip, "wide_programs(%r)" % chain_view)
 
 
-def unequal_workers(view):
+def deep_members(count):
     import paper_2208_14049_amd as ens
     from synth import nets as N, weights as W
-    V, nets = ctypes.CDLL(view), []
-    for i in range(2):
+    nets = []
+    for i in range(count):
         n = N.Net("deep%d" % i, 12, 12, 8, dtype="bf16")
         t = n.conv(0, 16, 3)
         for _ in range(15):
             t = n.conv(t, 16, 3)
         n.fc(n.gap(t), 8)
         nets.append(n)
-    E = ens.Ensemble(nets, [W.make_blob(n, 271, i) for i, n in enumerate(nets)])
+    return ens.Ensemble(nets, [W.make_blob(n, 271, i) for i, n in enumerate(nets)])
+
+
+def groups_give_up(view):
+    V, F, x = ctypes.CDLL(view), fake(), np.zeros((4, 12, 12, 3), np.float32)
+    E = deep_members(8)
+    E.ens_set_alloc([[8 + 8 * (i % 2) for i in range(8)]])       # (two batch sizes: members that share no launches)
+    E.ens_predict(x)
+    assert E.ens_debug_stats()["chained"] == 1
+    before = F.fake_launches()
+    V.chain_gave_up(E._h)
+    E.ens_predict(x)                                             # a chain, and then the launches of every layer
+    assert E.ens_debug_stats()["chained"] == 2 and F.fake_launches() - before > 16, F.fake_launches() - before
+    E.ens_predict(x[:1])
+    E.ens_predict(x)
+    assert E.ens_debug_stats()["chained"] == 2
+    E.ens_set_alloc([[8 + 8 * (i % 2) for i in range(8)]])
+    E.ens_predict(x)
+    assert E.ens_debug_stats()["chained"] == 3
+    E.close()
+    assert F.fake_used() == 0
+
+
+def test_a_chain_that_gives_up_is_answered_by_launches(fake_hip, chain_view):
+    """A group of compute units that waited in vain fails no request: its launches answer it, and those that follow until the next allocation."""
+    beside_fake_hip(fake_hip, "groups_give_up(%r)" % chain_view)
+
+
+def unequal_workers(view):
+    V, E = ctypes.CDLL(view), deep_members(2)
     for matrix, chains in (([[8, 16]], True), ([[8, 16], [8, 16]], True), ([[8, 16], [8, 0]], True), ([[8, 8], [16, 8]], False), ([[8, 16], [0, 8]], False), ([[16, 8], [0, 16]], False)):
         E.ens_set_alloc(matrix)
         assert [V.chain_steps(E._h, m) > 0 for m in range(2)] == [chains] * 2, matrix
