@@ -972,9 +972,9 @@ static int install_alloc(ens_handle* h, const ens_alloc& a, int segment_size) {
     h->args_stale = false;
     h->alloc = a;
     h->alloc.bytes = need;
-    install_chains(h, need);
+    if (copy_gangs(h, need) != ENS_OK) drop_copies(h);
+    install_chains(h, need + copy_bytes(h));                     // (what large requests gain from goes first where room is scarce)
     install_residents(h);
-    if (copy_gangs(h, need + h->chain_bytes) != ENS_OK) drop_copies(h);
     h->alloc.bytes = need + h->chain_bytes + copy_bytes(h);
     h->segment_size = segment_size;
     h->have_alloc = true;

@@ -256,6 +256,24 @@ def test_a_chain_that_gives_up_is_answered_by_launches(fake_hip, chain_view):
     beside_fake_hip(fake_hip, "groups_give_up(%r)" % chain_view)
 
 
+def copies_first(view):
+    V, E = ctypes.CDLL(view), deep_members(1)
+    weights, arena = E.ens_member_bytes(0, 8)
+    reserve = 8 * (12 * 12 * 3 + 2 * 8) * 4
+    opts = dict(domain=[8], slots=1, strategy=1, n_calib=8, repeats=1)
+    for extra, copies, chains in ((0, 3, False), (-1, 0, True), (1 << 20, 3, True)):
+        a = E.ens_plan(weights + 4 * arena + reserve + extra, **opts)
+        s = E.ens_debug_stats()
+        assert s["copies"] == copies and (V.chain_steps(E._h, 0) > 0) == chains, (extra, s, V.chain_steps(E._h, 0))
+        assert (a.bytes > weights + (1 + copies) * arena) == chains, (extra, a.bytes)
+    E.close()
+
+
+def test_copies_come_before_chains_in_a_budget(fake_hip, chain_view):
+    """What is kept for requests of a few images takes nothing of a budget that copies of the workers would have fitted into."""
+    beside_fake_hip(fake_hip, "copies_first(%r)" % chain_view)
+
+
 def unequal_workers(view):
     V, E = ctypes.CDLL(view), deep_members(2)
     for matrix, chains in (([[8, 16]], True), ([[8, 16], [8, 16]], True), ([[8, 16], [8, 0]], True), ([[8, 8], [16, 8]], False), ([[8, 16], [0, 8]], False), ([[16, 8], [0, 16]], False)):
