@@ -102,7 +102,7 @@ typedef struct {
     int32_t rows, cols;
     int32_t batch[ENS_MAX_SLOTS][ENS_MAX_MEMBERS];
     int64_t bytes;      /* out: device memory of the matrix as installed (weights, arenas and
-                           those of the copies and chains, see ens_set_alloc)                 */
+                           what is kept beside them, see ens_set_alloc)                       */
     double  score;      /* out: images per second measured for it, 0 if never benchmarked     */
     int32_t n_bench;    /* out: number of benchmarks the optimizer ran                        */
 } ens_alloc;
@@ -167,7 +167,8 @@ int ens_plan(ens_handle* h, uint64_t mem_budget_bytes, const ens_plan_opts* opts
  * batches overlap: as many as take a quarter of the free device memory at most and, after ens_plan, fit into its budget beside the
  * workers and the request buffers.  They are given back when a later call of the handle finds too little memory.  So is, under the same
  * conditions, what an ensemble of deep bf16 members keeps for requests of a few images (ens_predict): the steps of its members and a copy of
- * their convolutions' weights in the order of the matrix cores' operands, up to the size of the weights. */
+ * their convolutions' weights in the order of the matrix cores' operands, up to the size of the weights.  So is what one of small fp32
+ * members keeps, their weights and tables as LDS holds them. */
 int ens_set_alloc(ens_handle* h, const ens_alloc* a, int32_t segment_size);
 
 /* "Benchmark Mode" of section "The inference system": installs `a`, predicts n_calib synthetic

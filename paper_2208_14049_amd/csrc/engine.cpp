@@ -669,6 +669,13 @@ static void drop_chains(ens_handle* h) {
     for (Worker& w : h->workers) w.last_programs.clear();
 }
 
+static void drop_residents(ens_handle* h) {
+    h->residents.clear();
+    if (h->d_resident) (void)hipFree(h->d_resident);
+    h->d_resident = nullptr;
+    h->resident_bytes = 0;
+}
+
 static void destroy_workers(ens_handle* h) {
     h->flagged = false;                                          // the streams themselves
     (void)wait_lanes(h);
@@ -681,9 +688,7 @@ static void destroy_workers(ens_handle* h) {
         if (w.arena) (void)hipFree(w.arena);
     h->workers.clear();
     drop_chains(h);
-    h->residents.clear();
-    if (h->d_resident) (void)hipFree(h->d_resident);
-    h->d_resident = nullptr;
+    drop_residents(h);
     h->have_alloc = false;
 }
 
@@ -729,14 +734,24 @@ static void drop_copies(ens_handle* h) {
     (void)hipGetLastError();
 }
 
-// fn, which allocates device memory; once more without the copies and the recorded requests if there is not enough of it.
+// fn, which allocates device memory; once more without the copies and the recorded requests if there is not enough of it, and once more
+// without the members in LDS, which are much faster than their launches and take a few hundred KB.
 template <typename F>
 static int with_room(ens_handle* h, F&& fn) {
     int rc = fn();
     if (rc != ENS_E_NOMEM) return rc;
     (void)hipGetLastError();
-    if ((int)h->gangs.size() == h->own_gangs && h->graphs.empty() && h->chains.empty()) return rc;
-    drop_copies(h);
+    if ((int)h->gangs.size() > h->own_gangs || !h->graphs.empty() || !h->chains.empty()) {
+        drop_copies(h);
+        rc = fn();
+        if (rc != ENS_E_NOMEM) return rc;
+        (void)hipGetLastError();
+    }
+    if (h->residents.empty()) return rc;
+    h->flagged = false;
+    (void)wait_lanes(h);
+    h->alloc.bytes -= h->resident_bytes;
+    drop_residents(h);
     rc = fn();
     if (rc == ENS_E_NOMEM) (void)hipGetLastError();
     return rc;
@@ -869,7 +884,7 @@ static void install_chains(ens_handle* h, int64_t need) {
 }
 
 // The members in LDS, when all of them are small fp32 networks.
-static void install_residents(ens_handle* h) {
+static void install_residents(ens_handle* h, int64_t need) {
     if (h->keeps || h->members.size() > RESIDENT_MAX_MEMBERS) return;
     std::vector<Resident> all(h->members.size());
     std::vector<size_t> at;
@@ -880,6 +895,7 @@ static void install_residents(ens_handle* h) {
         at.push_back(fixed.size());
         fixed.insert(fixed.end(), all[c].fixed.begin(), all[c].fixed.end());
     }
+    if (h->budget && (uint64_t)need + fixed.size() * sizeof(float) + (uint64_t)h->reserve > h->budget) return;
     if (hipMalloc((void**)&h->d_resident, fixed.size() * sizeof(float)) != hipSuccess) { h->d_resident = nullptr; (void)hipGetLastError(); return; }
     if (hipMemcpyAsync(h->d_resident, fixed.data(), fixed.size() * sizeof(float), hipMemcpyHostToDevice, h->main_stream) != hipSuccess ||
         hipStreamSynchronize(h->main_stream) != hipSuccess) {
@@ -888,6 +904,7 @@ static void install_residents(ens_handle* h) {
         h->d_resident = nullptr;
         return;
     }
+    h->resident_bytes = (int64_t)(fixed.size() * sizeof(float));
     h->resident_at = at;
     h->residents = std::move(all);
 }
@@ -974,8 +991,8 @@ static int install_alloc(ens_handle* h, const ens_alloc& a, int segment_size) {
     h->alloc.bytes = need;
     if (copy_gangs(h, need) != ENS_OK) drop_copies(h);
     install_chains(h, need + copy_bytes(h));                     // (what large requests gain from goes first where room is scarce)
-    install_residents(h);
-    h->alloc.bytes = need + h->chain_bytes + copy_bytes(h);
+    install_residents(h, need + copy_bytes(h) + h->chain_bytes);
+    h->alloc.bytes = need + copy_bytes(h) + h->chain_bytes + h->resident_bytes;
     h->segment_size = segment_size;
     h->have_alloc = true;
     return ENS_OK;

@@ -217,6 +217,42 @@ def test_chains_within_the_widths_of_a_program(fake_hip, chain_view):
     beside_fake_hip(fake_hip, "wide_programs(%r)" % chain_view)
 
 
+def members_in_lds():
+    import paper_2208_14049_amd as ens
+    from synth import nets as N, weights as W
+    F, nets = fake(), [N.tiny_a(classes=8), N.tiny_b(classes=8)]
+    x = np.zeros((8, 32, 32, 3), np.float32)
+    E = ens.Ensemble(nets, [W.make_blob(n, 281, i) for i, n in enumerate(nets)])
+    bytes_of = [E.ens_member_bytes(m, 8) for m in range(2)]
+    plain, reserve = sum(w for w, _ in bytes_of) + 2 * sum(a for _, a in bytes_of), 8 * (32 * 32 * 3 + 3 * 8) * 4   # two workers and a copy of each
+    opts = dict(domain=[8], slots=1, strategy=1, n_calib=8, repeats=1)
+    E.ens_plan(plain + reserve, **opts)                          # a budget for launches only
+    assert E.ens_debug_stats()["copies"] == 2
+    ran = E.ens_debug_stats()["chained"]
+    E.ens_predict(x)
+    assert E.ens_debug_stats()["chained"] == ran
+    kept = E.ens_plan(1 << 30, **opts).bytes - plain
+    assert 0 < kept < 1 << 20, kept
+    ran = E.ens_debug_stats()["chained"]
+    E.ens_predict(x)
+    assert E.ens_debug_stats()["chained"] == ran + 1
+    # what a request needs and finds only without them
+    F.fake_limit(F.fake_used() + (1 << 20))
+    n = ((1 << 20) + E.ens_debug_stats()["copy_bytes"] + kept // 2) // (32 * 32 * 3 * 4 + 3 * 8 * 4)
+    E.ens_predict(np.zeros((n, 32, 32, 3), np.float32))
+    s = E.ens_debug_stats()
+    assert s["chained"] == ran + 1 and s["copies"] == 0, s
+    E.ens_predict(x)
+    assert E.ens_debug_stats()["chained"] == ran + 1
+    E.close()
+    assert F.fake_used() == 0
+
+
+def test_members_in_lds_are_part_of_the_budget(fake_hip):
+    """What small fp32 members keep on the device counts in their allocation's bytes and in a budget, and goes when a request finds no memory."""
+    beside_fake_hip(fake_hip, "members_in_lds()")
+
+
 def deep_members(count):
     import paper_2208_14049_amd as ens
     from synth import nets as N, weights as W
