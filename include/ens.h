@@ -154,7 +154,8 @@ int ens_set_io(ens_handle* h, int32_t base_h, int32_t base_w, int32_t images_on_
 /* ---- allocation ----------------------------------------------------------------------------
  * ens_plan: section "The allocation optimizer".  Algorithm 1 (worst-fit-decreasing) places every
  * member at default_batch within mem_budget_bytes, Algorithm 2 (bounded greedy) then benchmarks
- * neighbouring matrices on calibration images; the result is installed and returned.
+ * neighbouring matrices on calibration images; the result is installed and returned.  Its benchmarks go launch by launch, whatever
+ * ens_predict would do with as many images (one launch for a whole request depends little on the matrix): the score is theirs.
  * opts == NULL takes the paper's settings.  ENS_E_NOFIT if a member fits nowhere.
  */
 int ens_plan(ens_handle* h, uint64_t mem_budget_bytes, const ens_plan_opts* opts, ens_alloc* out);
@@ -268,14 +269,15 @@ int ens_spec_bytes(const ens_member_spec* spec, int32_t batch, int64_t* weight_b
                    int64_t* arena_bytes);
 /* Per-kernel timing.  With profiling on, every kernel launch of ens_predict / ens_bench carries
  * a pair of HIP events attached to its dispatch (stamped with the kernel's own begin and end), and
- * the durations are summed per kernel class after the call.  ens_profile_get enumerates the classes of the last call
+ * the durations are summed per kernel class after the call.  Requests go launch by launch then, also those that
+ * ens_predict would run in one launch otherwise.  ens_profile_get enumerates the classes of the last call
  * (idx = 0, 1, ...; ENS_E_INVALID past the end): name, summed milliseconds, launches, the
  * algorithmic flop and the algorithmic bytes (each input, weight and output read or written
  * once) of those launches.  ens_last_ms is the wall time of the last ens_predict. */
 int ens_set_profiling(ens_handle* h, int32_t on);
 /* Measurement aid: with one_stream on, every worker issues its kernels on one stream, so that each kernel
- * has the GPU to itself and ens_profile_get reports durations that no co-running kernel stretches.  Same
- * results, no overlap; not for serving. */
+ * has the GPU to itself and ens_profile_get reports durations that no co-running kernel stretches.  Launch by launch, no
+ * overlap; not for serving.  (Layers may go to other kernels, which add up in another order.) */
 int ens_debug_one_stream(ens_handle* h, int32_t on);
 int ens_profile_get(const ens_handle* h, int32_t idx, char* name, int32_t name_len, double* ms,
                     int64_t* launches, double* flop, double* bytes);

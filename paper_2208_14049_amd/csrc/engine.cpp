@@ -1655,7 +1655,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
     auto refresh = [&](int i) { return h->gangs[i].stale ? build_launches(h, h->gangs[i], may_alloc) : ENS_OK; };
     h->requests++;
     const bool plain_only = !may_alloc || h->profiling || h->fake_predictor || h->one_stream || mask != ~0ull;
-    if (!h->profiling && !h->fake_predictor && !h->one_stream && mask == ~0ull) {
+    if (!h->profiling && !h->fake_predictor && !h->one_stream && !h->planning && mask == ~0ull) {
         const ChainPlan* plan = chain_plan(h, n);
         if (plan) return run_chains(h, d_images, n, d_probs, *plan, host_images);
         if (n < (int64_t)1 << 30 && resident_wanted(h, n)) return run_resident(h, d_images, n, d_probs, host_images);
@@ -2194,6 +2194,12 @@ int ens_plan(ens_handle* h, uint64_t mem_budget_bytes, const ens_plan_opts* opts
         show(mat, ips);
         return ips;
     };
+    // A matrix is judged by its workers' batches: a request that runs in one launch hardly depends on it, and members timed alone go by launches
+    struct Planning {
+        ens_handle* h;
+        explicit Planning(ens_handle* handle) : h(handle) { h->planning = true; }
+        ~Planning() { h->planning = false; }
+    } planning(h);
     double score = 0.0;
     int32_t n_bench = 0;
     if (o.strategy == 0) {

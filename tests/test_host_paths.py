@@ -259,7 +259,7 @@ def deep_members(count):
     nets = []
     for i in range(count):
         n = N.Net("deep%d" % i, 12, 12, 8, dtype="bf16")
-        t = n.conv(0, 16, 3)
+        t = n.conv(0, 16 + 8 * i, 3)                              # of shapes of their own: they share no launches
         for _ in range(15):
             t = n.conv(t, 16, 3)
         n.fc(n.gap(t), 8)
@@ -270,7 +270,7 @@ def deep_members(count):
 def groups_give_up(view):
     V, F, x = ctypes.CDLL(view), fake(), np.zeros((4, 12, 12, 3), np.float32)
     E = deep_members(8)
-    E.ens_set_alloc([[8 + 8 * (i % 2) for i in range(8)]])       # (two batch sizes: members that share no launches)
+    E.ens_set_alloc([[8] * 8])
     E.ens_predict(x)
     assert E.ens_debug_stats()["chained"] == 1
     before = F.fake_launches()
@@ -280,7 +280,7 @@ def groups_give_up(view):
     E.ens_predict(x[:1])
     E.ens_predict(x)
     assert E.ens_debug_stats()["chained"] == 2
-    E.ens_set_alloc([[8 + 8 * (i % 2) for i in range(8)]])
+    E.ens_set_alloc([[8] * 8])
     E.ens_predict(x)
     assert E.ens_debug_stats()["chained"] == 3
     E.close()
@@ -308,6 +308,25 @@ def copies_first(view):
 def test_copies_come_before_chains_in_a_budget(fake_hip, chain_view):
     """What is kept for requests of a few images takes nothing of a budget that copies of the workers would have fitted into."""
     beside_fake_hip(fake_hip, "copies_first(%r)" % chain_view)
+
+
+def plans():
+    import paper_2208_14049_amd as ens
+    from synth import nets as N, weights as W
+    small = [N.tiny_a(classes=8), N.tiny_b(classes=8)]
+    for E, side in ((deep_members(8), 12), (ens.Ensemble(small, [W.make_blob(n, 281, i) for i, n in enumerate(small)]), 32)):
+        for strategy in (0, 1, 2):
+            a = E.ens_plan(0, domain=[8, 16], slots=1, strategy=strategy, n_calib=4, repeats=1, max_neighs=3, max_iter=1)
+            assert a.score > 0 and E.ens_debug_stats()["chained"] == 0, (strategy, E.ens_debug_stats())
+        E.ens_predict(np.zeros((4, side, side, 3), np.float32))
+        E.ens_bench([[8] * E.n_members], n_calib=4, repeats=1)
+        assert E.ens_debug_stats()["chained"] == 3, E.ens_debug_stats()   # the request, and the benchmark's warm-up and run
+        E.close()
+
+
+def test_plans_are_made_launch_by_launch(fake_hip):
+    """The optimizer compares matrices by their workers' batches, members alone and all of them by the same path; requests and single benchmarks take theirs."""
+    beside_fake_hip(fake_hip, "plans()")
 
 
 def unequal_workers(view):
