@@ -254,6 +254,8 @@ typedef struct {
     int64_t copies;      /* copies of groups of workers with arenas of their own (ens_set_alloc) */
     int64_t copy_bytes;  /* device memory of those arenas                                        */
     int64_t chained;     /* requests whose members ran in one launch (see ens_predict)           */
+    int64_t rows;        /* launches whose residual and output went through LDS in rows, replays
+                            of recorded ones not counted                                         */
 } ens_stats;
 int ens_debug_stats(const ens_handle* h, ens_stats* out);
 
@@ -279,6 +281,9 @@ int ens_set_profiling(ens_handle* h, int32_t on);
  * has the GPU to itself and ens_profile_get reports durations that no co-running kernel stretches.  Launch by launch, no
  * overlap; not for serving.  (Layers may go to other kernels, which add up in another order.) */
 int ens_debug_one_stream(ens_handle* h, int32_t on);
+/* For tests: with on = 0 no launch of the handle takes its residual and output through LDS in rows, as they do where
+ * three or four streams are in use.  The values are the same either way. */
+int ens_debug_rows(ens_handle* h, int32_t on);
 int ens_profile_get(const ens_handle* h, int32_t idx, char* name, int32_t name_len, double* ms,
                     int64_t* launches, double* flop, double* bytes);
 double ens_last_ms(const ens_handle* h);

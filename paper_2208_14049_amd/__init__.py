@@ -52,7 +52,7 @@ class EnsAlloc(ctypes.Structure):
 
 
 class EnsStats(ctypes.Structure):
-    _fields_ = [(f, ctypes.c_int64) for f in ("recorded", "replayed", "graphs", "handed_out", "copies", "copy_bytes", "chained")]
+    _fields_ = [(f, ctypes.c_int64) for f in ("recorded", "replayed", "graphs", "handed_out", "copies", "copy_bytes", "chained", "rows")]
 
 
 class EnsPlanOpts(ctypes.Structure):
@@ -78,7 +78,7 @@ BENCH_SINGLE_FN = ctypes.CFUNCTYPE(ctypes.c_double, ctypes.c_int32, ctypes.c_int
 EXPORTS = ("ens_load", "ens_free", "ens_set_io", "ens_plan", "ens_set_alloc", "ens_bench", "ens_predict",
            "ens_predict_static", "ens_static_scratch_bytes",
            "ens_member_logits", "ens_debug_tensor", "ens_debug_keep_tensors", "ens_classes", "ens_n_members", "ens_member_bytes",
-           "ens_spec_bytes", "ens_set_profiling", "ens_debug_one_stream", "ens_debug_stats", "ens_profile_get", "ens_last_ms", "ens_set_combination", "ens_debug_fake_predictor",
+           "ens_spec_bytes", "ens_set_profiling", "ens_debug_one_stream", "ens_debug_rows", "ens_debug_stats", "ens_profile_get", "ens_last_ms", "ens_set_combination", "ens_debug_fake_predictor",
            "ens_planner_fit_mem", "ens_planner_wfd", "ens_planner_neighbors", "ens_planner_greedy",
            "ens_planner_bbs", "ens_partition", "ens_hand_out", "ens_strerror", "ens_version")
 
@@ -116,6 +116,7 @@ def lib():
         L.ens_spec_bytes.argtypes = [P(EnsMemberSpec), i32, P(i64), P(i64)]
         L.ens_set_profiling.argtypes = [vp, i32]
         L.ens_debug_one_stream.argtypes = [vp, i32]
+        L.ens_debug_rows.argtypes = [vp, i32]
         L.ens_debug_stats.argtypes = [vp, P(EnsStats)]
         L.ens_set_combination.argtypes = [vp, i32, ctypes.POINTER(ctypes.c_float)]
         L.ens_debug_fake_predictor.argtypes = [vp, i32]
@@ -340,8 +341,11 @@ class Ensemble:
     def ens_debug_one_stream(self, on):
         _check(lib().ens_debug_one_stream(self._h, int(on)), "ens_debug_one_stream")
 
+    def ens_debug_rows(self, on):
+        _check(lib().ens_debug_rows(self._h, int(on)), "ens_debug_rows")
+
     def ens_debug_stats(self):
-        """{recorded, replayed, graphs, handed_out, copies, copy_bytes, chained} of the handle."""
+        """{recorded, replayed, graphs, handed_out, copies, copy_bytes, chained, rows} of the handle."""
         s = EnsStats()
         _check(lib().ens_debug_stats(self._h, ctypes.byref(s)), "ens_debug_stats")
         return {f: getattr(s, f) for f, _ in EnsStats._fields_}

@@ -108,7 +108,11 @@ __device__ __forceinline__ int bn_row(int px, int piece) {
 // three ResNet-18 15.8 -> 15.3, a grouped, a separable and an inverted-residual member 16.5 -> 16.0, twelve members 204 -> 201.  Alone a
 // workgroup has the L1 nearly to itself and the turn is a microsecond more at its end: 9.6 -> 10.6 us (56x56 bottleneck of 8 images
 // 18.3 -> 19.9, of 128 144.5 -> 141.8).
-inline bool rows_wanted() { return lanes_in_use() >= 3; }
+inline bool rows_wanted() {
+    const bool wanted = lanes_in_use() >= 3 && !rows_off();
+    rows_taken() += wanted;
+    return wanted;
+}
 // between the one order and the other: the wavefront's own LDS operations have ended
 __device__ __forceinline__ void bn_turn() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 

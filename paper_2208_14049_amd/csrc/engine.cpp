@@ -1839,7 +1839,10 @@ static void recover(ens_handle* h) {
 static int answer(ens_handle* h, const float* d_images, int64_t n, float* d_probs, uint64_t mask = ~0ull, bool may_alloc = true, const float* host_images = nullptr) {
     const bool flagged = h->flagged;
     for (;;) {
+        const int64_t rows = rows_taken();
+        rows_off() = h->no_rows;
         const int rc = run_device(h, d_images, n, d_probs, mask, may_alloc, host_images);
+        h->stats.rows += rows_taken() - rows;
         if (rc != ENS_OK) { recover(h); return rc; }
         HIP_TRY(wait_lanes(h));
         if (!__atomic_load_n(h->flag + CHAIN_FAILED_WORD, __ATOMIC_ACQUIRE)) break;
@@ -2364,6 +2367,13 @@ int ens_debug_one_stream(ens_handle* h, int32_t on) {
     if (!h) return ENS_E_INVALID;
     (void)hipDeviceSynchronize();
     h->one_stream = on != 0;
+    return ENS_OK;
+}
+
+int ens_debug_rows(ens_handle* h, int32_t on) {
+    if (!h) return ENS_E_INVALID;
+    if (h->no_rows != (on == 0)) drop_graphs(h);                 // they hold launches of the other kind
+    h->no_rows = on == 0;
     return ENS_OK;
 }
 

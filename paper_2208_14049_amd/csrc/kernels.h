@@ -192,6 +192,9 @@ int& cu_budget();
 int& lanes_busy();
 // Lanes that the request in flight is spread over; for choices that are made launch by launch.
 int& lanes_in_use();
+// Launches so far whose residual and output were turned into rows (conv_common.h), and that switched off: for tests.
+int64_t& rows_taken();
+bool& rows_off();
 
 }  // namespace ens
 

@@ -63,6 +63,16 @@ int& lanes_in_use() {
     return lanes;
 }
 
+int64_t& rows_taken() {
+    static thread_local int64_t launches = 0;
+    return launches;
+}
+
+bool& rows_off() {
+    static thread_local bool off = false;
+    return off;
+}
+
 LaunchEvents& next_launch_events() {
     static thread_local LaunchEvents ev;
     return ev;

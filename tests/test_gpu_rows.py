@@ -47,7 +47,8 @@ def layers(i, h, w, c):
 def test_rows(ens, images):
     nets = [layers(i, h, w, c) for i, (h, w, c) in enumerate([(29, 27, 8), (27, 31, 40), (30, 26, 56), (25, 33, 72)])]
     blobs = [W.quantise_weights_bf16(net, W.make_blob(net, synth.BASE_SEED + 71, i)) for i, net in enumerate(nets)]
-    imgs = W.round_bf16(W.make_images(synth.BASE_SEED + 1071, images, 29, 27, varied=True))
+    # two batches: a request of one would run as chains
+    imgs = W.round_bf16(W.make_images(synth.BASE_SEED + 1071, 2 * images, 29, 27, varied=True))
     E = ens.Ensemble(nets, blobs)
     E.set_base_size(29, 27)
     E.ens_set_alloc([[images] * 4])
@@ -55,17 +56,28 @@ def test_rows(ens, images):
 
     def ask():
         y = E.ens_predict(imgs)                                   # and the map in front of the pooling
-        return [y] + [E.ens_member_logits(m, images) for m in range(4)] + [E.ens_debug_tensor(m, pooled[m], net.tensors[pooled[m]], images) for m, net in enumerate(nets)]
+        return [y] + [E.ens_member_logits(m, 2 * images) for m in range(4)] + [E.ens_debug_tensor(m, pooled[m], net.tensors[pooled[m]], images) for m, net in enumerate(nets)]
 
     among = ask()
+    rows = E.ens_debug_stats()["rows"]
+    assert E.ens_debug_stats()["chained"] == 0
     E.ens_set_profiling(1)
     E.ens_predict(imgs)
-    ran = {k["name"] for k in E.ens_profile() if k["launches"]}
+    ran = {k["name"]: k["launches"] for k in E.ens_profile() if k["launches"]}
     E.ens_set_profiling(0)
-    print(sorted(ran), flush=True)
-    for name in ("conv1x1_direct_bf16<128x128>", "conv1x1_direct_bf16<128x256>", "conv1x1_pre_bf16<128x128>", "conv3x3_wreg_bf16<128,c64>",
-                 "bottleneck_bf16<c64>", "bottleneck_bf16<c128>"):
+    print(ran, flush=True)
+    in_rows = ("conv1x1_direct_bf16<128x128>", "conv1x1_direct_bf16<128x256>", "conv1x1_pre_bf16<128x128>", "conv3x3_wreg_bf16<128,c64>",
+               "bottleneck_bf16<c64>", "bottleneck_bf16<c128>")
+    for name in in_rows:
         assert name in ran, (name, ran)
+    # every launch of theirs took its rows, in both requests; with the turn switched off none does, and nothing else changes
+    assert rows == sum(ran[name] for name in in_rows) and E.ens_debug_stats()["rows"] == 2 * rows, (rows, E.ens_debug_stats())
+    E.ens_debug_rows(0)
+    apart = ask()
+    assert E.ens_debug_stats()["rows"] == 2 * rows
+    E.ens_debug_rows(1)
+    for a, b in zip(among, apart):
+        assert np.array_equal(a, b)
     E.ens_debug_one_stream(1)
     alone = ask()
     E.close()
