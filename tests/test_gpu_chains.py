@@ -129,3 +129,93 @@ def test_long_filters(ens):
     imgs = W.round_bf16(W.make_images(synth.BASE_SEED + 1045, 3, 45, 37, varied=True))
     # some 17 bf16 roundings of 2^-9 from the image to the logits, as for the members above; a dropped tap is an error of the size of the values
     ask_all_ways(ens, nets, blobs, imgs, (45, 37), 16, (1, 3), 0.08)
+
+
+def test_values_that_are_no_numbers(ens):
+    """An infinity, a NaN and the largest numbers in an image leave the others of its programs alone, and what they give is what the launches give:
+    numbers where those give numbers (most kernels' ReLU drops a NaN), NaN where those do."""
+    import torch
+    nets = [N.resnet18(size=64, classes=200), N.densenet121(size=64, classes=200), N.efficientnet(0, size=64, classes=200), N.inception_v3(size=107, classes=200),
+            N.resnext50(size=64, classes=200), N.xception(size=107, classes=200), N.mobilenet_v2(size=64, classes=200), N.vgg(16, size=64, classes=200)]
+    blobs = [W.quantise_weights_bf16(net, W.make_blob(net, synth.BASE_SEED + 47, i)) for i, net in enumerate(nets)]
+    imgs = W.round_bf16(W.make_images(synth.BASE_SEED + 1047, 5, 64, 64, varied=True))
+    odd = imgs.copy()
+    odd[1, 20, 31, 1], odd[2, 63, 0, :], odd[3] = np.inf, 3e38, np.nan
+    E = ens.Ensemble(nets, blobs)
+    E.set_base_size(64, 64)
+    E.ens_set_alloc([[16] * len(nets)])
+
+    def ask(x):
+        E.ens_predict(torch.from_numpy(x).cuda())
+        return [E.ens_member_logits(m, 5) for m in range(len(nets))]
+    clean, got = ask(imgs), ask(odd)
+    assert E.ens_debug_stats()["chained"] == 2
+    E.ens_debug_one_stream(1)
+    want = ask(odd)
+    assert E.ens_debug_stats()["chained"] == 2
+    nans = 0
+    for m, net in enumerate(nets):
+        assert np.array_equal(got[m][[0, 4]], clean[m][[0, 4]]), net.name
+        assert np.array_equal(np.isnan(got[m]), np.isnan(want[m])), net.name
+        nans += np.isnan(want[m]).sum()
+        for i in range(5):
+            if not np.isnan(want[m][i]).any():                    # the bound of the members above
+                spread = want[m][i].astype(np.float64).std()
+                assert np.abs(got[m][i].astype(np.float64) - want[m][i]).max() <= 0.08 * spread, (net.name, i)
+    assert nans > 0
+    E.close()
+
+
+def test_chains_beside_other_requests(ens):
+    """Requests that run as chains while another handle's request keeps three of the four streams full, and chains of two handles at once: the answers are
+    those that each gives alone.  (A chain's group is then made of the compute units that were free when it began, down to one.)"""
+    import threading
+    import torch
+    def deep(i, width):
+        n = N.Net("deep%d" % i, 28, 28, 16, dtype="bf16")
+        t = n.conv(0, width, 3)
+        for k in range(20):
+            t = n.conv(t, width, 3 if k % 2 else 1)
+        n.fc(n.gap(t), 16)
+        return n
+    busy = ens.Ensemble([deep(i, 192 + 64 * i) for i in range(3)], [W.make_blob(deep(i, 192 + 64 * i), synth.BASE_SEED + 48, i) for i in range(3)])
+    busy.ens_set_alloc([[128] * 3])
+    handles = []
+    for k in range(2):
+        nets = [deep(i, 32 + 16 * i) for i in range(6 + k)]
+        E = ens.Ensemble(nets, [W.make_blob(net, synth.BASE_SEED + 49 + k, i) for i, net in enumerate(nets)])
+        E.ens_set_alloc([[8] * len(nets)])
+        handles.append(E)
+    L = ens.lib()
+    x = torch.randn(512, 28, 28, 3, device="cuda")
+    y = torch.empty(512, 16, device="cuda")
+    busy.ens_predict(x, y)
+    alone, out = [], []
+    for E in handles:
+        alone.append([E.ens_predict(x[:n].contiguous()).clone() for n in (1, 2)])
+        out.append(torch.empty(2, 16, device="cuda"))
+    assert all(E.ens_debug_stats()["chained"] == 2 for E in handles) and busy.ens_debug_stats()["chained"] == 0
+    torch.cuda.synchronize()
+    wrong = []
+
+    def serve(k, requests):
+        for rep in range(requests):
+            for n in (1, 2):                                      # (through the C entry point: torch would wait for every stream)
+                if L.ens_predict(handles[k]._h, x.data_ptr(), n, out[k].data_ptr()) != 0:
+                    wrong.append((k, rep, n))
+                answers[k].append((n, out[k][:n].clone()))
+    answers = [[], []]
+    for threads in ([threading.Thread(target=lambda: [L.ens_predict(busy._h, x.data_ptr(), 512, y.data_ptr()) for _ in range(8)]), threading.Thread(target=serve, args=(0, 30))],
+                    [threading.Thread(target=serve, args=(k, 60)) for k in range(2)]):
+        for th in threads:
+            th.start()
+        for th in threads:
+            th.join()
+    assert not wrong, wrong[:5]
+    for k in range(2):
+        assert len(answers[k]) >= 120
+        for n, a in answers[k]:
+            assert torch.equal(a, alone[k][n - 1]), (k, n)
+        assert handles[k].ens_debug_stats()["chained"] == 2 + len(answers[k])
+    for E in handles + [busy]:
+        E.close()
