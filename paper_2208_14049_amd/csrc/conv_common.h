@@ -104,10 +104,10 @@ template <int ROW>
 __device__ __forceinline__ int bn_row(int px, int piece) {
     return px * ROW + ((piece ^ ((ROW == 64 ? px >> 2 : px >> 1) & (ROW / 16 - 1))) << 4);   // either order of 16 lanes covers the banks once
 }
-// Taken among the launches of other lanes, whose accesses these are in the way of: 1 024 images of a ResNet-50 in batches of 128, streamed, 17.1 -> 16.7 ms,
-// three ResNet-18 15.8 -> 15.3, a grouped, a separable and an inverted-residual member 16.5 -> 16.0, twelve members 204 -> 201.  Alone a
-// workgroup has the L1 nearly to itself and the turn is a microsecond more at its end: 9.6 -> 10.6 us (56x56 bottleneck of 8 images
-// 18.3 -> 19.9, of 128 144.5 -> 141.8).
+// Taken among the launches of other lanes, whose accesses these are in the way of: 1 024 images of a ResNet-50 in batches of 128, streamed, 16.9 -> 16.5 ms,
+// three ResNet-18 15.6 -> 15.2, a grouped, a separable and an inverted-residual member (215 images) 16.5 -> 16.0, twelve members 201.6 -> 198.8 (with
+// one side's runs up to 0.5 % apart).  Alone a workgroup has the L1 nearly to itself and the turn is a microsecond more at its end: 9.6 -> 10.6 us
+// (56x56 bottleneck of 8 images 18.3 -> 19.9, of 128 144.5 -> 141.8).
 inline bool rows_wanted() {
     const bool wanted = lanes_in_use() >= 3 && !rows_off();
     rows_taken() += wanted;

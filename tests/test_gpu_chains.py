@@ -131,6 +131,36 @@ def test_long_filters(ens):
     ask_all_ways(ens, nets, blobs, imgs, (45, 37), 16, (1, 3), 0.08)
 
 
+def test_chains_are_as_exact_as_launches(ens):
+    """The twelve full-size members on one image and on four: chains add up in another order than the launches, and lie no further from the oracle."""
+    import json
+    import os
+    import torch
+    from tests.golden import make_oracle_cache as cache
+    nets, blobs, imgs, z_ref = cache.load_or_make(4)
+    with open(os.path.join(os.path.dirname(ens.__file__), "allocations.json")) as f:
+        plan = json.load(f)["4"]
+    E = ens.Ensemble(nets, blobs)
+    E.ens_set_alloc(plan["matrix"], plan["segment"])
+
+    def errors(n):
+        z = []
+        for s in range(0, 12, n):
+            E.ens_predict(torch.from_numpy(imgs[s:s + n].copy()).cuda())
+            z.append(np.stack([E.ens_member_logits(m, n) for m in range(len(nets))]))
+        return np.sqrt(((np.concatenate(z, 1).astype(np.float64) - z_ref[:, :12]) ** 2).mean((1, 2))) / z_ref[:, :12].std((1, 2))
+    chains = errors(1), errors(4)
+    assert E.ens_debug_stats()["chained"] == 15
+    E.ens_debug_one_stream(1)
+    launches = errors(1), errors(4)
+    assert E.ens_debug_stats()["chained"] == 15
+    E.close()
+    for c, l in zip(chains, launches):
+        print("rms error of the logits / their spread: chains %s, launches %s" % (np.round(c, 5), np.round(l, 5)), flush=True)
+        # Two draws of the same roundings: over 12 images and all classes their root mean squares were within 4 % of each other for every member
+        assert (c <= 1.15 * l).all(), (c / l)
+
+
 def test_values_that_are_no_numbers(ens):
     """An infinity, a NaN and the largest numbers in an image leave the others of its programs alone, and what they give is what the launches give:
     numbers where those give numbers (most kernels' ReLU drops a NaN), NaN where those do."""
