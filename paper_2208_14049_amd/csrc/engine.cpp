@@ -811,7 +811,7 @@ constexpr size_t CHAIN_MIN_OPS = 16;
 static void install_chains(ens_handle* h, int64_t need) {
     std::vector<Chain> chains(h->members.size());
     h->chains_off = false;
-    if (h->keeps || !h->gangs_enabled) return;
+    if (h->keeps || !h->gangs_enabled || h->planning) return;
     for (const Worker& w : h->workers)
         for (const Worker& u : h->workers)
             if (u.member == w.member && u.batch != w.batch) return;
@@ -885,7 +885,7 @@ static void install_chains(ens_handle* h, int64_t need) {
 
 // The members in LDS, when all of them are small fp32 networks.
 static void install_residents(ens_handle* h, int64_t need) {
-    if (h->keeps || h->members.size() > RESIDENT_MAX_MEMBERS) return;
+    if (h->keeps || h->planning || h->members.size() > RESIDENT_MAX_MEMBERS) return;
     std::vector<Resident> all(h->members.size());
     std::vector<size_t> at;
     std::vector<float> fixed;
@@ -1655,7 +1655,7 @@ static int run_device(ens_handle* h, const float* d_images, int64_t n, float* d_
     auto refresh = [&](int i) { return h->gangs[i].stale ? build_launches(h, h->gangs[i], may_alloc) : ENS_OK; };
     h->requests++;
     const bool plain_only = !may_alloc || h->profiling || h->fake_predictor || h->one_stream || mask != ~0ull;
-    if (!h->profiling && !h->fake_predictor && !h->one_stream && !h->planning && mask == ~0ull) {
+    if (!h->profiling && !h->fake_predictor && !h->one_stream && mask == ~0ull) {
         const ChainPlan* plan = chain_plan(h, n);
         if (plan) return run_chains(h, d_images, n, d_probs, *plan, host_images);
         if (n < (int64_t)1 << 30 && resident_wanted(h, n)) return run_resident(h, d_images, n, d_probs, host_images);
@@ -2198,13 +2198,9 @@ int ens_plan(ens_handle* h, uint64_t mem_budget_bytes, const ens_plan_opts* opts
         return ips;
     };
     // A matrix is judged by its workers' batches: a request that runs in one launch hardly depends on it, and members timed alone go by launches
-    struct Planning {
-        ens_handle* h;
-        explicit Planning(ens_handle* handle) : h(handle) { h->planning = true; }
-        ~Planning() { h->planning = false; }
-    } planning(h);
     double score = 0.0;
     int32_t n_bench = 0;
+    h->planning = true;
     if (o.strategy == 0) {
         rc = greedy(p, A.data(), bench, &score, &n_bench);
     } else if (o.strategy == 1) {
@@ -2234,8 +2230,9 @@ int ens_plan(ens_handle* h, uint64_t mem_budget_bytes, const ens_plan_opts* opts
         for (int c = 0; c < M; c++) A[c] = best[c];
         score = bench(A.data());
     } else {
-        return ENS_E_INVALID;
+        rc = ENS_E_INVALID;
     }
+    h->planning = false;
     if (rc != ENS_OK) return rc;
     if (hip_rc != ENS_OK) return hip_rc;
     ens_alloc a = to_alloc(A.data());

@@ -304,7 +304,7 @@ struct ens_handle {
     bool keeps = false;                          // the installed workers were laid out that way
     bool fake_predictor = false;                 // overhead experiment: forward passes replaced by zeros
     bool no_rows = false;                        // test: rows_off() (kernels.h) of its requests
-    bool planning = false;                       // the optimizer's benchmarks: launch by launch
+    bool planning = false;                       // the optimizer's benchmarks: launch by launch, and nothing is prepared for other requests
     bool one_stream = false;                     // measurement: every worker issues on the first lane, one kernel at a time
     std::vector<ens::ProfClass> prof;
     std::vector<ens::ProfRec> prof_recs;
