@@ -1021,9 +1021,12 @@ hipError_t launch_se(const SeArgs& a, const SeArgs* argv, int G, int nb, bool bf
 }
 
 // ------------------------------------------------------------------ combination rule
-// One wavefront per sample: for each member a max-subtracted softmax of its logits row
-// (wavefront shuffles for the maximum and the sum), each term divided by M and added in
-// member order, one write of the combined row.
+// Per sample and member a max-subtracted softmax of the logits row, each term divided by M and added in
+// member order, one write of the combined row.  A member is a chain of a load and two reductions over a wavefront (2 us), so
+// a row has a wavefront per member where their terms fit LDS, and the terms are added from there in the same order.  With a wavefront per
+// row that took its members one after the other (1 000 classes, us alone, 1 and 1 024 images): twelve members 25 and 29, now 7 and 20, four
+// members 9 and 12, now 6 and 10, three 6.8 and 9.9, now 4.8 and 9.1.  An ensemble of one keeps that form, which is faster there by half a
+// microsecond, and so do more terms than LDS holds.
 //
 // The members run on several lanes, and each lane ends with this launch.  A workgroup adds one to its place in
 // `arrivals` and goes on only if it is the last of the lanes' workgroups for those rows (it then puts the zero back);
@@ -1031,6 +1034,8 @@ hipError_t launch_se(const SeArgs& a, const SeArgs* argv, int G, int nb, bool bf
 // launch began, and none of their lines is in this workgroup's caches: nobody read them since.  That takes the place of
 // an event per lane and a wait for each of them in front of the combination (10 us of host time per lane).
 constexpr int COMBINE_MAX_PER_LANE = 32;    // classes <= 64 * 32
+constexpr int COMBINE_WAVES = 16;           // of a workgroup at most
+constexpr int COMBINE_TERMS = 15 * 1024;    // floats of LDS
 
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
@@ -1043,9 +1048,48 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
+// A member's term: v[e] is the softmax, or the vote, of class lane + 64 e (of those that exist).
 template <int PER, int RULE>
-__global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a) {
-    const int lane = threadIdx.x & 63, classes = a.classes, n_members = a.n_members;
+__device__ __forceinline__ void combine_term(const float* z, const int classes, const int lane, float (&v)[PER]) {
+    float mx = -3.0e38f;
+    int arg = 0x7FFFFFFF;                                // class of this lane's maximum, lowest index first
+#pragma unroll
+    for (int e = 0; e < PER; e++) {
+        const int c = lane + 64 * e;
+        v[e] = c < classes ? z[c] : -3.0e38f;
+        if (RULE == COMBINE_VOTE && c < classes && (v[e] > mx || arg == 0x7FFFFFFF)) arg = c;
+        mx = fmaxf(mx, v[e]);
+    }
+    if (RULE == COMBINE_VOTE) {
+        // arg-max over the wave: the larger value wins, the lower class on equal values
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const float om = __shfl_xor(mx, off, 64);
+            const int oa = __shfl_xor(arg, off, 64);
+            if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
+        }
+#pragma unroll
+        for (int e = 0; e < PER; e++) v[e] = lane + 64 * e == arg ? 1.f : 0.f;
+        return;
+    }
+    mx = wave_max(mx);
+    float sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < PER; e++) {
+        v[e] = lane + 64 * e < classes ? expf(v[e] - mx) : 0.f;
+        sum += v[e];
+    }
+    sum = wave_sum(sum);
+#pragma unroll
+    for (int e = 0; e < PER; e++) v[e] /= sum;
+}
+
+// APART: `waves` wavefronts per row, `rows` rows at a time, the terms added from LDS.  Otherwise a wavefront per row.
+template <int PER, int RULE, bool APART>
+__global__ __launch_bounds__(APART ? 64 * COMBINE_WAVES : 256) void combine_kernel(const CombineArgs a, const int waves, const int rows) {
+    extern __shared__ float terms[];                     // APART: [row][member][class]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), classes = a.classes, n_members = a.n_members;
+    const int r = APART ? wave / waves : wave, first = APART ? wave - r * waves : 0, step = APART ? waves : 1;
     if (a.lanes > 1) {
         __shared__ unsigned before;
         if (threadIdx.x == 0) {
@@ -1058,65 +1102,62 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineArgs a) {
     }
     float* __restrict__ const y = a.slot ? a.slot->dst : a.y;
     const float* __restrict__ const weights = a.weights;
-    for (long long row = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); row < a.n; row += (long long)gridDim.x * (blockDim.x >> 6)) {
+    const float inv_m = 1.f / (float)n_members;
+    auto share = [&](int m) { return RULE == COMBINE_WEIGHTED ? weights[m] : inv_m; };
+    for (long long row0 = (long long)blockIdx.x * rows; row0 < a.n; row0 += (long long)gridDim.x * rows) {
+        const long long row = row0 + r;
         float acc[PER];
 #pragma unroll
         for (int e = 0; e < PER; e++) acc[e] = 0.f;
-        const float inv_m = 1.f / (float)n_members;
-        for (int m = 0; m < n_members; m++) {
-            const float* z = a.logits[m] + row * classes;
-            float v[PER];
-            float mx = -3.0e38f;
-            int arg = 0x7FFFFFFF;                        // class of this lane's maximum, lowest index first
+        if (row < a.n)
+            for (int m = first; m < n_members; m += step) {
+                float v[PER];
+                combine_term<PER, RULE>(a.logits[m] + row * classes, classes, lane, v);
 #pragma unroll
-            for (int e = 0; e < PER; e++) {
-                const int c = lane + 64 * e;
-                v[e] = c < classes ? z[c] : -3.0e38f;
-                if (RULE == COMBINE_VOTE && c < classes && (v[e] > mx || arg == 0x7FFFFFFF)) arg = c;
-                mx = fmaxf(mx, v[e]);
-            }
-            if (RULE == COMBINE_VOTE) {
-                // arg-max over the wave: the larger value wins, the lower class on equal values
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) {
-                    const float om = __shfl_xor(mx, off, 64);
-                    const int oa = __shfl_xor(arg, off, 64);
-                    if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
+                for (int e = 0; e < PER; e++) {
+                    const int c = lane + 64 * e;
+                    if (!APART) acc[e] = fmaf(v[e], share(m), acc[e]);
+                    else if (c < classes) terms[(r * n_members + m) * classes + c] = v[e];
                 }
-#pragma unroll
-                for (int e = 0; e < PER; e++) acc[e] += lane + 64 * e == arg ? inv_m : 0.f;
-                continue;
             }
-            mx = wave_max(mx);
-            float sum = 0.f;
+        if constexpr (!APART) {
+            if (row >= a.n) continue;
 #pragma unroll
             for (int e = 0; e < PER; e++) {
                 const int c = lane + 64 * e;
-                v[e] = c < classes ? expf(v[e] - mx) : 0.f;
-                sum += v[e];
+                if (c < classes) y[row * classes + c] = acc[e];
             }
-            sum = wave_sum(sum);
-            const float wm = RULE == COMBINE_WEIGHTED ? weights[m] : inv_m;
-#pragma unroll
-            for (int e = 0; e < PER; e++) acc[e] += (v[e] / sum) * wm;
-        }
-#pragma unroll
-        for (int e = 0; e < PER; e++) {
-            const int c = lane + 64 * e;
-            if (c < classes) y[row * classes + c] = acc[e];
+        } else {
+            __syncthreads();
+            if (row < a.n)
+                for (int c = first * 64 + lane; c < classes; c += waves * 64) {
+                    float sum = 0.f;
+                    for (int m = 0; m < n_members; m++) sum = fmaf(terms[(r * n_members + m) * classes + c], share(m), sum);
+                    y[row * classes + c] = sum;
+                }
+            __syncthreads();
         }
     }
 }
 
+template <int PER, int RULE>
+static void launch_combine_per(const CombineArgs& a, hipStream_t s) {
+    const int terms = a.n_members * a.classes;           // (64 members of 2 048 classes at most)
+    const bool apart = a.n_members > 1 && terms <= COMBINE_TERMS;
+    const int waves = apart ? std::min(a.n_members, COMBINE_WAVES) : 1, rows = apart ? std::max(1, std::min(4 / waves, COMBINE_TERMS / terms)) : 4;
+    const long long blocks = (a.n + rows - 1) / rows;
+    const dim3 g((unsigned)(blocks < COMBINE_MAX_BLOCKS ? blocks : COMBINE_MAX_BLOCKS)), b(64 * waves * rows);
+    if (apart) ENS_LAUNCH((combine_kernel<PER, RULE, true>), g, b, (size_t)rows * terms * sizeof(float), s, a, waves, rows);
+    else ENS_LAUNCH((combine_kernel<PER, RULE, false>), g, b, 0, s, a, waves, rows);
+}
+
 template <int RULE>
 static void launch_combine_rule(const CombineArgs& a, hipStream_t s) {
-    const long long blocks = (a.n + 3) / 4;
-    const dim3 g((unsigned)(blocks < COMBINE_MAX_BLOCKS ? blocks : COMBINE_MAX_BLOCKS)), b(256);
     const int per = (a.classes + 63) / 64;
-    if (per <= 1) ENS_LAUNCH((combine_kernel<1, RULE>), g, b, 0, s, a);
-    else if (per <= 4) ENS_LAUNCH((combine_kernel<4, RULE>), g, b, 0, s, a);
-    else if (per <= 16) ENS_LAUNCH((combine_kernel<16, RULE>), g, b, 0, s, a);
-    else ENS_LAUNCH((combine_kernel<32, RULE>), g, b, 0, s, a);
+    if (per <= 1) launch_combine_per<1, RULE>(a, s);
+    else if (per <= 4) launch_combine_per<4, RULE>(a, s);
+    else if (per <= 16) launch_combine_per<16, RULE>(a, s);
+    else launch_combine_per<32, RULE>(a, s);
 }
 
 hipError_t launch_combine(const CombineArgs& a, hipStream_t s) {

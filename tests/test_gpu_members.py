@@ -235,6 +235,33 @@ def test_vote_bf16_resnets(ens):
     assert np.array_equal(y[clear], oracle.combine_vote(z)[clear].astype(np.float32))
 
 
+# one member; a wavefront per member with several rows at a time and with one; more members than wavefronts; more terms than LDS holds; classes
+# at the edges of a wavefront's lanes; one image, and more rows than workgroups
+@pytest.mark.parametrize("members,classes,n", [(1, 65, 5), (2, 64, 4099), (3, 7, 1), (4, 257, 1030), (17, 130, 3), (9, 1707, 2), (8, 1920, 2)], ids=str)
+def test_combination_of_many_shapes(ens, members, classes, n):
+    def head(i):
+        net = N.Net("head%d" % i, 6, 6, classes, dtype="fp32")
+        net.fc(net.gap(net.conv(0, 8, 3)), classes)
+        return net
+    nets = [head(i) for i in range(members)]
+    E = ens.Ensemble(nets, [40.0 * W.make_blob(net, synth.BASE_SEED + 7, i) for i, net in enumerate(nets)])
+    E.ens_set_alloc([[64] * members])
+    imgs = W.make_images(synth.BASE_SEED + 1007, n, 6, 6, varied=True)
+    w = list(np.linspace(0.1, 1.3, members))
+    for rule, kw in (("mean", None), ("weighted", w), ("vote", None)):
+        E.ens_set_combination(rule, kw)
+        y = E.ens_predict(imgs)
+        z = [E.ens_member_logits(m, n) for m in range(members)]
+        probs = [oracle.softmax(v.astype(np.float64), dtype=np.float64) for v in z]
+        if rule == "vote":
+            assert np.array_equal(np.round(y * members), np.round(oracle.combine_vote(z) * members))
+        else:
+            want = oracle.combine_mean(probs, dtype=np.float64) if rule == "mean" else oracle.combine_weighted(probs, w)
+            # exponentials, a quotient and sums of up to 1 920 terms in fp32, a few 2^-24 of a value each
+            assert np.abs(y - want).max() <= 2e-6 * max(1.0, sum(w) if rule == "weighted" else 1.0)
+    E.close()
+
+
 def test_fake_predictor_overhead_run(ens):
     """The overhead experiment of section "Overhead of the inference system": with every forward
     pass replaced by zeros the accumulator still gathers all rows (softmax of zeros: uniform), and
