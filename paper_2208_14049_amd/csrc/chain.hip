@@ -3,7 +3,7 @@
 // One image through a deep member is a chain of 50 to 300 layers of which none fills the GPU, and a launch per layer costs 6 to 10 us
 // however little it does (twelve members, one image: 940 launches on four lanes, 2.97 ms).  Here the workgroups of an XCD, one per
 // compute unit, form a group that takes a member and some images and runs all its layers, with a barrier between layers that
-// depend on each other, and the eight groups take such programs from one queue, the longest first (1.27 ms).  The group's compute units
+// depend on each other, and the eight groups take such programs from one queue, the longest first (1.19 ms).  The group's compute units
 // share an L2: stores need only reach it (s_waitcnt vmcnt(0)), loads of what others stored bypass the L1 (device scope, sc1: 3.6 TB/s an XCD
 // from the L2 with it and without), and a barrier of the 32 workgroups is an atomic and a poll there, 1.0 us (over all eight XCDs it is 4 us,
 // and data would have to go through memory).
@@ -76,18 +76,21 @@ __device__ __forceinline__ u32x4 ch_pack(const float* f) {
     return u32x4{pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7])};
 }
 
-// The group's barrier, in two halves.  While the first wavefront waits, the others have the weights of the phase after the one that is
-// about to begin brought into the L2 (and its steps into the scalar cache), which hides the memory's latency behind a whole phase.
+// The group's barrier, in two halves, and what the phases to come need: the steps of the phase after the next one, and the next one's weights,
+// which are brought into the L2 (a word of each line, dealt to the group's threads).  Loads come back in the order they were asked for, so
+// whatever a wavefront asks for behind those waits for the memory too.  A workgroup that has to wait at the barrier asks for them there; one that
+// comes last, and that the others will wait for next, behind its loads of the phase.  (Asked for by all in front of the barrier, the workgroups
+// with a share of them came 1 to 3 us later than the others in every phase; twelve members, one image and two: 1.24 and 1.67 ms, now 1.19 and 1.63.)
 constexpr int CH_AHEAD = 2;
 struct ChainGroup {
     unsigned* arrived;
     unsigned target, size, ticket;
-    unsigned* misc;                                  // LDS: [0] verdict of the wait
+    unsigned* misc;                                  // LDS: [0] is everybody there, [5] verdict of the wait
     int* steps;                                      // LDS: the steps of this phase and of the next one, CHAIN_PHASE_STEPS each
     const int* next;                                 // the next phase's steps in memory
     int next_n, at;                                  // how many; which half of `steps` is this phase's
     bool pending;                                    // arrived at and not waited for yet
-    bool dead, loaded;
+    bool dead, fetched;                              // fetched: what the phases to come need has been asked for
     int word;                                        // of the next phase's steps, on its way to LDS
     unsigned ahead[CH_AHEAD];                        // what was touched
 
@@ -97,42 +100,50 @@ struct ChainGroup {
 #pragma unroll
         for (int i = 0; i < CH_AHEAD; i++) asm volatile("" ::"v"(ahead[i]));
         at ^= 1;
-        if (loaded && threadIdx.x >= 64 && (int)threadIdx.x - 64 < next_n * 64) steps[at * CHAIN_PHASE_STEPS * 64 + threadIdx.x - 64] = word;
-        loaded = false;
+        if (fetched && threadIdx.x >= 64 && (int)threadIdx.x - 64 < next_n * 64) steps[at * CHAIN_PHASE_STEPS * 64 + threadIdx.x - 64] = word;
+        fetched = false;
         __syncthreads();
         if (threadIdx.x == 0) (void)__hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);   // at the group's L2
         target += size;
         pending = true;
     }
-    __device__ __forceinline__ void wait(const Step s0) {         // s0: the first step of the phase
+    __device__ __forceinline__ void prefetch(const Step s0) {     // s0: the first step of the phase
+        if (fetched) return;
+        fetched = true;
+        if (threadIdx.x < 64) return;                            // (the first wavefront polls)
+        const int idx = (int)threadIdx.x - 64;
+        static_assert(CHAIN_PHASE_STEPS * 64 <= CHAIN_THREADS - 64, "a dword each");
+        if (idx < next_n * 64) word = ENS_GLOBAL(int, next)[idx];
+        const unsigned first = ticket * (CHAIN_THREADS - 64) + idx, all = size * (CHAIN_THREADS - 64);
+        const char* const w0 = (const char*)st_long(s0, offsetof(ChainStep, ahead) / 4);
+        const char* const w1 = (const char*)st_long(s0, offsetof(ChainStep, ahead) / 4 + 2);
+        const unsigned n0 = (unsigned)st_int(s0, offsetof(ChainStep, ahead_bytes) / 4) / 128u, n1 = (unsigned)st_int(s0, offsetof(ChainStep, ahead_bytes) / 4 + 1) / 128u;
+        if (first < n0) ahead[0] = *ENS_GLOBAL(unsigned, w0 + (size_t)first * 128);
+        if (n1) {
+            if (first < n1) ahead[1] = *ENS_GLOBAL(unsigned, w1 + (size_t)first * 128);
+        } else if (first + all < n0) {
+            ahead[1] = *ENS_GLOBAL(unsigned, w0 + (size_t)(first + all) * 128);
+        }
+    }
+    __device__ __forceinline__ bool all_there() const { return (int)(__hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) >= 0; }
+    __device__ __forceinline__ void wait(const Step s0) {
         if (!pending) return;
         pending = false;
-        loaded = true;
-        if (threadIdx.x >= 64) {
-            const int idx = (int)threadIdx.x - 64;
-            static_assert(CHAIN_PHASE_STEPS * 64 <= CHAIN_THREADS - 64, "a dword each");
-            if (idx < next_n * 64) word = ENS_GLOBAL(int, next)[idx];
-            const unsigned first = ticket * (CHAIN_THREADS - 64) + idx, all = size * (CHAIN_THREADS - 64);
-            const char* const w0 = (const char*)st_long(s0, offsetof(ChainStep, ahead) / 4);
-            const char* const w1 = (const char*)st_long(s0, offsetof(ChainStep, ahead) / 4 + 2);
-            const unsigned n0 = (unsigned)st_int(s0, offsetof(ChainStep, ahead_bytes) / 4) / 128u, n1 = (unsigned)st_int(s0, offsetof(ChainStep, ahead_bytes) / 4 + 1) / 128u;
-            if (first < n0) ahead[0] = *ENS_GLOBAL(unsigned, w0 + (size_t)first * 128);
-            if (n1) {
-                if (first < n1) ahead[1] = *ENS_GLOBAL(unsigned, w1 + (size_t)first * 128);
-            } else if (first + all < n0) {
-                ahead[1] = *ENS_GLOBAL(unsigned, w0 + (size_t)(first + all) * 128);
-            }
-        } else if (threadIdx.x == 0) {
+        if (threadIdx.x == 0) misc[0] = all_there();
+        __syncthreads();
+        if (misc[0]) return;
+        if (threadIdx.x == 0) {
             unsigned ok = 0;
             // Every workgroup of the group is running, so this ends; the limit (seconds) is for a mistake elsewhere
             for (int i = 0; i < (1 << 23); i++) {
-                if ((int)(__hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) >= 0) { ok = 1; break; }
+                if (all_there()) { ok = 1; break; }
                 __builtin_amdgcn_s_sleep(1);
             }
-            misc[0] = ok;
+            misc[5] = ok;
         }
+        prefetch(s0);
         __syncthreads();
-        if (!misc[0]) dead = true;
+        if (!misc[5]) dead = true;
     }
 };
 
@@ -356,6 +367,7 @@ __device__ __forceinline__ void chain_conv(const Step s, const Step s0_, char* c
         chunk(std::integral_constant<int, 0>{}, m);
         if (m + 1 < m1) chunk(std::integral_constant<int, 1>{}, m + 1);
     }
+    group.prefetch(s0_);
     // ---- the partial tiles, [pixel][channel] in groups of four that are shuffled by pixel, each wavefront's in its part of LDS
     float* const part = (float*)mine;
     if (live) {
@@ -965,6 +977,7 @@ __global__ __launch_bounds__(CHAIN_THREADS) void chain_kernel(const ChainArgs a_
                     done += units;
                 }
                 group.wait(s0);                      // also without a unit: nobody arrives twice
+                group.prefetch(s0);
                 if (ph + 1 == phases && ticket == 0 && t == 0) {
                     const unsigned next = __hip_atomic_fetch_add(&a.sync->queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     __hip_atomic_store(&g.program, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -973,7 +986,7 @@ __global__ __launch_bounds__(CHAIN_THREADS) void chain_kernel(const ChainArgs a_
             }
             group.next_n = 0;
             group.wait(Step{0});
-            group.loaded = false;
+            group.fetched = false;
             if (t == 0) misc[3] = __hip_atomic_load(&g.program, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
             program = __builtin_amdgcn_readfirstlane(misc[3]);

@@ -1572,7 +1572,7 @@ static double launches_seconds(ens_handle* h, int64_t n) {
 }
 
 // How a request of n images is cut into programs, or null when it goes launch by launch.  Measured both ways over six ensembles on 1 to 12
-// images (us, launches / chains): twelve members on 1, 2, 4 and 8 images 2967 / 1269, 3171 / 1712, 3637 / 2537 and 4414 / 4444; four members
+// images (us, launches / chains): twelve members on 1, 2, 4 and 8 images 2967 / 1195, 3171 / 1640, 3637 / 2560 and 4414 / 4444; four members
 // 825 / 637, 885 / 650, 1032 / 781 and 1338 / 1185; a ResNet-50 alone 334 / 394, 348 / 391, 385 / 391 and 469 / 426; three ResNet-18, whose launches
 // carry all three, 188 / 201 and 337 / 356 (1 and 8 images).  The estimates of chains are 10 to 20 % low: hence the margin, which leaves to the
 // launches what comes out even.
