@@ -467,6 +467,7 @@ const char* conv_bf16_variant_name(const ConvArgs& a, int G) {
     if (a.pair) return VARIANTS[pick_variant(a, P, (long long)a.kh * a.kw * a.cin, G)].name;
     if (conv_pw_applicable(a, a.nb, G)) return conv_pw_name(a, G);
     if (conv_taps_applicable(a, a.nb)) return conv_taps_name(a);
+    if (conv_narrow_applicable(a, a.nb, G)) return conv_narrow_name(a);
     if (conv_wreg_applicable(a, a.nb, G)) return conv_wreg_name(a);
     if (const int hv = conv_halo_pick(a, a.nb, G); hv >= 0) return conv_halo_name(hv);
     return VARIANTS[pick_variant(a, P, (long long)a.kh * a.kw * a.cin, G)].name;
@@ -520,6 +521,7 @@ hipError_t launch_conv_bf16(const ConvArgs& a, const ConvArgs* argv, int G, int 
     if (!a.pair) {                                               // the generic kernel takes pairs
         if (conv_pw_applicable(a, nb, G)) return launch_conv_pw(a, argv, G, nb, s);
         if (conv_taps_applicable(a, nb)) return launch_conv_taps(a, argv, G, nb, s);
+        if (conv_narrow_applicable(a, nb, G)) return launch_conv_narrow(a, argv, G, nb, s);
         if (conv_wreg_applicable(a, nb, G)) return launch_conv_wreg(a, argv, G, nb, s);
         if (const int hv = conv_halo_pick(a, nb, G); hv >= 0) return launch_conv_halo(a, argv, G, nb, hv, s);
     }

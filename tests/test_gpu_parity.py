@@ -261,6 +261,25 @@ def test_conv_layer_bf16(ens, case, nb):
     assert err.mean() <= 2.0 ** -8 * scale, (err.mean(), scale, kk)
 
 
+# Layers from 32 channels to 32, as grouped convolutions are cut into, with the filter in registers: more tiles of 256 positions than workgroups (on
+# the per-XCD runs and without), a last tile that is partly empty, rows of one pixel and the widest that the window's table holds, maps of odd
+# sides whose tiles span images, parts of 4, 8 and 32 groups, and rows a pixel wider, which the generic kernel keeps.
+NARROW = "conv3x3_narrow_bf16<256,c32>"
+
+
+@pytest.mark.parametrize("case,nb", [
+    ((56, 56, 128, 128, 3, 1, "same", {"groups": 32, "ran": NARROW}), 24),
+    ((28, 28, 64, 64, 3, 1, "same", {"groups": 16, "ran": NARROW, "act": "silu"}), 130),
+    ((14, 13, 512, 512, 3, 1, "same", {"groups": 64, "ran": NARROW, "act": None}), 21),
+    ((7, 7, 1024, 1024, 3, 1, "same", {"groups": 32, "ran": NARROW, "bn": False}), 33),
+    ((40, 126, 32, 32, 3, 1, "same", {"ran": NARROW}), 24),
+    ((300, 1, 32, 32, 3, 1, "same", {"ran": NARROW}), 400),
+    ((40, 127, 32, 32, 3, 1, "same", {"ran": "conv_igemm_bf16<128,32,k64>"}), 24),
+], ids=lambda c: "%dx%dx%d" % c[:3] if isinstance(c, tuple) else "n%d" % c)
+def test_filter_in_registers_32_channels(ens, case, nb):
+    test_conv_layer_bf16(ens, case, nb)
+
+
 def test_two_convolutions_in_one_launch(ens):
     """A residual block's strided 3x3 convolution and its 1x1 shortcut read the same tensor and write
     same-sized outputs: the engine runs them as one launch (argument blocks of both).  Both outputs
