@@ -58,7 +58,6 @@ __global__ __launch_bounds__(SP_T) void stem_pool_bf16(const ConvArgs* __restric
     constexpr int BP = SP_BP, BC = 64, NT = KH * KW;
 
     const int W1 = a.W + gw;
-    const float inv_w1 = __builtin_amdgcn_rcpf((float)W1);
     const int PH = pool.Ho, PW = pool.Wo;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -150,6 +149,17 @@ __global__ __launch_bounds__(SP_T) void stem_pool_bf16(const ConvArgs* __restric
         task_y[j] = ((jr * PW + pc) * pool.y.stride + pool.y.c0 + c0 + 8 * g) * 2;
     }
 
+    // Where the taps of this lane's position lie in a sub-tile's window, and the position itself, are the same in every sub-tile and band but for
+    // a sum (a sub-tile's 128 rows are a multiple of the swizzle's sixteen).  Worked out again for every tap and sub-tile they were half of the
+    // vector instructions, and the vector units are the busiest here: three members with 32 images of 224 x 224 each 80.4 -> 74.4 us, one with 128 94.8 -> 86.7, three with 8 28.1 -> 25.8.
+    uint32_t xoff[NT];
+#pragma unroll
+    for (int tap = 0; tap < NT; tap++) {
+        const uint32_t q = (uint32_t)(wp0 + lrow + (tap / KW) * W1 + tap % KW);
+        xoff[tap] = q * 32 + ((((uint32_t)lhalf) ^ ((q >> 3) & 1)) << 4);
+    }
+    const int adv_h = BP / W1, adv_w = BP - adv_h * W1, dr0 = (wp0 + lrow) / W1, dc0 = wp0 + lrow - dr0 * W1;
+
     // Per band: its window has landed; ask for the next band's; run the sub-tiles, each wave on
     // its own 32 positions and channels of every sub-tile with no barrier in between; then the maxima.
     for (int buf = 0; band < walk.end; band += walk.step, buf ^= 1) {
@@ -166,13 +176,14 @@ __global__ __launch_bounds__(SP_T) void stem_pool_bf16(const ConvArgs* __restric
         // order: tap t is complete once no more than the reads issued after it are outstanding).  The ring does
         // not live across sub-tiles: a value asked for by hand must not be moved by the compiler while in flight.
         bf16x8 xf[4];
-        auto issue_frag = [&](int sub, auto tap_c) {
+        auto issue_frag = [&](uint32_t at, auto tap_c) {
             constexpr int tap = decltype(tap_c)::value;
-            const uint32_t q = (uint32_t)(sub * BP + wp0 + lrow + (tap / KW) * W1 + tap % KW);
-            xf[tap & 3] = sp_lds_read<0>(halo0 + q * 32 + ((((uint32_t)lhalf) ^ ((q >> 3) & 1)) << 4));
+            xf[tap & 3] = sp_lds_read<0>(at + xoff[tap]);
         };
-        auto run_sub = [&](int sub) {
-            const int q0 = sub * BP + wp0 + lrow;                // this lane's position of the band
+        int dr = dr0, dc = dc0;                                  // this lane's position of the band: its row less the band's first, and column
+        auto run_sub = [&](int sub_no) {
+            const int q0 = sub_no * BP + wp0 + lrow;
+            const uint32_t sub = halo0 + (uint32_t)(sub_no * BP * 32);
             issue_frag(sub, std::integral_constant<int, 0>{});
             issue_frag(sub, std::integral_constant<int, 1>{});
             issue_frag(sub, std::integral_constant<int, 2>{});
@@ -187,11 +198,11 @@ __global__ __launch_bounds__(SP_T) void stem_pool_bf16(const ConvArgs* __restric
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wreg[tap], xf[tap & 3], acc, 0, 0, 0);
                 if constexpr (tap + 4 < NT) issue_frag(sub, std::integral_constant<int, (tap + 4 < NT ? tap + 4 : tap)>{});
             }, std::make_integer_sequence<int, NT>{});
-            // the stem row of this position, less the band's first: a float quotient (exact below 2^24 but for the last unit) and its correction
-            int dr = (int)((float)q0 * inv_w1);
-            int dc = q0 - dr * W1;
-            if (dc < 0) { dr--; dc += W1; } else if (dc >= W1) { dr++; dc -= W1; }
             const bool live = (unsigned)(first_row + dr) < (unsigned)a.Ho && dc < a.Wo;
+            dc += adv_w;                                         // of the next sub-tile
+            const int carry = dc >= W1 ? 1 : 0;
+            dc -= carry ? W1 : 0;
+            dr += adv_h + carry;
             // ---- this sub-tile's stem output into the band's tile: register v of a lane is channel
             //      wc0 + 16(v/8) + 8(lane/32) + v%8 of its position; scale, bias, ReLU, bf16
             unsigned char* const row = ctile + q0 * 128;
