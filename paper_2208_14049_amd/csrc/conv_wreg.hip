@@ -44,9 +44,12 @@ __device__ __forceinline__ void wreg_for_each(F&& f, std::integer_sequence<int, 
     (f(std::integral_constant<int, T>{}), ...);
 }
 
-template <int BP, int WPX, int WCG, bool ROWS>
+// STRIPS: rows of more than 62 pixels would make a window that LDS does not hold twice (nor a thread's row of the table); such a map is walked in
+// strips of `sw` columns, each with its neighbours' columns on both sides, as if every strip were an image of its own.  64 images, us alone, before on
+// the kernel of conv_halo.hip: 224x224x64 609 -> 242, 112x112 64 -> 128 177 -> 119; 16 images 147x147x64 43.0 -> 32.2; one image 224x224x64 16.4 -> 11.3.
+template <int BP, int WPX, int WCG, bool ROWS, bool STRIPS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const int hrows) {
+void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const int hrows, const int strips, const int sw) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     const ConvArgs a = argv[blockIdx.z];
     static_assert(WPX * WCG == 4, "four wavefronts per workgroup");
@@ -56,8 +59,8 @@ void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const i
     constexpr int ROWB = 128, BLK = 32 * ROWB;
     constexpr int NSTEP = 9 * 4;                     // matrix-core steps per tile: 9 taps x 64 channels / 16
 
-    const int W1 = a.W + 1, H1 = a.H + 1;
-    const int PP = nb_ * H1 * W1;
+    const int W1 = STRIPS ? sw + 2 : a.W + 1, H1 = a.H + 1;
+    const int PP = nb_ * (STRIPS ? strips : 1) * H1 * W1;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int px_w = wave % WPX, cg_w = wave / WPX;
@@ -92,6 +95,7 @@ void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const i
     // keeps that position as (image, row, column) and steps it from one of its tiles to the next
     // by a constant, so a table costs a few adds instead of two divisions per entry.
     const int img = H1 * W1;
+    const float inv_strips = 1.f / (float)strips;
     int tn, thi, twi;
     {
         const int pp = ptile * BP - (W1 + 1) + t + img;          // one image further on: never negative
@@ -112,10 +116,18 @@ void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const i
     // writes slot `slot` for the tile the thread's position stands at, then moves on to the next tile
     auto make_table = [&](int slot) {
         if (t < hrows) {
-            const bool ok = (unsigned)tn < (unsigned)nb_ && thi < a.H && twi < a.W;
-            const int pix = (tn * a.H + thi) * a.W + twi;
-            tblx[slot * hrows + t] = ok ? (unsigned)(pix * a.x.stride * 2) : OOBV;
-            tblp[slot * hrows + t] = ok ? pix : -1;
+            if constexpr (STRIPS) {
+                const int n = (int)(((float)tn + 0.5f) * inv_strips), col = (tn - n * strips) * sw + twi - 1;   // (exact: tn is far below 2^22)
+                const bool ok = (unsigned)tn < (unsigned)(nb_ * strips) && thi < a.H && (unsigned)col < (unsigned)a.W;
+                const int pix = (n * a.H + thi) * a.W + col;
+                tblx[slot * hrows + t] = ok ? (unsigned)(pix * a.x.stride * 2) : OOBV;
+                tblp[slot * hrows + t] = ok && twi >= 1 && twi <= sw ? pix : -1;
+            } else {
+                const bool ok = (unsigned)tn < (unsigned)nb_ && thi < a.H && twi < a.W;
+                const int pix = (tn * a.H + thi) * a.W + twi;
+                tblx[slot * hrows + t] = ok ? (unsigned)(pix * a.x.stride * 2) : OOBV;
+                tblp[slot * hrows + t] = ok ? pix : -1;
+            }
         }
         twi += adv_w;
         const int cw = twi >= W1 ? 1 : 0;
@@ -347,8 +359,9 @@ void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const i
 // ---- host side -----------------------------------------------------------------------------
 constexpr int WREG_LDS_LIMIT = 160 * 1024;
 constexpr int WREG_CUS = 256;
+constexpr int WREG_WIDEST = 62, WREG_STRIP = 61;     // 128 + 2 (W + 1) + 2 and 128 + 2 (W + 2) + 2 rows of the window in 256
 
-struct WregPlan { int hrows, wgs; size_t bytes; };
+struct WregPlan { int hrows, wgs, strips, sw; size_t bytes; };
 
 static bool wreg_plan(const ConvArgs& a, int nb, int G, WregPlan* pl) {
     if (a.kh != 3 || a.kw != 3 || a.sh != 1 || a.sw != 1 || a.pt != 1 || a.pl != 1) return false;
@@ -357,10 +370,14 @@ static bool wreg_plan(const ConvArgs& a, int nb, int G, WregPlan* pl) {
     if ((long long)nb * a.H * a.W * a.x.stride * 2 >= 0x7FFFFF00LL) return false;
     if ((long long)nb * a.H * a.W * a.y.stride * 2 >= 0x7FFFFF00LL) return false;
     if (a.res.p && (long long)nb * a.H * a.W * a.res.stride * 2 >= 0x7FFFFF00LL) return false;
-    const long long PP = (long long)nb * (a.H + 1) * (a.W + 1);
-    if (PP >= (1LL << 24)) return false;
     const int bp = 128;
-    const int need = bp + 2 * (a.W + 1) + 2;
+    // strips: as few and as even as can be
+    pl->strips = a.W <= WREG_WIDEST ? 1 : (a.W + WREG_STRIP - 1) / WREG_STRIP;
+    pl->sw = (a.W + pl->strips - 1) / pl->strips;
+    const int w1 = pl->strips > 1 ? pl->sw + 2 : a.W + 1;
+    const long long PP = (long long)nb * pl->strips * (a.H + 1) * w1;
+    if (PP >= (1LL << 24)) return false;
+    const int need = bp + 2 * w1 + 2;
     pl->hrows = (need + 31) / 32 * 32;
     if (pl->hrows > 256) return false;                           // one table row per thread
     // two windows, or one window and the stage the filter passes through, whichever is larger; tables; bias and scale
@@ -383,17 +400,17 @@ bool conv_wreg_applicable(const ConvArgs& a, int nb, int G) {
 
 const char* conv_wreg_name(const ConvArgs&) { return "conv3x3_wreg_bf16<128,c64>"; }
 
-template <bool ROWS>
+template <bool ROWS, bool STRIPS>
 static hipError_t launch_wreg_variant(const ConvArgs& a, const ConvArgs* argv, int G, int nb, const WregPlan& pl, hipStream_t s) {
     static bool raised = false;                                  // LDS above 64 KB has to be asked for once
     if (!raised) {
-        hipError_t e = hipFuncSetAttribute((const void*)&conv3x3_wreg_bf16<128, 2, 2, ROWS>,
+        hipError_t e = hipFuncSetAttribute((const void*)&conv3x3_wreg_bf16<128, 2, 2, ROWS, STRIPS>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, WREG_LDS_LIMIT);
         if (e != hipSuccess) return e;
         raised = true;
     }
     const dim3 grid((unsigned)pl.wgs, (unsigned)((a.cout + 63) / 64), G);
-    ENS_LAUNCH((conv3x3_wreg_bf16<128, 2, 2, ROWS>), grid, dim3(256), pl.bytes, s, argv, nb, pl.hrows);
+    ENS_LAUNCH((conv3x3_wreg_bf16<128, 2, 2, ROWS, STRIPS>), grid, dim3(256), pl.bytes, s, argv, nb, pl.hrows, pl.strips, pl.sw);
     return hipGetLastError();
 }
 
@@ -402,7 +419,8 @@ hipError_t launch_conv_wreg(const ConvArgs& a, const ConvArgs* argv, int G, int 
     if (!wreg_plan(a, nb, G, &pl)) return hipErrorInvalidValue;
     if (a.x.stride % 8 || a.x.c0 % 8 || a.y.stride % 8 || a.y.c0 % 8) return hipErrorInvalidValue;
     if (a.res.p && (a.res.stride % 8 || a.res.c0 % 8)) return hipErrorInvalidValue;
-    return rows_wanted() ? launch_wreg_variant<true>(a, argv, G, nb, pl, s) : launch_wreg_variant<false>(a, argv, G, nb, pl, s);
+    if (pl.strips > 1) return rows_wanted() ? launch_wreg_variant<true, true>(a, argv, G, nb, pl, s) : launch_wreg_variant<false, true>(a, argv, G, nb, pl, s);
+    return rows_wanted() ? launch_wreg_variant<true, false>(a, argv, G, nb, pl, s) : launch_wreg_variant<false, false>(a, argv, G, nb, pl, s);
 }
 
 }  // namespace ens

@@ -280,6 +280,22 @@ def test_filter_in_registers_32_channels(ens, case, nb):
     test_conv_layer_bf16(ens, case, nb)
 
 
+# 64-channel layers in strips of columns: the widest rows that need none, two strips of 32 and 31, three with a last one that is narrower, rows of whole
+# strips, a second and a half-empty channel tile, a residual, and one image (fewer tiles than workgroups).
+WREG = "conv3x3_wreg_bf16<128,c64>"
+
+
+@pytest.mark.parametrize("case,nb", [
+    ((33, 62, 64, 64, 3, 1, "same", {"ran": WREG}), 9),
+    ((33, 63, 64, 64, 3, 1, "same", {"ran": WREG, "res": True}), 9),
+    ((20, 143, 64, 96, 3, 1, "same", {"ran": WREG, "act": "silu"}), 7),
+    ((9, 122, 64, 160, 3, 1, "same", {"ran": WREG, "act": None}), 40),
+    ((224, 224, 64, 64, 3, 1, "same", {"ran": WREG}), 1),
+], ids=lambda c: "%dx%dx%d" % c[:3] if isinstance(c, tuple) else "n%d" % c)
+def test_filter_in_registers_strips(ens, case, nb):
+    test_conv_layer_bf16(ens, case, nb)
+
+
 def test_two_convolutions_in_one_launch(ens):
     """A residual block's strided 3x3 convolution and its 1x1 shortcut read the same tensor and write
     same-sized outputs: the engine runs them as one launch (argument blocks of both).  Both outputs
