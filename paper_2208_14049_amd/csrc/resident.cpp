@@ -6,7 +6,7 @@
 
 namespace ens {
 
-bool build_resident(const Member& m, Resident* out) {
+static bool build(const Member& m, Resident* out, bool pairs) {
     if (m.bf16 || m.ops.size() > RESIDENT_MAX_OPS) return false;
     const int NT = (int)m.tensors.size(), NO = (int)m.ops.size();
     // what a convolution's taps reach around a tensor
@@ -68,17 +68,25 @@ bool build_resident(const Member& m, Resident* out) {
         r.H = ts.h; r.W = ts.w; r.cin = o.cin; r.Ho = td.h; r.Wo = td.w; r.cout = o.cout;
         r.kh = o.kh; r.kw = o.kw; r.sh = o.sh; r.sw = o.sw; r.pt = o.pt; r.pl = o.pl; r.act = o.act;
         if (o.kind == ENS_OP_CONV) {
-            const int K = o.kh * o.kw * o.cin, steps = (K + 3) / 4, tiles = o.cout > 16 ? (o.cout + 31) / 32 * 2 : 1;   // in pairs where there are several
+            // Up to eight channels leave half of a tile's rows empty: two neighbouring pixels share it, with a column of the filter more.  (A weight of zero
+            // meets a pixel of the neighbour's then, which only the request's images are known to have finite: resident_kernel.)
+            const bool pair = pairs && o.src == 0 && o.cout <= 8 && o.kw > 1 && o.sw == 1 && (pool[i] == RS_MAX_POOL || pool[i] == RS_AVG_POOL);
+            const int kw = o.kw + (pair ? 1 : 0), K = o.kh * kw * o.cin, steps = (K + 3) / 4, tiles = o.cout > 16 ? (o.cout + 31) / 32 * 2 : 1;   // in pairs where there are several
             if ((size_t)tiles * steps * 64 > RESIDENT_LDS / 4) return false;
             r.steps = steps;
             r.w = (int)fixed.size();
             fixed.resize(fixed.size() + (size_t)tiles * steps * 64, 0.f);
             const float* const w = P + pl.w / 4;                 // [K][cout]
-            for (int k = 0; k < K; k++)
-                for (int c = 0; c < o.cout; c++) fixed[(size_t)r.w + ((size_t)(c / 16) * steps * 4 + k) * 16 + c % 16] = w[(size_t)k * o.cout + c];
+            r.pair = pair;
+            for (int k = 0; k < o.kh * o.kw * o.cin; k++)
+                for (int c = 0; c < o.cout; c++) {
+                    const int at = (k / (o.kw * o.cin) * kw + k / o.cin % o.kw) * o.cin + k % o.cin;
+                    fixed[(size_t)r.w + ((size_t)(c / 16) * steps * 4 + at) * 16 + c % 16] = w[(size_t)k * o.cout + c];
+                    if (pair) fixed[(size_t)r.w + (size_t)(at + o.cin) * 16 + 8 + c] = w[(size_t)k * o.cout + c];
+                }
             r.taps = (int)fixed.size();                          // filled in when the tensors have their places
             fixed.resize(fixed.size() + (size_t)steps * 4, 0.f);
-            macs += (double)td.h * td.w * tiles * 16 * steps * 4;
+            macs += (double)td.h * td.w / (pair ? 2 : 1) * tiles * 16 * steps * 4;
         }
         if (o.kind == ENS_OP_FC) {
             if ((size_t)o.cin * o.cout > RESIDENT_LDS / 4) return false;
@@ -96,6 +104,8 @@ bool build_resident(const Member& m, Resident* out) {
     // tensors: those with a border for themselves (the zeros stay), the others where memory is free while they live
     struct Place { int at = -1, p = 0, r = 0, floats = 0; };
     std::vector<Place> place(NT);
+    bool fours = false;                              // pooling reads pixels of whole fours
+    for (int i = 0; i < NO; i++) fours |= m.ops[i].op.src == 0 && !gone[i] && (m.ops[i].op.kind == ENS_OP_MAXPOOL || m.ops[i].op.kind == ENS_OP_AVGPOOL);
     int top = (int)fixed.size();
     for (int pass = 0; pass < 2; pass++) {
         const int floor = top;
@@ -104,7 +114,7 @@ bool build_resident(const Member& m, Resident* out) {
             if (t == m.out_tensor || pad[t].any() != (pass == 0)) continue;
             const TensorInfo& ti = m.tensors[t];
             Place& q = place[t];
-            q.p = ti.h * ti.w == 1 ? (ti.c + 3) / 4 * 4 : pitch(ti.c);
+            q.p = t == 0 && !fours ? ti.c : ti.h * ti.w == 1 ? (ti.c + 3) / 4 * 4 : pitch(ti.c);
             q.r = (ti.w + pad[t].l + pad[t].r) * q.p;
             q.floats = (ti.h + pad[t].t + pad[t].b) * q.r + 4;
             q.floats = (q.floats + 3) / 4 * 4;
@@ -148,9 +158,9 @@ bool build_resident(const Member& m, Resident* out) {
             r.yp = d.p; r.yr = d.r;
         }
         if (o.kind == ENS_OP_CONV)
-            for (int k = 0; k < o.kh * o.kw * o.cin; k++) {
+            for (int k = 0, kw = o.kw + r.pair; k < o.kh * kw * o.cin; k++) {
                 const int c = k % o.cin, tap = k / o.cin;
-                const int v = tap / o.kw * s.r + tap % o.kw * s.p + c;
+                const int v = tap / kw * s.r + tap % kw * s.p + c;
                 memcpy(&fixed[(size_t)r.taps + k], &v, 4);
             }
     }
@@ -165,6 +175,10 @@ bool build_resident(const Member& m, Resident* out) {
     // the matrix cores' 256 operations a clock and compute unit, and the steps between
     out->seconds = 2.0 * macs / 614e9 / 0.6 + 1e-6 * NO;
     return true;
+}
+
+bool build_resident(const Member& m, Resident* out) {
+    return build(m, out, true) || build(m, out, false);          // (the pairs' weights are larger)
 }
 
 }  // namespace ens

@@ -19,6 +19,8 @@ struct alignas(256) ResidentOp {
     int w, bias, taps;         // LDS: weights in tiles [16 channels][K][16] (FC: [K][cout]), biases, place of each k from the first tap's
     int pool;                  // convolution: what follows it in the same operation, RS_*_POOL: Ho x Wo is what that leaves
     int sums, sums_p;          // RS_MEAN_POOL: LDS for a row of sums per unit
+    int pair;                  // weights and places for two neighbouring pixels at once: kh * (kw + 1) * cin of them, rows 0..7 and 8..15 the channels of either
+    int odd;                   // of operation 0: one more than the last image with an infinity or a NaN
 };
 static_assert(sizeof(ResidentOp) == 256, "a dword for each lane");
 

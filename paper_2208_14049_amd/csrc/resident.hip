@@ -8,17 +8,19 @@
 // channels in steps of four.  The value a lane needs for its k is at a distance from the first tap's that is the same for every pixel: a
 // table in LDS.  Tensors that a padded convolution reads have a border of zeros of their own, so that no tap is outside.
 //
-// Measured, two members of 32 x 32 images: 8 images 61 -> 33 us, 1 000 images in batches of 8 2.5 ms -> 117 us, 8 192 images 2.84 -> 0.71 ms.  A first
+// Measured, two members of 32 x 32 images: 8 images 61 -> 32 us, 1 000 images in batches of 8 2.5 ms -> 117 us, 8 192 images 2.84 -> 0.61 ms.  A first
 // form kept every map in LDS (convolution, barrier, pooling): one workgroup a compute unit, 1.50 ms; with windows and means taken in
-// registers and the next image's pixels asked for ahead two of them fit.
-// No unit is full now (counters, 8 100 images): the matrix cores are busy 0.47 of the time, a fifth of that for channels and pixels that are padding, LDS
-// 0.47, half of that bank conflicts.  Of a wavefront's time 0.22 issues, 0.49 waits for its turn to issue (a matrix instruction holds its pipe for 32 clocks; for
-// LDS alone it is 0.02) and 0.29 for data and at barriers.
+// registers and the next image's pixels asked for ahead two of them fit.  8 100 images on the device, us, step by step: 710; the request's pixels three floats
+// apart instead of four (windows two pixels apart then lie on different banks) 699; two pixels of up to eight channels in a tile 628; the steps
+// behind the last whole four asked for at once, sums over lanes without LDS, 16 lanes a class 607.
+// No unit is full: the matrix cores are busy half of the time; of a wavefront's time 0.22 issues, 0.49 waits for its turn to issue (a matrix instruction
+// holds its pipe for 32 clocks; for LDS alone it is 0.02) and 0.29 for data and at barriers (counters of the 710 us form).
 #include "resident.h"
 #include "conv_common.h"
 #include "stage.h"
 
 #include <cstddef>
+#include <type_traits>
 
 namespace ens {
 
@@ -33,6 +35,16 @@ __device__ __forceinline__ int rs_div(int p, int d, float inv) {
     int q = (int)((float)p * inv);
     const int r = p - q * d;
     return q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
+}
+
+// the sum over 16 lanes side by side, in each of them
+__device__ __forceinline__ float rs_sum16(float v) {
+    auto from = [](float x, auto n) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + decltype(n)::value, 0xF, 0xF, false)); };   // row_ror
+    v += from(v, std::integral_constant<int, 8>{});
+    v += from(v, std::integral_constant<int, 4>{});
+    v += from(v, std::integral_constant<int, 2>{});
+    v += from(v, std::integral_constant<int, 1>{});
+    return v;
 }
 
 // PT x 16 pixels times CT x 16 channels at a time.  POOL: a lane's pixels are the four of a 2 x 2 window, whose maximum or mean is what leaves the
@@ -95,18 +107,27 @@ __device__ __forceinline__ void rs_conv(const int op, float* const lds) {
 #pragma unroll
                     for (int j = 0; j < PT; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][i], b[q][j], acc[i][j], 0, 0, 0);
         }
-        for (int s = whole; s < steps; s++) {                    // (behind K: a weight of zero times what is there could be a NaN)
-            const bool ok = 4 * s + kq < K;
-            const int o = taps[4 * s];
-            float a[CT], b[PT];
+        if (whole < steps) {                                     // (behind K: a weight of zero times what is there could be a NaN)
+            float a[U][CT], b[U][PT];
 #pragma unroll
-            for (int j = 0; j < PT; j++) b[j] = x[j][ok ? o : 0];
+            for (int q = 0; q < U; q++) {
+                const bool ok = 4 * (whole + q) + kq < K;
 #pragma unroll
-            for (int i = 0; i < CT; i++) a[i] = w[(i * steps + s) * 64];
+                for (int j = 0; j < PT; j++) {
+                    const float v = x[j][ok ? off[q] : 0];
+                    b[q][j] = ok ? v : 0.f;
+                }
 #pragma unroll
-            for (int i = 0; i < CT; i++)
+                for (int i = 0; i < CT; i++) a[q][i] = w[(i * steps + min(whole + q, steps - 1)) * 64];
+            }
 #pragma unroll
-                for (int j = 0; j < PT; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], ok ? b[j] : 0.f, acc[i][j], 0, 0, 0);
+            for (int q = 0; q < U; q++) {
+                if (whole + q >= steps) break;
+#pragma unroll
+                for (int i = 0; i < CT; i++)
+#pragma unroll
+                    for (int j = 0; j < PT; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][i], b[q][j], acc[i][j], 0, 0, 0);
+            }
         }
         // register v of a lane: channel 4 (lane / 16) + v of pixel lane % 16; whole fours are written (a pixel has room for them)
 #pragma unroll
@@ -134,9 +155,7 @@ __device__ __forceinline__ void rs_conv(const int op, float* const lds) {
 #pragma unroll
                     for (int e = 0; e < 4; e++) r[e] += yo[j] >= 0 ? v[j][e] : 0.f;
 #pragma unroll
-                for (int off = 8; off > 0; off >>= 1)
-#pragma unroll
-                    for (int e = 0; e < 4; e++) r[e] += __shfl_xor(r[e], off, 64);
+                for (int e = 0; e < 4; e++) r[e] = rs_sum16(r[e]);
                 if (l16 == 0 && c < cout) *(f32x4*)(lds + RS(sums) + pt * RS(sums_p) + c) = r;
             } else if (c < cout) {
 #pragma unroll
@@ -148,11 +167,124 @@ __device__ __forceinline__ void rs_conv(const int op, float* const lds) {
     if constexpr (FORM == RS_MEAN) {                 // the units' sums in order
         __syncthreads();
         const int n = (P + EACH - 1) / EACH;
+        const int sums_p = RS(sums_p);
+        const float *const sums = lds + RS(sums);
+        float* const y = lds + RS(y);
         for (int c = t; c < cout; c += RESIDENT_THREADS) {
             float sum = 0.f;
-            for (int q = 0; q < n; q++) sum += lds[RS(sums) + q * RS(sums_p) + c];
-            lds[RS(y) + c] = sum / (float)P;
+#pragma unroll 8
+            for (int q = 0; q < n; q++) sum += sums[q * sums_p + c];
+            y[c] = sum / (float)P;
         }
+    }
+}
+
+// Up to eight channels and windows of 2 x 2: the rows of a tile are the channels of the windows' left pixels and of their right ones, its columns
+// 16 windows, and K a column of the filter longer: kh * (kw + 1) * cin for half the tiles (5 x 5 x 3 to 8 channels on 32 x 32: 736 matrix instructions
+// instead of 1 216).  Four tiles at a time: 32 windows, both their rows.
+__device__ __forceinline__ void rs_conv_pair(const int op, float* const lds) {
+    const int t = threadIdx.x, lane = t & 63, l16 = lane & 15, kq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int Wo = RS(Wo), P = RS(Ho) * Wo, cout = RS(cout), steps = RS(steps), K = RS(kh) * (RS(kw) + 1) * RS(cin), xs = RS(xp), xrs = RS(xr) * RS(sh), act = RS(act);
+    const float inv = __builtin_amdgcn_rcpf((float)Wo);
+    const int* const taps = (const int*)lds + RS(taps) + kq;
+    const float* const w = lds + RS(w) + kq * 16 + l16;
+    const bool is_max = RS(pool) == RS_MAX_POOL;
+    for (int u = wave; u < (P + 31) / 32; u += RESIDENT_THREADS / 64) {
+        const float* x[4];
+        int yo = -1;                                 // of the window that this lane writes: the first 16 are the lower half's
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            const int p = u * 32 + j * 16 + l16, pc = min(p, P - 1), ho = rs_div(pc, Wo, inv), wo = pc - ho * Wo;
+            x[2 * j] = lds + RS(x) + 2 * ho * xrs + 2 * wo * xs;
+            x[2 * j + 1] = x[2 * j] + xrs;
+            if (j == kq >> 1 && p < P) yo = RS(y) + ho * RS(yr) + wo * RS(yp);
+        }
+        f32x4 acc[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // four steps at a time, the places of the next four on their way
+        constexpr int U = 4;
+        const int whole = K / (4 * U) * U;
+        int off[U];
+#pragma unroll
+        for (int q = 0; q < U; q++) off[q] = taps[4 * q];        // (behind the table lie other words of LDS)
+        for (int s = 0; s < whole; s += U) {
+            float a[U], b[U][4];
+#pragma unroll
+            for (int q = 0; q < U; q++) {
+#pragma unroll
+                for (int j = 0; j < 4; j++) b[q][j] = x[j][off[q]];
+                a[q] = w[(s + q) * 64];
+            }
+#pragma unroll
+            for (int q = 0; q < U; q++) off[q] = taps[4 * (s + U + q)];
+#pragma unroll
+            for (int q = 0; q < U; q++)
+#pragma unroll
+                for (int j = 0; j < 4; j++) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[q][j], acc[j], 0, 0, 0);
+        }
+        if (whole < steps) {                                     // (behind K: a weight of zero times what is there could be a NaN)
+            float a[U], b[U][4];
+#pragma unroll
+            for (int q = 0; q < U; q++) {
+                const bool ok = 4 * (whole + q) + kq < K;
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const float v = x[j][ok ? off[q] : 0];
+                    b[q][j] = ok ? v : 0.f;
+                }
+                a[q] = w[min(whole + q, steps - 1) * 64];
+            }
+#pragma unroll
+            for (int q = 0; q < U; q++) {
+                if (whole + q >= steps) break;
+#pragma unroll
+                for (int j = 0; j < 4; j++) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[q][j], acc[j], 0, 0, 0);
+            }
+        }
+        // register v of a lane: channel 4 (lane / 16 % 2) + v of the left pixel in the lower half, of the right one in the upper
+        const int c = 4 * (kq & 1);
+        const f32x4 bias = *(const f32x4*)(lds + RS(bias) + min(c, cout - 1) / 4 * 4);
+        f32x4 r[2];
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const float v0 = rs_act(acc[2 * j][e] + bias[e], act), v2 = rs_act(acc[2 * j + 1][e] + bias[e], act);
+                if (is_max) {
+                    const float m = fmaxf(v0, v2);
+                    r[j][e] = fmaxf(fmaxf(m, __shfl_xor(m, 32, 64)), -3.0e38f);   // as rs_pool begins
+                } else {                             // left and right, above and below
+                    const float o0 = __shfl_xor(v0, 32, 64), o2 = __shfl_xor(v2, 32, 64);
+                    r[j][e] = ((v0 + o0) + (kq < 2 ? v2 : o2) + (kq < 2 ? o2 : v2)) * 0.25f;
+                }
+            }
+        if (yo >= 0 && c < cout) *(f32x4*)(lds + yo + c) = kq < 2 ? r[0] : r[1];
+    }
+}
+
+// The same for an image with an infinity or a NaN, whose product with a zero of the pairs' weights would reach the neighbour: a thread per output.
+__device__ __forceinline__ void rs_conv_odd(const int op, float* const lds) {
+    const int Wo = RS(Wo), cout = RS(cout), cin = RS(cin), kh = RS(kh), each = RS(kw) * cin, P = RS(Ho) * Wo, act = RS(act), xs = RS(xp), xrs = RS(xr) * RS(sh), yr = RS(yr), yp = RS(yp);
+    const int* const taps = (const int*)lds + RS(taps);
+    const float *const x0 = lds + RS(x), *const w = lds + RS(w), *const bias = lds + RS(bias);
+    float* const y = lds + RS(y);
+    const bool is_max = RS(pool) == RS_MAX_POOL;
+    for (int it = threadIdx.x; it < P * cout; it += RESIDENT_THREADS) {
+        const int p = it / cout, c = it - p * cout, ho = p / Wo, wo = p - ho * Wo;
+        float most = -3.0e38f, sum = 0.f;
+#pragma unroll 1
+        for (int q = 0; q < 4; q++) {
+            const float* const x = x0 + (2 * ho + (q >> 1)) * xrs + (2 * wo + (q & 1)) * xs;
+            float v = 0.f;
+            for (int row = 0, k = 0; row < kh; row++, k += cin)  // (the left pixel's weights; the last column of a row is the right one's)
+                for (int i = 0; i < each; i++, k++) v = fmaf(x[taps[k]], w[k * 16 + c], v);
+            v = rs_act(v + bias[c], act);
+            most = fmaxf(most, v);
+            sum += v;
+        }
+        y[ho * yr + wo * yp + c] = is_max ? most : sum * 0.25f;
     }
 }
 
@@ -195,15 +327,19 @@ __device__ __forceinline__ void rs_gap(const int op, float* const lds) {
     }
 }
 
-// a wavefront per class
+// LANES lanes per class
+template <int LANES>
 __device__ __forceinline__ void rs_fc(const int op, float* const lds, float* const logits) {
-    const int t = threadIdx.x, lane = t & 63, K = RS(cin), classes = RS(cout);
-    for (int c = t >> 6; c < classes; c += RESIDENT_THREADS / 64) {
+    const int t = threadIdx.x, l = t & (LANES - 1), K = RS(cin), classes = RS(cout);
+    const float *const x = lds + RS(x), *const w = lds + RS(w), *const bias = lds + RS(bias);
+    for (int c0 = 0; c0 < classes; c0 += RESIDENT_THREADS / LANES) {
+        const int c = min(c0 + t / LANES, classes - 1);
         float sum = 0.f;
-        for (int k = lane; k < K; k += 64) sum = fmaf(lds[RS(x) + k], lds[RS(w) + k * classes + c], sum);
+        for (int k = l; k < K; k += LANES) sum = fmaf(x[k], w[k * classes + c], sum);
+        sum = rs_sum16(sum);
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-        if (lane == 0) logits[c] = sum + lds[RS(bias) + c];
+        for (int off = 16; off < LANES; off <<= 1) sum += __shfl_xor(sum, off, 64);
+        if (l == 0 && c0 + t / LANES < classes) logits[c] = sum + bias[c];
     }
 }
 
@@ -232,12 +368,14 @@ __global__ __launch_bounds__(RESIDENT_THREADS) void resident_kernel(const Reside
     for (int i = t; i < mb.lds_floats / 4; i += RESIDENT_THREADS)
         ((f32x4*)rlds)[i] = i < mb.fixed_floats / 4 ? ((const f32x4*)mb.fixed)[i] : f32x4{0.f, 0.f, 0.f, 0.f};   // and the borders' zeros
     const int* const ops = (const int*)rlds;         // the operations lie first
+    constexpr int ODD = offsetof(ResidentOp, odd) / 4;
     __syncthreads();
     for (; image < end; image += mb.blocks) {
         auto put = [&](int i, const float* p) {
             const int y = rs_div(i, mb.in_w, inv_w), x = i - y * mb.in_w;
             float* const d = rlds + mb.in + y * mb.in_r + x * mb.in_p;
             d[0] = p[0]; d[1] = p[1]; d[2] = p[2];
+            if (p[0] * 0.f + p[1] * 0.f + p[2] * 0.f != 0.f) ((int*)rlds)[ODD] = image + 1;
             if (image >= mb.last_first && image < mb.last_first + mb.last_n) {
                 float* const k = mb.input + ((size_t)(image - mb.last_first) * px + i) * 3;
                 k[0] = p[0]; k[1] = p[1]; k[2] = p[2];
@@ -266,12 +404,18 @@ __global__ __launch_bounds__(RESIDENT_THREADS) void resident_kernel(const Reside
                         if (RS(cout) > 16) rs_conv<2, 2, RS_PLAIN>(op, rlds); else rs_conv<4, 1, RS_PLAIN>(op, rlds);
                     } else if (RS(pool) == RS_MEAN_POOL) {
                         if (RS(cout) > 16) rs_conv<2, 2, RS_MEAN>(op, rlds); else rs_conv<2, 1, RS_MEAN>(op, rlds);
+                    } else if (RS(pair)) {
+                        if (ops[ODD] == image + 1) rs_conv_odd(op, rlds); else rs_conv_pair(op, rlds);
                     } else {
                         if (RS(cout) > 16) rs_conv<4, 2, RS_POOL>(op, rlds); else rs_conv<4, 1, RS_POOL>(op, rlds);
                     }
                     break;
                 case RS_GAP: rs_gap(op, rlds); break;
-                case RS_FC: rs_fc(op, rlds, mb.logits + (size_t)image * a.classes); break;
+                case RS_FC: {                        // (few products a class: the trips they take cost less than two more rounds of adding lanes up)
+                    float* const z = mb.logits + (size_t)image * a.classes;
+                    if (RS(cin) <= 256) rs_fc<16>(op, rlds, z); else rs_fc<64>(op, rlds, z);
+                    break;
+                }
                 default: rs_pool(op, rlds, RS(kind) == RS_MAXPOOL);
             }
             __syncthreads();

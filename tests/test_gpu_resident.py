@@ -95,3 +95,36 @@ def test_values_that_are_no_numbers(ens):
         assert np.array_equal(z[m][[0, 1, 3, 5, 7, 8]], clean[m][[0, 1, 3, 5, 7, 8]]), net.name
         np.testing.assert_allclose(z[m], E.ens_member_logits(m, 9), rtol=1e-4, atol=1e-4, err_msg=net.name)
     E.close()
+
+
+# Two neighbouring pixels in a tile: 1, 4, 5 and 8 channels, filters of 2 columns and of 7, K a column longer of no whole step and of whole fours, an odd
+# number of columns and windows of less than and more than 32; an infinity or a NaN reaches what the filters reach and nothing else.
+@pytest.mark.parametrize("size,width,k,act,pool", [((32, 32), 8, 5, "relu", "avg"), ((9, 19), 4, (1, 2), None, "max"), ((13, 30), 5, (4, 3), "silu", "avg"),
+                                                   ((23, 8), 1, (2, 7), "relu", "max")], ids=str)
+def test_two_pixels_in_a_tile(ens, size, width, k, act, pool):
+    net = N.Net("pair", size[0], size[1], 5, dtype="fp32")
+    t = net.conv(0, width, k, act=act)
+    t = net.avgpool(t, 2, 2) if pool == "avg" else net.maxpool(t, 2, 2)
+    net.fc(net.gap(net.conv(t, 9, 1, act=None)), 5)
+    blob = W.make_blob(net, synth.BASE_SEED + 57, 0)
+    imgs = W.make_images(synth.BASE_SEED + 1057, 12, size[0], size[1], varied=True)
+    ref = oracle.forward_logits(net, blob, imgs, real="f64")
+    E = ens.Ensemble([net], [blob])
+    E.set_base_size(*size)
+    E.ens_set_alloc([[8]])
+    E.ens_predict(imgs)
+    z = E.ens_member_logits(0, 12)
+    assert E.ens_debug_stats()["chained"] == 1
+    assert np.abs(z - ref).max() <= 4e-5 * ref.std()             # sqrt(K <= 75) 2^-24 of a value, three layers, the largest of many
+    bad = imgs.copy()
+    bad[1, 0, 1, 0], bad[5, size[0] - 2, size[1] - 2, 2], bad[9, 3, 4, :] = np.inf, np.nan, -np.inf
+    E.ens_predict(bad)
+    zb = E.ens_member_logits(0, 12)
+    pooled = E.ens_debug_tensor(0, t, net.tensors[t], 1)
+    E.ens_debug_one_stream(1)
+    E.ens_predict(bad)
+    rest = [i for i in range(12) if i not in (1, 5, 9)]
+    assert np.array_equal(zb[rest], z[rest])
+    np.testing.assert_allclose(zb, E.ens_member_logits(0, 12), rtol=1e-4, atol=1e-4)
+    np.testing.assert_allclose(pooled, E.ens_debug_tensor(0, t, net.tensors[t], 1), rtol=1e-5, atol=1e-5)
+    E.close()
