@@ -896,6 +896,8 @@ static void install_residents(ens_handle* h, int64_t need) {
         at.push_back(fixed.size());
         fixed.insert(fixed.end(), all[c].fixed.begin(), all[c].fixed.end());
     }
+    const size_t queue = fixed.size();                           // zeros: the words that a launch's workgroups draw images by
+    fixed.resize(fixed.size() + RESIDENT_MAX_MEMBERS + 1, 0.f);
     if (h->budget && (uint64_t)need + fixed.size() * sizeof(float) + (uint64_t)h->reserve > h->budget) return;
     if (hipMalloc((void**)&h->d_resident, fixed.size() * sizeof(float)) != hipSuccess) { h->d_resident = nullptr; (void)hipGetLastError(); return; }
     if (hipMemcpyAsync(h->d_resident, fixed.data(), fixed.size() * sizeof(float), hipMemcpyHostToDevice, h->main_stream) != hipSuccess ||
@@ -907,6 +909,7 @@ static void install_residents(ens_handle* h, int64_t need) {
     }
     h->resident_bytes = (int64_t)(fixed.size() * sizeof(float));
     h->resident_at = at;
+    h->resident_queue = (unsigned*)(h->d_resident + queue);
     h->residents = std::move(all);
 }
 
@@ -1479,6 +1482,9 @@ static int run_resident(ens_handle* h, const float* d_images, int64_t n, float* 
         at += blocks[m];
         lds = std::max(lds, r.lds_floats * 4);
     }
+    // images in turn up to two for each workgroup, drawn by who is ready beyond that
+    for (int m = 0; m < a.n_members; m++)
+        if (piece > 2 * blocks[m]) a.queue = h->resident_queue;
     a.src = d_images;
     a.base_h = h->base_h; a.base_w = h->base_w; a.classes = h->classes;
     const size_t image_floats = (size_t)h->base_h * h->base_w * 3;

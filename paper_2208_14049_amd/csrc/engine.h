@@ -274,6 +274,7 @@ struct ens_handle {
     // fp32 members that fit LDS (resident.h): one per member, or none at all; what LDS begins with in device memory, and where each begins
     std::vector<ens::Resident> residents;
     float* d_resident = nullptr;
+    unsigned* resident_queue = nullptr;              // in it
     int64_t resident_bytes = 0;
     std::vector<size_t> resident_at;
     std::vector<ens::RequestGraph> graphs;

@@ -20,7 +20,7 @@ struct alignas(256) ResidentOp {
     int pool;                  // convolution: what follows it in the same operation, RS_*_POOL: Ho x Wo is what that leaves
     int sums, sums_p;          // RS_MEAN_POOL: LDS for a row of sums per unit
     int pair;                  // weights and places for two neighbouring pixels at once: kh * (kw + 1) * cin of them, rows 0..7 and 8..15 the channels of either
-    int odd;                   // of operation 0: one more than the last image with an infinity or a NaN
+    int odd, drawn;            // of operation 0: one more than the last image with an infinity or a NaN; the number last drawn for an image
 };
 static_assert(sizeof(ResidentOp) == 256, "a dword for each lane");
 
@@ -36,6 +36,7 @@ struct ResidentMember {
 struct ResidentArgs {
     ResidentMember member[8];
     const float* src;
+    unsigned* queue;           // RESIDENT_MAX_MEMBERS + 1 zeros, which the launch leaves as zeros: images drawn by each member's workgroups beyond two each, workgroups gone
     int n_members, first, n, base_h, base_w, classes;   // images [first, first + n) of the request
 };
 static_assert(sizeof(ResidentArgs) <= 4000, "kernel arguments");

@@ -8,11 +8,12 @@
 // channels in steps of four.  The value a lane needs for its k is at a distance from the first tap's that is the same for every pixel: a
 // table in LDS.  Tensors that a padded convolution reads have a border of zeros of their own, so that no tap is outside.
 //
-// Measured, two members of 32 x 32 images: 8 images 61 -> 32 us, 1 000 images in batches of 8 2.5 ms -> 117 us, 8 192 images 2.84 -> 0.61 ms.  A first
+// Measured, two members of 32 x 32 images: 8 images 61 -> 32 us, 1 000 images in batches of 8 2.5 ms -> 117 us, 8 192 images 2.84 -> 0.58 ms.  A first
 // form kept every map in LDS (convolution, barrier, pooling): one workgroup a compute unit, 1.50 ms; with windows and means taken in
 // registers and the next image's pixels asked for ahead two of them fit.  8 100 images on the device, us, step by step: 710; the request's pixels three floats
 // apart instead of four (windows two pixels apart then lie on different banks) 699; two pixels of up to eight channels in a tile 628; the steps
-// behind the last whole four asked for at once, sums over lanes without LDS, 16 lanes a class 607.
+// behind the last whole four asked for at once, sums over lanes without LDS, 16 lanes a class 607; images drawn instead of dealt 584 (dealt, the workgroups of
+// a launch ended between 430 and 590 us).
 // No unit is full: the matrix cores are busy half of the time; of a wavefront's time 0.22 issues, 0.49 waits for its turn to issue (a matrix instruction
 // holds its pipe for 32 clocks; for LDS alone it is 0.02) and 0.29 for data and at barriers (counters of the 710 us form).
 #include "resident.h"
@@ -346,8 +347,12 @@ __device__ __forceinline__ void rs_fc(const int op, float* const lds, float* con
 __global__ __launch_bounds__(RESIDENT_THREADS) void resident_kernel(const ResidentArgs a) {
     extern __shared__ __attribute__((aligned(1024))) float rlds[];
     const int t = threadIdx.x;
+    // Of the two workgroups of a compute unit, one of either half of the grid, the earlier one is served first (16 us an image against 20): every
+    // other pair changes places, so that a member has as many of both, and still another member's beside them.
+    const int half = (int)(gridDim.x + 1) / 2, pair = (int)blockIdx.x % half;
+    const int block = pair % 2 && pair + half < (int)gridDim.x ? ((int)blockIdx.x < half ? pair + half : pair) : (int)blockIdx.x;
     int m = 0;
-    while (m + 1 < a.n_members && (int)blockIdx.x >= a.member[m + 1].first_block) m++;
+    while (m + 1 < a.n_members && block >= a.member[m + 1].first_block) m++;
     const ResidentMember& mb = a.member[m];
     const int px = mb.in_h * mb.in_w;
     const float inv_w = __builtin_amdgcn_rcpf((float)mb.in_w);
@@ -362,15 +367,18 @@ __global__ __launch_bounds__(RESIDENT_THREADS) void resident_kernel(const Reside
 #pragma unroll
             for (int c = 0; c < 3; c++) v[q][c] = t + q * RESIDENT_THREADS < px ? src[(t + q * RESIDENT_THREADS) * 3 + c] : 0.f;
     };
-    int image = a.first + (int)blockIdx.x - mb.first_block;
+    int image = a.first + block - mb.first_block, next = image + mb.blocks;
     const int end = a.first + a.n;
     if (ahead && image < end) ask(image);
     for (int i = t; i < mb.lds_floats / 4; i += RESIDENT_THREADS)
         ((f32x4*)rlds)[i] = i < mb.fixed_floats / 4 ? ((const f32x4*)mb.fixed)[i] : f32x4{0.f, 0.f, 0.f, 0.f};   // and the borders' zeros
     const int* const ops = (const int*)rlds;         // the operations lie first
-    constexpr int ODD = offsetof(ResidentOp, odd) / 4;
+    constexpr int ODD = offsetof(ResidentOp, odd) / 4, DRAWN = offsetof(ResidentOp, drawn) / 4;
     __syncthreads();
-    for (; image < end; image += mb.blocks) {
+    while (image < end) {
+        unsigned drawn = 0;
+        const bool draw = a.queue && next < end;     // the image after the next one: whoever is faster takes more
+        if (draw && t == 0) drawn = __hip_atomic_fetch_add(a.queue + m, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         auto put = [&](int i, const float* p) {
             const int y = rs_div(i, mb.in_w, inv_w), x = i - y * mb.in_w;
             float* const d = rlds + mb.in + y * mb.in_r + x * mb.in_p;
@@ -385,7 +393,7 @@ __global__ __launch_bounds__(RESIDENT_THREADS) void resident_kernel(const Reside
 #pragma unroll
             for (int q = 0; q < AHEAD; q++)
                 if (t + q * RESIDENT_THREADS < px) put(t + q * RESIDENT_THREADS, v[q]);
-            if (image + mb.blocks < end) ask(image + mb.blocks);
+            if (next < end) ask(next);
         } else {
             const float* const src = a.src + (size_t)image * a.base_h * a.base_w * 3;
             for (int i = t; i < px; i += RESIDENT_THREADS) {
@@ -418,9 +426,15 @@ __global__ __launch_bounds__(RESIDENT_THREADS) void resident_kernel(const Reside
                 }
                 default: rs_pool(op, rlds, RS(kind) == RS_MAXPOOL);
             }
+            if (i == 0 && draw && t == 0) ((int*)rlds)[DRAWN] = (int)drawn;   // (not before everybody has read the one before: the pixels' barrier)
             __syncthreads();
         }
+        image = next;
+        next = !a.queue ? next + mb.blocks : draw ? a.first + 2 * mb.blocks + ops[DRAWN] : end;
     }
+    // the last workgroup of the launch leaves zeros
+    if (a.queue && t == 0 && __hip_atomic_fetch_add(a.queue + RESIDENT_MAX_MEMBERS, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1)
+        for (int i = 0; i <= RESIDENT_MAX_MEMBERS; i++) __hip_atomic_store(a.queue + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 hipError_t launch_resident(const ResidentArgs& a, int lds_bytes, hipStream_t s) {

@@ -128,3 +128,23 @@ def test_two_pixels_in_a_tile(ens, size, width, k, act, pool):
     np.testing.assert_allclose(zb, E.ens_member_logits(0, 12), rtol=1e-4, atol=1e-4)
     np.testing.assert_allclose(pooled, E.ens_debug_tensor(0, t, net.tensors[t], 1), rtol=1e-5, atol=1e-5)
     E.close()
+
+
+def test_images_drawn_in_turn(ens):
+    """More images than two for each workgroup: every one is computed once, request after request, also as a recorded one, and a smaller one between them."""
+    import torch
+    nets = [N.tiny_a(classes=7), N.tiny_b(classes=7)]
+    blobs = [W.make_blob(net, synth.BASE_SEED + 59, i) for i, net in enumerate(nets)]
+    few = W.make_images(synth.BASE_SEED + 1059, 41, 32, 32, varied=True)
+    E = ens.Ensemble(nets, blobs)
+    E.set_base_size(32, 32)
+    E.ens_set_alloc([[32, 32]])
+    want = E.ens_predict(few)
+    for n in (1025, 41, 1600, 1600, 513):                        # 512 workgroups
+        imgs = torch.from_numpy(np.ascontiguousarray(few[np.arange(n) % 41])).cuda()
+        out = torch.empty((n, E.classes), device="cuda")
+        for _ in range(3):
+            out.fill_(-1)
+            E.ens_predict_static(imgs, out)
+            assert np.array_equal(out.cpu().numpy(), want[np.arange(n) % 41]), n
+    E.close()
