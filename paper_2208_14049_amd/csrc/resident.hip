@@ -8,12 +8,12 @@
 // channels in steps of four.  The value a lane needs for its k is at a distance from the first tap's that is the same for every pixel: a
 // table in LDS.  Tensors that a padded convolution reads have a border of zeros of their own, so that no tap is outside.
 //
-// Measured, two members of 32 x 32 images: 8 images 61 -> 32 us, 1 000 images in batches of 8 2.5 ms -> 117 us, 8 192 images 2.84 -> 0.58 ms.  A first
+// Measured, two members of 32 x 32 images: 8 images 61 -> 32 us, 1 000 images in batches of 8 2.5 ms -> 117 us, 8 192 images 2.84 -> 0.57 ms.  A first
 // form kept every map in LDS (convolution, barrier, pooling): one workgroup a compute unit, 1.50 ms; with windows and means taken in
 // registers and the next image's pixels asked for ahead two of them fit.  8 100 images on the device, us, step by step: 710; the request's pixels three floats
 // apart instead of four (windows two pixels apart then lie on different banks) 699; two pixels of up to eight channels in a tile 628; the steps
 // behind the last whole four asked for at once, sums over lanes without LDS, 16 lanes a class 607; images drawn instead of dealt 584 (dealt, the workgroups of
-// a launch ended between 430 and 590 us).
+// a launch ended between 430 and 590 us); a higher priority outside the convolutions' loops 565.
 // No unit is full: the matrix cores are busy half of the time; of a wavefront's time 0.22 issues, 0.49 waits for its turn to issue (a matrix instruction
 // holds its pipe for 32 clocks; for LDS alone it is 0.02) and 0.29 for data and at barriers (counters of the 710 us form).
 #include "resident.h"
@@ -90,6 +90,7 @@ __device__ __forceinline__ void rs_conv(const int op, float* const lds) {
         int off[U];
 #pragma unroll
         for (int q = 0; q < U; q++) off[q] = taps[4 * q];        // (behind the table lie other words of LDS)
+        __builtin_amdgcn_s_setprio(0);
         for (int s = 0; s < whole; s += U) {
             float a[U][CT], b[U][PT];
 #pragma unroll
@@ -130,6 +131,7 @@ __device__ __forceinline__ void rs_conv(const int op, float* const lds) {
                     for (int j = 0; j < PT; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][i], b[q][j], acc[i][j], 0, 0, 0);
             }
         }
+        __builtin_amdgcn_s_setprio(1);
         // register v of a lane: channel 4 (lane / 16) + v of pixel lane % 16; whole fours are written (a pixel has room for them)
 #pragma unroll
         for (int i = 0; i < CT; i++) {
@@ -210,6 +212,7 @@ __device__ __forceinline__ void rs_conv_pair(const int op, float* const lds) {
         int off[U];
 #pragma unroll
         for (int q = 0; q < U; q++) off[q] = taps[4 * q];        // (behind the table lie other words of LDS)
+        __builtin_amdgcn_s_setprio(0);
         for (int s = 0; s < whole; s += U) {
             float a[U], b[U][4];
 #pragma unroll
@@ -244,6 +247,7 @@ __device__ __forceinline__ void rs_conv_pair(const int op, float* const lds) {
                 for (int j = 0; j < 4; j++) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[q][j], acc[j], 0, 0, 0);
             }
         }
+        __builtin_amdgcn_s_setprio(1);
         // register v of a lane: channel 4 (lane / 16 % 2) + v of the left pixel in the lower half, of the right one in the upper
         const int c = 4 * (kq & 1);
         const f32x4 bias = *(const f32x4*)(lds + RS(bias) + min(c, cout - 1) / 4 * 4);
@@ -373,6 +377,8 @@ __global__ __launch_bounds__(RESIDENT_THREADS) void resident_kernel(const Reside
     for (int i = t; i < mb.lds_floats / 4; i += RESIDENT_THREADS)
         ((f32x4*)rlds)[i] = i < mb.fixed_floats / 4 ? ((const f32x4*)mb.fixed)[i] : f32x4{0.f, 0.f, 0.f, 0.f};   // and the borders' zeros
     const int* const ops = (const int*)rlds;         // the operations lie first
+    // A workgroup's short phases go before its neighbour's matrix instructions, which fill the gaps: rs_conv and rs_conv_pair step back for their loops
+    __builtin_amdgcn_s_setprio(1);
     constexpr int ODD = offsetof(ResidentOp, odd) / 4, DRAWN = offsetof(ResidentOp, drawn) / 4;
     __syncthreads();
     while (image < end) {
