@@ -267,7 +267,7 @@ const char* conv_regstage_name(const ConvArgs& a, int P);
 // partial sums in the workspace and applies bias, residual and activation; defined in conv_mfma.hip.
 hipError_t launch_conv_splitk_epilogue(const ConvArgs& a, const ConvArgs* argv, int G, int nb, int P, int splits, hipStream_t s);
 
-// 3x3 stride-1 kernel with the filter in registers, from 32 channels to up to 32; defined in conv_narrow.hip.
+// 3x3 stride-1 kernel with the filter in registers, from 32 channels to 32; defined in conv_narrow.hip.
 bool conv_narrow_applicable(const ConvArgs& a, int nb, int G);
 const char* conv_narrow_name(const ConvArgs& a);
 hipError_t launch_conv_narrow(const ConvArgs& a, const ConvArgs* argv, int G, int nb, hipStream_t s);

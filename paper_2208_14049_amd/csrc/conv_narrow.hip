@@ -1,4 +1,4 @@
-// 3x3, stride 1, padding 1 convolution from 32 channels to up to 32 on the CDNA4 matrix cores, the filter in registers: the parts that a
+// 3x3, stride 1, padding 1 convolution from 32 channels to 32 on the CDNA4 matrix cores, the filter in registers: the parts that a
 // grouped convolution is cut into.
 //
 // A pixel fragment meets one block of weights here, and 9 x 32 of K: on the generic kernel such a layer fetches every pixel nine times, with a
@@ -42,14 +42,16 @@ void conv3x3_narrow_bf16(const ConvArgs* __restrict__ argv, const int nb_, const
     float* const sb = (float*)(lds + hrows * ROWB);
     int* const tbl = (int*)(sb + 64);
 
-    // ---- the filter, in operand order
+    // ---- the filter: a lane's row is a channel with bits 2 and 3 swapped.  (A row's 576 bytes are taken 32 at a time, from the L1 after the first; once a
+    // workgroup that is nothing beside a copy in operand order.)
     bf16x8 wreg[9][STEPS];
     {
-        const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void*)a.wpk, 0, (9 * CIN + 63) / 64 * 4096, 0x00020000);
+        const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, 32 * 9 * CIN * 2, 0x00020000);
+        const unsigned row = (unsigned)((lrow & 0x13) | ((lrow & 4) << 1) | ((lrow & 8) >> 1)) * (9 * CIN * 2) + lhalf * 16u;
 #pragma unroll
         for (int tap = 0; tap < 9; tap++)
 #pragma unroll
-            for (int ks = 0; ks < STEPS; ks++) wreg[tap][ks] = bn_wload(wres, lane * 16u, (tap * STEPS + ks) * 1024);
+            for (int ks = 0; ks < STEPS; ks++) wreg[tap][ks] = bn_wload(wres, row, (tap * STEPS + ks) * 32);
     }
 
     // ---- the table: a thread keeps the positions of its rows as (image, row, column) and steps them from tile to tile
@@ -103,8 +105,8 @@ void conv3x3_narrow_bf16(const ConvArgs* __restrict__ argv, const int nb_, const
     };
     make_table(0);
     if (t < 32) {
-        sb[t] = t < a.cout ? ENS_GLOBAL(float, a.bias)[t] : 0.f;
-        sb[32 + t] = t < a.cout ? ENS_GLOBAL(float, a.scale)[t] : 1.f;
+        sb[t] = ENS_GLOBAL(float, a.bias)[t];
+        sb[32 + t] = ENS_GLOBAL(float, a.scale)[t];
     }
     __syncthreads();
     issue_window(0);
@@ -117,7 +119,7 @@ void conv3x3_narrow_bf16(const ConvArgs* __restrict__ argv, const int nb_, const
         const uint32_t q = (uint32_t)(wp0 + lrow + (tap / 3) * W1 + tap % 3);
         xoff[tap] = lds0 + q * ROWB + (((uint32_t)lhalf ^ key(q)) << 4);
     }
-    // ---- output side: channels 16 k + 8 lhalf ... + 7 (which exist as a whole or not at all) of this wavefront's positions
+    // ---- output side: channels 16 k + 8 lhalf ... + 7 of this wavefront's positions
     const unsigned npix = (unsigned)nb_ * (unsigned)(a.H * a.W);
     const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc((void*)a.y.p, 0, (int)(npix * (unsigned)a.y.stride * 2u), 0x00020000);
     auto store = [&](const f32x16& acc, int p) {
@@ -125,7 +127,7 @@ void conv3x3_narrow_bf16(const ConvArgs* __restrict__ argv, const int nb_, const
 #pragma unroll
         for (int k = 0; k < 2; k++) {
             const u32x4 o = bn_pack(acc, k, a.act, sb + 8 * lhalf, 32);
-            __builtin_amdgcn_raw_buffer_store_b128(o, yres, 16 * k + 8 * lhalf < a.cout ? at : OOBV, 32 * k, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(o, yres, at, 32 * k, 0);
         }
     };
 
@@ -173,7 +175,7 @@ struct NarrowPlan { int hrows, wgs; size_t bytes; };
 
 static bool narrow_plan(const ConvArgs& a, int nb, int G, NarrowPlan* pl) {
     if (a.kh != 3 || a.kw != 3 || a.sh != 1 || a.sw != 1 || a.pt != 1 || a.pl != 1 || a.Ho != a.H || a.Wo != a.W) return false;
-    if (a.pre_scale || a.gate || a.res.p || a.pair || !a.wpk || a.cin != NARROW_CIN || a.cout % 8 || a.cout < 8 || a.cout > 32) return false;
+    if (a.pre_scale || a.gate || a.res.p || a.pair || a.cin != NARROW_CIN || a.cout != 32) return false;
     if (a.x.stride % 8 || a.x.c0 % 8 || a.y.stride % 8 || a.y.c0 % 8) return false;
     // 32-bit byte offsets with 2^31 standing for 'outside'; quotients by float reciprocals
     const long long pixels = (long long)nb * a.H * a.W, img = (long long)(a.H + 1) * (a.W + 1), PP = nb * img;

@@ -114,7 +114,6 @@ static int fill_args(ens_handle* h, const Worker& w, const Worker& leader, int G
                 a.y.c0 += sub * pl.sub_cout;
                 if (a.res.p) a.res.c0 += sub * pl.sub_cout;
                 a.w = (const char*)a.w + (size_t)sub * pl.sub_cout * o.kh * o.kw * pl.cin_s * es;
-                if (a.wpk) a.wpk = (const char*)a.wpk + (size_t)sub * ((o.kh * o.kw * pl.cin_s + 63) / 64 * 4096);   // (32 rows each)
                 a.bias += (size_t)sub * pl.sub_cout;
                 a.scale += (size_t)sub * pl.sub_cout;
             }

@@ -413,16 +413,6 @@ int build_member(const ens_member_spec& spec, const float* params, Member* out) 
                 pack_operand_order(m.ops[i]);
         }
     }
-    // 3x3 layers from 32 channels to 32, as a grouped convolution is cut into: the kernel of conv_narrow.hip.  The blocks of a grouped
-    // layer's rows are its parts, one after the other.
-    if (m.bf16) {
-        for (int i = 0; i < spec.n_ops; i++) {
-            const ens_op& o = spec.ops[i];
-            if (o.kind == ENS_OP_CONV && o.kh == 3 && o.kw == 3 && o.sh == 1 && o.sw == 1 && o.pt == 1 && o.pl == 1 && !o.pre && o.res < 0 &&
-                m.ops[i].sub_cout == 32 && m.ops[i].cin_s == 32)
-                pack_operand_order(m.ops[i]);
-        }
-    }
     if (m.bf16) {
         std::vector<int> uses(m.tensors.size(), 0);              // readers and writers of every tensor
         for (int i = 0; i < spec.n_ops; i++) {
