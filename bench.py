@@ -40,7 +40,7 @@ TRAFFIC = {
     (4, "conv1x1_direct_bf16<128x256>"): dict(
         bytes_per_launch=88.6e6,                 # read + written (profiles/bench_config4_12members_b128.md)
         sources=["conv_wide.hip", "conv_direct.h", "conv_common.h", "kernels.h"],
-        sha256="d142baafc48db0260f8b73d17ebae7b76967555cf1e15b92a9433ee4b346b7f2"),
+        sha256="422059592fd60bdfe685877b770438a1f4f14d3d65e3f273fd8814f8e88e4a78"),
 }
 
 

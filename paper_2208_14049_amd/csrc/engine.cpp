@@ -1578,10 +1578,11 @@ static double launches_seconds(ens_handle* h, int64_t n) {
 }
 
 // How a request of n images is cut into programs, or null when it goes launch by launch.  Measured both ways over six ensembles on 1 to 12
-// images (us, launches / chains): twelve members on 1, 2, 4 and 8 images 2967 / 1195, 3171 / 1640, 3637 / 2560 and 4414 / 4444; four members
-// 825 / 637, 885 / 650, 1032 / 781 and 1338 / 1185; a ResNet-50 alone 334 / 394, 348 / 391, 385 / 391 and 469 / 426; three ResNet-18, whose launches
-// carry all three, 188 / 201 and 337 / 356 (1 and 8 images).  The estimates of chains are 10 to 20 % low: hence the margin, which leaves to the
-// launches what comes out even.
+// images (us, launches / chains): twelve members on 1, 2, 4 and 8 images 2924 / 1197, 3152 / 1672, 3574 / 2549 and 4396 / 4283; four members
+// 875 / 687, 968 / 687, 1093 / 822 and 1317 / 1148; a ResNet-50 alone 336 / 376, 354 / 376, 401 / 382 and 508 / 415; three ResNet-18, whose launches
+// carry all three, 187 / 210 and 358 / 374 (1 and 8 images).  The estimates of chains are 5 to 30 % low, those of launches 10 % either way: hence the
+// margin.  Of 54 requests it gave none to chains that were slower as one, and kept from them none that was more than 6 % faster, four members on 12
+// images (8 %) apart.
 constexpr double CHAIN_MARGIN = 1.25;
 
 static const ChainPlan* chain_plan(ens_handle* h, int64_t n) {

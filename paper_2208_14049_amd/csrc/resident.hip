@@ -14,8 +14,9 @@
 // apart instead of four (windows two pixels apart then lie on different banks) 699; two pixels of up to eight channels in a tile 628; the steps
 // behind the last whole four asked for at once, sums over lanes without LDS, 16 lanes a class 607; images drawn instead of dealt 584 (dealt, the workgroups of
 // a launch ended between 430 and 590 us); a higher priority outside the convolutions' loops 565.
-// No unit is full: the matrix cores are busy half of the time; of a wavefront's time 0.22 issues, 0.49 waits for its turn to issue (a matrix instruction
-// holds its pipe for 32 clocks; for LDS alone it is 0.02) and 0.29 for data and at barriers (counters of the 710 us form).
+// No unit is full (counters, 8 100 images): the matrix cores are busy 0.52 of the time, LDS 0.28, a sixth of that bank conflicts (before the image's
+// pixels lay three floats apart 0.48, half of it), vector units 0.43; of a wavefront's time 0.22 issues, 0.51 waits for its turn to issue (a matrix
+// instruction holds its pipe for 32 clocks; for LDS alone it is 0.01) and 0.26 for data and at barriers.
 #include "resident.h"
 #include "conv_common.h"
 #include "stage.h"
