@@ -1581,9 +1581,9 @@ static double launches_seconds(ens_handle* h, int64_t n) {
 // images (us, launches / chains): twelve members on 1, 2, 4 and 8 images 2924 / 1197, 3152 / 1672, 3574 / 2549 and 4396 / 4283; four members
 // 875 / 687, 968 / 687, 1093 / 822 and 1317 / 1148; a ResNet-50 alone 336 / 376, 354 / 376, 401 / 382 and 508 / 415; three ResNet-18, whose launches
 // carry all three, 187 / 210 and 358 / 374 (1 and 8 images).  The estimates of chains are 5 to 30 % low, those of launches 10 % either way: hence the
-// margin.  Of 54 requests it gave none to chains that were slower as one, and kept from them none that was more than 6 % faster, four members on 12
-// images (8 %) apart.
-constexpr double CHAIN_MARGIN = 1.25;
+// margin.  Of 54 requests it gave none to chains that were slower as one; at 1.25 a ResNet-50 of batch size 16 on 4 images was (estimated 1.252, 388 us as
+// launches, 410 as a chain).  What it keeps from them: the same on 12 images and four members on 12 (10 and 8 % faster as chains).
+constexpr double CHAIN_MARGIN = 1.28;
 
 static const ChainPlan* chain_plan(ens_handle* h, int64_t n) {
     if (h->chains.empty() || h->chains_off) return nullptr;
