@@ -104,61 +104,6 @@ double step_us(const ChainStep& s, int images, int size) {
     return 0.0;
 }
 
-// What a phase takes on one group: its units are dealt to the workgroups in turn, whatever step they are of.
-double phase_us(const std::vector<ChainStep>& steps, int images, int size) {
-    double load[GROUP] = {0};
-    int at = 0;
-    for (const ChainStep& s : steps) {
-        const int n = (int)units(s, images, s.choice[size]);
-        const double each = step_us(s, images, size) / std::max(1.0, std::ceil((double)n / GROUP));
-        for (int u = 0; u < n && u < 64 * GROUP; u++, at = (at + 1) % GROUP) load[at] += each;
-    }
-    return *std::max_element(load, load + GROUP);
-}
-
-// The tiles of a phase's convolutions for a number of images.  One by itself: the ones that take it the least time.  Several share the workgroups,
-// so that the best of each by itself make two rounds where less finely cut ones would make one (a strided layer and its shortcut, 26 and
-// 25 units): every step in turn is given what suits the others' best, from each one's best and from their coarsest cuts.
-// (Four members on 8 images, two programs each 1 181 -> 1 123 us; on 4 images as one program each 1 198 -> 1 078; members without such phases unchanged.)
-void choose_tiles(std::vector<ChainStep>& steps, int size) {
-    const int images = 1 << size;
-    int convs = 0;
-    for (const ChainStep& s : steps) convs += s.kind <= CH_CONV_PRE;
-    auto picks = [](const ChainStep& s, auto&& f) {
-        for (int side = 1; side <= 2; side++)
-            for (int split = 0; 1 << split <= CHAIN_WAVES; split++)
-                if (side == 1 || s.sub == 1) f(side | split << 8);
-    };
-    std::vector<ChainStep> best;
-    double best_us = 1e30;
-    for (int from = 0; from < (convs > 1 ? 2 : 1); from++) {
-        for (ChainStep& s : steps) {
-            if (s.kind > CH_CONV_PRE) continue;
-            double least = 1e30;
-            picks(s, [&](int pick) {
-                const double v = from ? units(s, images, pick) : conv_us(s, images, pick & 255, pick >> 8);
-                if (v < least) { least = v; s.choice[size] = pick; }
-            });
-        }
-        double us = phase_us(steps, images, size);
-        for (bool moved = convs > 1; moved;) {
-            moved = false;
-            for (ChainStep& s : steps) {
-                if (s.kind > CH_CONV_PRE) continue;
-                int take = s.choice[size];
-                picks(s, [&](int pick) {
-                    s.choice[size] = pick;
-                    const double t = phase_us(steps, images, size);
-                    if (t < us - 1e-6) { us = t; take = pick; moved = true; }
-                });
-                s.choice[size] = take;
-            }
-        }
-        if (us < best_us) { best_us = us; best = steps; }
-    }
-    steps = best;
-}
-
 }  // namespace
 
 int chain_size(int images) {
@@ -422,19 +367,8 @@ bool build_chain(const Member& m, const std::vector<Launch>& launches, char* bas
     for (size_t i = 0; i < nodes.size();) {
         size_t e = i;
         while (e < nodes.size() && nodes[e].level == nodes[i].level) e++;
-        std::vector<ChainStep> phase;
-        for (size_t j = i; j < e; j++) phase.push_back(nodes[j].s);
-        for (int z = 0; z < CHAIN_SIZES; z++) {
-            choose_tiles(phase, z);
-            out->seconds[z] += 1e-6 * phase_us(phase, 1 << z, z);
-            for (ChainStep& s : phase) {
-                const double n = units(s, 1 << z, s.choice[z]);
-                if (n > 65535.0) return false;
-                s.choice[z] |= (int)n << 16;
-            }
-        }
         for (size_t j = i; j < e; j++) {
-            ChainStep& s = phase[j - i];
+            ChainStep s = nodes[j].s;
             auto place = [&](int64_t t) { return t >= 0 ? (int64_t)out->place[t] : (int64_t)-1; };
             if (j == i) {
                 size_t f = e;
@@ -451,6 +385,20 @@ bool build_chain(const Member& m, const std::vector<Launch>& launches, char* bas
             if (s.kind != CH_SE_SUM && s.kind != CH_SE_HIDDEN && s.kind != CH_FC) s.y = place(s.y);
             s.res = place(s.res);
             s.scratch = place(s.scratch);
+            for (int z = 0; z < CHAIN_SIZES; z++) {
+                if (s.kind <= CH_CONV_PRE) {
+                    double best = 1e30;
+                    for (int side = 1; side <= 2; side++)
+                        for (int split = 0; 1 << split <= CHAIN_WAVES; split++) {
+                            if (side == 2 && s.sub > 1) continue;
+                            const double us = conv_us(s, 1 << z, side, split);
+                            if (us < best) { best = us; s.choice[z] = side | split << 8; }
+                        }
+                }
+                s.choice[z] |= (int)(std::min(units(s, 1 << z, s.choice[z]), 65535.0)) << 16;
+                out->seconds[z] += 1e-6 * step_us(s, 1 << z, z);
+                if (units(s, 1 << z, s.choice[z]) > 65535.0) return false;
+            }
             if (nodes[j].pack) {
                 out->packs.push_back(Chain::Pack{(int)out->steps.size(), s.sub, s.cout, s.K, out->pack_bytes, (size_t)s.wsize});
                 out->pack_bytes += ((size_t)s.wsize + 255) / 256 * 256;

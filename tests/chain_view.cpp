@@ -9,6 +9,13 @@ int chain_steps(ens_handle* h, int member) { return h->chains.empty() ? 0 : (int
 
 int chain_cap(ens_handle* h, int member) { return h->chains.empty() ? 0 : h->chains[member].cap; }
 
+// How many wavefronts share the K of a member's convolution with `K` and `cout` in a program of up to 1 << z images, as a power of two; -1: none such.
+int chain_split(ens_handle* h, int member, int K, int cout, int z) {
+    for (const ChainStep& s : h->chains[member].steps)
+        if (s.kind <= CH_CONV_PRE && s.K == K && s.cout == cout) return s.choice[z] >> 8 & 255;
+    return -1;
+}
+
 // What a group leaves that gave up waiting.
 void chain_gave_up(ens_handle* h) { h->flag[CHAIN_FAILED_WORD] = 1; }
 

@@ -182,6 +182,34 @@ def test_chains_read_no_weights_behind_a_layers_own(fake_hip, chain_view):
     beside_fake_hip(fake_hip, "odd_blocks(%r)" % chain_view)
 
 
+def splits(view):
+    import paper_2208_14049_amd as ens
+    from synth import nets as N, weights as W
+    V, nets = ctypes.CDLL(view), []
+    for short in (False, True):
+        n = N.Net("stage%d" % short, 32, 32, 16, dtype="bf16")
+        t = n.conv(n.conv(0, 32, 3, stride=2), 256, 1)
+        a = n.conv(t, 512, 3, stride=2)
+        t = n.conv(a, 512, 3, res=n.conv(t, 512, 1, stride=2, act=None) if short else None)
+        for _ in range(15):
+            t = n.conv(t, 32, 3)
+        n.fc(n.gap(t), 16)
+        nets.append(n)
+    E = ens.Ensemble(nets, [W.make_blob(n, 255, i) for i, n in enumerate(nets)])
+    E.ens_set_alloc([[32, 32]])
+    for K in (9 * 256, 9 * 512):                                 # the layer beside a shortcut, and the one behind both
+        s = [[V.chain_split(E._h, m, K, 512, z) for z in range(6)] for m in range(2)]
+        assert -1 not in s[0] and s[0] == s[1], (K, s)
+    assert V.chain_split(E._h, 0, 256, 512, 0) == -1 and V.chain_split(E._h, 1, 256, 512, 0) >= 0
+    E.close()
+
+
+def test_a_layers_sums_do_not_depend_on_its_neighbours(fake_hip, chain_view):
+    """In how many parts a layer's sums are added up, and so its answer's last bits, follows from the layer and the images of a program, not from what
+    else runs in its phase."""
+    beside_fake_hip(fake_hip, "splits(%r)" % chain_view)
+
+
 def wide_programs(view):
     import paper_2208_14049_amd as ens
     from synth import nets as N, weights as W
