@@ -1,5 +1,5 @@
 // What the host works out for the chains of a loaded ensemble (csrc/chain.h), for tests on a machine without a GPU.
-#include "chain.h"
+#include "chain.cpp"
 
 using namespace ens;
 
@@ -14,6 +14,35 @@ int chain_split(ens_handle* h, int member, int K, int cout, int z) {
     for (const ChainStep& s : h->chains[member].steps)
         if (s.kind <= CH_CONV_PRE && s.K == K && s.cout == cout) return s.choice[z] >> 8 & 255;
     return -1;
+}
+
+// The tiles of a member's phases beside those of each convolution by itself: 1: K in other parts; 2: the phase takes longer; 4: more units than a step counts;
+// 8: a phase of one step does not take what its step takes.  `better`: phases that take less, `most`: the most units of a step.
+int chain_tiles_wrong(ens_handle* h, int member, int* better, int* most) {
+    int wrong = 0;
+    *better = *most = 0;
+    const std::vector<ChainStep>& all = h->chains[member].steps;
+    for (size_t i = 0; i < all.size();) {
+        const int count = all[i].phase_steps & 255;
+        for (int z = 0; z < CHAIN_SIZES; z++) {
+            std::vector<ChainStep> chosen(all.begin() + i, all.begin() + i + count), own = chosen;
+            for (int j = 0; j < count; j++) {
+                ChainStep& s = own[j];
+                const double n = units(s, 1 << z, s.choice[z]);
+                if (n > 65535.0 || (int)((unsigned)s.choice[z] >> 16) != (int)n) wrong |= 4;
+                *most = std::max(*most, (int)n);
+                if (s.kind <= CH_CONV_PRE) s.choice[z] = own_tiles(s, 1 << z);
+                if (s.kind <= CH_CONV_PRE && (s.choice[z] >> 8 & 255) != (chosen[j].choice[z] >> 8 & 255)) wrong |= 1;
+                const double one = phase_us(&s, 1, 1 << z, z), step = step_us(s, 1 << z, z);
+                if (std::fabs(one - step) > 1e-9 * step) wrong |= 8;
+            }
+            const double us = phase_us(chosen.data(), count, 1 << z, z), by_own = phase_us(own.data(), count, 1 << z, z);
+            if (us > by_own + 1e-9) wrong |= 2;
+            *better += us < by_own - 1e-9;
+        }
+        i += count;
+    }
+    return wrong;
 }
 
 // What a group leaves that gave up waiting.

@@ -152,7 +152,8 @@ def test_recorded_requests_go_when_a_request_finds_no_memory(fake_hip):
 def chain_view(tmp_path_factory):
     lib = str(tmp_path_factory.mktemp("view") / "libchain_view.so")
     subprocess.check_call(["hipcc", "-O1", "-std=c++17", "-fPIC", "-shared", "-x", "hip", "--offload-arch=gfx950", "-I" + os.path.join(ROOT, "paper_2208_14049_amd", "csrc"),
-                           "-o", lib, os.path.join(ROOT, "tests", "chain_view.cpp")])
+                           "-Wl,-Bsymbolic", "-o", lib, os.path.join(ROOT, "tests", "chain_view.cpp"), "-x", "none",
+                           os.path.join(ROOT, "paper_2208_14049_amd", "libens_mi355x.so")])
     return lib
 
 
@@ -208,6 +209,35 @@ def test_a_layers_sums_do_not_depend_on_its_neighbours(fake_hip, chain_view):
     """In how many parts a layer's sums are added up, and so its answer's last bits, follows from the layer and the images of a program, not from what
     else runs in its phase."""
     beside_fake_hip(fake_hip, "splits(%r)" % chain_view)
+
+
+def tiles(view):
+    import paper_2208_14049_amd as ens
+    from synth import nets as N, weights as W
+    V, large = ctypes.CDLL(view), N.Net("large", 160, 160, 1000, dtype="bf16")
+    t = large.conv(0, 64, 3)
+    cat = large.tensor(160, 160, 256 + 256 + 64)                  # three branches; 32 images make 6 400 units of the first two
+    for c0, c, k in ((0, 256, 3), (256, 256, 1), (512, 64, 5)):
+        large.conv(t, c, k, dst=(cat, c0))
+    t = cat
+    for _ in range(15):
+        t = large.conv(t, 32, 1)
+    large.fc(large.gap(t), 1000)
+    nets = [N.inception_v3(size=299), N.resnet50(), N.densenet121(), large]
+    E = ens.Ensemble(nets, [W.make_blob(n, 257, i) for i, n in enumerate(nets)])
+    E.ens_set_alloc([[32] * len(nets)])
+    for m, net in enumerate(nets):
+        better, most = ctypes.c_int(), ctypes.c_int()
+        assert V.chain_tiles_wrong(E._h, m, ctypes.byref(better), ctypes.byref(most)) == 0, net.name
+        assert better.value > 0 or net.name not in ("inception_v3", "resnet50"), net.name
+    assert most.value > 2048
+    E.close()
+
+
+def test_tiles_of_a_phase(fake_hip, chain_view):
+    """The tiles that a phase's convolutions are given together are none worse by the estimate than each one's own and cut K as those do; the estimate of a phase
+    of one step is the step's, however many units it has."""
+    beside_fake_hip(fake_hip, "tiles(%r)" % chain_view)
 
 
 def wide_programs(view):
