@@ -412,7 +412,7 @@ bool build_chain(const Member& m, const std::vector<Launch>& launches, char* bas
     out->packs.clear();
     out->pack_bytes = 0;
     out->phases = phases;
-    for (double& v : out->seconds) v = 0.0;
+    for (int z = 0; z < CHAIN_SIZES; z++) out->seconds[z] = out->span[z] = 0.0;
     for (size_t i = 0; i < nodes.size();) {
         size_t e = i;
         while (e < nodes.size() && nodes[e].level == nodes[i].level) e++;
@@ -448,9 +448,10 @@ bool build_chain(const Member& m, const std::vector<Launch>& launches, char* bas
         ChainStep* const phase = &out->steps[out->steps.size() - (e - i)];
         for (int z = 0; z < CHAIN_SIZES; z++) {
             if (e - i > 1) suit_sides(phase, (int)(e - i), z);
+            out->seconds[z] += 1e-6 * PHASE_US;
+            out->span[z] += 1e-6 * (PHASE_US + phase_us(phase, (int)(e - i), 1 << z, z));
             for (size_t j = 0; j < e - i; j++) phase[j].choice[z] |= (int)units(phase[j], 1 << z, phase[j].choice[z]) << 16;
         }
-        for (double& v : out->seconds) v += 1e-6 * PHASE_US;
         i = e;
     }
     return true;

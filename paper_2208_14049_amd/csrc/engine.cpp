@@ -1514,16 +1514,20 @@ static int run_resident(ens_handle* h, const float* d_images, int64_t n, float* 
 
 // ---- requests as chains -----------------------------------------------------------------------------
 
-// A program's estimate from those of the numbers of images around it.
-static double program_seconds(const Chain& c, int images) {
+// A program's estimate from those of the numbers of images around it (Chain::seconds or ::span).
+static double program_seconds(const double (&of)[CHAIN_SIZES], int images) {
     const int z = chain_size(images);
-    if (images >= 1 << z) return c.seconds[z] * images / (1 << z);
+    if (images >= 1 << z) return of[z] * images / (1 << z);
     const double lo = 1 << (z - 1), hi = 1 << z;
-    return c.seconds[z - 1] + (c.seconds[z] - c.seconds[z - 1]) * (images - lo) / (hi - lo);
+    return of[z - 1] + (of[z] - of[z - 1]) * (images - lo) / (hi - lo);
 }
 
-// Cuts a request into programs for the eight groups: every member's images in the number of parts that ends first by the estimates, the
-// longest program first.  None: the request is not one for chains.
+// What a request in one launch takes by the spans of its programs (measured beside them: launches_seconds).
+constexpr double CHAIN_BASE = 60e-6, CHAIN_SPAN = 1.05;
+
+// Cuts a request into programs for the eight groups: every member's images in the number of parts that ends first by the sums of their
+// steps, the longest program first.  None: the request is not one for chains.  (Cut by the spans, four members of batch size 16 on 4 images took
+// 832 us instead of 777.)
 static ChainPlan plan_programs(const ens_handle* h, int64_t n) {
     ChainPlan best;
     constexpr int GROUPS = 8;                                    // XCDs
@@ -1534,7 +1538,7 @@ static ChainPlan plan_programs(const ens_handle* h, int64_t n) {
         for (size_t c = 0; c < h->chains.size(); c++)
             for (int first = 0; first < n; first += most) {
                 const int images = (int)std::min<int64_t>(most, n - first);
-                all.emplace_back(program_seconds(h->chains[c], images), ChainProgram{(short)c, (short)first, (short)images, (short)chain_size(images)});
+                all.emplace_back(program_seconds(h->chains[c].seconds, images), ChainProgram{(short)c, (short)first, (short)images, (short)chain_size(images)});
             }
         if (all.size() > CHAIN_MAX_PROGRAMS) break;
         std::stable_sort(all.begin(), all.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
@@ -1550,11 +1554,24 @@ static ChainPlan plan_programs(const ens_handle* h, int64_t n) {
             for (const auto& p : all) best.programs.push_back(p.second);
         }
     }
+    if (best.programs.empty()) return best;
+    double load[GROUPS] = {0};                                   // as the groups take them from the queue
+    for (const ChainProgram& p : best.programs) *std::min_element(load, load + GROUPS) += program_seconds(h->chains[p.member].span, p.images);
+    best.seconds = CHAIN_BASE + CHAIN_SPAN * *std::max_element(load, load + GROUPS);
     return best;
 }
 
 // What the launches of the request come to: a launch is a chain of round trips however little it does, one after the other on a lane, and
 // the work of all of them takes the GPU besides.
+//
+// 392 requests were measured both ways: nineteen ensembles of 1 to 12 members, batch sizes 8 to 128, one to 128 images.  The constants here and
+// CHAIN_BASE and CHAIN_SPAN were fitted together, to send as few as can be the way that is more than 3 % slower with what comes out even left to the
+// launches: 26 of them are, by 25 % at most (three Inception-shaped members on 8 images, whose launches take 1.4 times their estimate).  Chains take
+// 0.78 to 1.30 of their estimate (half of them 0.92 to 1.04), launches 0.77 to 1.71 (half of them 0.92 to 1.09; the most a VGG-16, far from either).
+// In us, launches / chains: twelve members on 1, 4, 7 and 10 images 2946 / 1226, 3638 / 2534, 4272 / 3980 and 4797 / 5336; four members on 1, 4, 8 and
+// 16 818 / 636, 1059 / 767, 1340 / 1154 and 1899 / 1954; a ResNet-50 on 1, 4, 8, 20 and 80 328 / 374, 403 / 397, 487 / 411, 711 / 782 and 1585 / 1806; with
+// a DenseNet-121 on 1 924 / 631; an Inception-shaped member on 1, 4 and 16 528 / 521, 600 / 553 and 1064 / 787; three ResNet-18, whose launches carry all
+// three, on 1 and 8 189 / 189 and 341 / 357.
 static double launches_seconds(ens_handle* h, int64_t n) {
     const std::vector<std::vector<int32_t>> owner(h->members.size(), std::vector<int32_t>(1, 0));   // (one segment: the first worker's)
     std::vector<double> floors(h->gangs.size(), 0.0);
@@ -1572,19 +1589,12 @@ static double launches_seconds(ens_handle* h, int64_t n) {
     std::sort(floors.begin(), floors.end(), [](double x, double y) { return x > y; });
     double load[LANES] = {0};
     for (double t : floors) *std::min_element(load, load + LANES) += t;
-    // (the floors are those of a launch among others' on four lanes: on a lane of its own a gang is faster, and twelve on four are slower)
-    const bool crowded = std::count_if(floors.begin(), floors.end(), [](double t) { return t > 0.0; }) > LANES;
-    return *std::max_element(load, load + LANES) * (crowded ? 1.08 : 0.85) + work;
+    // (the floors are those of a launch among others' on four lanes: on a lane of its own a gang is faster)
+    const bool several = std::count_if(floors.begin(), floors.end(), [](double t) { return t > 0.0; }) > 1;
+    return *std::max_element(load, load + LANES) * (several ? 1.05 : 0.88) + 0.7 * work;
 }
 
-// How a request of n images is cut into programs, or null when it goes launch by launch.  Measured both ways over six ensembles on 1 to 12
-// images (us, launches / chains): twelve members on 1, 2, 4 and 8 images 2924 / 1197, 3152 / 1672, 3574 / 2549 and 4396 / 4283; four members
-// 875 / 687, 968 / 687, 1093 / 822 and 1317 / 1148; a ResNet-50 alone 336 / 376, 354 / 376, 401 / 382 and 508 / 415; three ResNet-18, whose launches
-// carry all three, 187 / 210 and 358 / 374 (1 and 8 images).  The estimates of chains are 5 to 30 % low, those of launches 10 % either way: hence the
-// margin.  Of 54 requests it gave none to chains that were slower as one; at 1.25 a ResNet-50 of batch size 16 on 4 images was (estimated 1.252, 388 us as
-// launches, 410 as a chain).  What it keeps from them: the same on 12 images and four members on 12 (10 and 8 % faster as chains).
-constexpr double CHAIN_MARGIN = 1.28;
-
+// How a request of n images is cut into programs, or null when it goes launch by launch: whichever the estimates have end first.
 static const ChainPlan* chain_plan(ens_handle* h, int64_t n) {
     if (h->chains.empty() || h->chains_off) return nullptr;
     for (const Chain& c : h->chains)
@@ -1594,7 +1604,7 @@ static const ChainPlan* chain_plan(ens_handle* h, int64_t n) {
     if (!p.known) {
         p = plan_programs(h, n);
         p.known = true;
-        if (p.seconds * CHAIN_MARGIN > launches_seconds(h, n)) p.programs.clear();
+        if (p.seconds > launches_seconds(h, n)) p.programs.clear();
     }
     return p.programs.empty() ? nullptr : &p;
 }

@@ -194,7 +194,8 @@ struct Chain {
     size_t pack_bytes = 0;
     std::vector<size_t> place;               // of every tensor, for one image
     size_t image_bytes = 0;
-    double seconds[CHAIN_SIZES] = {};        // estimate of a program of 1, 2, 4 ... images
+    double seconds[CHAIN_SIZES] = {};        // of a program of 1, 2, 4 ... images: its steps added up, by which requests are cut into programs;
+    double span[CHAIN_SIZES] = {};           // the estimate proper, with the steps of a phase side by side
 };
 // A small fp32 member that runs in a compute unit's LDS (resident.h), worked out when an allocation is installed.
 struct Resident {

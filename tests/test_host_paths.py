@@ -240,6 +240,31 @@ def test_tiles_of_a_phase(fake_hip, chain_view):
     beside_fake_hip(fake_hip, "tiles(%r)" % chain_view)
 
 
+def routes():
+    import paper_2208_14049_amd as ens
+    from synth import nets as N
+    # images: is it a chain?  (us as launches and as a chain)
+    requests = [([N.resnet50(), N.densenet121()], 16, {1: True, 8: True}),                    # 924 / 631, 1024 / 769
+                ([N.efficientnet(0), N.efficientnet(2), N.efficientnet(4)], 16, {1: True, 16: False}),   # 1186 / 993, 2026 / 2741
+                ([N.resnet50()], 64, {1: False, 8: True, 45: False}),                         # 332 / 374, 473 / 410, 1217 / 1293
+                ([N.inception_v3()], 16, {8: True, 16: True}),                                # 790 / 593, 1156 / 787
+                ([N.xception()], 16, {1: False, 4: False}), ([N.vgg(16)], 16, {4: False})]    # 530 / 816, 660 / 895, 465 / 778
+    for nets, batch, sizes in requests:
+        E = ens.Ensemble(nets)
+        E.set_base_size(224, 224)
+        E.ens_set_alloc([[batch] * len(nets)])
+        for n, chain in sizes.items():
+            before = E.ens_debug_stats()["chained"]
+            E.ens_predict(np.zeros((n, 224, 224, 3), np.float32))
+            assert E.ens_debug_stats()["chained"] - before == chain, (nets[0].name, n)
+        E.close()
+
+
+def test_requests_go_the_faster_way(fake_hip):
+    """Requests that were measured both ways, chains and launches at least 6 % apart, go the way that was faster."""
+    beside_fake_hip(fake_hip, "routes()")
+
+
 def wide_programs(view):
     import paper_2208_14049_amd as ens
     from synth import nets as N, weights as W
