@@ -1023,10 +1023,13 @@ hipError_t launch_se(const SeArgs& a, const SeArgs* argv, int G, int nb, bool bf
 // ------------------------------------------------------------------ combination rule
 // Per sample and member a max-subtracted softmax of the logits row, each term divided by M and added in
 // member order, one write of the combined row.  A member is a chain of a load and two reductions over a wavefront (2 us), so
-// a row has a wavefront per member where their terms fit LDS, and the terms are added from there in the same order.  With a wavefront per
-// row that took its members one after the other (1 000 classes, us alone, 1 and 1 024 images): twelve members 25 and 29, now 7 and 20, four
-// members 9 and 12, now 6 and 10, three 6.8 and 9.9, now 4.8 and 9.1.  An ensemble of one keeps that form, which is faster there by half a
-// microsecond, and so do more terms than LDS holds.
+// a row has a wavefront per member where their terms fit LDS, and the terms are added from there in the same order: the same bits.  That shortens
+// the chain and takes two barriers and a pass through LDS, which pays while a row has a workgroup or a few rows have; where workgroups
+// make rounds anyway a wavefront takes a row with its members one after the other.  A wavefront per row and one per member, us alone, on 1, 1 024,
+// 2 048 and 8 192 rows: two members of 10 classes 4.1 / 4.1, 4.2 / 4.2, 4.2 / 4.2 and 5.0 / 6.3, of 1 000 5.1 / 4.6, 6.2 / 6.2, 8.5 / 8.5 and 23 / 25;
+// four of 1 000 8.1 / 4.5, 10 / 7.8, 14 / 14 and 38 / 44; twelve of 1 000 20 / 5.6, 26 / 18, 34 / 31 and 106 / 112, of 10 8.0 / 4.1, 9.2 / 6.2, 9.1 / 9.3
+// and 18 / 28.  Over 2 to 32 members of 2 to 2 000 classes the form for few rows took 0.20 to 1.05 of the other's time up to COMBINE_MAX_BLOCKS
+// rows, for four members and more 0.69 to 1.03 at twice as many (one of 41 shapes 1.16), and up to 1.67 beyond.
 //
 // The members run on several lanes, and each lane ends with this launch.  A workgroup adds one to its place in
 // `arrivals` and goes on only if it is the last of the lanes' workgroups for those rows (it then puts the zero back);
@@ -1143,7 +1146,7 @@ __global__ __launch_bounds__(APART ? 64 * COMBINE_WAVES : 256) void combine_kern
 template <int PER, int RULE>
 static void launch_combine_per(const CombineArgs& a, hipStream_t s) {
     const int terms = a.n_members * a.classes;           // (64 members of 2 048 classes at most)
-    const bool apart = a.n_members > 1 && terms <= COMBINE_TERMS;
+    const bool apart = a.n_members > 1 && terms <= COMBINE_TERMS && a.n <= (a.n_members >= 4 ? 2 : 1) * COMBINE_MAX_BLOCKS;
     const int waves = apart ? std::min(a.n_members, COMBINE_WAVES) : 1, rows = apart ? std::max(1, std::min(4 / waves, COMBINE_TERMS / terms)) : 4;
     const long long blocks = (a.n + rows - 1) / rows;
     const dim3 g((unsigned)(blocks < COMBINE_MAX_BLOCKS ? blocks : COMBINE_MAX_BLOCKS)), b(64 * waves * rows);

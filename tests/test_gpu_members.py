@@ -236,8 +236,9 @@ def test_vote_bf16_resnets(ens):
 
 
 # one member; a wavefront per member with several rows at a time and with one; more members than wavefronts; more terms than LDS holds; classes
-# at the edges of a wavefront's lanes; one image, and more rows than workgroups
-@pytest.mark.parametrize("members,classes,n", [(1, 65, 5), (2, 64, 4099), (3, 7, 1), (4, 257, 1030), (17, 130, 3), (9, 1707, 2), (8, 1920, 2)], ids=str)
+# at the edges of a wavefront's lanes; one image, and more rows than workgroups; as many rows as the form for few takes, and one more
+@pytest.mark.parametrize("members,classes,n", [(1, 65, 5), (2, 64, 4099), (3, 7, 1), (4, 257, 1030), (17, 130, 3), (9, 1707, 2), (8, 1920, 2),
+                                               (3, 63, 1024), (3, 63, 1025), (4, 11, 2048), (5, 65, 2049)], ids=str)
 def test_combination_of_many_shapes(ens, members, classes, n):
     def head(i):
         net = N.Net("head%d" % i, 6, 6, classes, dtype="fp32")
@@ -259,6 +260,10 @@ def test_combination_of_many_shapes(ens, members, classes, n):
             want = oracle.combine_mean(probs, dtype=np.float64) if rule == "mean" else oracle.combine_weighted(probs, w)
             # exponentials, a quotient and sums of up to 1 920 terms in fp32, a few 2^-24 of a value each
             assert np.abs(y - want).max() <= 2e-6 * max(1.0, sum(w) if rule == "weighted" else 1.0)
+        if n > 1024:                                             # both forms give the same bits
+            few = E.ens_predict(imgs[:1000])
+            if all(np.array_equal(E.ens_member_logits(m, 1000), z[m][:1000]) for m in range(members)):
+                assert np.array_equal(few, y[:1000])
     E.close()
 
 
