@@ -131,7 +131,8 @@ def test_two_pixels_in_a_tile(ens, size, width, k, act, pool):
 
 
 def test_images_drawn_in_turn(ens):
-    """More images than two for each workgroup: every one is computed once, request after request, also as a recorded one, and a smaller one between them."""
+    """More images than two for each workgroup: every one is computed once, request after request, with smaller ones between them, and in pieces of 1 024 from
+    host memory, the last one shorter."""
     import torch
     nets = [N.tiny_a(classes=7), N.tiny_b(classes=7)]
     blobs = [W.make_blob(net, synth.BASE_SEED + 59, i) for i, net in enumerate(nets)]
@@ -147,4 +148,8 @@ def test_images_drawn_in_turn(ens):
             out.fill_(-1)
             E.ens_predict_static(imgs, out)
             assert np.array_equal(out.cpu().numpy(), want[np.arange(n) % 41]), n
+    assert E.ens_debug_stats()["chained"] == 16                  # all of them ran in LDS
+    for n in (2600, 41, 2049, 2600):
+        assert np.array_equal(E.ens_predict(np.ascontiguousarray(few[np.arange(n) % 41])), want[np.arange(n) % 41]), n
+    assert E.ens_debug_stats()["chained"] == 20
     E.close()
