@@ -43,6 +43,52 @@ def layers(i, h, w, c):
     return n
 
 
+def strips(i, h, w):
+    """3x3 layers of 64 channels on maps of more than 62 columns, with and without residual, with a second and a half-empty tile of channels."""
+    n = N.Net("strips%d" % i, h, w, 16, dtype="bf16")
+    t = n.conv(0, 64, 1)
+    t = n.conv(t, 64, 3, res=t)
+    t = n.conv(t, 64, 3, act="silu")
+    t = n.conv(n.conv(t, 96 + 32 * (i % 2), 3), 64, 1)
+    t = n.conv(t, 64, 3, res=t, gamma=0.25)
+    n.fc(n.gap(t), 16)
+    return n
+
+
+def test_rows_in_strips(ens):
+    """Maps that are walked in strips of columns, the last one narrower: residuals and outputs in rows among other lanes' launches, and without."""
+    nets = [strips(i, h, w) for i, (h, w) in enumerate([(9, 67), (12, 130), (11, 63), (10, 125)])]
+    blobs = [W.quantise_weights_bf16(net, W.make_blob(net, synth.BASE_SEED + 73, i)) for i, net in enumerate(nets)]
+    imgs = W.round_bf16(W.make_images(synth.BASE_SEED + 1073, 80, 12, 130, varied=True))
+    E = ens.Ensemble(nets, blobs)
+    E.set_base_size(12, 130)
+    E.ens_set_alloc([[40] * 4])
+    pooled = [net.ops[-2]["src"] for net in nets]
+
+    def ask():
+        y = E.ens_predict(imgs)
+        return [y] + [E.ens_member_logits(m, 80) for m in range(4)] + [E.ens_debug_tensor(m, pooled[m], net.tensors[pooled[m]], 40) for m, net in enumerate(nets)]
+
+    among = ask()
+    rows = E.ens_debug_stats()["rows"]
+    E.ens_set_profiling(1)
+    E.ens_predict(imgs)
+    ran = {k["name"]: k["launches"] for k in E.ens_profile() if k["launches"]}
+    E.ens_set_profiling(0)
+    # four such layers in each of four members' two batches, all of which took their rows, in both requests
+    assert ran["conv3x3_wreg_bf16<128,c64>"] == 32 and rows >= 32 and E.ens_debug_stats()["rows"] == 2 * rows, (rows, ran, E.ens_debug_stats())
+    E.ens_debug_rows(0)
+    apart = ask()
+    assert E.ens_debug_stats()["rows"] == 2 * rows
+    for a, b in zip(among, apart):
+        assert np.array_equal(a, b)
+    E.close()
+    for m, net in enumerate(nets):
+        ref = oracle.forward_logits(net, blobs[m], oracle.resize_bilinear(imgs, net.in_h, net.in_w), real="f32")
+        # some eight bf16 roundings of 2^-9 one after the other: less than the members above have
+        assert np.abs(among[1 + m] - ref).max() <= 0.08 * ref.std(), net.name
+
+
 @pytest.mark.parametrize("images", [25, 37], ids=str)             # (pixels that end within a row of a tile, in different places)
 def test_rows(ens, images):
     nets = [layers(i, h, w, c) for i, (h, w, c) in enumerate([(29, 27, 8), (27, 31, 40), (30, 26, 56), (25, 33, 72)])]
