@@ -3,7 +3,7 @@
 // One image through a deep member is a chain of 50 to 300 layers of which none fills the GPU, and a launch per layer costs 6 to 10 us
 // however little it does (twelve members, one image: 940 launches on four lanes, 2.97 ms).  Here the workgroups of an XCD, one per
 // compute unit, form a group that takes a member and some images and runs all its layers, with a barrier between layers that
-// depend on each other, and the eight groups take such programs from one queue, the longest first (1.19 ms).  The group's compute units
+// depend on each other, and the eight groups take such programs from one queue, the longest first (1.23 ms).  The group's compute units
 // share an L2: stores need only reach it (s_waitcnt vmcnt(0)), loads of what others stored bypass the L1 (device scope, sc1: 3.6 TB/s an XCD
 // from the L2 with it and without), and a barrier of the 32 workgroups is an atomic and a poll there, 1.0 us (over all eight XCDs it is 4 us,
 // and data would have to go through memory).
@@ -80,7 +80,7 @@ __device__ __forceinline__ u32x4 ch_pack(const float* f) {
 // which are brought into the L2 (a word of each line, dealt to the group's threads).  Loads come back in the order they were asked for, so
 // whatever a wavefront asks for behind those waits for the memory too.  A workgroup that has to wait at the barrier asks for them there; one that
 // comes last, and that the others will wait for next, behind its loads of the phase.  (Asked for by all in front of the barrier, the workgroups
-// with a share of them came 1 to 3 us later than the others in every phase; twelve members, one image and two: 1.24 and 1.67 ms, now 1.19 and 1.63.)
+// with a share of them came 1 to 3 us later than the others in every phase; twelve members, one image and two: 1.26 and 1.68 ms, now 1.22 and 1.65.)
 constexpr int CH_AHEAD = 2;
 struct ChainGroup {
     unsigned* arrived;

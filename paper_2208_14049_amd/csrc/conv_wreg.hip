@@ -47,6 +47,9 @@ __device__ __forceinline__ void wreg_for_each(F&& f, std::integer_sequence<int, 
 // STRIPS: rows of more than 62 pixels would make a window that LDS does not hold twice (nor a thread's row of the table); such a map is walked in
 // strips of `sw` columns, each with its neighbours' columns on both sides, as if every strip were an image of its own.  64 images, us alone, before on
 // the kernel of conv_halo.hip: 224x224x64 609 -> 242, 112x112 64 -> 128 177 -> 119; 16 images 147x147x64 43.0 -> 32.2; one image 224x224x64 16.4 -> 11.3.
+// A VGG-16 by itself takes 0.84 to 0.97 of its time, four VGGs 0.84 to 0.91, with a ResNet-50 0.87 to 1.04.  Beside longer members it depends on what the
+// lanes hold at the same time: 0.82 to 1.09 over 90 requests of six ensembles (0.96 on average; a ResNet-50, a ResNet-101, a DenseNet-121 and a VGG-19 on 16
+// to 36 images 1.02 to 1.07, on 64 and more 0.93 to 0.99).  Half as many workgroups, or workgroups of 8 or 16 tiles, are no different there.
 template <int BP, int WPX, int WCG, bool ROWS, bool STRIPS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void conv3x3_wreg_bf16(const ConvArgs* __restrict__ argv, const int nb_, const int hrows, const int strips, const int sw) {
