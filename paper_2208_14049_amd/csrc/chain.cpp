@@ -32,7 +32,7 @@ constexpr int GROUP = 32;                    // compute units of an XCD
 
 // What a convolution takes on one group, in microseconds: rounds of workgroups, and in each the chunks of 64 along K of a wavefront, one
 // after the other.  Fitted to the phases of nine networks on 1 to 8 images with each tile and split forced in turn (11 352 of them, half
-// of them within 9 %); what it picks is within 1 % of the best there.  A phase costs another PHASE_US.
+// of them within 9 %); what it picks for a layer by itself is within 1 % of the best there (several in a phase: suit_sides).  A phase costs another PHASE_US.
 constexpr double PHASE_US = 1.85;
 double conv_us(const ChainStep& s, int images, int side, int lg) {
     const double P = (double)images * s.px;
